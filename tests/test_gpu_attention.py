@@ -61,6 +61,16 @@ def test_single_key_and_tile_edges(lsp, oracle, dtype):
     _check_full(lsp, oracle, w, pl, sl)
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("P,N", [(0, 1), (1, 1), (15, 2), (16, 16), (127, 17), (128, 15), (129, 33), (1024, 256)])
+def test_f32_key_split_edges(lsp, oracle, D, P, N):
+    """One key in all, waves of the eight-way key split that see no tile, tiles that straddle the cache
+    and the suffix, query and key tiles with a remainder, several rounds per wave; a suffix buffer
+    that is longer than what is active.  The bound is the fp32 one of this file."""
+    w = W.scaled(W.C2, dtype="f32", B=2, S=N + 20, P=P, C=max(P, 1), Hq=6, Hkv=3, D=D, seed=300 + P + N)
+    _check_full(lsp, oracle, w, torch.tensor([P, P // 2], dtype=torch.int32), torch.tensor([N, max(1, N - 1)], dtype=torch.int32))
+
+
 @pytest.mark.parametrize("dtype,B,Hq,S", [("f32", 2, 2, 150), ("bf16", 2, 2, 150), ("bf16", 8, 16, 320)])
 def test_large_scores_and_moving_maximum(lsp, oracle, dtype, B, Hq, S):
     """Scores spanning hundreds of units whose maximum keeps rising along the key
