@@ -16,8 +16,10 @@ FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
 
 def build(verbose: bool = False, jobs: int = 6) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    # the hand-scheduled attention loop is generated (csrc/gen_attn_pipe.py -> csrc/lsp_attn_pipe_loop.inc, lsp_attn_pipe_idle_loop.inc)
-    subprocess.run([sys.executable, os.path.join(CSRC, "gen_attn_pipe.py")], check=True, stdout=subprocess.DEVNULL)
+    # the hand-scheduled loops are generated (csrc/gen_attn_pipe.py -> csrc/lsp_attn_pipe_loop.inc, lsp_attn_pipe_idle_loop.inc;
+    # csrc/gen_lm_head.py -> csrc/lsp_lm_head_loop_{256,128,64}.inc)
+    for gen in ("gen_attn_pipe.py", "gen_lm_head.py"):
+        subprocess.run([sys.executable, os.path.join(CSRC, gen)], check=True, stdout=subprocess.DEVNULL)
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     procs = []

@@ -3,28 +3,31 @@
 // same kernel to top-1 id, logit margin (Eq. 1) and top-1 probability, so the
 // [rows x V] logits never reach memory.
 //
-// Formulation.  A workgroup owns a tile of TV = 256 vocabulary entries x TR =
-// 256 rows and walks K in steps of 64.  It computes the TRANSPOSED logits tile
+// Formulation.  A workgroup computes tiles of 256 vocabulary entries x 256, 128 or
+// 64 rows of the TRANSPOSED logits
 //   Z^T[v, row] = W[v, :] . H[row, :]      (A operand = weight, B = hidden)
-// with v_mfma_f32_32x32x16_bf16, so that a lane's accumulator registers hold
-// 16 vocabulary entries of ONE row per 32x32 block: the running (max, runner-up,
+// with v_mfma_f32_16x16x32_bf16, so that a lane's accumulator registers hold four
+// vocabulary entries of ONE row per 16x16 block: the running (max, runner-up,
 // arg-max, sum of exponentials) of Eq. 1 is per-lane state, updated in
-// increasing vocabulary order, and only the last combine crosses lanes (the two
-// half-columns of a block, then the waves that share the rows).  Every
+// increasing vocabulary order, and only the last combine crosses lanes (the four
+// quarter-columns of a block, then the waves that share the rows).  Every
 // (row, vocabulary tile) leaves one 16-byte partial; a second, tiny kernel
 // folds a row's partials.
 //
-// Main loop.  Both operand tiles of a K step go from global memory straight
-// into LDS (no registers, no LDS store instructions), one step ahead of the
-// products, into the buffer freed at the last barrier.  Fragments of k-step
-// kk+1 are read while the matrix instructions of kk run, and the issue order
-// of a whole step is pinned: one LDS read or one global load after each matrix
-// instruction, global loads first.
+// Only ACTIVE rows are computed: tiles are cut from the list of them, over all
+// sequences (127 rows left in four buffers of 256 are one tile of 128, not four
+// of 256: 191 against 1122 us at 126 464 entries and K = 4096).
 //
-// Tiles go to the 8 XCDs round-robin by workgroup id; ids are laid out so that
-// the 32 workgroups an XCD runs at a time form a block of VB vocabulary tiles x
-// RB row tiles: each weight slice is then read by RB and each hidden slice by
-// VB workgroups out of the same L2.
+// The K loop is generated (gen_lm_head.py: fragments read one slice ahead, one
+// barrier per K step, loads that never drain); workgroups are persistent, one
+// per compute unit, and request the next tile's first steps before they reduce
+// the current tile.
+//
+// What bounds it.  Many rows: the board's power limit, as in the library's product
+// (8192 rows x 126 464 x 4096: 5.97 ms = 1.42 PFLOP/s with Eq. 1, 4.69 on operands that
+// do not toggle; the library's product alone 5.75 and 4.55; the compiler-scheduled
+// loop this replaced 7.7 and 6.6).  Few rows: the weight stream from HBM (128 rows:
+// 185 us = 5.6 TB/s, of which 167 us = 6.2 TB/s are what the bare stream takes).
 #include <float.h>
 
 #include "lsp_common.h"
@@ -39,10 +42,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr float kLog2e = 1.4426950408889634f;
 
 constexpr int TV = 256;          // vocabulary entries per tile
-constexpr int TR = 256;          // rows per tile
-constexpr int BK = 64;           // K step
-constexpr int TILE_BYTES = 256 * BK * 2;  // one operand tile of a K step in LDS: 256 rows of 128 bytes
-constexpr int STAGE = 2 * TILE_BYTES;     // weight tile, then hidden tile
 
 struct Partial {
   float m1, m2, s;
@@ -55,8 +54,11 @@ struct LmArgs {
   int64_t hrs, hbs, wrs;  // element strides
   const int32_t *suffix_len;
   Partial *partials;
-  int32_t VT, RT, VB, RB;  // tile counts, XCD block shape
+  int32_t VT;
 };
+
+// what a lane fetches in place of elements beyond K (and beyond its last tile)
+__device__ __attribute__((aligned(1024))) unsigned char g_zeros[1024];
 
 __device__ __forceinline__ float fmax_raw(float a, float b) {
   float d;
@@ -90,19 +92,6 @@ __device__ __forceinline__ Partial fold(Partial a, Partial b) {
   return r;
 }
 
-// Tile coordinates of this workgroup (vt, rt) or vt = -1 for a padding id.
-__device__ __forceinline__ void tile_of(const LmArgs &a, int &vt, int &rt) {
-  const int n = blockIdx.x;
-  const int x = n & 7, m = n >> 3;
-  const int per = a.VB * a.RB;
-  const int sb = m / per, loc = m % per;
-  const int RG = (a.RT + a.RB - 1) / a.RB;
-  const int vgroup = sb / RG, rgroup = sb % RG;
-  vt = (vgroup * a.VB + loc % a.VB) * 8 + x;
-  rt = rgroup * a.RB + loc / a.VB;
-  if (vt >= a.VT || rt >= a.RT) vt = -1;
-}
-
 // One wave-wide load from global memory straight into LDS: lane l fetches 16
 // bytes at its own address g and they land at lds_base + 16 l (lds_base is
 // wave-uniform; the counter to wait on is vmcnt).
@@ -110,213 +99,364 @@ __device__ __forceinline__ void load_to_lds(const char *g, unsigned char *lds_ba
   __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void *)lds_base, 16, 0, 0);
 }
 
-// WV x WR waves: WV along the vocabulary, WR along the rows.
-template <int WV, int WR>
-__global__ __launch_bounds__(64 * WV * WR, 512 / (64 * WV * WR) >= 2 ? 1 : 2) void lm_head_kernel(LmArgs a) {
-  constexpr int NT = 64 * WV * WR;
-  constexpr int MV = TV / WV / 32;  // 32x32 blocks per wave along the vocabulary
-  constexpr int MR = TR / WR / 32;  // ... along the rows
-  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
-  __shared__ int s_any;
-  int vt, rt;
-  tile_of(a, vt, rt);
-  if (vt < 0) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wv = wave % WV, wr = wave / WV;
-  const int lq = lane & 31, hf = lane >> 5;
-  const int rows = a.B * a.S;
-  const int v0 = vt * TV, r0 = rt * TR;
+// ---- active rows ---------------------------------------------------------------
+// Rows are numbered over the ACTIVE ones only: compact row c is row i of sequence b
+// with sum(N_0 .. N_{b-1}) + i = c.  `pre` holds the first compact row of every
+// group of G = ceil(B / 512) sequences (G = 1 in any ordinary batch).
+struct RowMap {
+  const int32_t *pre;
+  int32_t G, n;  // sequences per group, groups
+  int32_t R;     // active rows
+};
+constexpr int kThreads = 512;
+constexpr int kComputeUnits = 256;
 
-  // a tile none of whose rows is active does nothing
-  if (a.suffix_len != nullptr) {
-    if (tid == 0) s_any = 0;
-    __syncthreads();
-    bool act = false;
-    for (int t = tid; t < TR; t += NT) {
-      const int r = r0 + t;
-      if (r < rows) act |= (r % a.S) < a.suffix_len[r / a.S];
-    }
-    if (act) s_any = 1;
-    __syncthreads();
-    if (!s_any) return;
+__device__ __forceinline__ int active_of(const LmArgs &a, int b) { return min(max(a.suffix_len[b], 0), a.S); }
+
+__device__ __forceinline__ RowMap map_rows(const LmArgs &a, int32_t *pre, int32_t *wave_sum) {
+  RowMap m;
+  m.pre = pre;
+  if (a.suffix_len == nullptr) {
+    m.G = 0; m.n = 0; m.R = a.B * a.S;
+    return m;
   }
-
-  // Loader.  Operand tiles go from global memory straight into LDS
-  // (global_load_lds_dwordx4: lane l of a wave-wide load deposits its 16 bytes at
-  // LDS base + 16 l, so one load fills 1 KB = 8 tile rows of 128 bytes).  Rows
-  // are stored unpadded; to keep the fragment reads (16 consecutive rows, one
-  // 16-byte chunk each) on distinct banks, chunk c of row r is kept at chunk
-  // position c ^ ((r >> 1) & 7), which the loading lane applies to its GLOBAL
-  // address.  Wave w issues loads w, w + NW, ... of the tile's 32.
-  constexpr int NW = NT / 64;
-  const int wave_s = __builtin_amdgcn_readfirstlane(wave);  // wave-uniform, for the scalar LDS base
-  constexpr int LPW = 32 / NW;  // wave-wide loads per wave, per operand tile and K step
-  const char *wp[LPW], *hp[LPW];
-  int chunk[LPW];
+  m.G = (a.B + kThreads - 1) / kThreads;
+  m.n = (a.B + m.G - 1) / m.G;
+  const int tid = threadIdx.x, lane = tid & 63;
+  int own = 0;
+  for (int b = tid * m.G; b < min((tid + 1) * m.G, a.B); ++b) own += active_of(a, b);
+  int x = own;
 #pragma unroll
-  for (int i = 0; i < LPW; ++i) {
-    const int row = 8 * (wave + NW * i) + (lane >> 3);
-    chunk[i] = (lane & 7) ^ ((row >> 1) & 7);
-    const int v = min(v0 + row, a.V - 1);     // rows beyond V or the row count repeat the last valid one
-    const int r = min(r0 + row, rows - 1);    // (their results are masked or never written)
-    wp[i] = reinterpret_cast<const char *>(a.weight + int64_t(v) * a.wrs) + 16 * chunk[i];
-    hp[i] = reinterpret_cast<const char *>(a.hidden + int64_t(r / a.S) * a.hbs + int64_t(r % a.S) * a.hrs) + 16 * chunk[i];
+  for (int d = 1; d < 64; d <<= 1) {
+    const int o = __shfl_up(x, d);
+    x += lane >= d ? o : 0;
   }
-  const int KS = (a.K + BK - 1) / BK;
-  const int tail_chunks = (a.K % BK) / 8;  // valid 16-byte chunks of a ragged last step (0 = none ragged)
-  auto issue = [&](int ks, int buf, int i) {
-    unsigned char *st = smem + buf * STAGE + 1024 * (wave_s + NW * i);
-    int back = 0;  // a lane whose chunk lies beyond K fetches the row's chunk 0 of this step instead (zeroed below)
-    if (tail_chunks != 0 && ks == KS - 1 && chunk[i] >= tail_chunks) back = 16 * chunk[i];
-    const int kbyte = ks * BK * 2 - back;
-    load_to_lds(wp[i] + kbyte, st);
-    load_to_lds(hp[i] + kbyte, st + TILE_BYTES);
-  };
-  // after the loads of a ragged last step have landed: the lanes that fetched a
-  // stand-in overwrite their own LDS slots with zeros
-  auto zero_tail = [&](int ks) {
-    if (tail_chunks == 0 || ks != KS - 1) return;
-#pragma unroll
-    for (int i = 0; i < LPW; ++i)
-      if (chunk[i] >= tail_chunks) {
-        unsigned char *st = smem + (ks & 1) * STAGE + 1024 * (wave + NW * i) + 16 * lane;
-        *reinterpret_cast<u32x4 *>(st) = u32x4{0, 0, 0, 0};
-        *reinterpret_cast<u32x4 *>(st + TILE_BYTES) = u32x4{0, 0, 0, 0};
-      }
-  };
-
-  f32x16 acc[MV][MR];
-#pragma unroll
-  for (int i = 0; i < MV; ++i)
-#pragma unroll
-    for (int j = 0; j < MR; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-
-#pragma unroll
-  for (int i = 0; i < LPW; ++i) issue(0, 0, i);
-  __builtin_amdgcn_s_waitcnt(0);  // vmcnt = 0: the loads have written LDS
-  zero_tail(0);
+  if (lane == 63) wave_sum[tid >> 6] = x;
   __syncthreads();
-  // fragment of 32x32 block i at k-step kk: row (block base + lq), chunk 2 kk + hf, swizzled
-  const int y16 = 16 * (hf ^ ((lq >> 1) & 7));
-  const int a_row = (wv * (TV / WV) + lq) * 128;
-  const int b_row = TILE_BYTES + (wr * (TR / WR) + lq) * 128;
-  auto read_frags = [&](const unsigned char *st, int kk, bf16x8 (&af)[MV], bf16x8 (&bf)[MR]) {
-    const int off = (32 * kk) ^ y16;
+  int before = 0, total = 0;
 #pragma unroll
-    for (int i = 0; i < MV; ++i) af[i] = *reinterpret_cast<const bf16x8 *>(st + a_row + i * 32 * 128 + off);
+  for (int w = 0; w < kThreads / 64; ++w) {
+    before += w < (tid >> 6) ? wave_sum[w] : 0;
+    total += wave_sum[w];
+  }
+  pre[tid] = before + x - own;
+  m.R = __builtin_amdgcn_readfirstlane(total);
+  __syncthreads();
+  return m;
+}
+// sequence and row of compact row c < R
+__device__ __forceinline__ void row_at(const LmArgs &a, const RowMap &m, int c, int &b, int &i) {
+  if (m.G == 0) {
+    b = c / a.S;
+    i = c - b * a.S;
+    return;
+  }
+  int lo = 0, hi = m.n;  // the last group that starts at or before c
+  while (hi - lo > 1) {
+    const int mid = (lo + hi) >> 1;
+    if (m.pre[mid] <= c) lo = mid; else hi = mid;
+  }
+  b = lo * m.G;
+  i = c - m.pre[lo];
+  if (m.G > 1) {
+    for (int n = active_of(a, b); i >= n; n = active_of(a, b)) { i -= n; ++b; }
+  }
+}
+
+// ---- tiles of a workgroup ---------------------------------------------------------
+// Workgroups go to the 8 XCDs round-robin by id; XCD x owns the vocabulary tiles
+// congruent to x mod 8 and its workgroups take its tiles in turn.  In that order, up to four
+// row tiles of a group of vocabulary tiles come side by side: the 32 workgroups an XCD
+// runs at a time read every weight slice four times and every hidden slice
+// eight times out of one L2.
+struct Tiles {
+  int32_t *row;              // place b * S + i of the rows of two row tiles ...
+  int64_t *off;              // ... and their byte offset in `hidden`; table k starts at k * cap
+  int cap;
+  RowMap map;
+  int tr;                    // rows per row tile
+  int nv, RT, VB, total;
+};
+// How high row tiles are.  256 rows share a weight slice best and win wherever they are full; lower tiles
+//  - where tiles of 256 would be mostly padding: up to 128 rows (128 rows x 126 464 entries x K = 4096:
+//    185 us, 277 in one tile of 256), and 257-384 rows (300 rows: 414 against 476 us);
+//    not 129-256 (256 rows: 298 against 279 us) or more (640 rows would need five);
+//  - where a launch has fewer tiles than compute units (400 rows x 5000 entries: 41 us in 140 tiles of
+//    64, 55 in 80 of 128, 82 in 40 of 256).
+// Both kernels of a launch take the same decision; tiles of 256 are the tall kernel's.
+__device__ __forceinline__ void cut_rows(const LmArgs &a, Tiles &t, bool tall) {
+  const int R = t.map.R;
+  t.tr = int64_t(a.VT) * ((R + 63) / 64) <= kComputeUnits                                               ? 64
+         : int64_t(a.VT) * ((R + 127) / 128) <= kComputeUnits || R <= 128 || (R > 256 && R <= 384) ? 128
+                                                                                               : 256;
+  t.RT = tall == (t.tr == 256) ? (R + t.tr - 1) / t.tr : 0;
+  const int xcd = blockIdx.x & 7, slots = gridDim.x >> 3;
+  t.nv = (a.VT - xcd + 7) / 8;
+  t.VB = max(1, slots / max(1, min(t.RT, 4)));
+  t.total = t.nv * t.RT;
+}
+struct Cursor {
+  int m, vt, rt, buf;  // index in the list, tile, which of the two row tables holds its rows
+};
+__device__ __forceinline__ void tile_at(const Tiles &t, int m, int &vt, int &rt) {
+  const int per = t.VB * t.RT, vg = m / per, q = m - vg * per;
+  const int g = min(t.VB, t.nv - vg * t.VB);
+  vt = (vg * t.VB + q % g) * 8 + int(blockIdx.x & 7);
+  rt = q / g;
+}
+__device__ __forceinline__ void fill_rows(const LmArgs &a, const Tiles &t, int buf, int rt) {
+  const int i = threadIdx.x;
+  if (i < t.cap) {
+    int b, r;
+    row_at(a, t.map, min(rt * t.tr + i, t.map.R - 1), b, r);  // rows beyond the last repeat it (never written)
+    t.row[buf * t.cap + i] = b * a.S + r;
+    t.off[buf * t.cap + i] = (int64_t(b) * a.hbs + int64_t(r) * a.hrs) * 2;
+  }
+  __syncthreads();
+}
+
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x8 __attribute__((ext_vector_type(8)));
+
+// Eq. 1 on N logits of one row held by a lane: element e is vocabulary entry vbase + 16 (e/4) + e%4.
+template <int N>
+__device__ __forceinline__ Partial reduce(float (&x)[N], int vbase, int V, bool ragged) {
+  if (ragged) {  // (a branch of its own, nothing of it formed ahead: two more instructions per logit otherwise)
+    int left = V - vbase;
+    asm volatile("" : "+v"(left));
 #pragma unroll
-    for (int j = 0; j < MR; ++j) bf[j] = *reinterpret_cast<const bf16x8 *>(st + b_row + j * 32 * 128 + off);
-  };
-  constexpr int KSTEPS = BK / 16;
-  for (int ks = 0; ks < KS; ++ks) {
-    // Step ks+1 is fetched into the buffer every wave finished reading before the
-    // last barrier (the last step fetches itself again, into the idle buffer, so
-    // that the loop body stays free of branches).  Within a k-step the
-    // fragments of the NEXT k-step are read and a share of the global loads is
-    // issued between the matrix instructions of this one.
-    const int kn = min(ks + 1, KS - 1);
-    const unsigned char *st = smem + (ks & 1) * STAGE;
-    bf16x8 af[2][MV], bf[2][MR];
-    read_frags(st, 0, af[0], bf[0]);
-    constexpr int NREAD = MV + MR, NMFMA = MV * MR;
-    constexpr int LOADS_PER_K = (NMFMA - NREAD) / 2 > 0 ? (NMFMA - NREAD) / 2 : 1;  // operand-pair loads per k-step, earliest first
+    for (int e = 0; e < N; ++e) x[e] = 16 * (e >> 2) + (e & 3) >= left ? -INFINITY : x[e];
+  }
+  float m1 = -INFINITY, m2 = -INFINITY;
+  int code = 0;
 #pragma unroll
-    for (int kk = 0; kk < KSTEPS; ++kk) {
-      const int cur = kk & 1;
-      if (kk + 1 < KSTEPS) read_frags(st, kk + 1, af[cur ^ 1], bf[cur ^ 1]);
+  for (int e = 0; e < N; ++e) {
+    code = x[e] > m1 ? e : code;
+    m2 = fmed3_raw(m1, m2, x[e]);
+    m1 = fmax_raw(m1, x[e]);
+  }
+  // sum of exp2(z*log2e - rc) against the ROUNDED product rc = m1*log2e (one fma +
+  // exp2 per logit), then taken off that reference with an fma of its own, which
+  // cancels the rounding of rc exactly
+  const float ref = m1 == -INFINITY ? 0.f : m1;
+  const float rc = ref * kLog2e;
+  float s = 0.f;
 #pragma unroll
-      for (int i = kk * LOADS_PER_K; i < (kk + 1) * LOADS_PER_K && i < LPW; ++i) issue(kn, (ks + 1) & 1, i);
+  for (int e = 0; e < N; ++e) s += __builtin_amdgcn_exp2f(__builtin_fmaf(x[e], kLog2e, -rc));
+  s *= __builtin_amdgcn_exp2f(__builtin_fmaf(-ref, kLog2e, rc));
+  Partial p;
+  p.m1 = m1; p.m2 = m2; p.s = s;
+  p.idx = vbase + 16 * (code >> 2) + (code & 3);
+  return p;
+}
+// The four lanes of a row fold their results, each pair exchanging half of its row blocks: lanes 32
+// apart first, then lanes 16 apart, so that no lane folds what another one folds as well.
+__device__ __forceinline__ Partial exchange(const Partial &lo, const Partial &hi, bool upper, int d) {
+  const Partial keep = upper ? hi : lo, send = upper ? lo : hi;
+  Partial o;
+  o.m1 = __shfl_xor(send.m1, d); o.m2 = __shfl_xor(send.m2, d); o.s = __shfl_xor(send.s, d); o.idx = __shfl_xor(send.idx, d);
+  return fold(keep, o);
+}
+// One thread per row folds the N waves' results of a tile and leaves the tile's partial result.
+template <int N>
+__device__ __forceinline__ void finish_tile(const LmArgs &a, const Tiles &tb, const Partial *lds_part, const Cursor &cur, int vt) {
+  const int t = threadIdx.x;
+  if (t >= tb.tr || cur.rt * tb.tr + t >= tb.map.R) return;
+  Partial p = lds_part[t * N];
 #pragma unroll
-      for (int i = 0; i < MV; ++i)
-#pragma unroll
-        for (int j = 0; j < MR; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(af[cur][i], bf[cur][j], acc[i][j], 0, 0, 0);
+  for (int u = 1; u < N; ++u) p = fold(p, lds_part[t * N + u]);
+  a.partials[int64_t(tb.row[cur.buf * tb.cap + t]) * a.VT + vt] = p;
+}
+
+// ---- tiles -----------------------------------------------------------------------------
+// Geometry by tile height (the same table as in gen_lm_head.py): waves along vocabulary and rows, LDS stages.
+template <int H> struct Shape;
+template <> struct Shape<256> { static constexpr int WV = 2, WR = 4, NS = 2; };
+template <> struct Shape<128> { static constexpr int WV = 4, WR = 2, NS = 3; };
+template <> struct Shape<64> { static constexpr int WV = 4, WR = 2, NS = 3; };
+constexpr int KB = 64, TILE_W = TV * KB * 2;  // K step, bytes of a weight tile's step
+template <int H> constexpr int stage_bytes() { return (TV + H) * KB * 2; }
+// behind the stages: the next tile's hidden pointers (H = 256), then the waves' partial results
+template <int H> constexpr int lds_bytes() { return Shape<H>::NS * stage_bytes<H>() + (H == 256 ? 16384 : H * Shape<H>::WV * 16); }
+
+template <int N> struct UVec;
+template <> struct UVec<2> { typedef u32x2 T; };
+template <> struct UVec<4> { typedef u32x4 T; };
+template <> struct UVec<8> { typedef u32x8 T; };
+
+// All tiles of a workgroup: K loop, Eq. 1, one partial result per row and tile.
+template <int H>
+__device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, const Tiles &tb, Cursor cur) {
+  constexpr int WV = Shape<H>::WV, WR = Shape<H>::WR, NS = Shape<H>::NS, STG = stage_bytes<H>();
+  constexpr int MV = TV / WV / 16, MR = H / WR / 16, LH = H / 64;  // 16x16 blocks per wave, hidden loads per lane and step
+  unsigned char *part = smem + NS * STG;
+  const int KS_real = (a.K + KB - 1) / KB, KS = max(KS_real, NS);
+  const int tail = (a.K % KB) / 8;
+  const uint64_t zeros = reinterpret_cast<uint64_t>(g_zeros);
+  int stage = 0;           // stage that holds step 0 of the current tile
+  bool requested = false;  // its first steps have been requested by the previous tile's loop
+  // First K step (see gen_lm_head.py): by the place of the workgroup's vocabulary tile among the 32 workgroups of
+  // its XCD.  Those that share a weight slice stay together, and the hidden rows are read inside a window of
+  // VB steps, 1 MB of the XCD's L2.
+  const int k0 = tail == 0 && KS_real > NS ? (tb.RT > 1 ? int(blockIdx.x >> 3) % tb.VB : int(blockIdx.x) * 5) % (KS - NS) : 0;
+  for (;;) {
+    // (opaque: what is derived from the thread id is formed again for every tile - kept across the loop it would spill)
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wv = wave % WV, wr = wave / WV, l16 = lane & 15, grp = lane >> 4;
+    // loader: this lane's row (of 8) and 16-byte chunk of it
+    const int lrow = lane >> 3, chunk = (lane & 7) ^ (4 * (wave & 1) + (lane >> 4));
+    const int vt = cur.vt, v0 = vt * TV;
+    int vn = vt, rn = cur.rt, nbuf = cur.buf;
+    const bool more = cur.m + int(gridDim.x >> 3) < tb.total;
+    if (more) tile_at(tb, cur.m + (gridDim.x >> 3), vn, rn);
+    if (rn != cur.rt) {
+      nbuf = cur.buf ^ 1;
+      fill_rows(a, tb, nbuf, rn);
     }
-    // Issue order of the whole step (one scheduling region): the first k-step's
-    // fragment reads; then, per k-step, after each matrix instruction one LDS read
-    // (fragments of the next k-step) or one global load.  The global loads all go
-    // out in the first k-steps so that they have the rest of the step to land.
+    auto hidden_at = [&](int buf, int i) {  // this lane's piece of load i of a hidden tile, at k = 0
+      return reinterpret_cast<uint64_t>(a.hidden) + tb.off[buf * tb.cap + 8 * (wave + 8 * i) + lrow] + 16 * chunk;
+    };
+    uint64_t w[4], h[LH];  // this lane's pieces of a step: weight rows, hidden rows
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      w[i] = reinterpret_cast<uint64_t>(a.weight) + int64_t(min(v0 + 8 * (wave + 8 * i) + lrow, a.V - 1)) * a.wrs * 2 + 16 * chunk + k0 * (2 * KB);
+#pragma unroll
+    for (int i = 0; i < LH; ++i) h[i] = hidden_at(cur.buf, i) + k0 * (2 * KB);
+    if (!requested) {
+      stage = 0;
+#pragma unroll
+      for (int p = 0; p < NS; ++p) {
+        const bool in = (k0 + p) * KB + 8 * chunk < a.K;
+        unsigned char *st = smem + p * STG + 1024 * wave;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) load_to_lds(reinterpret_cast<const char *>(in ? w[i] + p * 2 * KB : zeros), st + 8192 * i);
+#pragma unroll
+        for (int i = 0; i < LH; ++i) load_to_lds(reinterpret_cast<const char *>(in ? h[i] + p * 2 * KB : zeros), st + TILE_W + 8192 * i);
+      }
+    }
+    u32x8 wptr;  // of the next step to request
+    typename UVec<2 * LH>::T hptr;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const uint64_t p = w[i] + NS * 2 * KB;
+      wptr[2 * i] = uint32_t(p);
+      wptr[2 * i + 1] = uint32_t(p >> 32);
+    }
+#pragma unroll
+    for (int i = 0; i < LH; ++i) {
+      const uint64_t p = h[i] + NS * 2 * KB;
+      hptr[2 * i] = uint32_t(p);
+      hptr[2 * i + 1] = uint32_t(p >> 32);
+    }
+
+    // The loads of a tile's last steps are followed by the first ones of the next tile where that is plain
+    // pointer arithmetic: whole K steps, no vocabulary entry beyond V in either.
+    const bool cross = more && tail == 0 && KS_real > NS && v0 + TV <= a.V && vn * TV + TV <= a.V;
+    const uint64_t wstep = int64_t(vn - vt) * TV * a.wrs * 2 - (k0 == 0 ? int64_t(KS) * (2 * KB) : 0);
+
+    f32x16 acc[MV * MR / 4];
+#pragma unroll
+    for (int k = 0; k < MV * MR / 4; ++k)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[k][r] = 0.f;
     {
-      static_assert(KSTEPS * LOADS_PER_K >= LPW, "all loads of a step fit into its k-steps");
-      __builtin_amdgcn_sched_group_barrier(0x100, NREAD, 0);
+      const uint32_t lds0 = uint32_t(uintptr_t((__attribute__((address_space(3))) unsigned char *)smem));
+      u32x4 addr[NS];  // fragment addresses per stage: weight and hidden of k-slice 0, of k-slice 1
 #pragma unroll
-      for (int kk = 0; kk < KSTEPS; ++kk) {
-        const bool reads = kk + 1 < KSTEPS;
-        const int first = kk * LOADS_PER_K;
-        const int nl = first >= LPW ? 0 : (LPW - first < LOADS_PER_K ? LPW - first : LOADS_PER_K);
-        if (reads) {
+      for (int st = 0; st < NS; ++st)
 #pragma unroll
-          for (int q = 0; q < NREAD; ++q) {
-            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-            __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          }
+        for (int kk = 0; kk < 2; ++kk) {
+          const uint32_t c = 16 * ((4 * kk + grp) ^ (l16 >> 1));
+          addr[st][2 * kk] = lds0 + st * STG + (wv * (TV / WV) + l16) * (2 * KB) + c;
+          addr[st][2 * kk + 1] = lds0 + st * STG + TILE_W + (wr * (H / WR) + l16) * (2 * KB) + c;
         }
+      const uint32_t ldsw = lds0 + 1024 * wave, ks = KS, phase = stage, go_on = __builtin_amdgcn_readfirstlane(int(cross));
+      // the first thing to happen to the pointers: back to k = 0, the ragged end of K, or the next tile
+      const uint32_t wrap = k0 > 0 ? KS - k0 : ~0u, event = k0 > 0 ? KS - k0 : min(KS, max(a.K / KB, NS));
+      const uint64_t kback = -uint64_t(KS) * (2 * KB);
+      const uint32_t zlo = uint32_t(zeros), zhi = uint32_t(zeros >> 32);
+      const uint64_t zmask = __ballot(chunk >= tail);
+      if constexpr (H == 256) {
+        // registers are full: the next tile's hidden pointers wait in LDS (a lane reads what it wrote)
 #pragma unroll
-        for (int q = 0; q < 2 * nl; ++q) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+        for (int i = 0; i < LH; i += 2) {
+          const uint64_t h0 = hidden_at(nbuf, i) + k0 * 2 * KB, h1 = hidden_at(nbuf, i + 1) + k0 * 2 * KB;
+          *reinterpret_cast<u32x4 *>(part + 4096 * i + 16 * tid) = u32x4{uint32_t(h0), uint32_t(h0 >> 32), uint32_t(h1), uint32_t(h1 >> 32)};
         }
-        // the remaining matrix instructions of the k-step, one group each (sizes must be literals)
+        const uint32_t next = lds0 + NS * STG + 16 * tid;
+#include "lsp_lm_head_loop_256.inc"
+      } else {
+        typename UVec<2 * LH>::T next;
 #pragma unroll
-        for (int q = (reads ? NREAD : 0) + 2 * nl; q < NMFMA; ++q) __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        for (int i = 0; i < LH; ++i) {
+          const uint64_t h = hidden_at(nbuf, i) + k0 * 2 * KB;
+          next[2 * i] = uint32_t(h);
+          next[2 * i + 1] = uint32_t(h >> 32);
+        }
+        if constexpr (H == 128) {
+#include "lsp_lm_head_loop_128.inc"
+        } else {
+#include "lsp_lm_head_loop_64.inc"
+        }
       }
     }
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's share of step ks+1 is in LDS
-    zero_tail(ks + 1);
-    __syncthreads();
-  }
+    requested = cross;
+    stage = (stage + KS) % NS;
 
-  // ---- Eq. 1 on the accumulators ------------------------------------------------
-  // acc[i][j][r] = z[v][row] with v = v0 + wv*(TV/WV) + 32 i + 8 (r/4) + 4 hf + r%4
-  // (increasing in (i, r)) and row = r0 + wr*(TR/WR) + 32 j + lq.
-  const int vbase = v0 + wv * (TV / WV) + 4 * hf;
-  const bool ragged = v0 + TV > a.V;
-  Partial *lds_part = reinterpret_cast<Partial *>(smem);  // [TR][WV] after the last barrier
+    // element r of 16x16 block (i, j) is z[v][row], v = v0 + wv*(TV/WV) + 16 i + 4 grp + r (increasing in (i, r)),
+    // row = wr*(H/WR) + 16 j + l16
+    Partial pj[MR];
 #pragma unroll
-  for (int j = 0; j < MR; ++j) {
-    float m1 = -INFINITY, m2 = -INFINITY;
-    int code = 0;
+    for (int j = 0; j < MR; ++j) {
+      float x[4 * MV];
 #pragma unroll
-    for (int i = 0; i < MV; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        float x = acc[i][j][r];
-        if (ragged && vbase + 32 * i + 8 * (r >> 2) + (r & 3) >= a.V) x = acc[i][j][r] = -INFINITY;
-        code = x > m1 ? 16 * i + r : code;
-        m2 = fmed3_raw(m1, m2, x);
-        m1 = fmax_raw(m1, x);
-      }
-    // sum of exp2(z*log2e - rc) against the ROUNDED product rc = m1*log2e (one fma +
-    // exp2 per logit), then taken off that reference with an fma of its own, which
-    // cancels the rounding of rc exactly
-    const float ref = m1 == -INFINITY ? 0.f : m1;
-    const float rc = ref * kLog2e;
-    float s = 0.f;
-#pragma unroll
-    for (int i = 0; i < MV; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) s += __builtin_amdgcn_exp2f(__builtin_fmaf(acc[i][j][r], kLog2e, -rc));
-    s *= __builtin_amdgcn_exp2f(__builtin_fmaf(-ref, kLog2e, rc));
+      for (int e = 0; e < 4 * MV; ++e) x[e] = acc[(j * MV + e / 4) / 4][4 * ((j * MV + e / 4) % 4) + e % 4];
+      pj[j] = reduce<4 * MV>(x, v0 + wv * (TV / WV) + 4 * grp, a.V, v0 + TV > a.V);
+    }
+    const bool up32 = lane >= 32, up16 = (lane & 16) != 0;
     Partial p;
-    p.m1 = m1; p.m2 = m2; p.s = s;
-    p.idx = vbase + 32 * (code >> 4) + 8 * ((code & 15) >> 2) + (code & 3);
-    // the other half-column of the 32x32 blocks (lane +-32) holds the rows' other vocabulary entries
-    Partial o;
-    o.m1 = __shfl_xor(p.m1, 32); o.m2 = __shfl_xor(p.m2, 32); o.s = __shfl_xor(p.s, 32); o.idx = __shfl_xor(p.idx, 32);
-    p = fold(p, o);
-    if (hf == 0) lds_part[(wr * (TR / WR) + 32 * j + lq) * WV + wv] = p;
+    int j;
+    if constexpr (MR == 4) {
+      p = exchange(exchange(pj[0], pj[2], up32, 32), exchange(pj[1], pj[3], up32, 32), up16, 16);
+      j = 2 * up32 + up16;
+    } else {
+      p = exchange(pj[0], pj[1], up32, 32);
+      p = exchange(p, p, false, 16);
+      j = up32;
+    }
+    Partial *lds_part = reinterpret_cast<Partial *>(part);  // [H][WV]
+    lds_part[(wr * (H / WR) + 16 * j + l16) * WV + wv] = p;
+    __syncthreads();
+    finish_tile<WV>(a, tb, lds_part, cur, vt);
+    __syncthreads();  // the partial results and the row tables may be overwritten
+    cur.m += gridDim.x >> 3;
+    cur.vt = vn; cur.rt = rn; cur.buf = nbuf;
+    if (!more) break;
   }
-  __syncthreads();
-  // one thread per row of the tile folds the WV waves' results and writes the partial
-  for (int t = tid; t < TR; t += NT) {
-    Partial p = lds_part[t * WV];
-#pragma unroll
-    for (int u = 1; u < WV; ++u) p = fold(p, lds_part[t * WV + u]);
-    const int r = r0 + t;
-    if (r < rows) a.partials[int64_t(r) * a.VT + vt] = p;
-  }
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing is still on its way into LDS
+}
+
+// Persistent kernels: one workgroup per compute unit walks its tiles.
+template <bool TALL>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void lm_head_kernel(LmArgs a) {
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
+  __shared__ int32_t s_pre[kThreads], s_wave[kThreads / 64];
+  constexpr int CAP = TALL ? 256 : 128;
+  __shared__ int32_t s_row[2 * CAP];
+  __shared__ int64_t s_off[2 * CAP];
+  Tiles tb;
+  tb.row = s_row; tb.off = s_off; tb.cap = CAP;
+  tb.map = map_rows(a, s_pre, s_wave);
+  cut_rows(a, tb, TALL);
+  Cursor cur = {int(blockIdx.x >> 3), 0, 0, 0};
+  if (cur.m >= tb.total) return;
+  tile_at(tb, cur.m, cur.vt, cur.rt);
+  fill_rows(a, tb, 0, cur.rt);
+  if constexpr (TALL) run_tiles<256>(a, smem, tb, cur);
+  else if (min(tb.tr, tb.map.R) <= 64) run_tiles<64>(a, smem, tb, cur);
+  else run_tiles<128>(a, smem, tb, cur);
 }
 
 // One wave per row folds the row's VT partials and writes the three results.
@@ -345,25 +485,26 @@ __global__ __launch_bounds__(256) void lm_head_finish_kernel(const Partial *__re
   }
 }
 
-template <int WV, int WR>
-int32_t launch_lm_head_t(const LmArgs &a, int64_t nwg, hipStream_t st) {
-  const size_t lds = 2 * size_t(STAGE);  // two K steps in LDS
-  auto kern = lm_head_kernel<WV, WR>;
+template <bool TALL>
+int32_t launch_lm_head_t(const LmArgs &a, int64_t row_tiles, size_t lds, hipStream_t st) {
+  // at most one workgroup per compute unit, a multiple of 8 (the same number on every XCD)
+  const int64_t per_xcd = (int64_t(a.VT) + 7) / 8 * row_tiles;
+  const unsigned nwg = 8 * unsigned(per_xcd < kComputeUnits / 8 ? per_xcd : kComputeUnits / 8);
+  auto kern = lm_head_kernel<TALL>;
   static std::atomic<uint64_t> configured{0};  // per instantiation, one bit per device
   if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured, "lsp_lm_head_confidence: hipFuncSetAttribute")) return rc;
-  kern<<<dim3(static_cast<unsigned>(nwg)), 64 * WV * WR, lds, st>>>(a);
+  kern<<<dim3(nwg), kThreads, lds, st>>>(a);
   LSP_CHECK_LAUNCH("lsp_lm_head_confidence: launch");
   return LSP_OK;
 }
 
-int32_t launch_lm_head(const LmArgs &a, int64_t nwg, hipStream_t st) {
-  // Four waves of 128 x 128 outputs each need the fewest LDS reads per matrix
-  // instruction (8 fragment reads feed 16 instructions; eight waves of 128 x 64
-  // need 6 for 8) and win once several row tiles share every weight tile.  With
-  // few rows the weight matrix streams from HBM once and nothing is re-used: two
-  // waves per SIMD then cover the longer load latency better (measured).
-  if (a.RT >= 4) return launch_lm_head_t<2, 2>(a, nwg, st);
-  return launch_lm_head_t<2, 4>(a, nwg, st);
+int32_t launch_lm_head(const LmArgs &a, hipStream_t st) {
+  // How many rows are active is only known on the device, so both kernels are launched
+  // (each leaves at once where nothing is its own) unless the buffers decide.
+  const int64_t rows = int64_t(a.B) * a.S;
+  if (rows > 128)
+    if (const int32_t rc = launch_lm_head_t<true>(a, (rows + 255) / 256, lds_bytes<256>(), st)) return rc;
+  return launch_lm_head_t<false>(a, (rows + 63) / 64, lds_bytes<128>(), st);
 }
 
 }  // namespace
@@ -412,19 +553,12 @@ extern "C" int32_t lsp_lm_head_confidence(int32_t dtype, const void *hidden, con
   a.partials = static_cast<Partial *>(workspace);
   const int64_t rows = int64_t(B) * S;
   a.VT = (V + TV - 1) / TV;
-  a.RT = int32_t((rows + TR - 1) / TR);
-  a.RB = a.RT < 4 ? a.RT : 4;
-  a.VB = 32 / a.RB;
-  const int64_t RG = (a.RT + a.RB - 1) / a.RB;
-  const int64_t per_xcd_vt = (a.VT + 7) / 8;                    // vocabulary tiles an XCD owns
-  const int64_t VG = (per_xcd_vt + a.VB - 1) / a.VB;
-  const int64_t nwg = VG * RG * a.VB * a.RB * 8;
-  if (nwg > 0x7fffffff) {
-    set_error("lsp_lm_head_confidence: launch of %lld workgroups is too large", (long long)nwg);
+  if (int64_t(a.VT) * ((rows + 63) / 64) > 0x7fffffff) {
+    set_error("lsp_lm_head_confidence: %lld tiles are too many", (long long)(int64_t(a.VT) * ((rows + 63) / 64)));
     return LSP_ERR_UNSUPPORTED;
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int32_t rc = launch_lm_head(a, nwg, st);
+  const int32_t rc = launch_lm_head(a, st);
   if (rc != LSP_OK) return rc;
   lm_head_finish_kernel<<<dim3(static_cast<unsigned>((rows + 3) / 4)), 256, 0, st>>>(
       a.partials, int(rows), S, a.VT, suffix_len, top1_id, top1_prob, margin);

@@ -81,6 +81,40 @@ def test_exact_integer_logits_bitwise_with_ties(lsp, oracle):
     _compare(got, ref[:3], ref[3], exact=True)
 
 
+def _integer_case(lsp, oracle, B, S, K, V, lens, seed):
+    """Small-integer operands (logits exact in fp32 whatever the order of summation): bit-exact."""
+    g = torch.Generator().manual_seed(seed)
+    h = torch.randint(-3, 4, (B, S, K), generator=g).to(torch.bfloat16)
+    w = torch.randint(-3, 4, (V, K), generator=g).to(torch.bfloat16)
+    sl = None if lens is None else torch.tensor(lens, dtype=torch.int32)
+    ref = oracle.lm_head_confidence(h, w, suffix_len=sl)
+    _compare(_run(lsp, h.cuda(), w.cuda(), sl), ref, None, exact=True)
+
+
+@pytest.mark.parametrize("rows", [1, 63, 64, 65, 128, 129, 256, 257, 385])
+@pytest.mark.parametrize("V", [256, 2 * 256 + 1, 70 * 256 - 3])
+def test_tile_heights(lsp, oracle, rows, V):
+    """Active rows at the edges of the tile heights (64, 128, 256 and the 257-384 rule), spread over three
+    sequences; few vocabulary tiles (lower tiles fill the chip) and more tiles than compute units (a
+    workgroup goes on to a second tile), with a ragged last vocabulary tile."""
+    a, b = rows // 2, rows // 5
+    _integer_case(lsp, oracle, 3, rows + 3, 64 * 5, V, [a, rows - a - b, b], seed=rows + V)
+
+
+@pytest.mark.parametrize("rows", [40, 100, 300, 600])
+@pytest.mark.parametrize("K", [8, 64, 120, 128, 136, 192, 200, 64 * 37])
+def test_k_steps(lsp, oracle, rows, K):
+    """K below, at and just beyond the steps that are in flight at the loop's start, with and without a ragged
+    last step, and long enough for every staggered start; 600 rows take tiles of 256."""
+    _integer_case(lsp, oracle, 1, rows, K, 33 * 256 + 5, None, seed=rows + K)
+
+
+def test_more_sequences_than_threads(lsp, oracle):
+    """700 sequences of up to three rows: two sequences per entry of the row map, empty ones among them."""
+    g = torch.Generator().manual_seed(3)
+    _integer_case(lsp, oracle, 700, 3, 64, 600, torch.randint(0, 4, (700,), generator=g).tolist(), seed=1)
+
+
 def test_inactive_rows_and_whole_inactive_tiles(lsp, oracle):
     w = W.scaled(W.C2, B=3, S=300, V=520, seed=2101)
     hidden, weight, _ = W.make_lm_head(w, 128)
