@@ -5,6 +5,11 @@ live on the GPU, passes their pointers and the current HIP stream to the C-ABI
 entry point of the same name (include/lsp.h) and returns the output tensors.
 There is no fallback: importing works without the built library (so that the
 package can be inspected), but the first call raises if liblsp.so is missing.
+
+The calls of a scheduler step go through a native module (csrc/binding.cpp)
+when their arguments are in the ordinary form (device tensors of the right type
+and layout, outputs given); it answers None otherwise, and the code here then checks
+argument by argument, raises, or allocates what is missing.
 """
 from __future__ import annotations
 
@@ -16,6 +21,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblsp.so")
 _lib = None
+_nat = None     # the native marshalling module, bound to the loaded library
 
 LSP_F32, LSP_BF16 = 0, 1
 FLAG_CACHE_FULL, FLAG_TOKENS_FULL = 1, 2
@@ -52,7 +58,7 @@ EXPORTS = ["lsp_version", "lsp_last_error", "lsp_attn_workspace_bytes", "lsp_att
 
 def lib() -> ctypes.CDLL:
     """The loaded C-ABI library; raises LspError when it has not been built."""
-    global _lib
+    global _lib, _nat
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise LspError(f"{LIB_PATH} is missing: run `python -m paper_2603_05454_amd.build` "
@@ -66,7 +72,15 @@ def lib() -> ctypes.CDLL:
         for n in ("lsp_attn_step", "lsp_attn_step_layers", "lsp_confidence", "lsp_confidence_static", "lsp_commit", "lsp_flip_update", "lsp_select_scattered",
                   "lsp_kv_gather_append", "lsp_attn_step_gather", "lsp_lm_head_confidence", "lsp_bench_read", "lsp_bench_mfma"):
             getattr(L, n).restype = ctypes.c_int32
-        _lib = L
+        try:
+            from . import _binding
+        except ImportError as e:
+            raise LspError(f"the native binding module is missing ({e}): run `python -m paper_2603_05454_amd.build` "
+                           "(or __graft_entry__.build()) first") from e
+        _binding.bind(*[ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in (
+            "lsp_attn_workspace_bytes", "lsp_attn_step", "lsp_attn_step_layers", "lsp_confidence_workspace_bytes", "lsp_confidence",
+            "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_commit", "lsp_flip_update")])
+        _lib, _nat = L, _binding
     return _lib
 
 
@@ -154,6 +168,13 @@ def attn_step(q, k_suf, v_suf, k_cache, v_cache, prefix_len, suffix_len, scale=0
     prefix_len/suffix_len int32 [B].  Returns out [B,S,Hq,D] (same dtype as q);
     rows >= suffix_len[b] are not written.  cache_row_index int32 [B,C] selects
     lsp_attn_step_gather (key t of the prefix is cache row cache_row_index[b,t])."""
+    if _nat is not None and cache_row_index is None:
+        if out is None:
+            out = torch.empty(q.shape, dtype=q.dtype, device=q.device)
+        rc = _nat.attn_step(q, k_suf, v_suf, k_cache, v_cache, prefix_len, suffix_len, scale, out, workspace)
+        if rc is not None:
+            _check(rc, "lsp_attn_step")
+            return out
     _dev(q, k_suf, v_suf, k_cache, v_cache, prefix_len, suffix_len, cache_row_index, out)
     B, S, Hq, D = q.shape
     if out is None:
@@ -210,11 +231,17 @@ class AttnLayerTable:
         self.desc.cache_stride = _strides3(k_cache[0])
         self.desc.o_stride = _strides3(out[0])
         self.out = out
+        self.plain = (ctypes.addressof(self.desc), n, *[ctypes.addressof(a) for a in self.arrays])   # for the native module
 
 
 def attn_step_layers(table: AttnLayerTable, prefix_len, suffix_len, scale=0.0, workspace=None):
     """lsp_attn_step_layers: the attention of every layer of `table` in one launch.
     Returns the list of per-layer outputs (table.out)."""
+    if _nat is not None:
+        rc = _nat.attn_step_layers(table.plain, prefix_len, suffix_len, scale, workspace)
+        if rc is not None:
+            _check(rc, "lsp_attn_step_layers")
+            return table.out
     _dev(prefix_len, suffix_len)
     _need("prefix_len", prefix_len, torch.int32, (table.desc.B,))
     _need("suffix_len", suffix_len, torch.int32, (table.desc.B,))
@@ -235,16 +262,28 @@ def confidence_workspace_bytes(B, S, V) -> int:
     return lib().lsp_confidence_workspace_bytes(B, S, V)
 
 
+def _conf_out(t):
+    """Uninitialised (top1_id, top1_prob, margin) for the rows of t [B, S, ...]."""
+    shape, dev = t.shape[:2], t.device
+    return (torch.empty(shape, dtype=torch.int32, device=dev), torch.empty(shape, dtype=torch.float32, device=dev),
+            torch.empty(shape, dtype=torch.float32, device=dev))
+
+
 def confidence(logits, suffix_len=None, out=None, workspace=None):
     """lsp_confidence: logits [B,S,V] -> (top1_id int32, top1_prob f32, margin f32), [B,S]."""
+    if _nat is not None:
+        if out is None:
+            out = _conf_out(logits)
+        rc = _nat.confidence(logits, suffix_len, out, workspace)
+        if rc is not None:
+            _check(rc, "lsp_confidence")
+            return out
     _dev(logits, suffix_len)
     B, S, V = logits.shape
     if logits.stride(2) != 1:
         raise LspError("logits rows must be contiguous")
     if out is None:
-        out = (torch.empty((B, S), dtype=torch.int32, device=logits.device),
-               torch.empty((B, S), dtype=torch.float32, device=logits.device),
-               torch.empty((B, S), dtype=torch.float32, device=logits.device))
+        out = _conf_out(logits)
     _dev(*out)
     _need_conf_out(out, B, S)
     _need("suffix_len", suffix_len, torch.int32, (B,), optional=True)
@@ -284,6 +323,11 @@ def lm_head_confidence(hidden, weight, suffix_len=None, out=None, workspace=None
     """lsp_lm_head_confidence: hidden [B,S,K], weight [V,K] (bf16) ->
     (top1_id int32, top1_prob f32, margin f32), [B,S], of the logits hidden @ weight.T,
     which are never stored."""
+    if _nat is not None and out is not None and workspace is not None:
+        rc = _nat.lm_head_confidence(hidden, weight, suffix_len, out, workspace)
+        if rc is not None:
+            _check(rc, "lsp_lm_head_confidence")
+            return out
     _dev(hidden, weight, suffix_len)
     B, S, K = hidden.shape
     V = weight.shape[0]
@@ -292,9 +336,7 @@ def lm_head_confidence(hidden, weight, suffix_len=None, out=None, workspace=None
     if hidden.stride(2) != 1 or weight.stride(1) != 1:
         raise LspError("hidden and weight rows must be contiguous")
     if out is None:
-        out = (torch.empty((B, S), dtype=torch.int32, device=hidden.device),
-               torch.empty((B, S), dtype=torch.float32, device=hidden.device),
-               torch.empty((B, S), dtype=torch.float32, device=hidden.device))
+        out = _conf_out(hidden)
     _dev(*out)
     _need_conf_out(out, B, S)
     _need("suffix_len", suffix_len, torch.int32, (B,), optional=True)
@@ -338,6 +380,8 @@ class LayerTable:
         self.C = k_cache[0].shape[1]
         self.suf_bs = k_suf[0].stride(0)
         self.cache_bs = k_cache[0].stride(0)
+        self.plain = (*[ctypes.addressof(a) for a in self.arrays], self.kv_dtype, self.B, self.S, self.Hkv, self.D, self.C, n,
+                      self.suf_bs, self.cache_bs)      # for the native module
 
 
 def commit(margin, top1_id, bitmap, V, tau, window, min_commit, snap_enabled,
@@ -346,6 +390,12 @@ def commit(margin, top1_id, bitmap, V, tau, window, min_commit, snap_enabled,
     """lsp_commit.  Mutates tokens, prefix_len, suffix_len and the caches of
     `layers` in place.  Returns dict(stable_mask, raw_boundary, snapped_boundary,
     commit_len, status_flags, tau_used)."""
+    if _nat is not None and out is not None and (layers is not None or C is not None):
+        rc = _nat.commit(margin, top1_id, bitmap, prefix_len, suffix_len, tokens, None if layers is None else layers.plain, out,
+                         (V, tau, window, min_commit, snap_enabled, adaptive, alpha, beta, max_commit, 0 if C is None else C))
+        if rc is not None:
+            _check(rc, "lsp_commit")
+            return out
     _dev(margin, top1_id, bitmap, prefix_len, suffix_len, tokens)
     B, S = margin.shape
     dev = margin.device
@@ -396,6 +446,11 @@ def flip_update(top1_id, prefix_len, suffix_len, base_prefix_len, last_id, count
     """lsp_flip_update: accumulate counters (int64[4]: flips, positions compared, and the
     same two for sequences whose committed count lies in window = (lo, hi), inclusive);
     step_counts int32 [B,2], when given, receives this call's per-sequence counts."""
+    if _nat is not None:
+        lo, hi = (1, 0) if window is None else window
+        rc = _nat.flip_update(top1_id, prefix_len, suffix_len, base_prefix_len, last_id, counters, lo, hi, step_counts)
+        if rc is not None:
+            return _check(rc, "lsp_flip_update")
     _dev(top1_id, prefix_len, suffix_len, base_prefix_len, last_id, counters, step_counts)
     B, S = top1_id.shape
     _need("top1_id", top1_id, torch.int32, (B, S))

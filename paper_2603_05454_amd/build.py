@@ -1,4 +1,4 @@
-"""Build liblsp.so (the C-ABI HIP library) for gfx950, in-tree."""
+"""Build liblsp.so (the C-ABI HIP library) for gfx950 and the native part of its Python binding, in-tree."""
 import os
 import subprocess
 import sys
@@ -7,11 +7,25 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "liblsp.so")
+BINDING = os.path.join(HERE, "_binding.so")
 SOURCES = ["lsp_common.hip", "lsp_confidence.hip", "lsp_commit.hip", "lsp_attn.hip",
            "lsp_attn_f32.hip", "lsp_attn_bf16.hip", "lsp_scattered.hip", "lsp_lm_head.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-I", os.path.join(ROOT, "include"), "-I", CSRC, "-Wall", "-Wno-unused-result"]
+
+
+def binding_command():
+    """The marshalling module is host code against torch's own headers (tensor layout, current stream)."""
+    import sysconfig
+    import torch
+    from torch.utils.cpp_extension import include_paths
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    incs = [os.path.join(ROOT, "include"), *include_paths(), os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    return [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch.compiled_with_cxx11_abi())}", *[x for i in incs for x in ("-isystem", i)],
+            os.path.join(CSRC, "binding.cpp"), "-o", BINDING, "-L", libs, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
 
 
 def build(verbose: bool = False, jobs: int = 6) -> str:
@@ -36,11 +50,12 @@ def build(verbose: bool = False, jobs: int = 6) -> str:
                 if p.poll() is None:
                     p.wait()
                     break
+    procs.append(("binding.cpp", subprocess.Popen(binding_command(), stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)))
     for src, p in procs:
         out, _ = p.communicate()
         lines = [l for l in out.splitlines() if "packed-fp32-ops" not in l]
         if p.returncode != 0:
-            raise RuntimeError(f"hipcc failed on {src}:\n" + "\n".join(lines))
+            raise RuntimeError(f"the compiler failed on {src}:\n" + "\n".join(lines))
         if verbose and lines:
             print("\n".join(lines))
     subprocess.run([hipcc, "--offload-arch=gfx950", "-shared", "-fPIC", *objs, "-o", LIB], check=True)

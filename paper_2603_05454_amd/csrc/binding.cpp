@@ -1,0 +1,292 @@
+// Native argument marshalling of the Python binding: each function takes the
+// tensors of the Python call of the same name, checks what a plain pointer would
+// hide (device, element type, shape, layout) and calls the C entry point on the
+// current stream.  It answers with the call's status, or with None when any
+// argument is not in its ordinary form - the caller then takes the general path
+// in Python, which raises the error or handles the rarer form.
+//
+// Why: through ctypes a call cost 9-18 us on the host (attribute reads, checks and
+// conversions of up to 20 arguments in the interpreter), more than many of
+// the kernels behind it take; here it is 3-7 us, most of it the launch itself.
+#include <Python.h>
+#include <hip/hip_runtime_api.h>
+
+#include <ATen/core/Tensor.h>
+#include <c10/hip/HIPStream.h>
+#include <torch/csrc/autograd/python_variable.h>
+
+#include "lsp.h"
+
+namespace {
+
+// Entry points of the loaded liblsp.so (addresses handed over once by bind()).
+struct Entry {
+  decltype(&lsp_attn_workspace_bytes) attn_workspace_bytes;
+  decltype(&lsp_attn_step) attn_step;
+  decltype(&lsp_attn_step_layers) attn_step_layers;
+  decltype(&lsp_confidence_workspace_bytes) confidence_workspace_bytes;
+  decltype(&lsp_confidence) confidence;
+  decltype(&lsp_lm_head_confidence_workspace_bytes) lm_head_confidence_workspace_bytes;
+  decltype(&lsp_lm_head_confidence) lm_head_confidence;
+  decltype(&lsp_commit) commit;
+  decltype(&lsp_flip_update) flip_update;
+} g;
+constexpr int kEntries = 9;
+
+const at::Tensor *tensor(PyObject *o) { return THPVariable_Check(o) ? &THPVariable_Unpack(o) : nullptr; }
+const at::Tensor *device_tensor(PyObject *o) {
+  const at::Tensor *t = tensor(o);
+  return t && t->is_cuda() ? t : nullptr;
+}
+// a contiguous device tensor of this element type and, where given, shape
+const at::Tensor *plain(PyObject *o, at::ScalarType type, int64_t d0 = -1, int64_t d1 = -1) {
+  const at::Tensor *t = device_tensor(o);
+  if (!t || t->scalar_type() != type || !t->is_contiguous()) return nullptr;
+  if (d0 < 0) return t;
+  if (d1 < 0) return t->dim() == 1 && t->size(0) == d0 ? t : nullptr;
+  return t->dim() == 2 && t->size(0) == d0 && t->size(1) == d1 ? t : nullptr;
+}
+bool element_type(const at::Tensor &t, int32_t &type) {
+  if (t.scalar_type() == at::kBFloat16) type = LSP_BF16;
+  else if (t.scalar_type() == at::kFloat) type = LSP_F32;
+  else return false;
+  return true;
+}
+template <typename T>
+T *data(const at::Tensor *t) {
+  return t ? static_cast<T *>(t->mutable_data_ptr()) : nullptr;
+}
+int64_t bytes_of(const at::Tensor *t) { return t ? int64_t(t->nbytes()) : 0; }
+void *stream() { return c10::hip::getCurrentHIPStream().stream(); }
+bool shape4(const at::Tensor &t, int64_t a, int64_t b, int64_t c, int64_t d) {
+  return t.dim() == 4 && t.size(0) == a && t.size(1) == b && t.size(2) == c && t.size(3) == d;
+}
+bool strides3(const at::Tensor &t, int64_t (&s)[3]) {
+  if (t.stride(3) != 1) return false;
+  for (int k = 0; k < 3; ++k) s[k] = t.stride(k);
+  return true;
+}
+bool same_strides(const at::Tensor &a, const at::Tensor &b) { return a.strides() == b.strides(); }
+
+PyObject *status(int32_t rc) { return PyLong_FromLong(rc); }
+#define ORDINARY(cond) \
+  if (!(cond)) Py_RETURN_NONE
+
+PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  if (n != kEntries) {
+    PyErr_Format(PyExc_TypeError, "bind: %d addresses expected", kEntries);
+    return nullptr;
+  }
+  void *p[kEntries];
+  for (int k = 0; k < kEntries; ++k) p[k] = PyLong_AsVoidPtr(a[k]);
+  if (PyErr_Occurred()) return nullptr;
+  g.attn_workspace_bytes = reinterpret_cast<decltype(g.attn_workspace_bytes)>(p[0]);
+  g.attn_step = reinterpret_cast<decltype(g.attn_step)>(p[1]);
+  g.attn_step_layers = reinterpret_cast<decltype(g.attn_step_layers)>(p[2]);
+  g.confidence_workspace_bytes = reinterpret_cast<decltype(g.confidence_workspace_bytes)>(p[3]);
+  g.confidence = reinterpret_cast<decltype(g.confidence)>(p[4]);
+  g.lm_head_confidence_workspace_bytes = reinterpret_cast<decltype(g.lm_head_confidence_workspace_bytes)>(p[5]);
+  g.lm_head_confidence = reinterpret_cast<decltype(g.lm_head_confidence)>(p[6]);
+  g.commit = reinterpret_cast<decltype(g.commit)>(p[7]);
+  g.flip_update = reinterpret_cast<decltype(g.flip_update)>(p[8]);
+  Py_RETURN_NONE;
+}
+
+// (q, k_suf, v_suf, k_cache, v_cache, prefix_len, suffix_len, scale, out, workspace)
+PyObject *attn_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  ORDINARY(n == 10 && g.attn_step);
+  const at::Tensor *q = device_tensor(a[0]), *ks = device_tensor(a[1]), *vs = device_tensor(a[2]), *kc = device_tensor(a[3]),
+                   *vc = device_tensor(a[4]), *out = device_tensor(a[8]);
+  ORDINARY(q && ks && vs && kc && vc && out && q->dim() == 4 && ks->dim() == 4 && kc->dim() == 4);
+  const int64_t B = q->size(0), S = q->size(1), Hq = q->size(2), D = q->size(3), Hkv = ks->size(2), C = kc->size(1);
+  const auto type = q->scalar_type();
+  ORDINARY(ks->scalar_type() == type && vs->scalar_type() == type && kc->scalar_type() == type && vc->scalar_type() == type &&
+           out->scalar_type() == type);
+  ORDINARY(shape4(*ks, B, S, Hkv, D) && shape4(*vs, B, S, Hkv, D) && shape4(*kc, B, C, Hkv, D) && shape4(*vc, B, C, Hkv, D) &&
+           shape4(*out, B, S, Hq, D) && same_strides(*ks, *vs) && same_strides(*kc, *vc));
+  const at::Tensor *pl = plain(a[5], at::kInt, B), *sl = plain(a[6], at::kInt, B);
+  ORDINARY(pl && sl);
+  lsp_attn_desc d = {};
+  ORDINARY(element_type(*q, d.dtype));
+  d.B = int32_t(B); d.S = int32_t(S); d.Hq = int32_t(Hq); d.Hkv = int32_t(Hkv); d.D = int32_t(D); d.C = int32_t(C);
+  d.scale = float(PyFloat_AsDouble(a[7]));
+  if (PyErr_Occurred()) return nullptr;
+  ORDINARY(strides3(*q, d.q_stride) && strides3(*ks, d.kv_suf_stride) && strides3(*kc, d.cache_stride) && strides3(*out, d.o_stride));
+  const at::Tensor *ws = a[9] == Py_None ? nullptr : device_tensor(a[9]);
+  const int64_t need = int64_t(g.attn_workspace_bytes(&d));
+  ORDINARY(bytes_of(ws) >= need);
+  return status(g.attn_step(&d, q->const_data_ptr(), ks->const_data_ptr(), vs->const_data_ptr(), kc->const_data_ptr(),
+                            vc->const_data_ptr(), data<int32_t>(pl), data<int32_t>(sl), data<void>(out), data<void>(ws),
+                            size_t(bytes_of(ws)), stream()));
+}
+
+// (descriptor address, layers, six table addresses, B, prefix_len, suffix_len, scale)
+PyObject *attn_step_layers(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  ORDINARY(n == 5 && g.attn_step_layers && PyTuple_Check(a[0]) && PyTuple_GET_SIZE(a[0]) == 8);
+  void *p[8];
+  for (int k = 0; k < 8; ++k) p[k] = PyLong_AsVoidPtr(PyTuple_GET_ITEM(a[0], k));
+  lsp_attn_desc *d = static_cast<lsp_attn_desc *>(p[0]);
+  const float scale = float(PyFloat_AsDouble(a[3]));
+  if (PyErr_Occurred()) return nullptr;
+  const at::Tensor *pl = plain(a[1], at::kInt, d->B), *sl = plain(a[2], at::kInt, d->B);
+  ORDINARY(pl && sl);
+  const at::Tensor *ws = a[4] == Py_None ? nullptr : device_tensor(a[4]);
+  lsp_attn_desc own = *d;
+  own.scale = scale;
+  ORDINARY(bytes_of(ws) >= int64_t(g.attn_workspace_bytes(&own)));
+  auto in = [&](int k) { return static_cast<const void *const *>(p[k]); };
+  return status(g.attn_step_layers(&own, int32_t(reinterpret_cast<intptr_t>(p[1])), in(2), in(3), in(4), in(5), in(6), data<int32_t>(pl),
+                                   data<int32_t>(sl), static_cast<void *const *>(p[7]), data<void>(ws), size_t(bytes_of(ws)),
+                                   stream()));
+}
+
+struct ConfOut {
+  int32_t *id;
+  float *prob, *margin;
+};
+bool conf_out(PyObject *o, int64_t B, int64_t S, ConfOut &r) {
+  if (!PyTuple_Check(o) || PyTuple_GET_SIZE(o) != 3) return false;
+  const at::Tensor *id = plain(PyTuple_GET_ITEM(o, 0), at::kInt, B, S), *prob = plain(PyTuple_GET_ITEM(o, 1), at::kFloat, B, S),
+                   *margin = plain(PyTuple_GET_ITEM(o, 2), at::kFloat, B, S);
+  if (!id || !prob || !margin) return false;
+  r = {data<int32_t>(id), data<float>(prob), data<float>(margin)};
+  return true;
+}
+
+// (logits, suffix_len or None, out, workspace or None)
+PyObject *confidence(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  ORDINARY(n == 4 && g.confidence);
+  const at::Tensor *z = device_tensor(a[0]);
+  int32_t type;
+  ORDINARY(z && z->dim() == 3 && z->stride(2) == 1 && element_type(*z, type));
+  const int64_t B = z->size(0), S = z->size(1), V = z->size(2);
+  const at::Tensor *sl = a[1] == Py_None ? nullptr : plain(a[1], at::kInt, B);
+  ORDINARY(sl || a[1] == Py_None);
+  ConfOut o;
+  ORDINARY(conf_out(a[2], B, S, o));
+  const at::Tensor *ws = a[3] == Py_None ? nullptr : device_tensor(a[3]);
+  ORDINARY(bytes_of(ws) >= int64_t(g.confidence_workspace_bytes(int32_t(B), int32_t(S), int32_t(V))));
+  return status(g.confidence(type, z->const_data_ptr(), int32_t(B), int32_t(S), int32_t(V), z->stride(1), z->stride(0),
+                             data<int32_t>(sl), o.id, o.prob, o.margin, data<void>(ws), size_t(bytes_of(ws)), stream()));
+}
+
+// (hidden, weight, suffix_len or None, out, workspace)
+PyObject *lm_head_confidence(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  ORDINARY(n == 5 && g.lm_head_confidence);
+  const at::Tensor *h = device_tensor(a[0]), *w = device_tensor(a[1]);
+  int32_t type;
+  ORDINARY(h && w && h->dim() == 3 && w->dim() == 2 && h->stride(2) == 1 && w->stride(1) == 1 && element_type(*h, type));
+  const int64_t B = h->size(0), S = h->size(1), K = h->size(2), V = w->size(0);
+  ORDINARY(w->size(1) == K && w->scalar_type() == h->scalar_type());
+  const at::Tensor *sl = a[2] == Py_None ? nullptr : plain(a[2], at::kInt, B);
+  ORDINARY(sl || a[2] == Py_None);
+  ConfOut o;
+  ORDINARY(conf_out(a[3], B, S, o));
+  const at::Tensor *ws = device_tensor(a[4]);
+  ORDINARY(ws && bytes_of(ws) >= int64_t(g.lm_head_confidence_workspace_bytes(int32_t(B), int32_t(S), int32_t(V))));
+  return status(g.lm_head_confidence(type, h->const_data_ptr(), w->const_data_ptr(), int32_t(B), int32_t(S), int32_t(K), int32_t(V),
+                                     h->stride(1), h->stride(0), w->stride(0), data<int32_t>(sl), o.id, o.prob, o.margin,
+                                     data<void>(ws), size_t(bytes_of(ws)), stream()));
+}
+
+PyObject *k_mask, *k_raw, *k_snapped, *k_len, *k_flags, *k_tau;  // keys of commit's result
+
+// (margin, top1_id, bitmap, prefix_len, suffix_len, tokens or None, layer table or None, out,
+//  (V, tau, window, min_commit, snap_enabled, adaptive, alpha, beta, max_commit, C))
+PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  ORDINARY(n == 9 && g.commit && PyDict_Check(a[7]) && PyTuple_Check(a[8]) && PyTuple_GET_SIZE(a[8]) == 10);
+  const at::Tensor *margin = device_tensor(a[0]);
+  ORDINARY(margin && margin->dim() == 2);
+  const int64_t B = margin->size(0), S = margin->size(1);
+  margin = plain(a[0], at::kFloat, B, S);
+  const at::Tensor *id = plain(a[1], at::kInt, B, S), *pl = plain(a[3], at::kInt, B), *sl = plain(a[4], at::kInt, B);
+  const at::Tensor *bm = device_tensor(a[2]);
+  ORDINARY(margin && id && pl && sl && bm && bm->is_contiguous() && (bm->scalar_type() == at::kInt || bm->scalar_type() == at::kUInt32));
+  const at::Tensor *tokens = a[5] == Py_None ? nullptr : device_tensor(a[5]);
+  ORDINARY(a[5] == Py_None || (tokens && tokens->dim() == 2 && plain(a[5], at::kInt, B, tokens->size(1))));
+  long i[10];
+  double f[10];
+  for (int k = 0; k < 10; ++k) {
+    PyObject *x = PyTuple_GET_ITEM(a[8], k);
+    if (k == 1 || k == 6 || k == 7) f[k] = PyFloat_AsDouble(x);
+    else i[k] = PyLong_AsLong(x);
+  }
+  if (PyErr_Occurred()) {  // a number of an unusual type
+    PyErr_Clear();
+    Py_RETURN_NONE;
+  }
+  ORDINARY(bm->numel() >= (i[0] + 31) / 32);
+  lsp_commit_desc d = {};
+  d.B = int32_t(B); d.S = int32_t(S); d.V = int32_t(i[0]); d.tau = float(f[1]); d.window = int32_t(i[2]); d.min_commit = int32_t(i[3]);
+  d.snap_enabled = int32_t(i[4]); d.adaptive = i[5] != 0; d.alpha = float(f[6]); d.beta = float(f[7]); d.max_commit = int32_t(i[8]);
+  d.T = tokens ? int32_t(tokens->size(1)) : 0;
+  const void *const *tab[4] = {nullptr, nullptr, nullptr, nullptr};
+  if (a[6] != Py_None) {  // (four table addresses, kv_dtype, B, S, Hkv, D, C, layers, suffix and cache batch strides)
+    ORDINARY(PyTuple_Check(a[6]) && PyTuple_GET_SIZE(a[6]) == 13);
+    long long t[13];
+    for (int k = 0; k < 13; ++k) t[k] = PyLong_AsLongLong(PyTuple_GET_ITEM(a[6], k));
+    if (PyErr_Occurred()) return nullptr;
+    ORDINARY(t[5] == B && t[6] == S);
+    for (int k = 0; k < 4; ++k) tab[k] = reinterpret_cast<const void *const *>(t[k]);
+    d.kv_dtype = int32_t(t[4]); d.Hkv = int32_t(t[7]); d.D = int32_t(t[8]); d.C = int32_t(t[9]); d.num_layers = int32_t(t[10]);
+    d.suf_batch_stride = t[11]; d.cache_batch_stride = t[12];
+  } else {
+    d.C = int32_t(i[9]);
+  }
+  auto per_sequence = [&](PyObject *key, at::ScalarType type) -> const at::Tensor * {
+    PyObject *o = PyDict_GetItemWithError(a[7], key);
+    return o ? plain(o, type, B) : nullptr;
+  };
+  PyObject *mask_o = PyDict_GetItemWithError(a[7], k_mask);
+  const at::Tensor *mask = mask_o ? plain(mask_o, at::kByte, B, S) : nullptr, *raw = per_sequence(k_raw, at::kInt),
+                   *snapped = per_sequence(k_snapped, at::kInt), *len = per_sequence(k_len, at::kInt),
+                   *flags = per_sequence(k_flags, at::kInt), *tau = per_sequence(k_tau, at::kFloat);
+  if (PyErr_Occurred()) return nullptr;
+  ORDINARY(mask && raw && snapped && len && flags && tau);
+  return status(g.commit(&d, data<float>(margin), data<int32_t>(id), data<uint32_t>(bm), tab[0], tab[1],
+                         const_cast<void *const *>(tab[2]), const_cast<void *const *>(tab[3]), data<int32_t>(tokens), data<int32_t>(pl),
+                         data<int32_t>(sl), data<uint8_t>(mask), data<int32_t>(raw), data<int32_t>(snapped), data<int32_t>(len),
+                         data<int32_t>(flags), data<float>(tau), nullptr, 0, stream()));
+}
+
+// (top1_id, prefix_len, suffix_len, base_prefix_len, last_id, counters, window_lo, window_hi, step_counts or None)
+PyObject *flip_update(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  ORDINARY(n == 9 && g.flip_update);
+  const at::Tensor *id = device_tensor(a[0]), *last = device_tensor(a[4]);
+  ORDINARY(id && id->dim() == 2 && last && last->dim() == 2);
+  const int64_t B = id->size(0), S = id->size(1), G = last->size(1);
+  id = plain(a[0], at::kInt, B, S);
+  last = plain(a[4], at::kInt, B, G);
+  const at::Tensor *pl = plain(a[1], at::kInt, B), *sl = plain(a[2], at::kInt, B), *base = plain(a[3], at::kInt, B),
+                   *counters = plain(a[5], at::kLong, 4), *steps = a[8] == Py_None ? nullptr : plain(a[8], at::kInt, B, 2);
+  ORDINARY(id && last && pl && sl && base && counters && (steps || a[8] == Py_None));
+  const long lo = PyLong_AsLong(a[6]), hi = PyLong_AsLong(a[7]);
+  if (PyErr_Occurred()) {
+    PyErr_Clear();
+    Py_RETURN_NONE;
+  }
+  return status(g.flip_update(data<int32_t>(id), int32_t(B), int32_t(S), int32_t(G), data<int32_t>(pl), data<int32_t>(sl),
+                              data<int32_t>(base), data<int32_t>(last), data<int64_t>(counters), int32_t(lo), int32_t(hi),
+                              data<int32_t>(steps), stream()));
+}
+
+template <typename F>
+PyMethodDef fast(const char *name, F f) {
+  return {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr};
+}
+PyMethodDef methods[] = {fast("bind", bind), fast("attn_step", attn_step), fast("attn_step_layers", attn_step_layers),
+                         fast("confidence", confidence), fast("lm_head_confidence", lm_head_confidence), fast("commit", commit),
+                         fast("flip_update", flip_update), {nullptr, nullptr, 0, nullptr}};
+PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
+
+}  // namespace
+
+PyMODINIT_FUNC PyInit__binding() {
+  k_mask = PyUnicode_InternFromString("stable_mask");
+  k_raw = PyUnicode_InternFromString("raw_boundary");
+  k_snapped = PyUnicode_InternFromString("snapped_boundary");
+  k_len = PyUnicode_InternFromString("commit_len");
+  k_flags = PyUnicode_InternFromString("status_flags");
+  k_tau = PyUnicode_InternFromString("tau_used");
+  return PyModule_Create(&module);
+}
