@@ -13,7 +13,7 @@
 // copies, per (layer, K|V, sequence), the single contiguous block of
 // L * Hkv * D elements from the suffix buffer to cache row P with 16-byte
 // loads and stores; the block length is read from device memory, so the host
-// never learns L and the grid is sized for the worst case with early exit.
+// never learns L.
 #include <limits.h>
 
 #include "lsp_common.h"
@@ -198,51 +198,95 @@ struct LayerPtrs {
   char *dst[2 * kMaxLayersPerLaunch];
 };
 
-// grid: (workgroups per block copy, B, 2 * layers in this launch); a workgroup walks the
-// block in chunks of NT*VECS*16 bytes with stride gridDim.x chunks.  (The commit length is
-// only known on the device; a grid sized for S rows per copy costs a quarter of a
-// millisecond in launch-and-exit alone when a decode step commits a few rows.)
+// grid: (workgroups, groups of 64 sequences).  The commit lengths are only known on the
+// device, so a fixed number of workgroups (eight per compute unit) shares the work there: the
+// chunks of 8 KB of all blocks, numbered layer (K, V) by layer, sequence by sequence, so
+// that the chunks being copied at a time are neighbours in memory.  The loads of the next two
+// chunks are in flight while one is stored.
+// Bound by HBM where suffixes are committed whole, by latency where a few rows are.  A grid
+// sized for whole suffixes with a fixed set of chunks per workgroup (64 K workgroups) copied
+// 300 rows x 8 sequences x 32 layers in 440 us (now 431, 5.8 TB/s) but took 38 us for the
+// 2 rows x 16 sequences of an ordinary decode step, nearly all of it starting workgroups that
+// had nothing to do (now 8.2); fewer workgroups with those fixed sets cost 5 % on
+// the large copy, because neighbouring chunks were no longer copied together.
 // prefix_len already holds P + L; the block starts at row P = prefix_len - L.
-template <int NT, int VECS>
-__global__ __launch_bounds__(NT) void append_kernel(
-    LayerPtrs ptrs, int64_t row_bytes, int64_t suf_batch_bytes, int64_t cache_batch_bytes,
+constexpr int kAppendThreads = 256, kAppendVecs = 2, kAppendDepth = 3, kAppendGrid = 2048;
+__global__ __launch_bounds__(kAppendThreads) void append_kernel(
+    LayerPtrs ptrs, int copies, int B, int64_t row_bytes, int64_t suf_batch_bytes, int64_t cache_batch_bytes,
     const int32_t *__restrict__ prefix_len, const int32_t *__restrict__ commit_len) {
+  constexpr int NT = kAppendThreads, VECS = kAppendVecs, DEP = kAppendDepth;
   constexpr int kBytes = NT * VECS * 16;
-  const int b = blockIdx.y;
-  const int L = commit_len[b];
-  const int64_t total = int64_t(L) * row_bytes;
-  if (int64_t(blockIdx.x) * kBytes >= total) return;
-  const int P = prefix_len[b] - L;
-  const char *src = ptrs.src[blockIdx.z] + int64_t(b) * suf_batch_bytes;
-  char *dst = ptrs.dst[blockIdx.z] + int64_t(b) * cache_batch_bytes + int64_t(P) * row_bytes;
-  for (int64_t off0 = int64_t(blockIdx.x) * kBytes; off0 < total; off0 += int64_t(gridDim.x) * kBytes) {
-    u32x4 v[VECS];
-#pragma unroll
-    for (int k = 0; k < VECS; ++k) {
-      const int64_t o = off0 + (int64_t(k) * NT + threadIdx.x) * 16;
-      if (o < total) v[k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src + o));
+  const int lane = threadIdx.x & (kWave - 1);
+  // lane l looks after sequence 64 * blockIdx.y + l (in every wave alike)
+  const int b0 = blockIdx.y * kWave, bl = min(b0 + lane, B - 1);
+  const int L = b0 + lane < B ? commit_len[bl] : 0;
+  const int P = prefix_len[bl] - L;
+  const int chunks = int((int64_t(L) * row_bytes + kBytes - 1) / kBytes);
+  int upto = chunks;  // chunks of this group's sequences up to and including this lane's: a scan on the DPP network
+  upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xf, 0xf, false);  // row_shr:1
+  upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xf, 0xf, false);  // row_shr:2
+  upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xf, 0xf, false);  // row_shr:4
+  upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xf, 0xf, false);  // row_shr:8
+  upto += __builtin_amdgcn_update_dpp(0, upto, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+  upto += __builtin_amdgcn_update_dpp(0, upto, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+  const int total = __builtin_amdgcn_readlane(upto, kWave - 1);
+  if (total == 0) return;
+
+  struct Chunk {
+    const char *src;
+    char *dst;
+    int64_t left;  // bytes of the block from here on
+  };
+  int z = 0, rem = blockIdx.x;  // copy (layer, K or V) and chunk of it
+  auto locate = [&]() {
+    if (rem >= total) {
+      const int q = rem / total;
+      z += q;
+      rem -= q * total;
     }
+    Chunk c = {nullptr, nullptr, 0};
+    if (z >= copies) return c;
+    const int s = __popcll(__ballot(upto <= rem));  // first sequence whose chunks reach beyond rem
+    const int first = __builtin_amdgcn_readlane(upto, s) - __builtin_amdgcn_readlane(chunks, s);
+    const int64_t off = int64_t(rem - first) * kBytes;
+    c.src = ptrs.src[z] + int64_t(b0 + s) * suf_batch_bytes + off;
+    c.dst = ptrs.dst[z] + int64_t(b0 + s) * cache_batch_bytes + int64_t(__builtin_amdgcn_readlane(P, s)) * row_bytes + off;
+    c.left = int64_t(__builtin_amdgcn_readlane(L, s)) * row_bytes - off;
+    rem += gridDim.x;
+    return c;
+  };
+  Chunk c[DEP];
+  u32x4 v[DEP][VECS];
+  auto load = [&](int d) {
+    c[d] = locate();
 #pragma unroll
     for (int k = 0; k < VECS; ++k) {
-      const int64_t o = off0 + (int64_t(k) * NT + threadIdx.x) * 16;
-      if (o < total) __builtin_nontemporal_store(v[k], reinterpret_cast<u32x4 *>(dst + o));
+      const int o = (k * NT + int(threadIdx.x)) * 16;
+      if (o < c[d].left) v[d][k] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(c[d].src + o));
+    }
+  };
+#pragma unroll
+  for (int d = 0; d < DEP - 1; ++d) load(d);
+  for (;;) {
+#pragma unroll
+    for (int d = 0; d < DEP; ++d) {
+      load((d + DEP - 1) % DEP);
+      if (c[d].left == 0) return;
+#pragma unroll
+      for (int k = 0; k < VECS; ++k) {
+        const int o = (k * NT + int(threadIdx.x)) * 16;
+        if (o < c[d].left) __builtin_nontemporal_store(v[d][k], reinterpret_cast<u32x4 *>(c[d].dst + o));
+      }
     }
   }
 }
 
-template <int NT, int VECS>
 void launch_append(const LayerPtrs &p, int64_t max_bytes, int B, int nl, hipStream_t st, int64_t row_bytes,
                    int64_t suf_bb, int64_t cache_bb, const int32_t *prefix_len, const int32_t *commit_len) {
-  constexpr int kBytes = NT * VECS * 16;
-  // enough workgroups to fill the chip when whole suffixes are committed (about 64 K in all), never more
-  // than the block has chunks
-  const int64_t all_chunks = (max_bytes + kBytes - 1) / kBytes;
-  const int64_t copies = int64_t(B) * 2 * nl;
-  int64_t per_copy = (65536 + copies - 1) / copies;
-  if (per_copy > all_chunks) per_copy = all_chunks;
-  if (per_copy < 1) per_copy = 1;
-  const unsigned chunks = unsigned(per_copy);
-  append_kernel<NT, VECS><<<dim3(chunks, B, 2 * nl), NT, 0, st>>>(p, row_bytes, suf_bb, cache_bb, prefix_len, commit_len);
+  constexpr int kBytes = kAppendThreads * kAppendVecs * 16;
+  const int64_t most = (max_bytes + kBytes - 1) / kBytes * (B < kWave ? B : kWave) * 2 * nl;
+  append_kernel<<<dim3(unsigned(most < kAppendGrid ? most : kAppendGrid), (B + kWave - 1) / kWave), kAppendThreads, 0, st>>>(
+      p, 2 * nl, B, row_bytes, suf_bb, cache_bb, prefix_len, commit_len);
 }
 
 }  // namespace
@@ -319,10 +363,7 @@ extern "C" int32_t lsp_commit(const lsp_commit_desc *d, const float *margin, con
         p.src[l] = nullptr;
         p.dst[l] = nullptr;
       }
-      // 256 threads x two 16-byte vectors per thread: the fastest of the shapes
-      // measured (1..8 vectors, 256..1024 threads) when only the first rows of
-      // every block are live, and within 3 % of the best for full blocks
-      launch_append<256, 2>(p, max_bytes, d->B, nl, st, row_bytes, suf_bb, cache_bb, prefix_len, commit_len);
+      launch_append(p, max_bytes, d->B, nl, st, row_bytes, suf_bb, cache_bb, prefix_len, commit_len);
       LSP_CHECK_LAUNCH("lsp_commit: append launch");
     }
   }

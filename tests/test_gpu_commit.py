@@ -227,6 +227,23 @@ def test_many_layers_more_than_one_launch(lsp, oracle):
 
 
 # ---- adaptive threshold (Section 3.2 targeted block sizing, Eq. 2) and commit cap (Table 2) ----
+@pytest.mark.parametrize("B,S,heads,layers", [(1, 1, 1, 1), (3, 70, 1, 2), (64, 9, 8, 2), (65, 9, 8, 1), (130, 40, 4, 1), (2, 700, 40, 3)])
+def test_append_work_shared_over_sequences(lsp, oracle, B, S, heads, layers):
+    """Blocks of zero, one and many 8 KB chunks with remainders, sequences that commit nothing between others that do,
+    the edges of the groups of 64 sequences, more chunks than the launch has workgroups (the last one)."""
+    g = torch.Generator().manual_seed(B + S)
+    w = W.scaled(W.C2, B=B, S=S, P=5, C=S + 5, Hq=heads, Hkv=heads, D=8 if heads == 1 else 64, layers=layers, seed=500 + B)
+    kv = [W.make_layer_kv(w, i) for i in range(layers)]
+    n = torch.randint(0, S + 1, (B,), generator=g, dtype=torch.int32)
+    n[0] = S
+    stable = torch.randint(0, S + 1, (B, 1), generator=g)
+    stable[0] = S
+    margin = torch.where(torch.arange(S).view(1, S) < stable, 1.0, 0.0)
+    ids = torch.randint(0, V, (B, S), generator=g, dtype=torch.int32)
+    _both(lsp, oracle, margin, ids, _bitmap([DELIM]), V, 0.5, 3, 0, 1, torch.full((B,), 5, dtype=torch.int32), n,
+          tokens=W.make_tokens(W.scaled(w, V=V), w.C), layers=kv)
+
+
 @pytest.mark.parametrize("alpha,beta", [(0.25, 0.5), (0.5, 0.5), (0.2, 1.0), (0.75, 0.75)])
 def test_adaptive_every_small_margin_vector(lsp, oracle, alpha, beta):
     N = 5
