@@ -12,12 +12,12 @@ struct AttnArgs {
   float scale;
   int64_t qs[3], ks[3], cs[3], os[3];  // element strides: batch, row, head
   void *workspace;
-  int32_t unit_group;  // set by the bf16 launcher: units per placement group
+  int32_t unit_group, spread, layers, rep, chunk;  // placement of the workgroups, set by the bf16 launcher
   const int32_t *cache_rows;  // gather form only: key t < P_b of sequence b is cache row cache_rows[b*C + t]; else null
 };
 
 // Operands of several layers for ONE launch (lsp_attn_step_layers): passed to the
-// kernels by value, the layer is the slow grid index.  n = 0: single-layer call,
+// kernels by value, the layer is the slow index of the placement.  n = 0: single-layer call,
 // the pointers in AttnArgs are used as they are.
 constexpr int kMaxAttnLayers = 32;
 struct AttnLayers {
@@ -26,15 +26,12 @@ struct AttnLayers {
   const void *k_cache[kMaxAttnLayers], *v_cache[kMaxAttnLayers];
   void *out[kMaxAttnLayers];
 };
-// This workgroup's layer (grid index y) replaces the operand pointers.
-__device__ __forceinline__ AttnArgs for_layer(const AttnArgs &in, const AttnLayers &L) {
-  AttnArgs a = in;
+// This workgroup's layer replaces the operand pointers.
+__device__ __forceinline__ void for_layer(AttnArgs &a, const AttnLayers &L, int l) {
   if (L.n > 0) {
-    const int l = blockIdx.y;
     a.q = L.q[l]; a.k_suf = L.k_suf[l]; a.v_suf = L.v_suf[l];
     a.k_cache = L.k_cache[l]; a.v_cache = L.v_cache[l]; a.out = L.out[l];
   }
-  return a;
 }
 
 // Cache row that holds key t (t < P_b) of sequence b.

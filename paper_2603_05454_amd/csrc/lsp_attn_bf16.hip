@@ -218,36 +218,66 @@ constexpr int kShortSuffix = 64;  // sequences with at most this many active row
 // without a query, a tile with two active waves is faster than two key-split workgroups - 38 against
 // 50 us per C5 layer - while a tile with one active wave is slower than one key-split workgroup)
 constexpr int kShortSuffixPipe = 32;
+constexpr int kGridBits = 20;  // a grid dimension is limited in THREADS to 2^32: larger launches go on in y
 struct Place {
-  int b, g, h, q0;
+  int layer, b, g, h, q0;
   bool valid;
 };
+// Units are numbered over layers, sequences and KV heads.  When they are few, each is cut into
+// `spread` pieces (runs of its (head, tile) list) so that every XCD gets as many: four KV heads of
+// one sequence kept four of the eight XCDs idle (28 query heads, one layer, prefix 4096, suffix
+// 1024: 234 us whole, 139 us in two pieces).
 __device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
   Place p;
   const int QT = (a.S + qtile - 1) / qtile;
-  const int rep = a.Hq / a.Hkv;
-  const int per_unit = rep * QT;
-  const int n = blockIdx.x;
+  const int rep = a.rep, chunk = a.chunk;
+  const int n = blockIdx.y << kGridBits | blockIdx.x;
   const int m8 = n >> 3;
   const int G = a.unit_group;
-  const int grp = m8 / (G * per_unit), r = m8 % (G * per_unit);
-  const int wu = r / G;
-  const int unit = (grp * G + r % G) * 8 + (n & 7);
-  p.valid = unit < a.B * a.Hkv;
+  const int grp = m8 / (G * chunk), r = m8 - grp * (G * chunk);
+  int wu = r / G, unit = (grp * G + r - wu * G) * 8 + (n & 7), layer = 0;
+  // (an integer division is some forty dependent instructions on the way to the first load)
+  if (a.spread > 1) {
+    const int piece = unit;
+    unit = piece / a.spread;
+    wu += (piece - unit * a.spread) * chunk;
+  }
+  const int units = a.B * a.Hkv;
+  if (a.layers > 1) {
+    layer = unit / units;
+    unit -= layer * units;
+  }
+  p.valid = layer < a.layers && unit < units && wu < rep * QT;
+  p.layer = layer;
   p.b = unit / a.Hkv;
-  p.g = unit % a.Hkv;
-  p.h = p.g * rep + wu / QT;
-  p.q0 = (wu % QT) * qtile;
+  p.g = unit - p.b * a.Hkv;
+  const int hr = wu / QT;
+  p.h = p.g * rep + hr;
+  p.q0 = (wu - hr * QT) * qtile;
   return p;
 }
-// group size (stored in a.unit_group) and number of workgroups of that placement
-inline int64_t place_grid(AttnArgs &a, int qtile) {
-  const int64_t QT = (a.S + qtile - 1) / qtile;
-  const int64_t units8 = (int64_t(a.B) * a.Hkv + 7) / 8;  // units per XCD
-  int64_t G = units8 < kUnitGroup ? units8 : kUnitGroup;
+// fields of that placement in `a`, and its number of workgroups
+inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile) {
+  const int64_t QT = (a.S + qtile - 1) / qtile, per_unit = a.Hq / a.Hkv * QT;
+  a.layers = layers.n > 0 ? layers.n : 1;
+  const int64_t units = int64_t(a.layers) * a.B * a.Hkv;
+  int64_t spread = 1;  // with 32 units or more an XCD has at most a quarter more than its share
+  if (units < 32)
+    while (units * spread % 8 != 0) spread *= 2;
+  a.spread = int32_t(spread < per_unit ? spread : per_unit);
+  const int64_t chunk = (per_unit + a.spread - 1) / a.spread;
+  a.rep = a.Hq / a.Hkv;
+  a.chunk = int32_t(chunk);
+  const int64_t pieces8 = (units * a.spread + 7) / 8;  // pieces per XCD
+  const int64_t G = pieces8 < kUnitGroup ? pieces8 : kUnitGroup;
   a.unit_group = int32_t(G);
-  const int64_t groups = (units8 + G - 1) / G;
-  return groups * G * (a.Hq / a.Hkv) * QT * 8;
+  return (pieces8 + G - 1) / G * G * chunk * 8;
+}
+
+constexpr int64_t kMaxGrid = int64_t(0x7ff) << kGridBits;
+inline dim3 grid_of(int64_t nwg) {
+  const int64_t x = int64_t(1) << kGridBits;
+  return nwg <= x ? dim3(unsigned(nwg)) : dim3(unsigned(x), unsigned((nwg + x - 1) / x));
 }
 
 // Final step shared by both kernels: the WK partial results of every query
@@ -553,12 +583,15 @@ __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, 
   merge_store<D, WM, WK>(a, oacc, mref, lsum, smem, b, h, q0, N);
 }
 
-template <int D, int WM, int WK, bool GATHER>
+// ONE: a single layer, whose operand pointers need not wait for the placement (0.1 of 11 us)
+template <int D, int WM, int WK, bool GATHER, bool ONE>
 __global__ __launch_bounds__(64 * WM * WK, 2) void attn_bf16_kernel(AttnArgs a_in, AttnLayers layers) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
-  const AttnArgs a = for_layer(a_in, layers);
+  AttnArgs a = a_in;
+  if (ONE) a.layers = 1;
   const Place pl = place(a, 32 * WM);
   if (!pl.valid) return;
+  if (!ONE) for_layer(a, layers, pl.layer);
   const int N = min(max(a.suffix_len[pl.b], 0), a.S);
   if (pl.q0 >= N) return;
   const int P = min(max(a.prefix_len[pl.b], 0), a.C);
@@ -567,17 +600,16 @@ __global__ __launch_bounds__(64 * WM * WK, 2) void attn_bf16_kernel(AttnArgs a_i
 
 template <int D, int WM, int WK, bool GATHER>
 int32_t launch_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
-  const int64_t nwg = place_grid(a, 32 * WM);
-  if (nwg > 0x7fffffff) {
+  const int64_t nwg = place_grid(a, layers, 32 * WM);
+  if (nwg > kMaxGrid) {
     set_error("lsp_attn_step: launch of %lld workgroups is too large", (long long)nwg);
     return LSP_ERR_UNSUPPORTED;
   }
-  const dim3 grid(static_cast<unsigned>(nwg), layers.n > 0 ? layers.n : 1, 1);
   const size_t lds = size_t(WM * WK) * Geo<D>::WAVE_LDS + size_t(WM) * 32 * Geo<D>::KPITCH;  // wave regions + Q rows
-  auto kern = attn_bf16_kernel<D, WM, WK, GATHER>;
-  static std::atomic<uint64_t> configured{0};  // per instantiation, one bit per device
-  if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured, "lsp_attn_step: hipFuncSetAttribute")) return rc;
-  kern<<<grid, 64 * WM * WK, lds, st>>>(a, layers);
+  auto kern = layers.n == 0 ? attn_bf16_kernel<D, WM, WK, GATHER, true> : attn_bf16_kernel<D, WM, WK, GATHER, false>;
+  static std::atomic<uint64_t> configured[2];  // per instantiation, one bit per device
+  if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured[layers.n == 0], "lsp_attn_step: hipFuncSetAttribute")) return rc;
+  kern<<<grid_of(nwg), 64 * WM * WK, lds, st>>>(a, layers);
   LSP_CHECK_LAUNCH("lsp_attn_step: bf16 launch");
   return LSP_OK;
 }
@@ -593,7 +625,7 @@ struct TileGeo {
 
 template <int D, int WM, int OCC, int PD, bool GATHER>
 __global__ __launch_bounds__(64 * WM, OCC) void attn_bf16_tile_kernel(AttnArgs a_in, AttnLayers layers) {
-  const AttnArgs a = for_layer(a_in, layers);
+  AttnArgs a = a_in;
   using TG = TileGeo<D>;
   constexpr int NT = 64 * WM;
   constexpr int KK = D / 16;
@@ -605,6 +637,7 @@ __global__ __launch_bounds__(64 * WM, OCC) void attn_bf16_tile_kernel(AttnArgs a
 
   const Place pl = place(a, 32 * WM);
   if (!pl.valid) return;
+  for_layer(a, layers, pl.layer);
   const int b = pl.b, g = pl.g, h = pl.h, q0 = pl.q0;
   const int N = min(max(a.suffix_len[b], 0), a.S);
   const int P = min(max(a.prefix_len[b], 0), a.C);
@@ -762,8 +795,8 @@ __global__ __launch_bounds__(64 * WM, OCC) void attn_bf16_tile_kernel(AttnArgs a
 
 template <int D, int WM, int OCC, int PD, bool GATHER>
 int32_t launch_tile_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
-  const int64_t nwg = place_grid(a, 32 * WM);
-  if (nwg > 0x7fffffff) {
+  const int64_t nwg = place_grid(a, layers, 32 * WM);
+  if (nwg > kMaxGrid) {
     set_error("lsp_attn_step: launch of %lld workgroups is too large", (long long)nwg);
     return LSP_ERR_UNSUPPORTED;
   }
@@ -771,7 +804,7 @@ int32_t launch_tile_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
   auto kern = attn_bf16_tile_kernel<D, WM, OCC, PD, GATHER>;
   static std::atomic<uint64_t> configured{0};  // per instantiation, one bit per device
   if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured, "lsp_attn_step: hipFuncSetAttribute")) return rc;
-  kern<<<dim3(static_cast<unsigned>(nwg), layers.n > 0 ? layers.n : 1, 1), 64 * WM, lds, st>>>(a, layers);
+  kern<<<grid_of(nwg), 64 * WM, lds, st>>>(a, layers);
   LSP_CHECK_LAUNCH("lsp_attn_step: bf16 tile launch");
   return LSP_OK;
 }
@@ -829,13 +862,14 @@ __device__ __forceinline__ void ring_issue(RingLoad L, int jb, unsigned char *kd
 }
 template <int NS, int BS, bool GATHER>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_ring_kernel(AttnArgs a_in, AttnLayers layers) {
-  const AttnArgs a = for_layer(a_in, layers);
+  AttnArgs a = a_in;
   constexpr int D = 128, WM = 8, KK = D / 16, DB = D / 32;
   constexpr int TILE = 32 * D * 2, VBASE = NS * TILE;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
   const Place pl = place(a, 32 * WM);
   if (!pl.valid) return;
+  for_layer(a, layers, pl.layer);
   const int b = pl.b, g = pl.g, h = pl.h, q0 = pl.q0;
   const int N = min(max(a.suffix_len[b], 0), a.S);
   const int P = min(max(a.prefix_len[b], 0), a.C);
@@ -998,8 +1032,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 
 template <int NS, int BS, bool GATHER>
 int32_t launch_ring_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
-  const int64_t nwg = place_grid(a, 256);
-  if (nwg > 0x7fffffff) {
+  const int64_t nwg = place_grid(a, layers, 256);
+  if (nwg > kMaxGrid) {
     set_error("lsp_attn_step: launch of %lld workgroups is too large", (long long)nwg);
     return LSP_ERR_UNSUPPORTED;
   }
@@ -1010,7 +1044,7 @@ int32_t launch_ring_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
   auto kern = attn_bf16_ring_kernel<NS, BS, GATHER>;
   static std::atomic<uint64_t> configured{0};  // per instantiation, one bit per device
   if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured, "lsp_attn_step: hipFuncSetAttribute")) return rc;
-  kern<<<dim3(static_cast<unsigned>(nwg), layers.n > 0 ? layers.n : 1, 1), 512, lds, st>>>(a, layers);
+  kern<<<grid_of(nwg), 512, lds, st>>>(a, layers);
   LSP_CHECK_LAUNCH("lsp_attn_step: bf16 ring launch");
   return LSP_OK;
 }
@@ -1030,13 +1064,14 @@ int32_t launch_ring_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
 typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_pipe_kernel(AttnArgs a_in,
                                                                                                        AttnLayers layers) {
-  const AttnArgs a = for_layer(a_in, layers);
+  AttnArgs a = a_in;
   constexpr int D = 128, WM = 8, KK = D / 16, DB = D / 32, NS = 8;
   constexpr int TILE = 32 * D * 2, VBASE = NS * TILE;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
   const Place pl = place(a, 32 * WM);
   if (!pl.valid) return;
+  for_layer(a, layers, pl.layer);
   const int b = pl.b, g = pl.g, h = pl.h, q0 = pl.q0;
   const int N = min(max(a.suffix_len[b], 0), a.S);
   const int P = min(max(a.prefix_len[b], 0), a.C);
@@ -1170,8 +1205,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
 }
 
 int32_t launch_pipe(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
-  const int64_t nwg = place_grid(a, 256);
-  if (nwg > 0x7fffffff) {
+  const int64_t nwg = place_grid(a, layers, 256);
+  if (nwg > kMaxGrid) {
     set_error("lsp_attn_step: launch of %lld workgroups is too large", (long long)nwg);
     return LSP_ERR_UNSUPPORTED;
   }
@@ -1181,7 +1216,7 @@ int32_t launch_pipe(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
   auto kern = attn_bf16_pipe_kernel;
   static std::atomic<uint64_t> configured{0};
   if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured, "lsp_attn_step: hipFuncSetAttribute")) return rc;
-  kern<<<dim3(static_cast<unsigned>(nwg), layers.n > 0 ? layers.n : 1, 1), 512, lds, st>>>(a, layers);
+  kern<<<grid_of(nwg), 512, lds, st>>>(a, layers);
   LSP_CHECK_LAUNCH("lsp_attn_step: bf16 pipelined launch");
   return LSP_OK;
 }

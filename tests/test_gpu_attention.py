@@ -71,6 +71,27 @@ def test_f32_key_split_edges(lsp, oracle, D, P, N):
     _check_full(lsp, oracle, w, torch.tensor([P, P // 2], dtype=torch.int32), torch.tensor([N, max(1, N - 1)], dtype=torch.int32))
 
 
+@pytest.mark.parametrize("B,Hq,Hkv", [(1, 1, 1), (1, 2, 1), (1, 28, 4), (3, 28, 4), (5, 3, 3), (7, 5, 5), (31, 2, 1), (33, 2, 1)])
+@pytest.mark.parametrize("S", [40, 150])
+def test_every_unit_count_reaches_every_tile(lsp, oracle, B, Hq, Hkv, S):
+    """The placement cuts few (layer, sequence, KV head) units into pieces for the XCDs: unit counts around
+    8 and 32, tile lists that the piece count does not divide.  Several layers at once reach the same rows as
+    one layer at a time."""
+    w = W.scaled(W.C2, B=B, S=S, P=30, C=64, Hq=Hq, Hkv=Hkv, D=128, seed=500 + B + Hq)
+    pl = torch.tensor([(30 - b) % 31 for b in range(B)], dtype=torch.int32)
+    sl = torch.tensor([S - b for b in range(B)], dtype=torch.int32)
+    _check_full(lsp, oracle, w, pl, sl)
+    layers = [{k: v.cuda() for k, v in W.make_layer_kv(w, l, prefix_len=pl).items()} for l in range(3)]
+    names = ("q", "k_suf", "v_suf", "k_cache", "v_cache")
+    outs = [torch.full(L["q"].shape, 123.0, dtype=L["q"].dtype, device="cuda") for L in layers]
+    lsp.attn_step_layers(lsp.AttnLayerTable(*[[L[k] for L in layers] for k in names], outs), pl.cuda(), sl.cuda())
+    for L, got in zip(layers, outs):
+        one = torch.full(L["q"].shape, 123.0, dtype=L["q"].dtype, device="cuda")
+        lsp.attn_step(*[L[k] for k in names], pl.cuda(), sl.cuda(), out=one)
+        assert torch.equal(got != 123.0, one != 123.0)
+        assert (got.float() - one.float()).abs().max().item() <= TOL["bf16"]   # another launch size may take another kernel
+
+
 @pytest.mark.parametrize("dtype,B,Hq,S", [("f32", 2, 2, 150), ("bf16", 2, 2, 150), ("bf16", 8, 16, 320)])
 def test_large_scores_and_moving_maximum(lsp, oracle, dtype, B, Hq, S):
     """Scores spanning hundreds of units whose maximum keeps rising along the key
