@@ -270,13 +270,23 @@ PyObject *flip_update(PyObject *, PyObject *const *a, Py_ssize_t n) {
                               data<int32_t>(steps), stream()));
 }
 
-template <typename F>
-PyMethodDef fast(const char *name, F f) {
-  return {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(f)), METH_FASTCALL, nullptr};
+// No C++ exception may reach the interpreter: torch throws where a tensor has no strides or no
+// storage (sparse, batched by vmap) or there is no device, and the general path then raises it.
+template <PyObject *(*F)(PyObject *, PyObject *const *, Py_ssize_t)>
+PyObject *guarded(PyObject *self, PyObject *const *a, Py_ssize_t n) {
+  try {
+    return F(self, a, n);
+  } catch (...) {
+    Py_RETURN_NONE;
+  }
 }
-PyMethodDef methods[] = {fast("bind", bind), fast("attn_step", attn_step), fast("attn_step_layers", attn_step_layers),
-                         fast("confidence", confidence), fast("lm_head_confidence", lm_head_confidence), fast("commit", commit),
-                         fast("flip_update", flip_update), {nullptr, nullptr, 0, nullptr}};
+template <PyObject *(*F)(PyObject *, PyObject *const *, Py_ssize_t)>
+PyMethodDef fast(const char *name) {
+  return {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(guarded<F>)), METH_FASTCALL, nullptr};
+}
+PyMethodDef methods[] = {fast<bind>("bind"), fast<attn_step>("attn_step"), fast<attn_step_layers>("attn_step_layers"),
+                         fast<confidence>("confidence"), fast<lm_head_confidence>("lm_head_confidence"), fast<commit>("commit"),
+                         fast<flip_update>("flip_update"), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace
