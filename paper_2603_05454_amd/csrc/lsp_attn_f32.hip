@@ -109,7 +109,12 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a) {
     f32x4 s = s0 + s1;
     if (t0 + kTile > T) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) s[r] = t0 + 4 * grp + r < T ? s[r] : -INFINITY;
+      for (int r = 0; r < 4; ++r) {
+        const bool key = t0 + 4 * grp + r < T;
+        s[r] = key ? s[r] : -INFINITY;
+#pragma unroll
+        for (int c = 0; c < CV; ++c) vf[r][c] = key ? vf[r][c] : zero;  // (0 x an infinite last row would be NaN)
+      }
     }
     const float bm = group_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))) * sc;  // finite: key t0 is valid
     const float mn = fmaxf(m, bm);

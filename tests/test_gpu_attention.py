@@ -92,6 +92,16 @@ def test_every_unit_count_reaches_every_tile(lsp, oracle, B, Hq, Hkv, S):
         assert (got.float() - one.float()).abs().max().item() <= TOL["bf16"]   # another launch size may take another kernel
 
 
+def test_f32_infinite_value_in_the_last_row(lsp, oracle):
+    """Key tiles with a remainder repeat the last row with probability 0: an infinity there stays one and spoils nothing else."""
+    w = W.scaled(W.C2, dtype="f32", B=1, S=5, P=16, C=16, Hq=2, Hkv=2, D=64, seed=41)
+    kv, (pl, sl) = W.make_layer_kv(w, 0), W.make_lengths(w)
+    kv["v_suf"][0, 4, 0, 3] = float("inf")
+    got, ref = _run(lsp, kv, pl, sl), oracle.attention(**kv, prefix_len=pl, suffix_len=sl)
+    assert torch.isinf(ref[0, :, 0, 3]).all() and torch.isfinite(ref).sum() == ref.numel() - 5
+    assert torch.equal(torch.isinf(got), torch.isinf(ref)) and not torch.isnan(got).any()
+
+
 @pytest.mark.parametrize("dtype,B,Hq,S", [("f32", 2, 2, 150), ("bf16", 2, 2, 150), ("bf16", 8, 16, 320)])
 def test_large_scores_and_moving_maximum(lsp, oracle, dtype, B, Hq, S):
     """Scores spanning hundreds of units whose maximum keeps rising along the key
