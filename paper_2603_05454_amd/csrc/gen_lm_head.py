@@ -23,11 +23,11 @@ ALL loads in flight and the fragments of a step were read in a burst.  Here
 The statement takes the stage that step 0 sits in (`phase`) and enters the unrolled
 loop there.  Loads in flight at entry: steps 0 .. NSTG-1 of this tile, in order.
 
-K starts at a different step in different workgroups (`wrap`: the step after which the
-pointers go back to k = 0).  Rows are 8 KB apart for K = 4096, so with every workgroup at
-the same k the whole chip asks for pieces at a power-of-two distance and a few memory
-channels do all the work: nothing but the loads of a 1 GB weight matrix takes 218 us
-in step and 167 us (6.2 TB/s) staggered.
+Every tile is summed from k = 0 upwards, whatever its height, place and workgroup: a logit
+has the same bits wherever its row stands in the batch and however many rows are
+active, and equal weight rows give equal logits.  (Starting K at a different step in
+different workgroups would spread a power-of-two row pitch over the memory channels, but
+gives that up; the kernel starts its workgroups at different TIMES instead.)
 """
 import os
 
@@ -177,8 +177,6 @@ def generate(M):
         e(f".Lcold_{u}_%=:")
         e(f"s_cmp_eq_u32 {li}, %[ks]")
         e(f"s_cbranch_scc1 .Lswap_{u}_%=")
-        e(f"s_cmp_eq_u32 {li}, %[wrap]")
-        e(f"s_cbranch_scc1 .Lwrap_{u}_%=")
         # the end of K: the ragged step (lanes whose chunk lies beyond K fetch zeros), then steps wholly beyond it
         e(f"s_cmp_eq_u32 {li}, %[event]")
         e("s_cselect_b64 exec, %[zmask], -1")
@@ -188,11 +186,6 @@ def generate(M):
             e(f"v_mov_b32 v{p}, %[zlo]")
             e(f"v_mov_b32 v{p + 1}, %[zhi]")
         e("s_mov_b64 exec, -1")
-        e(f"s_branch .Lback_{u}_%=")
-        e(f".Lwrap_{u}_%=:")                        # end of the rows: on with k = 0
-        for p in range(M.wptr, M.hptr + 2 * M.LH, 2):
-            e(f"v_lshl_add_u64 {v(p, 2)}, {v(p, 2)}, 0, %[kback]")
-        e(f"s_mov_b32 {ev}, %[ks]")
         e(f"s_branch .Lback_{u}_%=")
         e(f".Lswap_{u}_%=:")
         e(f"s_mov_b32 {ev}, -1")
@@ -225,14 +218,14 @@ def text(M):
     clob = [f"v{r}" for r in range(2 * M.setr)] + [f"s{r}" for r in range(64, 71)] + ["scc", "memory"]
     t = f"""// GENERATED by gen_lm_head.py - do not edit; the pipeline and the register map are described there.
 // Expects in scope: f32x16 acc[{nv}]; u32x{2 * M.LW} wptr; u32x{2 * M.LH} hptr; u32x{2 * M.NK} addr[{M.NSTG}]; next;
-// uint32_t ldsw, ks, event, wrap, phase, go_on, zlo, zhi; uint64_t zmask, wstep, kback.
+// uint32_t ldsw, ks, event, phase, go_on, zlo, zhi; uint64_t zmask, wstep.
 asm volatile(
 {body}
     : {acc},
       "+{{{v(M.wptr, 2 * M.LW)}}}"(wptr), "+{{{v(M.hptr, 2 * M.LH)}}}"(hptr)
     : {", ".join(f'"{{{v(M.addr + 2 * M.NK * k, 2 * M.NK)}}}"(addr[{k}])' for k in range(M.NSTG))}, "{{{v(M.next, 1 if M.TR == 256 else 2 * M.LH)}}}"(next),
-      [ldsw] "s"(ldsw), [ks] "s"(ks), [event] "s"(event), [wrap] "s"(wrap), [phase] "s"(phase), [zlo] "s"(zlo), [zhi] "s"(zhi),
-      [more] "s"(go_on), [zmask] "s"(zmask), [wstep] "s"(wstep), [kback] "s"(kback)
+      [ldsw] "s"(ldsw), [ks] "s"(ks), [event] "s"(event), [phase] "s"(phase), [zlo] "s"(zlo), [zhi] "s"(zhi),
+      [more] "s"(go_on), [zmask] "s"(zmask), [wstep] "s"(wstep)
     : {", ".join(f'"{c}"' for c in clob)});
 """
     return t

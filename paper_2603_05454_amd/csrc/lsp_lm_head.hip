@@ -16,7 +16,7 @@
 //
 // Only ACTIVE rows are computed: tiles are cut from the list of them, over all
 // sequences (127 rows left in four buffers of 256 are one tile of 128, not four
-// of 256: 191 against 1122 us at 126 464 entries and K = 4096).
+// of 256: 212 against 1100 us at 126 464 entries and K = 4096).
 //
 // The K loop is generated (gen_lm_head.py: fragments read one slice ahead, one
 // barrier per K step, loads that never drain); workgroups are persistent, one
@@ -26,8 +26,9 @@
 // What bounds it.  Many rows: the board's power limit, as in the library's product
 // (8192 rows x 126 464 x 4096: 5.97 ms = 1.42 PFLOP/s with Eq. 1, 4.69 on operands that
 // do not toggle; the library's product alone 5.75 and 4.55; the compiler-scheduled
-// loop this replaced 7.7 and 6.6).  Few rows: the weight stream from HBM (128 rows:
-// 185 us = 5.6 TB/s, of which 167 us = 6.2 TB/s are what the bare stream takes).
+// loop this replaced 7.7 and 6.6).  Few rows: the weight stream from HBM (37 rows:
+// 198 us = 5.2 TB/s; the bare stream takes 167 us = 6.2 TB/s where the workgroups
+// are at different k, 218 us where they move in step).
 #include <float.h>
 
 #include "lsp_common.h"
@@ -179,8 +180,8 @@ struct Tiles {
 };
 // How high row tiles are.  256 rows share a weight slice best and win wherever they are full; lower tiles
 //  - where tiles of 256 would be mostly padding: up to 128 rows (128 rows x 126 464 entries x K = 4096:
-//    185 us, 277 in one tile of 256), and 257-384 rows (300 rows: 414 against 476 us);
-//    not 129-256 (256 rows: 298 against 279 us) or more (640 rows would need five);
+//    212 us, 270 in one tile of 256), and 257-384 rows (300 rows: 385 against 443 us);
+//    not 129-256 (256 rows: 284 against 272 us) or more (640 rows would need five);
 //  - where a launch has fewer tiles than compute units (400 rows x 5000 entries: 41 us in 140 tiles of
 //    64, 55 in 80 of 128, 82 in 40 of 256).
 // Both kernels of a launch take the same decision; tiles of 256 are the tall kernel's.
@@ -295,10 +296,13 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
   const uint64_t zeros = reinterpret_cast<uint64_t>(g_zeros);
   int stage = 0;           // stage that holds step 0 of the current tile
   bool requested = false;  // its first steps have been requested by the previous tile's loop
-  // First K step (see gen_lm_head.py): by the place of the workgroup's vocabulary tile among the 32 workgroups of
-  // its XCD.  Those that share a weight slice stay together, and the hidden rows are read inside a window of
-  // VB steps, 1 MB of the XCD's L2.
-  const int k0 = tail == 0 && KS_real > NS ? (tb.RT > 1 ? int(blockIdx.x >> 3) % tb.VB : int(blockIdx.x) * 5) % (KS - NS) : 0;
+  // Weight rows a multiple of 4 KB apart (K = 2048, 4096, 8192) keep all workgroups that are at the same k on
+  // the same few memory channels, so where the weight stream is the bound - one low row tile, every
+  // compute unit busy - the workgroups of an XCD start a K step's time (3200 cycles) apart in 16 phases.
+  // 37 rows x 126 464 entries: K = 4096 235 -> 198 us, 2048 131 -> 112, 8192 366 -> 355; it costs 5 % at other pitches
+  // (K = 3584 159 -> 169), 9 % at K = 1024 (16 steps per tile), 2 % where not every unit has a tile.
+  if (H <= 128 && tb.RT == 1 && tb.nv >= kComputeUnits / 8 && KS_real >= 32 && a.wrs % 2048 == 0)
+    for (int p = int(blockIdx.x >> 3) & 15; p > 0; --p) __builtin_amdgcn_s_sleep(50);
   for (;;) {
     // (opaque: what is derived from the thread id is formed again for every tile - kept across the loop it would spill)
     int tid = threadIdx.x;
@@ -321,14 +325,14 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
     uint64_t w[4], h[LH];  // this lane's pieces of a step: weight rows, hidden rows
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-      w[i] = reinterpret_cast<uint64_t>(a.weight) + int64_t(min(v0 + 8 * (wave + 8 * i) + lrow, a.V - 1)) * a.wrs * 2 + 16 * chunk + k0 * (2 * KB);
+      w[i] = reinterpret_cast<uint64_t>(a.weight) + int64_t(min(v0 + 8 * (wave + 8 * i) + lrow, a.V - 1)) * a.wrs * 2 + 16 * chunk;
 #pragma unroll
-    for (int i = 0; i < LH; ++i) h[i] = hidden_at(cur.buf, i) + k0 * (2 * KB);
+    for (int i = 0; i < LH; ++i) h[i] = hidden_at(cur.buf, i);
     if (!requested) {
       stage = 0;
 #pragma unroll
       for (int p = 0; p < NS; ++p) {
-        const bool in = (k0 + p) * KB + 8 * chunk < a.K;
+        const bool in = p * KB + 8 * chunk < a.K;
         unsigned char *st = smem + p * STG + 1024 * wave;
 #pragma unroll
         for (int i = 0; i < 4; ++i) load_to_lds(reinterpret_cast<const char *>(in ? w[i] + p * 2 * KB : zeros), st + 8192 * i);
@@ -354,7 +358,7 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
     // The loads of a tile's last steps are followed by the first ones of the next tile where that is plain
     // pointer arithmetic: whole K steps, no vocabulary entry beyond V in either.
     const bool cross = more && tail == 0 && KS_real > NS && v0 + TV <= a.V && vn * TV + TV <= a.V;
-    const uint64_t wstep = int64_t(vn - vt) * TV * a.wrs * 2 - (k0 == 0 ? int64_t(KS) * (2 * KB) : 0);
+    const uint64_t wstep = int64_t(vn - vt) * TV * a.wrs * 2 - int64_t(KS) * (2 * KB);
 
     f32x16 acc[MV * MR / 4];
 #pragma unroll
@@ -373,16 +377,14 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
           addr[st][2 * kk + 1] = lds0 + st * STG + TILE_W + (wr * (H / WR) + l16) * (2 * KB) + c;
         }
       const uint32_t ldsw = lds0 + 1024 * wave, ks = KS, phase = stage, go_on = __builtin_amdgcn_readfirstlane(int(cross));
-      // the first thing to happen to the pointers: back to k = 0, the ragged end of K, or the next tile
-      const uint32_t wrap = k0 > 0 ? KS - k0 : ~0u, event = k0 > 0 ? KS - k0 : min(KS, max(a.K / KB, NS));
-      const uint64_t kback = -uint64_t(KS) * (2 * KB);
+      const uint32_t event = min(KS, max(a.K / KB, NS));  // the first thing to happen to the pointers: the ragged end of K, or the next tile
       const uint32_t zlo = uint32_t(zeros), zhi = uint32_t(zeros >> 32);
       const uint64_t zmask = __ballot(chunk >= tail);
       if constexpr (H == 256) {
         // registers are full: the next tile's hidden pointers wait in LDS (a lane reads what it wrote)
 #pragma unroll
         for (int i = 0; i < LH; i += 2) {
-          const uint64_t h0 = hidden_at(nbuf, i) + k0 * 2 * KB, h1 = hidden_at(nbuf, i + 1) + k0 * 2 * KB;
+          const uint64_t h0 = hidden_at(nbuf, i), h1 = hidden_at(nbuf, i + 1);
           *reinterpret_cast<u32x4 *>(part + 4096 * i + 16 * tid) = u32x4{uint32_t(h0), uint32_t(h0 >> 32), uint32_t(h1), uint32_t(h1 >> 32)};
         }
         const uint32_t next = lds0 + NS * STG + 16 * tid;
@@ -391,7 +393,7 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
         typename UVec<2 * LH>::T next;
 #pragma unroll
         for (int i = 0; i < LH; ++i) {
-          const uint64_t h = hidden_at(nbuf, i) + k0 * 2 * KB;
+          const uint64_t h = hidden_at(nbuf, i);
           next[2 * i] = uint32_t(h);
           next[2 * i + 1] = uint32_t(h >> 32);
         }

@@ -169,3 +169,31 @@ def test_c4_shape_sampled_rows_and_tile_invariants(lsp, oracle):
         r = torch.tensor(rows)
         ref = oracle.lm_head_confidence(hidden[b:b + 1, r].cpu(), weight_cpu, return_logits=True)
         _compare(tuple(t[b:b + 1, r] for t in got), ref[:3], ref[3])
+
+
+# rows: where the repeated rows stand in the batch, and so which tile heights and places they get (300 vocabulary
+# tiles: 64, 128, 256, 128 and 256 rows per tile)
+@pytest.mark.parametrize("K", [64 * 9, 2048])
+def test_a_row_does_not_depend_on_the_batch_and_equal_entries_tie(lsp, K):
+    """Real-valued operands, whole K steps: every logit is summed in one order, so a row's id and margin have the same bits in every
+    batch, and vocabulary entries with equal weight rows tie exactly - margin 0, the lowest id - in whichever tiles they lie."""
+    g = torch.Generator(device="cuda").manual_seed(K)
+    V, n = 300 * 256 - 3, 32
+    w = torch.randn((V, K), generator=g, device="cuda", dtype=torch.bfloat16).div_(K ** 0.5)
+    src = torch.randint(0, 100 * 256, (n,), generator=g, device="cuda")
+    dup = torch.randint(100 * 256, V, (n,), generator=g, device="cuda")
+    w[dup[::2]] = w[src[::2]]
+    t = w[src].float()
+    rows = (torch.randn((n, K), generator=g, device="cuda") + 12.0 * t / (t * t).sum(-1, keepdim=True)).to(torch.bfloat16)
+    first = None
+    for total in (n, 100, 200, 300, 600):
+        for at in {0, total - n, (total - n) // 3}:
+            h = torch.randn((2, total, K), generator=g, device="cuda", dtype=torch.bfloat16)
+            h[0, at:at + n] = rows
+            got = _run(lsp, h, w, torch.tensor([total, 0], dtype=torch.int32))
+            ids, p, m = (x[0, at:at + n] for x in got)
+            if first is None:
+                first = ids, p, m
+                assert torch.equal(ids.long(), src.cpu())
+                assert (m[::2] == 0).all() and (m[1::2] > 1).all()
+            assert torch.equal(ids, first[0]) and torch.equal(m, first[2]), (total, at)
