@@ -305,7 +305,7 @@ int32_t lsp_attn_step_gather(const lsp_attn_desc *desc, const void *q, const voi
  * results match an exact evaluation to fp32 accumulation error (about
  * 1e-6 * sum_k |h_k w_k|), the id is the exact arg-max wherever the exact margin
  * exceeds that error, vocabulary entries with equal weight rows tie, and a row's
- * id and margin do not depend on the other rows or on suffix_len.
+ * results do not depend on the other rows or on suffix_len.
  * Rows i >= N_b are not written.
  * ------------------------------------------------------------------------- */
 size_t lsp_lm_head_confidence_workspace_bytes(int32_t B, int32_t S, int32_t V);

@@ -78,17 +78,18 @@ __device__ __forceinline__ float fmed3_raw(float a, float b, float c) {
 }
 
 // Fold of two partial results of one row; ties on the maximum keep the lower index.
+// Symmetric bit by bit: which of the two a lane holds depends on where the row lies in its tile.
 __device__ __forceinline__ Partial fold(Partial a, Partial b) {
   const float am = a.m1, bm = b.m1;
   const int ai = a.idx, bi = b.idx;
-  const float M = fmax_raw(am, bm);
-  const float wa = am == M ? 1.f : __builtin_amdgcn_exp2f((am - M) * kLog2e);
-  const float wb = bm == M ? 1.f : __builtin_amdgcn_exp2f((bm - M) * kLog2e);
+  const float M = fmax_raw(am, bm), low = fmin_raw(am, bm);
+  const float w = low == M ? 1.f : __builtin_amdgcn_exp2f((low - M) * kLog2e);
+  const bool a_top = am == M;
   const bool take_b = bm > am || (bm == am && bi < ai);
   Partial r;
   r.m1 = M;
-  r.m2 = fmax_raw(fmin_raw(am, bm), fmax_raw(a.m2, b.m2));
-  r.s = a.s * wa + b.s * wb;
+  r.m2 = fmax_raw(low, fmax_raw(a.m2, b.m2));
+  r.s = __builtin_fmaf(a_top ? b.s : a.s, w, a_top ? a.s : b.s);
   r.idx = take_b ? bi : ai;
   return r;
 }
@@ -258,14 +259,13 @@ __device__ __forceinline__ Partial exchange(const Partial &lo, const Partial &hi
   o.m1 = __shfl_xor(send.m1, d); o.m2 = __shfl_xor(send.m2, d); o.s = __shfl_xor(send.s, d); o.idx = __shfl_xor(send.idx, d);
   return fold(keep, o);
 }
-// One thread per row folds the N waves' results of a tile and leaves the tile's partial result.
-template <int N>
+// One thread per row folds the results of the tile's four groups of entries and leaves the tile's partial result.
 __device__ __forceinline__ void finish_tile(const LmArgs &a, const Tiles &tb, const Partial *lds_part, const Cursor &cur, int vt) {
   const int t = threadIdx.x;
   if (t >= tb.tr || cur.rt * tb.tr + t >= tb.map.R) return;
-  Partial p = lds_part[t * N];
+  Partial p = lds_part[t * 4];
 #pragma unroll
-  for (int u = 1; u < N; ++u) p = fold(p, lds_part[t * N + u]);
+  for (int u = 1; u < 4; ++u) p = fold(p, lds_part[t * 4 + u]);
   a.partials[int64_t(tb.row[cur.buf * tb.cap + t]) * a.VT + vt] = p;
 }
 
@@ -277,8 +277,8 @@ template <> struct Shape<128> { static constexpr int WV = 4, WR = 2, NS = 3; };
 template <> struct Shape<64> { static constexpr int WV = 4, WR = 2, NS = 3; };
 constexpr int KB = 64, TILE_W = TV * KB * 2;  // K step, bytes of a weight tile's step
 template <int H> constexpr int stage_bytes() { return (TV + H) * KB * 2; }
-// behind the stages: the next tile's hidden pointers (H = 256), then the waves' partial results
-template <int H> constexpr int lds_bytes() { return Shape<H>::NS * stage_bytes<H>() + (H == 256 ? 16384 : H * Shape<H>::WV * 16); }
+// behind the stages: the next tile's hidden pointers (H = 256), then the partial results of four groups of entries per row
+template <int H> constexpr int lds_bytes() { return Shape<H>::NS * stage_bytes<H>() + H * 4 * 16; }
 
 template <int N> struct UVec;
 template <> struct UVec<2> { typedef u32x2 T; };
@@ -299,7 +299,7 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
   // Weight rows a multiple of 4 KB apart (K = 2048, 4096, 8192) keep all workgroups that are at the same k on
   // the same few memory channels, so where the weight stream is the bound - one low row tile, every
   // compute unit busy - the workgroups of an XCD start a K step's time (3200 cycles) apart in 16 phases.
-  // 37 rows x 126 464 entries: K = 4096 235 -> 198 us, 2048 131 -> 112, 8192 366 -> 355; it costs 5 % at other pitches
+  // 37 rows x 126 464 entries: K = 4096 235 -> 198-203 us, 2048 131 -> 112, 8192 366 -> 355; it costs 5 % at other pitches
   // (K = 3584 159 -> 169), 9 % at K = 1024 (16 steps per tile), 2 % where not every unit has a tile.
   if (H <= 128 && tb.RT == 1 && tb.nv >= kComputeUnits / 8 && KS_real >= 32 && a.wrs % 2048 == 0)
     for (int p = int(blockIdx.x >> 3) & 15; p > 0; --p) __builtin_amdgcn_s_sleep(50);
@@ -409,29 +409,34 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
 
     // element r of 16x16 block (i, j) is z[v][row], v = v0 + wv*(TV/WV) + 16 i + 4 grp + r (increasing in (i, r)),
     // row = wr*(H/WR) + 16 j + l16
-    Partial pj[MR];
-#pragma unroll
-    for (int j = 0; j < MR; ++j) {
-      float x[4 * MV];
-#pragma unroll
-      for (int e = 0; e < 4 * MV; ++e) x[e] = acc[(j * MV + e / 4) / 4][4 * ((j * MV + e / 4) % 4) + e % 4];
-      pj[j] = reduce<4 * MV>(x, v0 + wv * (TV / WV) + 4 * grp, a.V, v0 + TV > a.V);
-    }
+    // Four groups of 64 entries per row and tile at every height, so that a row's sum of exponentials has one order
+    // (a wave of the 256-row tile holds two of them: reduced together they would save 0.6 us of a 100 us tile).
+    Partial *lds_part = reinterpret_cast<Partial *>(part);  // [H][4]
     const bool up32 = lane >= 32, up16 = (lane & 16) != 0;
-    Partial p;
-    int j;
-    if constexpr (MR == 4) {
-      p = exchange(exchange(pj[0], pj[2], up32, 32), exchange(pj[1], pj[3], up32, 32), up16, 16);
-      j = 2 * up32 + up16;
-    } else {
-      p = exchange(pj[0], pj[1], up32, 32);
-      p = exchange(p, p, false, 16);
-      j = up32;
+#pragma unroll
+    for (int u = 0; u < MV / 4; ++u) {
+      Partial pj[MR];
+#pragma unroll
+      for (int j = 0; j < MR; ++j) {
+        float x[16];
+#pragma unroll
+        for (int e = 0; e < 16; ++e) x[e] = acc[(j * MV + 4 * u) / 4][e];
+        pj[j] = reduce<16>(x, v0 + wv * (TV / WV) + 64 * u + 4 * grp, a.V, v0 + TV > a.V);
+      }
+      Partial p;
+      int j;
+      if constexpr (MR == 4) {
+        p = exchange(exchange(pj[0], pj[2], up32, 32), exchange(pj[1], pj[3], up32, 32), up16, 16);
+        j = 2 * up32 + up16;
+      } else {
+        p = exchange(pj[0], pj[1], up32, 32);
+        p = exchange(p, p, false, 16);
+        j = up32;
+      }
+      lds_part[(wr * (H / WR) + 16 * j + l16) * 4 + wv * (MV / 4) + u] = p;
     }
-    Partial *lds_part = reinterpret_cast<Partial *>(part);  // [H][WV]
-    lds_part[(wr * (H / WR) + 16 * j + l16) * WV + wv] = p;
     __syncthreads();
-    finish_tile<WV>(a, tb, lds_part, cur, vt);
+    finish_tile(a, tb, lds_part, cur, vt);
     __syncthreads();  // the partial results and the row tables may be overwritten
     cur.m += gridDim.x >> 3;
     cur.vt = vn; cur.rt = rn; cur.buf = nbuf;

@@ -175,8 +175,8 @@ def test_c4_shape_sampled_rows_and_tile_invariants(lsp, oracle):
 # tiles: 64, 128, 256, 128 and 256 rows per tile)
 @pytest.mark.parametrize("K", [64 * 9, 2048])
 def test_a_row_does_not_depend_on_the_batch_and_equal_entries_tie(lsp, K):
-    """Real-valued operands, whole K steps: every logit is summed in one order, so a row's id and margin have the same bits in every
-    batch, and vocabulary entries with equal weight rows tie exactly - margin 0, the lowest id - in whichever tiles they lie."""
+    """Real-valued operands, whole K steps: every logit is summed in one order and so are the exponentials of a row: its results have the
+    same bits in every batch, and vocabulary entries with equal weight rows tie exactly - margin 0, the lowest id - in whichever tiles they lie."""
     g = torch.Generator(device="cuda").manual_seed(K)
     V, n = 300 * 256 - 3, 32
     w = torch.randn((V, K), generator=g, device="cuda", dtype=torch.bfloat16).div_(K ** 0.5)
@@ -196,4 +196,4 @@ def test_a_row_does_not_depend_on_the_batch_and_equal_entries_tie(lsp, K):
                 first = ids, p, m
                 assert torch.equal(ids.long(), src.cpu())
                 assert (m[::2] == 0).all() and (m[1::2] > 1).all()
-            assert torch.equal(ids, first[0]) and torch.equal(m, first[2]), (total, at)
+            assert torch.equal(ids, first[0]) and torch.equal(m, first[2]) and torch.equal(p, first[1]), (total, at)
