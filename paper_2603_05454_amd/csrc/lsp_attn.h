@@ -34,6 +34,16 @@ __device__ __forceinline__ void for_layer(AttnArgs &a, const AttnLayers &L, int 
   }
 }
 
+// A grid dimension is limited in THREADS to 2^32: launches of more workgroups than this go on in y.
+// (The last row of such a grid may reach beyond the workgroups asked for: kernels check their id.)
+constexpr int kGridBits = 20;
+constexpr int64_t kMaxGrid = int64_t(0x7ff) << kGridBits;
+inline dim3 grid_of(int64_t nwg) {
+  const int64_t x = int64_t(1) << kGridBits;
+  return nwg <= x ? dim3(unsigned(nwg)) : dim3(unsigned(x), unsigned((nwg + x - 1) / x));
+}
+__device__ __forceinline__ int workgroup_id() { return blockIdx.y << kGridBits | blockIdx.x; }
+
 // Cache row that holds key t (t < P_b) of sequence b.
 template <bool GATHER>
 __device__ __forceinline__ int cache_row(const AttnArgs &a, int b, int t) {

@@ -218,7 +218,6 @@ constexpr int kShortSuffix = 64;  // sequences with at most this many active row
 // without a query, a tile with two active waves is faster than two key-split workgroups - 38 against
 // 50 us per C5 layer - while a tile with one active wave is slower than one key-split workgroup)
 constexpr int kShortSuffixPipe = 32;
-constexpr int kGridBits = 20;  // a grid dimension is limited in THREADS to 2^32: larger launches go on in y
 struct Place {
   int layer, b, g, h, q0;
   bool valid;
@@ -231,7 +230,7 @@ __device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
   Place p;
   const int QT = (a.S + qtile - 1) / qtile;
   const int rep = a.rep, chunk = a.chunk;
-  const int n = blockIdx.y << kGridBits | blockIdx.x;
+  const int n = workgroup_id();
   const int m8 = n >> 3;
   const int G = a.unit_group;
   const int grp = m8 / (G * chunk), r = m8 - grp * (G * chunk);
@@ -272,12 +271,6 @@ inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile) {
   const int64_t G = pieces8 < kUnitGroup ? pieces8 : kUnitGroup;
   a.unit_group = int32_t(G);
   return (pieces8 + G - 1) / G * G * chunk * 8;
-}
-
-constexpr int64_t kMaxGrid = int64_t(0x7ff) << kGridBits;
-inline dim3 grid_of(int64_t nwg) {
-  const int64_t x = int64_t(1) << kGridBits;
-  return nwg <= x ? dim3(unsigned(nwg)) : dim3(unsigned(x), unsigned((nwg + x - 1) / x));
 }
 
 // Final step shared by both kernels: the WK partial results of every query

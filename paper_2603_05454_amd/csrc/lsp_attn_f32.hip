@@ -51,8 +51,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a) {
   constexpr int OP = D + 4;   // floats per merged O row
   // All query tiles of one (sequence, KV head) get workgroup ids congruent mod 8: one XCD's L2 holds their keys.
   const int tiles = (a.S + kTile - 1) / kTile, rep = a.Hq / a.Hkv, per_unit = rep * tiles;
-  const int n8 = blockIdx.x >> 3;
-  const int unit = (n8 / per_unit) * 8 + (blockIdx.x & 7);
+  const int n = workgroup_id(), n8 = n >> 3;
+  const int unit = (n8 / per_unit) * 8 + (n & 7);
   if (unit >= a.B * a.Hkv) return;
   const int b = unit / a.Hkv, g = unit % a.Hkv, wu = n8 % per_unit;
   const int h = g * rep + wu / tiles, q0 = (wu % tiles) * kTile;
@@ -177,11 +177,11 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a) {
 template <int D>
 int32_t launch(const AttnArgs &a, hipStream_t st) {
   const int64_t nwg = (int64_t(a.B) * a.Hkv + 7) / 8 * 8 * (a.Hq / a.Hkv) * ((a.S + kTile - 1) / kTile);
-  if (nwg > 0x7fffffff) {
+  if (nwg > kMaxGrid) {
     set_error("lsp_attn_step: launch of %lld workgroups is too large", (long long)nwg);
     return LSP_ERR_UNSUPPORTED;
   }
-  attn_f32_kernel<D><<<dim3(unsigned(nwg)), 64 * kWaves, 0, st>>>(a);
+  attn_f32_kernel<D><<<grid_of(nwg), 64 * kWaves, 0, st>>>(a);
   LSP_CHECK_LAUNCH("lsp_attn_step: fp32 launch");
   return LSP_OK;
 }

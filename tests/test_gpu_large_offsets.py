@@ -109,3 +109,20 @@ def test_attention_over_caches_beyond_2_31_elements(lsp, oracle, S):
         worst = max(worst, (sel - ref).abs().max().item())
         assert torch.all(out[b, n:].float() == 123.0) and not torch.isnan(out[b, :n].float()).any()
     assert worst <= 2e-2, worst
+
+
+def test_f32_attention_in_more_workgroups_than_one_grid_dimension_holds(lsp, oracle):
+    """65535 sequences x 32 heads x 5 query tiles: 10.5 million workgroups of 512 threads, where a grid dimension ends at
+    2**32 threads.  All sequences share one set of operands (batch stride 0) and all but two have no active row."""
+    B, S, H, D, P = 65535, 65, 32, 64, 20
+    w = W.scaled(W.C2, dtype="f32", B=1, S=S, P=P, C=P, Hq=H, Hkv=H, D=D, seed=91)
+    kv = W.make_layer_kv(w, 0)
+    for b, n in ((0, 17), (B - 1, S)):
+        sl = torch.zeros(B, dtype=torch.int32, device="cuda")
+        sl[b] = n
+        out = torch.full((1, S, H, D), 123.0, device="cuda")
+        g = {k: v.cuda().expand(B, -1, -1, -1) for k, v in kv.items()}
+        lsp.attn_step(g["q"], g["k_suf"], g["v_suf"], g["k_cache"], g["v_cache"], torch.full_like(sl, P), sl, out=out.expand(B, -1, -1, -1))
+        torch.cuda.synchronize()
+        ref = oracle.attention(**kv, prefix_len=torch.tensor([P], dtype=torch.int32), suffix_len=torch.tensor([n], dtype=torch.int32))
+        assert (out[:, :n].cpu() - ref[:, :n]).abs().max().item() <= 1e-5 and torch.all(out[:, n:] == 123.0)
