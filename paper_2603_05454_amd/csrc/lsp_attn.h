@@ -8,11 +8,12 @@ struct AttnArgs {
   const void *q, *k_suf, *v_suf, *k_cache, *v_cache;
   void *out;
   const int32_t *prefix_len, *suffix_len;
-  int32_t B, S, Hq, Hkv, D, C;
+  int32_t B, S, Hq, Hkv;
+  int32_t rep, chunk, spread, layers, unit_group;  // placement of the workgroups (place_grid); read first, with the line above
+  int32_t D, C;
   float scale;
   int64_t qs[3], ks[3], cs[3], os[3];  // element strides: batch, row, head
   void *workspace;
-  int32_t unit_group, spread, layers, rep, chunk;  // placement of the workgroups, set by the bf16 launcher
   const int32_t *cache_rows;  // gather form only: key t < P_b of sequence b is cache row cache_rows[b*C + t]; else null
 };
 
@@ -43,6 +44,78 @@ inline dim3 grid_of(int64_t nwg) {
   return nwg <= x ? dim3(unsigned(nwg)) : dim3(unsigned(x), unsigned((nwg + x - 1) / x));
 }
 __device__ __forceinline__ int workgroup_id() { return blockIdx.y << kGridBits | blockIdx.x; }
+
+// Workgroup placement of all attention kernels.  Workgroups are handed to the 8
+// XCDs round-robin by linear id, and each XCD has its own L2.  All workgroups
+// that read the same K/V stream - the query tiles of every query head of one
+// (sequence, KV head) unit - are therefore given ids that are congruent modulo
+// 8, so the stream is fetched into one L2 instead of eight.
+// Within an XCD the order is: groups of kUnitGroup units; inside a group the
+// query tile is the slow index and the unit the fast one.  Tiles at or beyond
+// the active length exit at once, and in a decode loop that is most tiles of
+// every unit: with the tile as the fast index the surviving workgroups would sit
+// at a fixed stride of the dispatch order, which the hardware maps onto a fixed
+// subset of the compute units (measured: the time did not drop at all when the
+// active length fell from 1024 to 256).  Runs of kUnitGroup live workgroups
+// spread over all of them, and the tiles of one unit still run close enough
+// together to share its K/V stream in L2.
+constexpr int kUnitGroup = 8;
+struct Place {
+  int layer, b, g, h, q0;
+  bool valid;
+};
+// Units are numbered over layers, sequences and KV heads.  When they are few, each is cut into
+// 2^spread pieces (runs of its (head, tile) list) so that every XCD gets as many: four KV heads of
+// one sequence kept four of the eight XCDs idle (28 query heads, one layer, prefix 4096, suffix
+// 1024: 234 us whole, 139 us in two pieces; fp32, 8 query heads of 64 on one KV head, same lengths:
+// 905 us whole, 122 in eight).
+template <bool GROUPS = true>  // false: groups of one unit
+__device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
+  Place p;
+  const int QT = (a.S + qtile - 1) / qtile;
+  const int rep = a.rep, chunk = a.chunk;
+  const int n = workgroup_id();
+  const int m8 = n >> 3;
+  const int G = GROUPS ? a.unit_group : 1;
+  const int grp = m8 / (G * chunk), r = m8 - grp * (G * chunk);
+  // (an integer division is some forty dependent instructions on the way to the first load)
+  int wu = r / G, layer = 0;
+  int unit = (grp * G + r - wu * G) * 8 + (n & 7);
+  if (a.spread > 0) {
+    wu += (unit & ((1 << a.spread) - 1)) * chunk;
+    unit >>= a.spread;
+  }
+  const int units = a.B * a.Hkv;
+  if (a.layers > 1) {
+    layer = unit / units;
+    unit -= layer * units;
+  }
+  p.valid = layer < a.layers && unit < units && wu < rep * QT;
+  p.layer = layer;
+  p.b = unit / a.Hkv;
+  p.g = unit - p.b * a.Hkv;
+  const int hr = wu / QT;
+  p.h = p.g * rep + hr;
+  p.q0 = (wu - hr * QT) * qtile;
+  return p;
+}
+// Fields of that placement in `a`, and its number of workgroups.  Units are cut only where an XCD would get more than
+// `enough` workgroups.
+inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile, int unit_group = kUnitGroup, int enough = 0) {
+  const int64_t QT = (a.S + qtile - 1) / qtile, per_unit = a.Hq / a.Hkv * QT;
+  a.layers = layers.n > 0 ? layers.n : 1;
+  const int64_t units = int64_t(a.layers) * a.B * a.Hkv;
+  a.spread = 0;  // with 32 units or more an XCD has at most a quarter more than its share
+  if (units < 32 && (units + 7) / 8 * per_unit > enough)
+    while ((units << a.spread) % 8 != 0) ++a.spread;
+  const int64_t chunk = (per_unit + (1 << a.spread) - 1) >> a.spread;
+  a.rep = a.Hq / a.Hkv;
+  a.chunk = int32_t(chunk);
+  const int64_t pieces8 = ((units << a.spread) + 7) / 8;  // pieces per XCD
+  const int64_t G = pieces8 < unit_group ? pieces8 : unit_group;
+  a.unit_group = int32_t(G);
+  return (pieces8 + G - 1) / G * G * chunk * 8;
+}
 
 // Cache row that holds key t (t < P_b) of sequence b.
 template <bool GATHER>

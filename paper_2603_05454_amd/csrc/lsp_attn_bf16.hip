@@ -198,80 +198,11 @@ __device__ __forceinline__ void softmax_pv(f32x16 &s, f32x16 (&oacc)[D / 32], fl
       oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[db][k2], pf[k2], oacc[db], 0, 0, 0);
 }
 
-// Workgroup placement shared by both kernels.  Workgroups are handed to the 8
-// XCDs round-robin by linear id, and each XCD has its own L2.  All workgroups
-// that read the same K/V stream - the query tiles of every query head of one
-// (sequence, KV head) unit - are therefore given ids that are congruent modulo
-// 8, so the stream is fetched into one L2 instead of eight.
-// Within an XCD the order is: groups of kUnitGroup units; inside a group the
-// query tile is the slow index and the unit the fast one.  Tiles at or beyond
-// the active length exit at once, and in a decode loop that is most tiles of
-// every unit: with the tile as the fast index the surviving workgroups would sit
-// at a fixed stride of the dispatch order, which the hardware maps onto a fixed
-// subset of the compute units (measured: the time did not drop at all when the
-// active length fell from 1024 to 256).  Runs of kUnitGroup live workgroups
-// spread over all of them, and the tiles of one unit still run close enough
-// together to share its K/V stream in L2.
-constexpr int kUnitGroup = 8;
 constexpr int kShortSuffix = 64;  // sequences with at most this many active rows take the key-split kernel
 // (the hand-scheduled kernel decides per TILE and at 32 rows: with its loader-only loop for waves
 // without a query, a tile with two active waves is faster than two key-split workgroups - 38 against
 // 50 us per C5 layer - while a tile with one active wave is slower than one key-split workgroup)
 constexpr int kShortSuffixPipe = 32;
-struct Place {
-  int layer, b, g, h, q0;
-  bool valid;
-};
-// Units are numbered over layers, sequences and KV heads.  When they are few, each is cut into
-// `spread` pieces (runs of its (head, tile) list) so that every XCD gets as many: four KV heads of
-// one sequence kept four of the eight XCDs idle (28 query heads, one layer, prefix 4096, suffix
-// 1024: 234 us whole, 139 us in two pieces).
-__device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
-  Place p;
-  const int QT = (a.S + qtile - 1) / qtile;
-  const int rep = a.rep, chunk = a.chunk;
-  const int n = workgroup_id();
-  const int m8 = n >> 3;
-  const int G = a.unit_group;
-  const int grp = m8 / (G * chunk), r = m8 - grp * (G * chunk);
-  int wu = r / G, unit = (grp * G + r - wu * G) * 8 + (n & 7), layer = 0;
-  // (an integer division is some forty dependent instructions on the way to the first load)
-  if (a.spread > 1) {
-    const int piece = unit;
-    unit = piece / a.spread;
-    wu += (piece - unit * a.spread) * chunk;
-  }
-  const int units = a.B * a.Hkv;
-  if (a.layers > 1) {
-    layer = unit / units;
-    unit -= layer * units;
-  }
-  p.valid = layer < a.layers && unit < units && wu < rep * QT;
-  p.layer = layer;
-  p.b = unit / a.Hkv;
-  p.g = unit - p.b * a.Hkv;
-  const int hr = wu / QT;
-  p.h = p.g * rep + hr;
-  p.q0 = (wu - hr * QT) * qtile;
-  return p;
-}
-// fields of that placement in `a`, and its number of workgroups
-inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile) {
-  const int64_t QT = (a.S + qtile - 1) / qtile, per_unit = a.Hq / a.Hkv * QT;
-  a.layers = layers.n > 0 ? layers.n : 1;
-  const int64_t units = int64_t(a.layers) * a.B * a.Hkv;
-  int64_t spread = 1;  // with 32 units or more an XCD has at most a quarter more than its share
-  if (units < 32)
-    while (units * spread % 8 != 0) spread *= 2;
-  a.spread = int32_t(spread < per_unit ? spread : per_unit);
-  const int64_t chunk = (per_unit + a.spread - 1) / a.spread;
-  a.rep = a.Hq / a.Hkv;
-  a.chunk = int32_t(chunk);
-  const int64_t pieces8 = (units * a.spread + 7) / 8;  // pieces per XCD
-  const int64_t G = pieces8 < kUnitGroup ? pieces8 : kUnitGroup;
-  a.unit_group = int32_t(G);
-  return (pieces8 + G - 1) / G * G * chunk * 8;
-}
 
 // Final step shared by both kernels: the WK partial results of every query
 // block are combined through LDS (each wave's region holds O^T as [query][d]

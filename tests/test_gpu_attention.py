@@ -92,6 +92,15 @@ def test_every_unit_count_reaches_every_tile(lsp, oracle, B, Hq, Hkv, S):
         assert (got.float() - one.float()).abs().max().item() <= TOL["bf16"]   # another launch size may take another kernel
 
 
+@pytest.mark.parametrize("B,Hq,Hkv", [(1, 1, 1), (1, 7, 1), (1, 28, 4), (3, 3, 3), (7, 5, 5), (31, 2, 1), (33, 2, 1)])
+@pytest.mark.parametrize("S", [12, 75])
+def test_f32_every_unit_count_reaches_every_tile(lsp, oracle, B, Hq, Hkv, S):
+    """The same for the fp32 kernel, whose tiles are 16 queries high: lists of one tile and of tiles that the pieces do not divide."""
+    w = W.scaled(W.C2, dtype="f32", B=B, S=S, P=30, C=64, Hq=Hq, Hkv=Hkv, D=64, seed=700 + B + Hq)
+    _check_full(lsp, oracle, w, torch.tensor([(30 - b) % 31 for b in range(B)], dtype=torch.int32),
+                torch.tensor([max(S - b, 0) for b in range(B)], dtype=torch.int32))
+
+
 def test_f32_infinite_value_in_the_last_row(lsp, oracle):
     """Key tiles with a remainder repeat the last row with probability 0: an infinity there stays one and spoils nothing else."""
     w = W.scaled(W.C2, dtype="f32", B=1, S=5, P=16, C=16, Hq=2, Hkv=2, D=64, seed=41)
