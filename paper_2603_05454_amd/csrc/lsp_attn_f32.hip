@@ -114,10 +114,10 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a_in)
         for (int c = 0; c < CV; ++c) vf[r][c] = key ? vf[r][c] : zero;  // (0 x an infinite last row would be NaN)
       }
     }
-    const float bm = group_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))) * sc;  // finite: key t0 is valid
-    const float mn = fmaxf(m, bm);
-    const float alpha = __builtin_amdgcn_exp2f(m - mn);  // 0 on the first tile
-    m = mn;
+    const float mo = m, bm = group_max(fmaxf(fmaxf(s[0], s[1]), fmaxf(s[2], s[3]))) * sc;
+    m = fmaxf(mo, bm);
+    const float mn = m == -INFINITY ? 0.f : m;  // only scores of -infinity so far: weights 0, not exp(-inf + inf)
+    const float alpha = __builtin_amdgcn_exp2f(mo - mn);  // 0 on the first tile
     l *= alpha;
     f32x4 p;
 #pragma unroll
@@ -156,14 +156,14 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a_in)
   for (int it = tid; it < kTile * (D / 4); it += 64 * kWaves) {
     const int qq = it / (D / 4), d = 4 * (it % (D / 4));
     if (q0 + qq >= N) continue;
-    float M = sm[0][qq];  // the first wave has at least one key
+    float M = sm[0][qq];
 #pragma unroll
     for (int w = 1; w < kWaves; ++w) M = fmaxf(M, sm[w][qq]);
     f32x4 acc = zero;
     float den = 0.f;
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      const float wgt = __builtin_amdgcn_exp2f(sm[w][qq] - M);  // 0 for a wave that saw no key
+      const float wgt = __builtin_amdgcn_exp2f(sm[w][qq] - M);  // 0 for a wave that saw no key (or only scores of -infinity)
       den += sl[w][qq] * wgt;
       acc += *reinterpret_cast<const f32x4 *>(&so[w][qq][d]) * wgt;
     }

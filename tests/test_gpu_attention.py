@@ -111,6 +111,18 @@ def test_f32_infinite_value_in_the_last_row(lsp, oracle):
     assert torch.equal(torch.isinf(got), torch.isinf(ref)) and not torch.isnan(got).any()
 
 
+@pytest.mark.parametrize("lo,hi", [(48, 64), (0, 16), (30, 190), (128, 256)])
+def test_f32_scores_of_minus_infinity(lsp, oracle, lo, hi):
+    """Keys lo..hi-1 carry -infinity in a dimension where every query holds one: weight 0, and no NaN where they fill a
+    key tile, all first tiles of some waves, or everything that a wave sees."""
+    w = W.scaled(W.C2, dtype="f32", B=1, S=20, P=260, C=260, Hq=2, Hkv=2, D=64, seed=43)
+    kv, (pl, sl) = W.make_layer_kv(w, 0), W.make_lengths(w)
+    kv["q"][..., 5] = 1.0
+    kv["k_cache"][:, lo:hi, :, 5] = -float("inf")
+    got, ref = _run(lsp, kv, pl, sl), oracle.attention(**kv, prefix_len=pl, suffix_len=sl)
+    assert torch.isfinite(ref).all() and (got - ref).abs().max().item() <= TOL["f32"]
+
+
 @pytest.mark.parametrize("dtype,B,Hq,S", [("f32", 2, 2, 150), ("bf16", 2, 2, 150), ("bf16", 8, 16, 320)])
 def test_large_scores_and_moving_maximum(lsp, oracle, dtype, B, Hq, S):
     """Scores spanning hundreds of units whose maximum keeps rising along the key
