@@ -68,6 +68,14 @@ bool strides3(const at::Tensor &t, int64_t (&s)[3]) {
 }
 bool same_strides(const at::Tensor &a, const at::Tensor &b) { return a.strides() == b.strides(); }
 
+// false for what is not a number by itself (the general path may still make one of it)
+bool number(PyObject *o, float &x) {
+  x = float(PyFloat_AsDouble(o));
+  if (!PyErr_Occurred()) return true;
+  PyErr_Clear();
+  return false;
+}
+
 PyObject *status(int32_t rc) { return PyLong_FromLong(rc); }
 #define ORDINARY(cond) \
   if (!(cond)) Py_RETURN_NONE
@@ -109,8 +117,7 @@ PyObject *attn_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
   lsp_attn_desc d = {};
   ORDINARY(element_type(*q, d.dtype));
   d.B = int32_t(B); d.S = int32_t(S); d.Hq = int32_t(Hq); d.Hkv = int32_t(Hkv); d.D = int32_t(D); d.C = int32_t(C);
-  d.scale = float(PyFloat_AsDouble(a[7]));
-  if (PyErr_Occurred()) return nullptr;
+  ORDINARY(number(a[7], d.scale));
   ORDINARY(strides3(*q, d.q_stride) && strides3(*ks, d.kv_suf_stride) && strides3(*kc, d.cache_stride) && strides3(*out, d.o_stride));
   const at::Tensor *ws = a[9] == Py_None ? nullptr : device_tensor(a[9]);
   const int64_t need = int64_t(g.attn_workspace_bytes(&d));
@@ -126,8 +133,8 @@ PyObject *attn_step_layers(PyObject *, PyObject *const *a, Py_ssize_t n) {
   void *p[8];
   for (int k = 0; k < 8; ++k) p[k] = PyLong_AsVoidPtr(PyTuple_GET_ITEM(a[0], k));
   lsp_attn_desc *d = static_cast<lsp_attn_desc *>(p[0]);
-  const float scale = float(PyFloat_AsDouble(a[3]));
-  if (PyErr_Occurred()) return nullptr;
+  float scale;
+  ORDINARY(number(a[3], scale));
   const at::Tensor *pl = plain(a[1], at::kInt, d->B), *sl = plain(a[2], at::kInt, d->B);
   ORDINARY(pl && sl);
   const at::Tensor *ws = a[4] == Py_None ? nullptr : device_tensor(a[4]);
@@ -194,7 +201,7 @@ PyObject *k_mask, *k_raw, *k_snapped, *k_len, *k_flags, *k_tau;  // keys of comm
 // (margin, top1_id, bitmap, prefix_len, suffix_len, tokens or None, layer table or None, out,
 //  (V, tau, window, min_commit, snap_enabled, adaptive, alpha, beta, max_commit, C))
 PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  ORDINARY(n == 9 && g.commit && PyDict_Check(a[7]) && PyTuple_Check(a[8]) && PyTuple_GET_SIZE(a[8]) == 10);
+  ORDINARY(n == 9 && g.commit && PyDict_Check(a[7]) && PyDict_GET_SIZE(a[7]) == 6 && PyTuple_Check(a[8]) && PyTuple_GET_SIZE(a[8]) == 10);
   const at::Tensor *margin = device_tensor(a[0]);
   ORDINARY(margin && margin->dim() == 2);
   const int64_t B = margin->size(0), S = margin->size(1);
@@ -271,12 +278,14 @@ PyObject *flip_update(PyObject *, PyObject *const *a, Py_ssize_t n) {
 }
 
 // No C++ exception may reach the interpreter: torch throws where a tensor has no strides or no
-// storage (sparse, batched by vmap) or there is no device, and the general path then raises it.
+// storage (sparse, batched by vmap), there is no device or a subclass written in Python raises (the error is then
+// set as well), and the general path meets the same and raises it.
 template <PyObject *(*F)(PyObject *, PyObject *const *, Py_ssize_t)>
 PyObject *guarded(PyObject *self, PyObject *const *a, Py_ssize_t n) {
   try {
     return F(self, a, n);
   } catch (...) {
+    PyErr_Clear();
     Py_RETURN_NONE;
   }
 }

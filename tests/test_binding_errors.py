@@ -18,6 +18,44 @@ def test_an_exception_from_torch_is_raised_in_python():
             lsp.confidence(z, None, out=out)
 
 
+class _Raises(torch.Tensor):
+    """A device tensor of a subclass whose own Python code raises when its layout is asked for."""
+
+    @staticmethod
+    def __new__(cls, *shape, dtype=torch.float32):
+        return torch.Tensor._make_wrapper_subclass(cls, shape, dtype=dtype, device="cuda", dispatch_sizes_strides_policy="strides")
+
+    @classmethod
+    def __torch_dispatch__(cls, func, types, args=(), kwargs=None):
+        raise KeyError("asked for its layout")
+
+
+def test_an_exception_from_python_code_under_torch_is_the_one_raised():
+    lsp.lib()
+    z = _Raises(2, 4, 64)
+    out = (torch.empty(2, 4, dtype=torch.int32), torch.empty(2, 4), torch.empty(2, 4))
+    assert lsp._nat.confidence(z, None, out, None) is None
+    with pytest.raises(KeyError, match="asked for its layout"):
+        lsp.confidence(z, None, out=out)
+
+
+@pytest.mark.gpu
+def test_numbers_and_outputs_of_rarer_forms_go_to_the_general_path():
+    """A scale that float() makes a number of is taken, an output dict with a stray host tensor refused, as without the module."""
+    lsp.lib()
+    q = torch.randn(1, 20, 2, 64, device="cuda")
+    pl, sl = (torch.tensor([x], dtype=torch.int32, device="cuda") for x in (9, 20))
+    a, b = (lsp.attn_step(q, q, q, q, q, pl, sl, scale=s, out=torch.zeros_like(q)) for s in (0.5, "0.5"))
+    assert torch.equal(a, b)
+    table = lsp.AttnLayerTable([q], [q], [q], [q], [q], [torch.zeros_like(q)])
+    assert torch.equal(lsp.attn_step_layers(table, pl, sl, scale="0.5")[0], a)
+    out = {k: torch.zeros(1, dtype=torch.int32, device="cuda") for k in ("raw_boundary", "snapped_boundary", "commit_len", "status_flags")}
+    out.update(stable_mask=torch.zeros((1, 20), dtype=torch.uint8, device="cuda"), tau_used=torch.zeros(1, device="cuda"), notes=torch.zeros(1))
+    m, ids = torch.ones((1, 20), device="cuda"), torch.zeros((1, 20), dtype=torch.int32, device="cuda")
+    with pytest.raises(lsp.LspError, match="device tensors only"):
+        lsp.commit(m, ids, torch.zeros(2, dtype=torch.int32, device="cuda"), 64, 0.5, 4, 1, 1, pl, sl, C=64, out=out)
+
+
 @pytest.mark.gpu
 def test_a_sparse_tensor_is_refused_in_python():
     lsp.lib()
