@@ -55,6 +55,10 @@ EXPORTS = ["lsp_version", "lsp_last_error", "lsp_attn_workspace_bytes", "lsp_att
            "lsp_commit", "lsp_flip_update", "lsp_select_scattered", "lsp_kv_gather_append",
            "lsp_attn_step_gather", "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_bench_read", "lsp_bench_mfma"]
 
+# entry points that the native module calls, in the order of its table
+NATIVE_ENTRIES = ("lsp_attn_workspace_bytes", "lsp_attn_step", "lsp_attn_step_layers", "lsp_confidence_workspace_bytes", "lsp_confidence",
+                  "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_commit", "lsp_flip_update")
+
 
 def lib() -> ctypes.CDLL:
     """The loaded C-ABI library; raises LspError when it has not been built."""
@@ -77,9 +81,7 @@ def lib() -> ctypes.CDLL:
         except ImportError as e:
             raise LspError(f"the native binding module is missing ({e}): run `python -m paper_2603_05454_amd.build` "
                            "(or __graft_entry__.build()) first") from e
-        _binding.bind(*[ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in (
-            "lsp_attn_workspace_bytes", "lsp_attn_step", "lsp_attn_step_layers", "lsp_confidence_workspace_bytes", "lsp_confidence",
-            "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_commit", "lsp_flip_update")])
+        _binding.bind(*[ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in NATIVE_ENTRIES])
         _lib, _nat = L, _binding
     return _lib
 

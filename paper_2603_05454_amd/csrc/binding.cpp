@@ -76,7 +76,16 @@ bool number(PyObject *o, float &x) {
   return false;
 }
 
-PyObject *status(int32_t rc) { return PyLong_FromLong(rc); }
+// The entry point itself runs without the interpreter lock: a launch waits for a full queue, and a kernel's first one
+// loads its code.  What it reads of Python's is held by the caller's references meanwhile.
+template <typename... P, typename... A>
+PyObject *status(int32_t (*entry)(P...), A... args) {
+  int32_t rc;
+  Py_BEGIN_ALLOW_THREADS;
+  rc = entry(args...);
+  Py_END_ALLOW_THREADS;
+  return PyLong_FromLong(rc);
+}
 #define ORDINARY(cond) \
   if (!(cond)) Py_RETURN_NONE
 
@@ -122,9 +131,9 @@ PyObject *attn_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
   const at::Tensor *ws = a[9] == Py_None ? nullptr : device_tensor(a[9]);
   const int64_t need = int64_t(g.attn_workspace_bytes(&d));
   ORDINARY(bytes_of(ws) >= need);
-  return status(g.attn_step(&d, q->const_data_ptr(), ks->const_data_ptr(), vs->const_data_ptr(), kc->const_data_ptr(),
-                            vc->const_data_ptr(), data<int32_t>(pl), data<int32_t>(sl), data<void>(out), data<void>(ws),
-                            size_t(bytes_of(ws)), stream()));
+  return status(g.attn_step, &d, q->const_data_ptr(), ks->const_data_ptr(), vs->const_data_ptr(), kc->const_data_ptr(),
+                vc->const_data_ptr(), data<int32_t>(pl), data<int32_t>(sl), data<void>(out), data<void>(ws),
+                size_t(bytes_of(ws)), stream());
 }
 
 // (descriptor address, layers, six table addresses, B, prefix_len, suffix_len, scale)
@@ -142,9 +151,9 @@ PyObject *attn_step_layers(PyObject *, PyObject *const *a, Py_ssize_t n) {
   own.scale = scale;
   ORDINARY(bytes_of(ws) >= int64_t(g.attn_workspace_bytes(&own)));
   auto in = [&](int k) { return static_cast<const void *const *>(p[k]); };
-  return status(g.attn_step_layers(&own, int32_t(reinterpret_cast<intptr_t>(p[1])), in(2), in(3), in(4), in(5), in(6), data<int32_t>(pl),
-                                   data<int32_t>(sl), static_cast<void *const *>(p[7]), data<void>(ws), size_t(bytes_of(ws)),
-                                   stream()));
+  return status(g.attn_step_layers, &own, int32_t(reinterpret_cast<intptr_t>(p[1])), in(2), in(3), in(4), in(5), in(6), data<int32_t>(pl),
+                data<int32_t>(sl), static_cast<void *const *>(p[7]), data<void>(ws), size_t(bytes_of(ws)),
+                stream());
 }
 
 struct ConfOut {
@@ -173,8 +182,8 @@ PyObject *confidence(PyObject *, PyObject *const *a, Py_ssize_t n) {
   ORDINARY(conf_out(a[2], B, S, o));
   const at::Tensor *ws = a[3] == Py_None ? nullptr : device_tensor(a[3]);
   ORDINARY(bytes_of(ws) >= int64_t(g.confidence_workspace_bytes(int32_t(B), int32_t(S), int32_t(V))));
-  return status(g.confidence(type, z->const_data_ptr(), int32_t(B), int32_t(S), int32_t(V), z->stride(1), z->stride(0),
-                             data<int32_t>(sl), o.id, o.prob, o.margin, data<void>(ws), size_t(bytes_of(ws)), stream()));
+  return status(g.confidence, type, z->const_data_ptr(), int32_t(B), int32_t(S), int32_t(V), z->stride(1), z->stride(0),
+                data<int32_t>(sl), o.id, o.prob, o.margin, data<void>(ws), size_t(bytes_of(ws)), stream());
 }
 
 // (hidden, weight, suffix_len or None, out, workspace)
@@ -191,9 +200,9 @@ PyObject *lm_head_confidence(PyObject *, PyObject *const *a, Py_ssize_t n) {
   ORDINARY(conf_out(a[3], B, S, o));
   const at::Tensor *ws = device_tensor(a[4]);
   ORDINARY(ws && bytes_of(ws) >= int64_t(g.lm_head_confidence_workspace_bytes(int32_t(B), int32_t(S), int32_t(V))));
-  return status(g.lm_head_confidence(type, h->const_data_ptr(), w->const_data_ptr(), int32_t(B), int32_t(S), int32_t(K), int32_t(V),
-                                     h->stride(1), h->stride(0), w->stride(0), data<int32_t>(sl), o.id, o.prob, o.margin,
-                                     data<void>(ws), size_t(bytes_of(ws)), stream()));
+  return status(g.lm_head_confidence, type, h->const_data_ptr(), w->const_data_ptr(), int32_t(B), int32_t(S), int32_t(K), int32_t(V),
+                h->stride(1), h->stride(0), w->stride(0), data<int32_t>(sl), o.id, o.prob, o.margin,
+                data<void>(ws), size_t(bytes_of(ws)), stream());
 }
 
 PyObject *k_mask, *k_raw, *k_snapped, *k_len, *k_flags, *k_tau;  // keys of commit's result
@@ -250,10 +259,10 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
                    *flags = per_sequence(k_flags, at::kInt), *tau = per_sequence(k_tau, at::kFloat);
   if (PyErr_Occurred()) return nullptr;
   ORDINARY(mask && raw && snapped && len && flags && tau);
-  return status(g.commit(&d, data<float>(margin), data<int32_t>(id), data<uint32_t>(bm), tab[0], tab[1],
-                         const_cast<void *const *>(tab[2]), const_cast<void *const *>(tab[3]), data<int32_t>(tokens), data<int32_t>(pl),
-                         data<int32_t>(sl), data<uint8_t>(mask), data<int32_t>(raw), data<int32_t>(snapped), data<int32_t>(len),
-                         data<int32_t>(flags), data<float>(tau), nullptr, 0, stream()));
+  return status(g.commit, &d, data<float>(margin), data<int32_t>(id), data<uint32_t>(bm), tab[0], tab[1],
+                const_cast<void *const *>(tab[2]), const_cast<void *const *>(tab[3]), data<int32_t>(tokens), data<int32_t>(pl),
+                data<int32_t>(sl), data<uint8_t>(mask), data<int32_t>(raw), data<int32_t>(snapped), data<int32_t>(len),
+                data<int32_t>(flags), data<float>(tau), nullptr, 0, stream());
 }
 
 // (top1_id, prefix_len, suffix_len, base_prefix_len, last_id, counters, window_lo, window_hi, step_counts or None)
@@ -272,9 +281,9 @@ PyObject *flip_update(PyObject *, PyObject *const *a, Py_ssize_t n) {
     PyErr_Clear();
     Py_RETURN_NONE;
   }
-  return status(g.flip_update(data<int32_t>(id), int32_t(B), int32_t(S), int32_t(G), data<int32_t>(pl), data<int32_t>(sl),
-                              data<int32_t>(base), data<int32_t>(last), data<int64_t>(counters), int32_t(lo), int32_t(hi),
-                              data<int32_t>(steps), stream()));
+  return status(g.flip_update, data<int32_t>(id), int32_t(B), int32_t(S), int32_t(G), data<int32_t>(pl), data<int32_t>(sl),
+                data<int32_t>(base), data<int32_t>(last), data<int64_t>(counters), int32_t(lo), int32_t(hi),
+                data<int32_t>(steps), stream());
 }
 
 // No C++ exception may reach the interpreter: torch throws where a tensor has no strides or no

@@ -1,5 +1,10 @@
 """The native marshalling module (csrc/binding.cpp) against the general path in Python: same results, and
 arguments that are not in their ordinary form are left to the general path, which refuses or handles them."""
+import ctypes
+import subprocess
+import threading
+import time
+
 import pytest
 import torch
 
@@ -79,6 +84,31 @@ def test_native_and_general_path_agree(lsp, monkeypatch, with_tokens, with_layer
     monkeypatch.setattr(lsp, "_nat", None)
     b = _step(lsp, with_tokens, with_layers, counts)
     assert len(a) == len(b) and all(torch.equal(x, y) for x, y in zip(a, b))
+
+
+def test_other_threads_run_during_a_call(lsp, tmp_path):
+    """The entry point is replaced by a host function that waits up to two seconds for a flag, which another Python thread sets."""
+    src = tmp_path / "wait.c"
+    src.write_text("#include <unistd.h>\nvolatile int flag;\nint wait_for_flag(void) {\n"
+                   "  for (int i = 0; i < 2000 && !flag; ++i) usleep(1000);\n  return flag ? 0 : 7;\n}\n")
+    subprocess.run(["gcc", "-shared", "-fPIC", str(src), "-o", str(tmp_path / "wait.so")], check=True)
+    fake = ctypes.CDLL(str(tmp_path / "wait.so"))
+    addr = [ctypes.cast(getattr(lsp.lib(), n), ctypes.c_void_p).value for n in lsp.NATIVE_ENTRIES]
+    i32 = [torch.zeros(n, dtype=torch.int32, device="cuda") for n in ((2, 3), 2, 2, 2, (2, 3))]
+
+    def release():
+        time.sleep(0.05)
+        ctypes.c_int.in_dll(fake, "flag").value = 1
+
+    lsp._nat.bind(*[ctypes.cast(fake.wait_for_flag, ctypes.c_void_p).value if n == "lsp_flip_update" else a for n, a in zip(lsp.NATIVE_ENTRIES, addr)])
+    try:
+        t = threading.Thread(target=release)
+        t.start()
+        rc = lsp._nat.flip_update(*i32, torch.zeros(4, dtype=torch.int64, device="cuda"), 1, 0, None)
+        t.join()
+    finally:
+        lsp._nat.bind(*addr)
+    assert rc == 0
 
 
 def test_unusual_arguments_reach_the_general_path(lsp):
