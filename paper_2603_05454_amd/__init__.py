@@ -233,14 +233,13 @@ class AttnLayerTable:
         self.desc.cache_stride = _strides3(k_cache[0])
         self.desc.o_stride = _strides3(out[0])
         self.out = out
-        self.plain = (ctypes.addressof(self.desc), n, *[ctypes.addressof(a) for a in self.arrays])   # for the native module
 
 
 def attn_step_layers(table: AttnLayerTable, prefix_len, suffix_len, scale=0.0, workspace=None):
     """lsp_attn_step_layers: the attention of every layer of `table` in one launch.
     Returns the list of per-layer outputs (table.out)."""
     if _nat is not None:
-        rc = _nat.attn_step_layers(table.plain, prefix_len, suffix_len, scale, workspace)
+        rc = _nat.attn_step_layers(table.desc, table.n, table.arrays, prefix_len, suffix_len, scale, workspace)
         if rc is not None:
             _check(rc, "lsp_attn_step_layers")
             return table.out
@@ -382,8 +381,6 @@ class LayerTable:
         self.C = k_cache[0].shape[1]
         self.suf_bs = k_suf[0].stride(0)
         self.cache_bs = k_cache[0].stride(0)
-        self.plain = (*[ctypes.addressof(a) for a in self.arrays], self.kv_dtype, self.B, self.S, self.Hkv, self.D, self.C, n,
-                      self.suf_bs, self.cache_bs)      # for the native module
 
 
 def commit(margin, top1_id, bitmap, V, tau, window, min_commit, snap_enabled,
@@ -393,7 +390,7 @@ def commit(margin, top1_id, bitmap, V, tau, window, min_commit, snap_enabled,
     `layers` in place.  Returns dict(stable_mask, raw_boundary, snapped_boundary,
     commit_len, status_flags, tau_used)."""
     if _nat is not None and out is not None and (layers is not None or C is not None):
-        rc = _nat.commit(margin, top1_id, bitmap, prefix_len, suffix_len, tokens, None if layers is None else layers.plain, out,
+        rc = _nat.commit(margin, top1_id, bitmap, prefix_len, suffix_len, tokens, layers, out,
                          (V, tau, window, min_commit, snap_enabled, adaptive, alpha, beta, max_commit, 0 if C is None else C))
         if rc is not None:
             _check(rc, "lsp_commit")

@@ -76,6 +76,40 @@ bool number(PyObject *o, float &x) {
   return false;
 }
 
+bool integer(PyObject *o, long &x) {
+  x = o ? PyLong_AsLong(o) : 0;
+  if (!PyErr_Occurred()) return true;
+  PyErr_Clear();
+  return false;
+}
+struct Object {  // a reference of one's own
+  PyObject *o;
+  explicit Object(PyObject *p) : o(p) {}
+  ~Object() { Py_XDECREF(o); }
+  Object(const Object &) = delete;
+};
+// The memory of a ctypes object, held while this lives.
+struct Memory {
+  Py_buffer view = {};
+  Memory() = default;
+  ~Memory() { PyBuffer_Release(&view); }
+  Memory(const Memory &) = delete;
+  bool of(PyObject *o, size_t bytes) {
+    if (PyObject_GetBuffer(o, &view, PyBUF_SIMPLE) == 0) return size_t(view.len) >= bytes;
+    PyErr_Clear();
+    return false;
+  }
+};
+// a list of N tables of `layers` pointers each
+template <int N>
+bool tables(PyObject *list, Memory (&tab)[N], long layers) {
+  if (!list) PyErr_Clear();
+  if (!list || !PyList_Check(list) || PyList_GET_SIZE(list) != N) return false;
+  for (int k = 0; k < N; ++k)
+    if (!tab[k].of(PyList_GET_ITEM(list, k), size_t(layers) * sizeof(void *))) return false;
+  return true;
+}
+
 // The entry point itself runs without the interpreter lock: a launch waits for a full queue, and a kernel's first one
 // loads its code.  What it reads of Python's is held by the caller's references meanwhile.
 template <typename... P, typename... A>
@@ -88,12 +122,14 @@ PyObject *status(int32_t (*entry)(P...), A... args) {
 }
 #define ORDINARY(cond) \
   if (!(cond)) Py_RETURN_NONE
+#define ARGUMENTS(count)                                                              \
+  if (n != count) {                                                                   \
+    PyErr_Format(PyExc_TypeError, "%s: %d arguments expected, got %zd", __func__, count, n); \
+    return nullptr;                                                                   \
+  }
 
 PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  if (n != kEntries) {
-    PyErr_Format(PyExc_TypeError, "bind: %d addresses expected", kEntries);
-    return nullptr;
-  }
+  ARGUMENTS(kEntries);
   void *p[kEntries];
   for (int k = 0; k < kEntries; ++k) p[k] = PyLong_AsVoidPtr(a[k]);
   if (PyErr_Occurred()) return nullptr;
@@ -111,7 +147,7 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
 
 // (q, k_suf, v_suf, k_cache, v_cache, prefix_len, suffix_len, scale, out, workspace)
 PyObject *attn_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  ORDINARY(n == 10 && g.attn_step);
+  ARGUMENTS(10);
   const at::Tensor *q = device_tensor(a[0]), *ks = device_tensor(a[1]), *vs = device_tensor(a[2]), *kc = device_tensor(a[3]),
                    *vc = device_tensor(a[4]), *out = device_tensor(a[8]);
   ORDINARY(q && ks && vs && kc && vc && out && q->dim() == 4 && ks->dim() == 4 && kc->dim() == 4);
@@ -136,24 +172,21 @@ PyObject *attn_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
                 size_t(bytes_of(ws)), stream());
 }
 
-// (descriptor address, layers, six table addresses, B, prefix_len, suffix_len, scale)
+// (table descriptor, layers, list of six tables, prefix_len, suffix_len, scale, workspace or None)
 PyObject *attn_step_layers(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  ORDINARY(n == 5 && g.attn_step_layers && PyTuple_Check(a[0]) && PyTuple_GET_SIZE(a[0]) == 8);
-  void *p[8];
-  for (int k = 0; k < 8; ++k) p[k] = PyLong_AsVoidPtr(PyTuple_GET_ITEM(a[0], k));
-  lsp_attn_desc *d = static_cast<lsp_attn_desc *>(p[0]);
-  float scale;
-  ORDINARY(number(a[3], scale));
-  const at::Tensor *pl = plain(a[1], at::kInt, d->B), *sl = plain(a[2], at::kInt, d->B);
+  ARGUMENTS(7);
+  Memory desc, tab[6];
+  long layers;
+  ORDINARY(integer(a[1], layers) && layers > 0 && desc.of(a[0], sizeof(lsp_attn_desc)) && tables(a[2], tab, layers));
+  lsp_attn_desc own = *static_cast<const lsp_attn_desc *>(desc.view.buf);
+  ORDINARY(number(a[5], own.scale));
+  const at::Tensor *pl = plain(a[3], at::kInt, own.B), *sl = plain(a[4], at::kInt, own.B);
   ORDINARY(pl && sl);
-  const at::Tensor *ws = a[4] == Py_None ? nullptr : device_tensor(a[4]);
-  lsp_attn_desc own = *d;
-  own.scale = scale;
+  const at::Tensor *ws = a[6] == Py_None ? nullptr : device_tensor(a[6]);
   ORDINARY(bytes_of(ws) >= int64_t(g.attn_workspace_bytes(&own)));
-  auto in = [&](int k) { return static_cast<const void *const *>(p[k]); };
-  return status(g.attn_step_layers, &own, int32_t(reinterpret_cast<intptr_t>(p[1])), in(2), in(3), in(4), in(5), in(6), data<int32_t>(pl),
-                data<int32_t>(sl), static_cast<void *const *>(p[7]), data<void>(ws), size_t(bytes_of(ws)),
-                stream());
+  auto in = [&](int k) { return static_cast<const void *const *>(tab[k].view.buf); };
+  return status(g.attn_step_layers, &own, int32_t(layers), in(0), in(1), in(2), in(3), in(4), data<int32_t>(pl), data<int32_t>(sl),
+                static_cast<void *const *>(tab[5].view.buf), data<void>(ws), size_t(bytes_of(ws)), stream());
 }
 
 struct ConfOut {
@@ -171,7 +204,7 @@ bool conf_out(PyObject *o, int64_t B, int64_t S, ConfOut &r) {
 
 // (logits, suffix_len or None, out, workspace or None)
 PyObject *confidence(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  ORDINARY(n == 4 && g.confidence);
+  ARGUMENTS(4);
   const at::Tensor *z = device_tensor(a[0]);
   int32_t type;
   ORDINARY(z && z->dim() == 3 && z->stride(2) == 1 && element_type(*z, type));
@@ -188,7 +221,7 @@ PyObject *confidence(PyObject *, PyObject *const *a, Py_ssize_t n) {
 
 // (hidden, weight, suffix_len or None, out, workspace)
 PyObject *lm_head_confidence(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  ORDINARY(n == 5 && g.lm_head_confidence);
+  ARGUMENTS(5);
   const at::Tensor *h = device_tensor(a[0]), *w = device_tensor(a[1]);
   int32_t type;
   ORDINARY(h && w && h->dim() == 3 && w->dim() == 2 && h->stride(2) == 1 && w->stride(1) == 1 && element_type(*h, type));
@@ -206,11 +239,15 @@ PyObject *lm_head_confidence(PyObject *, PyObject *const *a, Py_ssize_t n) {
 }
 
 PyObject *k_mask, *k_raw, *k_snapped, *k_len, *k_flags, *k_tau;  // keys of commit's result
+// attributes of a layer table: the tables, then numbers
+PyObject *k_arrays, *k_numbers[9];
+constexpr const char *kNumbers[9] = {"kv_dtype", "B", "S", "Hkv", "D", "C", "n", "suf_bs", "cache_bs"};
 
 // (margin, top1_id, bitmap, prefix_len, suffix_len, tokens or None, layer table or None, out,
 //  (V, tau, window, min_commit, snap_enabled, adaptive, alpha, beta, max_commit, C))
 PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  ORDINARY(n == 9 && g.commit && PyDict_Check(a[7]) && PyDict_GET_SIZE(a[7]) == 6 && PyTuple_Check(a[8]) && PyTuple_GET_SIZE(a[8]) == 10);
+  ARGUMENTS(9);
+  ORDINARY(PyDict_Check(a[7]) && PyDict_GET_SIZE(a[7]) == 6 && PyTuple_Check(a[8]) && PyTuple_GET_SIZE(a[8]) == 10);
   const at::Tensor *margin = device_tensor(a[0]);
   ORDINARY(margin && margin->dim() == 2);
   const int64_t B = margin->size(0), S = margin->size(1);
@@ -236,16 +273,17 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
   d.B = int32_t(B); d.S = int32_t(S); d.V = int32_t(i[0]); d.tau = float(f[1]); d.window = int32_t(i[2]); d.min_commit = int32_t(i[3]);
   d.snap_enabled = int32_t(i[4]); d.adaptive = i[5] != 0; d.alpha = float(f[6]); d.beta = float(f[7]); d.max_commit = int32_t(i[8]);
   d.T = tokens ? int32_t(tokens->size(1)) : 0;
-  const void *const *tab[4] = {nullptr, nullptr, nullptr, nullptr};
-  if (a[6] != Py_None) {  // (four table addresses, kv_dtype, B, S, Hkv, D, C, layers, suffix and cache batch strides)
-    ORDINARY(PyTuple_Check(a[6]) && PyTuple_GET_SIZE(a[6]) == 13);
-    long long t[13];
-    for (int k = 0; k < 13; ++k) t[k] = PyLong_AsLongLong(PyTuple_GET_ITEM(a[6], k));
-    if (PyErr_Occurred()) return nullptr;
-    ORDINARY(t[5] == B && t[6] == S);
-    for (int k = 0; k < 4; ++k) tab[k] = reinterpret_cast<const void *const *>(t[k]);
-    d.kv_dtype = int32_t(t[4]); d.Hkv = int32_t(t[7]); d.D = int32_t(t[8]); d.C = int32_t(t[9]); d.num_layers = int32_t(t[10]);
-    d.suf_batch_stride = t[11]; d.cache_batch_stride = t[12];
+  Memory tab[4];
+  if (a[6] != Py_None) {
+    long t[9];
+    for (int k = 0; k < 9; ++k) {
+      Object x(PyObject_GetAttr(a[6], k_numbers[k]));
+      ORDINARY(integer(x.o, t[k]));
+    }
+    Object arrays(PyObject_GetAttr(a[6], k_arrays));
+    ORDINARY(t[1] == B && t[2] == S && t[6] > 0 && tables(arrays.o, tab, t[6]));
+    d.kv_dtype = int32_t(t[0]); d.Hkv = int32_t(t[3]); d.D = int32_t(t[4]); d.C = int32_t(t[5]); d.num_layers = int32_t(t[6]);
+    d.suf_batch_stride = t[7]; d.cache_batch_stride = t[8];
   } else {
     d.C = int32_t(i[9]);
   }
@@ -259,15 +297,15 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
                    *flags = per_sequence(k_flags, at::kInt), *tau = per_sequence(k_tau, at::kFloat);
   if (PyErr_Occurred()) return nullptr;
   ORDINARY(mask && raw && snapped && len && flags && tau);
-  return status(g.commit, &d, data<float>(margin), data<int32_t>(id), data<uint32_t>(bm), tab[0], tab[1],
-                const_cast<void *const *>(tab[2]), const_cast<void *const *>(tab[3]), data<int32_t>(tokens), data<int32_t>(pl),
-                data<int32_t>(sl), data<uint8_t>(mask), data<int32_t>(raw), data<int32_t>(snapped), data<int32_t>(len),
+  return status(g.commit, &d, data<float>(margin), data<int32_t>(id), data<uint32_t>(bm), static_cast<const void *const *>(tab[0].view.buf),
+                static_cast<const void *const *>(tab[1].view.buf), static_cast<void *const *>(tab[2].view.buf),
+                static_cast<void *const *>(tab[3].view.buf), data<int32_t>(tokens), data<int32_t>(pl), data<int32_t>(sl), data<uint8_t>(mask), data<int32_t>(raw), data<int32_t>(snapped), data<int32_t>(len),
                 data<int32_t>(flags), data<float>(tau), nullptr, 0, stream());
 }
 
 // (top1_id, prefix_len, suffix_len, base_prefix_len, last_id, counters, window_lo, window_hi, step_counts or None)
 PyObject *flip_update(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  ORDINARY(n == 9 && g.flip_update);
+  ARGUMENTS(9);
   const at::Tensor *id = device_tensor(a[0]), *last = device_tensor(a[4]);
   ORDINARY(id && id->dim() == 2 && last && last->dim() == 2);
   const int64_t B = id->size(0), S = id->size(1), G = last->size(1);
@@ -316,5 +354,7 @@ PyMODINIT_FUNC PyInit__binding() {
   k_len = PyUnicode_InternFromString("commit_len");
   k_flags = PyUnicode_InternFromString("status_flags");
   k_tau = PyUnicode_InternFromString("tau_used");
+  k_arrays = PyUnicode_InternFromString("arrays");
+  for (int k = 0; k < 9; ++k) k_numbers[k] = PyUnicode_InternFromString(kNumbers[k]);
   return PyModule_Create(&module);
 }

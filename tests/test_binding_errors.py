@@ -18,6 +18,13 @@ def test_an_exception_from_torch_is_raised_in_python():
             lsp.confidence(z, None, out=out)
 
 
+def test_a_wrong_number_of_arguments_is_an_error():
+    lsp.lib()
+    for name in ("bind", "attn_step", "attn_step_layers", "confidence", "lm_head_confidence", "commit", "flip_update"):
+        with pytest.raises(TypeError, match=name):
+            getattr(lsp._nat, name)(1, 2)
+
+
 class _Raises(torch.Tensor):
     """A device tensor of a subclass whose own Python code raises when its layout is asked for."""
 

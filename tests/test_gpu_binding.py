@@ -86,6 +86,31 @@ def test_native_and_general_path_agree(lsp, monkeypatch, with_tokens, with_layer
     assert len(a) == len(b) and all(torch.equal(x, y) for x, y in zip(a, b))
 
 
+def test_replaced_attributes_of_a_table_are_the_ones_used(lsp):
+    """A table's descriptor and pointer arrays belong to the table: a caller that exchanges them (to point one table at another
+    set of buffers) gets what the new ones say, on the native path as on the general one."""
+    w, kv, pl, sl, _, bm, tok = _state()
+    cols = {k: [l[k] for l in kv] for k in kv[0]}
+    names = ("q", "k_suf", "v_suf", "k_cache", "v_cache")
+    other = {k: [torch.randn_like(t) for t in cols[k]] for k in names}
+    table = lsp.AttnLayerTable(*[cols[k] for k in names], [torch.zeros_like(q) for q in cols["q"]])
+    want = lsp.AttnLayerTable(*[other[k] for k in names], [torch.zeros_like(q) for q in cols["q"]])
+    lsp.attn_step_layers(want, pl, sl)
+    table.arrays = [type(a)(*a) for a in want.arrays[:5]] + [table.arrays[5]]
+    table.desc = lsp.AttnDesc.from_buffer_copy(table.desc)
+    rc = lsp._nat.attn_step_layers(table.desc, table.n, table.arrays, pl, sl, 0.0, None)
+    assert rc == 0 and all(torch.equal(a, b) for a, b in zip(table.out, want.out))
+    assert lsp._nat.attn_step_layers(table.desc, table.n + 1, table.arrays, pl, sl, 0.0, None) is None     # arrays too short
+    kvt = lsp.LayerTable(*[cols[k] for k in names[1:]])
+    before = [t.clone() for t in cols["k_cache"]]
+    kvt.arrays = [type(a)(*a) for a in lsp.LayerTable(*[other[k] for k in names[1:]]).arrays]
+    margin, ids, p0 = torch.ones((w.B, w.S), device="cuda"), torch.zeros((w.B, w.S), dtype=torch.int32, device="cuda"), pl.clone()
+    got = lsp.commit(margin, ids, bm, w.V, 0.5, 0, 1, 0, pl, sl, tokens=tok, layers=kvt, out=_commit_out(w.B, w.S))
+    assert (got["commit_len"] > 0).all() and all(torch.equal(a, b) for a, b in zip(before, cols["k_cache"]))
+    for b, (p, n) in enumerate(zip(p0.tolist(), got["commit_len"].tolist())):
+        assert all(torch.equal(c[b, p:p + n], s[b, :n]) for c, s in zip(other["k_cache"], other["k_suf"]))
+
+
 def test_other_threads_run_during_a_call(lsp, tmp_path):
     """The entry point is replaced by a host function that waits up to two seconds for a flag, which another Python thread sets."""
     src = tmp_path / "wait.c"
