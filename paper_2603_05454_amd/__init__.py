@@ -15,13 +15,14 @@ from __future__ import annotations
 
 import ctypes
 import os
+import warnings
 
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblsp.so")
 _lib = None
-_nat = None     # the native marshalling module, bound to the loaded library
+_nat = None     # the native marshalling module, bound to the loaded library (None: not loaded, or not built)
 
 LSP_F32, LSP_BF16 = 0, 1
 FLAG_CACHE_FULL, FLAG_TOKENS_FULL = 1, 2
@@ -78,11 +79,13 @@ def lib() -> ctypes.CDLL:
             getattr(L, n).restype = ctypes.c_int32
         try:
             from . import _binding
-        except ImportError as e:
-            raise LspError(f"the native binding module is missing ({e}): run `python -m paper_2603_05454_amd.build` "
-                           "(or __graft_entry__.build()) first") from e
-        _binding.bind(*[ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in NATIVE_ENTRIES])
-        _lib, _nat = L, _binding
+        except ImportError as e:    # every call has its general path, which only costs more host time
+            warnings.warn(f"the native binding module cannot be loaded ({e}), calls are marshalled in Python: "
+                          "run `python -m paper_2603_05454_amd.build` (or __graft_entry__.build())", RuntimeWarning, stacklevel=2)
+        else:
+            _binding.bind(*[ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in NATIVE_ENTRIES])
+            _nat = _binding
+        _lib = L
     return _lib
 
 

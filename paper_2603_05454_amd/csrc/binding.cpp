@@ -7,7 +7,7 @@
 //
 // Why: through ctypes a call cost 9-18 us on the host (attribute reads, checks and
 // conversions of up to 20 arguments in the interpreter), more than many of
-// the kernels behind it take; here it is 3-7 us, most of it the launch itself.
+// the kernels behind it take; here it is 4-10 us, most of it the launch itself.
 #include <Python.h>
 #include <hip/hip_runtime_api.h>
 

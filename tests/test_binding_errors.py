@@ -25,6 +25,20 @@ def test_a_wrong_number_of_arguments_is_an_error():
             getattr(lsp._nat, name)(1, 2)
 
 
+def test_the_library_loads_without_the_module(monkeypatch):
+    """liblsp.so alone is enough: the general path makes every call."""
+    import sys
+    monkeypatch.setattr(lsp, "_lib", None)
+    monkeypatch.setattr(lsp, "_nat", None)
+    monkeypatch.delattr(lsp, "_binding", raising=False)
+    monkeypatch.setitem(sys.modules, "paper_2603_05454_amd._binding", None)
+    with pytest.warns(RuntimeWarning, match="native binding module"):
+        assert "gfx950" in lsp.version()
+    assert lsp._nat is None
+    with pytest.raises(lsp.LspError, match="device tensors only"):
+        lsp.confidence(torch.zeros(1, 2, 8))
+
+
 class _Raises(torch.Tensor):
     """A device tensor of a subclass whose own Python code raises when its layout is asked for."""
 
