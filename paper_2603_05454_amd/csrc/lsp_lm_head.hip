@@ -466,29 +466,31 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   else run_tiles<128>(a, smem, tb, cur);
 }
 
-// One wave per row folds the row's VT partials and writes the three results.
+// One wave per row folds the row's VT partials and writes the three results.  (A grid dimension ends at 2^32 threads and a
+// launch beyond loses its last workgroups without an error: more rows than kFinishGrid workgroups hold are taken in turn.)
+constexpr int kFinishGrid = 1 << 20;
 __global__ __launch_bounds__(256) void lm_head_finish_kernel(const Partial *__restrict__ partials, int rows, int S, int VT,
                                                              const int32_t *__restrict__ suffix_len,
                                                              int32_t *__restrict__ top1_id,
                                                              float *__restrict__ top1_prob,
                                                              float *__restrict__ margin) {
   const int lane = threadIdx.x & 63;
-  const int r = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (r >= rows) return;
-  if (suffix_len != nullptr && (r % S) >= suffix_len[r / S]) return;
-  Partial p;
-  p.m1 = -INFINITY; p.m2 = -INFINITY; p.s = 0.f; p.idx = 0x7fffffff;
-  for (int t = lane; t < VT; t += 64) p = fold(p, partials[int64_t(r) * VT + t]);
+  for (int r = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6); r < rows; r += gridDim.x * (blockDim.x >> 6)) {
+    if (suffix_len != nullptr && (r % S) >= suffix_len[r / S]) continue;
+    Partial p;
+    p.m1 = -INFINITY; p.m2 = -INFINITY; p.s = 0.f; p.idx = 0x7fffffff;
+    for (int t = lane; t < VT; t += 64) p = fold(p, partials[int64_t(r) * VT + t]);
 #pragma unroll
-  for (int d = 32; d >= 1; d >>= 1) {
-    Partial o;
-    o.m1 = __shfl_xor(p.m1, d); o.m2 = __shfl_xor(p.m2, d); o.s = __shfl_xor(p.s, d); o.idx = __shfl_xor(p.idx, d);
-    p = fold(p, o);
-  }
-  if (lane == 0) {
-    top1_id[r] = p.idx;
-    margin[r] = p.m1 - p.m2;
-    top1_prob[r] = 1.0f / p.s;
+    for (int d = 32; d >= 1; d >>= 1) {
+      Partial o;
+      o.m1 = __shfl_xor(p.m1, d); o.m2 = __shfl_xor(p.m2, d); o.s = __shfl_xor(p.s, d); o.idx = __shfl_xor(p.idx, d);
+      p = fold(p, o);
+    }
+    if (lane == 0) {
+      top1_id[r] = p.idx;
+      margin[r] = p.m1 - p.m2;
+      top1_prob[r] = 1.0f / p.s;
+    }
   }
 }
 
@@ -567,7 +569,8 @@ extern "C" int32_t lsp_lm_head_confidence(int32_t dtype, const void *hidden, con
   hipStream_t st = static_cast<hipStream_t>(stream);
   const int32_t rc = launch_lm_head(a, st);
   if (rc != LSP_OK) return rc;
-  lm_head_finish_kernel<<<dim3(static_cast<unsigned>((rows + 3) / 4)), 256, 0, st>>>(
+  const int64_t finish = (rows + 3) / 4;
+  lm_head_finish_kernel<<<dim3(unsigned(finish < kFinishGrid ? finish : kFinishGrid)), 256, 0, st>>>(
       a.partials, int(rows), S, a.VT, suffix_len, top1_id, top1_prob, margin);
   LSP_CHECK_LAUNCH("lsp_lm_head_confidence: finish launch");
   return LSP_OK;

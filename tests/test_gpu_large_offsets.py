@@ -126,3 +126,22 @@ def test_f32_attention_in_more_workgroups_than_one_grid_dimension_holds(lsp, ora
         torch.cuda.synchronize()
         ref = oracle.attention(**kv, prefix_len=torch.tensor([P], dtype=torch.int32), suffix_len=torch.tensor([n], dtype=torch.int32))
         assert (out[:, :n].cpu() - ref[:, :n]).abs().max().item() <= 1e-5 and torch.all(out[:, n:] == 123.0)
+
+
+def test_lm_head_on_more_rows_than_one_grid_dimension_holds_waves(lsp, oracle):
+    """1100 x 61440 rows (67.6 million, one wave each in the second kernel, where a grid dimension ends at 2**26 waves): rows at
+    both ends, either side of the mark and around the last full grid are bit-exact on small integers, and none is left out."""
+    B, S, K, V = 1100, 61440, 8, 5
+    g = torch.Generator(device="cuda").manual_seed(8)
+    h = torch.randint(-3, 4, (B, S, K), generator=g, device="cuda", dtype=torch.int8).to(torch.bfloat16)
+    w = torch.randint(-3, 4, (V, K), generator=g, device="cuda").to(torch.bfloat16)
+    out = (torch.full((B, S), -7, dtype=torch.int32, device="cuda"), torch.full((B, S), -7.0, device="cuda"), torch.full((B, S), -7.0, device="cuda"))
+    ids, p, m = (x.view(-1) for x in lsp.lm_head_confidence(h, w, out=out))
+    torch.cuda.synchronize()
+    R = B * S
+    rows = torch.tensor([0, 1, 2**22 - 1, 2**22, 2**26 - 1, 2**26, 2**26 + 1, 2**26 + 300000, R - 2, R - 1], device="cuda")
+    ids_r, p_r, m_r = oracle.lm_head_confidence(h.view(-1, K)[rows].cpu().unsqueeze(0), w.cpu())
+    assert torch.equal(ids[rows].cpu(), ids_r[0]) and torch.equal(m[rows].cpu(), m_r[0])
+    assert (p[rows].cpu() - p_r[0]).abs().max().item() <= 1e-6
+    # p = 1 / (fp32 sum of V exponentials, the largest of which is 1 up to rounding): within 1e-6 of [1 / V, 1]
+    assert ((ids >= 0) & (ids < V)).all() and (m >= 0).all() and ((p >= 1 / V - 1e-6) & (p <= 1 + 1e-6)).all()
