@@ -150,7 +150,16 @@ def test_unusual_arguments_reach_the_general_path(lsp):
         lsp.commit(out[2], out[0], bm[:1].contiguous(), w.V, 0.9, 4, 1, 1, pl, sl, C=w.C, out=_commit_out(w.B, w.S))
     with pytest.raises(lsp.LspError, match="NaN"):         # an error of the library itself
         lsp.commit(out[2], out[0], bm, w.V, float("nan"), 4, 1, 1, pl, sl, C=w.C, out=_commit_out(w.B, w.S))
-    few = z[:, :5].contiguous()                            # split rows: the general path allocates the workspace
-    assert lsp.confidence_workspace_bytes(*few.shape) == 0 or few.shape[2] > 0
-    got = lsp.confidence(few, None, out=_conf_out(w.B, 5))
-    assert torch.equal(got[0].long(), few.float().argmax(-1))
+
+
+def test_a_missing_workspace_is_allocated_by_the_general_path(lsp):
+    g = torch.Generator(device="cuda").manual_seed(5)
+    z = torch.randn((1, 5, 40000), generator=g, device="cuda")         # few long rows are split over workgroups
+    out = _conf_out(1, 5)
+    assert lsp.confidence_workspace_bytes(*z.shape) > 0 and lsp._nat.confidence(z, None, out, None) is None
+    assert torch.equal(lsp.confidence(z, None, out=out)[0].long(), z.argmax(-1))
+    h, wt = (torch.randint(-3, 4, s, generator=g, device="cuda").to(torch.bfloat16) for s in ((1, 5, 64), (600, 64)))
+    small = torch.empty(lsp.lm_head_confidence_workspace_bytes(1, 5, 600) - 16, dtype=torch.uint8, device="cuda")
+    assert lsp._nat.lm_head_confidence(h, wt, None, out, small) is None
+    top = (h.float() @ wt.float().T).topk(2, -1).values                # integers: exact
+    assert torch.equal(lsp.lm_head_confidence(h, wt, None, out=out, workspace=small)[2], top[..., 0] - top[..., 1])

@@ -226,7 +226,6 @@ def test_many_layers_more_than_one_launch(lsp, oracle):
     _both(lsp, oracle, margin, ids, _bitmap([]), V, 0.9, 16, 1, 1, pl, sl, layers=layers)
 
 
-# ---- adaptive threshold (Section 3.2 targeted block sizing, Eq. 2) and commit cap (Table 2) ----
 @pytest.mark.parametrize("B,S,heads,layers", [(1, 1, 1, 1), (3, 70, 1, 2), (64, 9, 8, 2), (65, 9, 8, 1), (130, 40, 4, 1), (2, 700, 40, 3)])
 def test_append_work_shared_over_sequences(lsp, oracle, B, S, heads, layers):
     """Blocks of zero, one and many 8 KB chunks with remainders, sequences that commit nothing between others that do,
@@ -244,6 +243,7 @@ def test_append_work_shared_over_sequences(lsp, oracle, B, S, heads, layers):
           tokens=W.make_tokens(W.scaled(w, V=V), w.C), layers=kv)
 
 
+# ---- adaptive threshold (Section 3.2 targeted block sizing, Eq. 2) and commit cap (Table 2) ----
 @pytest.mark.parametrize("alpha,beta", [(0.25, 0.5), (0.5, 0.5), (0.2, 1.0), (0.75, 0.75)])
 def test_adaptive_every_small_margin_vector(lsp, oracle, alpha, beta):
     N = 5

@@ -94,9 +94,9 @@ def _integer_case(lsp, oracle, B, S, K, V, lens, seed):
 @pytest.mark.parametrize("rows", [1, 63, 64, 65, 128, 129, 256, 257, 385])
 @pytest.mark.parametrize("V", [256, 2 * 256 + 1, 70 * 256 - 3])
 def test_tile_heights(lsp, oracle, rows, V):
-    """Active rows at the edges of the tile heights (64, 128, 256 and the 257-384 rule), spread over three
-    sequences; few vocabulary tiles (lower tiles fill the chip) and more tiles than compute units (a
-    workgroup goes on to a second tile), with a ragged last vocabulary tile."""
+    """Active rows at multiples of the tile heights and one beside them, spread over three sequences; one to 70
+    vocabulary tiles, the last one ragged.  A launch this small takes tiles of 64 or 128 rows (385 rows x 70 tiles: 256),
+    one per workgroup."""
     a, b = rows // 2, rows // 5
     _integer_case(lsp, oracle, 3, rows + 3, 64 * 5, V, [a, rows - a - b, b], seed=rows + V)
 
@@ -105,8 +105,34 @@ def test_tile_heights(lsp, oracle, rows, V):
 @pytest.mark.parametrize("K", [8, 64, 120, 128, 136, 192, 200, 64 * 37])
 def test_k_steps(lsp, oracle, rows, K):
     """K below, at and just beyond the steps that are in flight at the loop's start, with and without a ragged
-    last step, and long enough for every staggered start; 600 rows take tiles of 256."""
+    last step; tiles of 64 rows (600 rows: of 128), one per workgroup."""
     _integer_case(lsp, oracle, 1, rows, K, 33 * 256 + 5, None, seed=rows + K)
+
+
+def _dispatch(rows, V):
+    """The kernel's own rule for `rows` active rows in a buffer of as many: rows per tile, row tiles, tiles of the busiest workgroup."""
+    vt = -(-V // 256)
+    tiles = lambda h: -(-rows // h)
+    tr = 64 if vt * tiles(64) <= 256 else 128 if vt * tiles(128) <= 256 or rows <= 128 or 256 < rows <= 384 else 256
+    slots = min(32, -(-vt // 8) * tiles(256 if tr == 256 else 64))
+    return 64 if min(tr, rows) <= 64 else tr, tiles(tr), -(-(-(-vt // 8) * tiles(tr)) // slots)
+
+
+@pytest.mark.parametrize("rows,vt,plan", [(40, 300, (64, 1, 2)), (100, 300, (128, 1, 2)), (300, 140, (128, 3, 2)), (600, 130, (256, 3, 2)), (250, 600, (256, 1, 3))])
+@pytest.mark.parametrize("K", [8, 64, 128, 136, 192, 200, 256, 320, 64 * 37])
+def test_a_workgroup_goes_on_to_its_next_tile(lsp, oracle, rows, vt, plan, K):
+    """Every tile height with more than one tile per workgroup, the last vocabulary tile ragged: the loop hands over to the next tile
+    (whole K steps, more of them than are in flight; other rows of the hidden matrix where there are three row tiles) or starts anew
+    (ragged or short K, into and out of the ragged tile), from every stage that a tile can end in.  Small integers: bit-exact on
+    rows from all over the list."""
+    V = vt * 256 - 3
+    assert _dispatch(rows, V) == plan
+    g = torch.Generator(device="cuda").manual_seed(rows + K)
+    h = torch.randint(-3, 4, (1, rows, K), generator=g, device="cuda").to(torch.bfloat16)
+    w = torch.randint(-3, 4, (V, K), generator=g, device="cuda").to(torch.bfloat16)
+    got = _run(lsp, h, w)
+    pick = torch.unique(torch.linspace(0, rows - 1, 24).round().long())
+    _compare(tuple(x[:, pick] for x in got), oracle.lm_head_confidence(h[:, pick].cpu(), w.cpu()), None, exact=True)
 
 
 def test_more_sequences_than_threads(lsp, oracle):
