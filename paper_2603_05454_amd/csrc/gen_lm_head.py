@@ -26,8 +26,8 @@ loop there.  Loads in flight at entry: steps 0 .. NSTG-1 of this tile, in order.
 Every tile is summed from k = 0 upwards, whatever its height, place and workgroup: a logit
 has the same bits wherever its row stands in the batch and however many rows are
 active, and equal weight rows give equal logits.  (Starting K at a different step in
-different workgroups would spread a power-of-two row pitch over the memory channels, but
-gives that up; the kernel starts its workgroups at different TIMES instead.)
+different workgroups spreads a power-of-two row pitch over the memory channels, but
+gives that up; the kernel gives its XCDs runs of tiles and its workgroups different start TIMES.)
 """
 import os
 
@@ -75,6 +75,8 @@ class Mode:
 
 MODES = {256: Mode(256, 256, 64, 2, 4, 2, 18), 128: Mode(256, 128, 64, 4, 2, 3, 11), 64: Mode(256, 64, 64, 4, 2, 3, 6)}
 
+HINT = "<weight hint>"     # in the emitted text: a string macro of the including code
+
 SG = dict(m0save=64, inc=66, li=68, js=69, ev=70)
 
 
@@ -104,7 +106,7 @@ def generate(M):
             i = k if w else k - M.LW
             p = (M.wptr if w else M.hptr) + 2 * i
             dst = st * M.STAGE + (0 if w else M.TILE_W) + 1024 * NW * i
-            r.append((f"s_add_u32 m0, %[ldsw], {dst}", f"global_load_lds_dwordx4 {v(p, 2)}, off",
+            r.append((f"s_add_u32 m0, %[ldsw], {dst}", f"global_load_lds_dwordx4 {v(p, 2)}, off{HINT if w else ''}",
                       f"v_lshl_add_u64 {v(p, 2)}, {v(p, 2)}, 0, {inc}"))
         return r
 
@@ -212,13 +214,14 @@ def generate(M):
 
 def text(M):
     lines = generate(M)
-    body = "\n".join(f'    "{x}\\n"' for x in lines)
+    body = "\n".join(f'    "{x}\\n"' for x in lines).replace(HINT, '" LSP_WEIGHT_HINT "')
     nv = M.nacc // 16
     acc = ", ".join(f'"+{{{v(M.acc + 16 * k, 16)}}}"(acc[{k}])' for k in range(nv))
     clob = [f"v{r}" for r in range(2 * M.setr)] + [f"s{r}" for r in range(64, 71)] + ["scc", "memory"]
     t = f"""// GENERATED by gen_lm_head.py - do not edit; the pipeline and the register map are described there.
 // Expects in scope: f32x16 acc[{nv}]; u32x{2 * M.LW} wptr; u32x{2 * M.LH} hptr; u32x{2 * M.NK} addr[{M.NSTG}]; next;
-// uint32_t ldsw, ks, event, phase, go_on, zlo, zhi; uint64_t zmask, wstep.
+// uint32_t ldsw, ks, event, phase, go_on, zlo, zhi; uint64_t zmask, wstep;
+// LSP_WEIGHT_HINT: cache hint of the weight loads ("" or " nt").
 asm volatile(
 {body}
     : {acc},

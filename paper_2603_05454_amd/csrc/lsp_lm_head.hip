@@ -16,7 +16,7 @@
 //
 // Only ACTIVE rows are computed: tiles are cut from the list of them, over all
 // sequences (127 rows left in four buffers of 256 are one tile of 128, not four
-// of 256: 212 against 1100 us at 126 464 entries and K = 4096).
+// of 256: 195 against 1100 us at 126 464 entries and K = 4096).
 //
 // The K loop is generated (gen_lm_head.py: fragments read one slice ahead, one
 // barrier per K step, loads that never drain); workgroups are persistent, one
@@ -27,9 +27,10 @@
 // (8192 rows x 126 464 x 4096: 5.97 ms = 1.42 PFLOP/s with Eq. 1, 4.69 on operands that
 // do not toggle; the library's product alone 5.75 and 4.55; the compiler-scheduled
 // loop this replaced 7.7 and 6.6).  Few rows: the weight stream from HBM (37 rows:
-// 198 us = 5.2 TB/s; the bare stream takes 167 us = 6.2 TB/s where the workgroups
-// are at different k, 218 us where they move in step).
+// 169 us = 6.1 TB/s; 128 rows: 182 us).
 #include <float.h>
+
+#include <type_traits>
 
 #include "lsp_common.h"
 
@@ -97,8 +98,9 @@ __device__ __forceinline__ Partial fold(Partial a, Partial b) {
 // One wave-wide load from global memory straight into LDS: lane l fetches 16
 // bytes at its own address g and they land at lds_base + 16 l (lds_base is
 // wave-uniform; the counter to wait on is vmcnt).
+template <bool STREAM = false>  // true: with the non-temporal hint
 __device__ __forceinline__ void load_to_lds(const char *g, unsigned char *lds_base) {
-  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void *)lds_base, 16, 0, 0);
+  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void *)lds_base, 16, 0, STREAM ? 2 : 0);
 }
 
 // ---- active rows ---------------------------------------------------------------
@@ -166,8 +168,10 @@ __device__ __forceinline__ void row_at(const LmArgs &a, const RowMap &m, int c, 
 }
 
 // ---- tiles of a workgroup ---------------------------------------------------------
-// Workgroups go to the 8 XCDs round-robin by id; XCD x owns the vocabulary tiles
-// congruent to x mod 8 and its workgroups take its tiles in turn.  In that order, up to four
+// Workgroups go to the 8 XCDs round-robin by id; an XCD owns a run of consecutive
+// vocabulary tiles and its workgroups take them in turn (tiles dealt to the XCDs one by one
+// put all eight at the same distance of few powers of two, see the start times in run_tiles:
+// 37 rows x 126 464 entries x K = 4096 in step 236 us, in runs 177).  In that order, up to four
 // row tiles of a group of vocabulary tiles come side by side: the 32 workgroups an XCD
 // runs at a time read every weight slice four times and every hidden slice
 // eight times out of one L2.
@@ -177,12 +181,12 @@ struct Tiles {
   int cap;
   RowMap map;
   int tr;                    // rows per row tile
-  int nv, RT, VB, total;
+  int first, nv, RT, VB, total;  // the XCD's vocabulary tiles, row tiles, vocabulary tiles per group, tiles
 };
 // How high row tiles are.  256 rows share a weight slice best and win wherever they are full; lower tiles
 //  - where tiles of 256 would be mostly padding: up to 128 rows (128 rows x 126 464 entries x K = 4096:
-//    212 us, 270 in one tile of 256), and 257-384 rows (300 rows: 385 against 443 us);
-//    not 129-256 (256 rows: 284 against 272 us) or more (640 rows would need five);
+//    182 us, 250 in one tile of 256), and 257-384 rows (300 rows: 384 against 443 us);
+//    not 129-256 (256 rows: 284 against 254 us) or more (640 rows would need five);
 //  - where a launch has fewer tiles than compute units (400 rows x 5000 entries: 41 us in 140 tiles of
 //    64, 55 in 80 of 128, 82 in 40 of 256).
 // Both kernels of a launch take the same decision; tiles of 256 are the tall kernel's.
@@ -193,7 +197,8 @@ __device__ __forceinline__ void cut_rows(const LmArgs &a, Tiles &t, bool tall) {
                                                                                                : 256;
   t.RT = tall == (t.tr == 256) ? (R + t.tr - 1) / t.tr : 0;
   const int xcd = blockIdx.x & 7, slots = gridDim.x >> 3;
-  t.nv = (a.VT - xcd + 7) / 8;
+  t.nv = a.VT / 8 + (xcd < a.VT % 8);
+  t.first = xcd * (a.VT / 8) + min(xcd, a.VT % 8);
   t.VB = max(1, slots / max(1, min(t.RT, 4)));
   t.total = t.nv * t.RT;
 }
@@ -203,7 +208,7 @@ struct Cursor {
 __device__ __forceinline__ void tile_at(const Tiles &t, int m, int &vt, int &rt) {
   const int per = t.VB * t.RT, vg = m / per, q = m - vg * per;
   const int g = min(t.VB, t.nv - vg * t.VB);
-  vt = (vg * t.VB + q % g) * 8 + int(blockIdx.x & 7);
+  vt = t.first + vg * t.VB + q % g;
   rt = q / g;
 }
 __device__ __forceinline__ void fill_rows(const LmArgs &a, const Tiles &t, int buf, int rt) {
@@ -286,7 +291,10 @@ template <> struct UVec<4> { typedef u32x4 T; };
 template <> struct UVec<8> { typedef u32x8 T; };
 
 // All tiles of a workgroup: K loop, Eq. 1, one partial result per row and tile.
-template <int H>
+// STREAM: weights that no cache can hold, read once (one row tile), are loaded with the non-temporal hint (37 rows x
+// 126 464 entries: K = 3584 159 -> 141 us, 4096 in step 236 -> 212; 200 rows 262 -> 252).  With more row tiles a slice
+// is read again out of L2, and the hint costs what it saves there (300 rows 386 -> 457).
+template <int H, bool STREAM>
 __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, const Tiles &tb, Cursor cur) {
   constexpr int WV = Shape<H>::WV, WR = Shape<H>::WR, NS = Shape<H>::NS, STG = stage_bytes<H>();
   constexpr int MV = TV / WV / 16, MR = H / WR / 16, LH = H / 64;  // 16x16 blocks per wave, hidden loads per lane and step
@@ -296,11 +304,12 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
   const uint64_t zeros = reinterpret_cast<uint64_t>(g_zeros);
   int stage = 0;           // stage that holds step 0 of the current tile
   bool requested = false;  // its first steps have been requested by the previous tile's loop
-  // Weight rows a multiple of 4 KB apart (K = 2048, 4096, 8192) keep all workgroups that are at the same k on
-  // the same few memory channels, so where the weight stream is the bound - one low row tile, every
-  // compute unit busy - the workgroups of an XCD start a K step's time (3200 cycles) apart in 16 phases.
-  // 37 rows x 126 464 entries: K = 4096 235 -> 198-203 us, 2048 131 -> 112, 8192 366 -> 355; it costs 5 % at other pitches
-  // (K = 3584 159 -> 169), 9 % at K = 1024 (16 steps per tile), 2 % where not every unit has a tile.
+  // Weight rows a multiple of 4 KB apart (K = 2048, 4096, 8192) keep workgroups that are at the same k on few memory
+  // channels, so where the weight stream is the bound - one low row tile, every compute unit busy - the
+  // workgroups of an XCD start a K step's time (3200 cycles) apart in 16 phases.  37 rows: K = 2048 115 -> 99 us
+  // (126 464 entries) and 140 -> 125 (152 064), K = 4096 151 -> 138 (80 000) and 216 -> 217 (152 064), 8192 325 -> 315;
+  // at 126 464 x 4096, where the runs of the XCDs happen to lie well, 157 -> 169.  It costs 5 % at other pitches,
+  // 9 % at K = 1024 (16 steps per tile), 2 % where not every unit has a tile.
   if (H <= 128 && tb.RT == 1 && tb.nv >= kComputeUnits / 8 && KS_real >= 32 && a.wrs % 2048 == 0)
     for (int p = int(blockIdx.x >> 3) & 15; p > 0; --p) __builtin_amdgcn_s_sleep(50);
   for (;;) {
@@ -335,7 +344,7 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
         const bool in = p * KB + 8 * chunk < a.K;
         unsigned char *st = smem + p * STG + 1024 * wave;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) load_to_lds(reinterpret_cast<const char *>(in ? w[i] + p * 2 * KB : zeros), st + 8192 * i);
+        for (int i = 0; i < 4; ++i) load_to_lds<STREAM>(reinterpret_cast<const char *>(in ? w[i] + p * 2 * KB : zeros), st + 8192 * i);
 #pragma unroll
         for (int i = 0; i < LH; ++i) load_to_lds(reinterpret_cast<const char *>(in ? h[i] + p * 2 * KB : zeros), st + TILE_W + 8192 * i);
       }
@@ -388,7 +397,15 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
           *reinterpret_cast<u32x4 *>(part + 4096 * i + 16 * tid) = u32x4{uint32_t(h0), uint32_t(h0 >> 32), uint32_t(h1), uint32_t(h1 >> 32)};
         }
         const uint32_t next = lds0 + NS * STG + 16 * tid;
+        if constexpr (STREAM) {
+#define LSP_WEIGHT_HINT " nt"
 #include "lsp_lm_head_loop_256.inc"
+#undef LSP_WEIGHT_HINT
+        } else {
+#define LSP_WEIGHT_HINT ""
+#include "lsp_lm_head_loop_256.inc"
+#undef LSP_WEIGHT_HINT
+        }
       } else {
         typename UVec<2 * LH>::T next;
 #pragma unroll
@@ -397,10 +414,22 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
           next[2 * i] = uint32_t(h);
           next[2 * i + 1] = uint32_t(h >> 32);
         }
-        if constexpr (H == 128) {
+        if constexpr (H == 128 && STREAM) {
+#define LSP_WEIGHT_HINT " nt"
 #include "lsp_lm_head_loop_128.inc"
-        } else {
+#undef LSP_WEIGHT_HINT
+        } else if constexpr (H == 128) {
+#define LSP_WEIGHT_HINT ""
+#include "lsp_lm_head_loop_128.inc"
+#undef LSP_WEIGHT_HINT
+        } else if constexpr (STREAM) {
+#define LSP_WEIGHT_HINT " nt"
 #include "lsp_lm_head_loop_64.inc"
+#undef LSP_WEIGHT_HINT
+        } else {
+#define LSP_WEIGHT_HINT ""
+#include "lsp_lm_head_loop_64.inc"
+#undef LSP_WEIGHT_HINT
         }
       }
     }
@@ -445,6 +474,12 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): nothing is still on its way into LDS
 }
 
+// Weights (elements) from which they are streamed: 320 MB, a quarter more than the chip's last-level cache holds.  Smaller
+// ones are partly or wholly still there from the step before, as long as they are loaded without the hint.  The same
+// weights step after step, 37 rows, with and without it: 268 MB (65 536 x 2048) 68 and 52 us, 328 MB (40 000 x 4096)
+// 70 and 70, 450 MB (110 000 x 2048) 93 and 102.
+constexpr int64_t kStreamWeights = int64_t(320) << 19;
+
 // Persistent kernels: one workgroup per compute unit walks its tiles.
 template <bool TALL>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void lm_head_kernel(LmArgs a) {
@@ -461,9 +496,14 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))
   if (cur.m >= tb.total) return;
   tile_at(tb, cur.m, cur.vt, cur.rt);
   fill_rows(a, tb, 0, cur.rt);
-  if constexpr (TALL) run_tiles<256>(a, smem, tb, cur);
-  else if (min(tb.tr, tb.map.R) <= 64) run_tiles<64>(a, smem, tb, cur);
-  else run_tiles<128>(a, smem, tb, cur);
+  auto run = [&](auto stream) {
+    constexpr bool STREAM = decltype(stream)::value;
+    if constexpr (TALL) run_tiles<256, STREAM>(a, smem, tb, cur);
+    else if (min(tb.tr, tb.map.R) <= 64) run_tiles<64, STREAM>(a, smem, tb, cur);
+    else run_tiles<128, STREAM>(a, smem, tb, cur);
+  };
+  if (tb.RT == 1 && int64_t(a.V) * a.wrs >= kStreamWeights) run(std::true_type{});
+  else run(std::false_type{});
 }
 
 // One wave per row folds the row's VT partials and writes the three results.  (A grid dimension ends at 2^32 threads and a

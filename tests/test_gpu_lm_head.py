@@ -197,14 +197,15 @@ def test_c4_shape_sampled_rows_and_tile_invariants(lsp, oracle):
         _compare(tuple(t[b:b + 1, r] for t in got), ref[:3], ref[3])
 
 
-# rows: where the repeated rows stand in the batch, and so which tile heights and places they get (300 vocabulary
-# tiles: 64, 128, 256, 128 and 256 rows per tile)
+# The repeated rows stand at several places of batches whose tiles are 64, 128, 256, 128 and 256 rows high (330 vocabulary
+# tiles); with K = 2048 the weights are large enough to be streamed (346 MB) where one row tile reads them, and their
+# pitch is one at which workgroups start at different times.
 @pytest.mark.parametrize("K", [64 * 9, 2048])
 def test_a_row_does_not_depend_on_the_batch_and_equal_entries_tie(lsp, K):
     """Real-valued operands, whole K steps: every logit is summed in one order and so are the exponentials of a row: its results have the
     same bits in every batch, and vocabulary entries with equal weight rows tie exactly - margin 0, the lowest id - in whichever tiles they lie."""
     g = torch.Generator(device="cuda").manual_seed(K)
-    V, n = 300 * 256 - 3, 32
+    V, n = 330 * 256 - 3, 32
     w = torch.randn((V, K), generator=g, device="cuda", dtype=torch.bfloat16).div_(K ** 0.5)
     src = torch.randint(0, 100 * 256, (n,), generator=g, device="cuda")
     dup = torch.randint(100 * 256, V, (n,), generator=g, device="cuda")
