@@ -258,11 +258,24 @@ __device__ __forceinline__ Partial reduce(float (&x)[N], int vbase, int V, bool 
 }
 // The four lanes of a row fold their results, each pair exchanging half of its row blocks: lanes 32
 // apart first, then lanes 16 apart, so that no lane folds what another one folds as well.
-__device__ __forceinline__ Partial exchange(const Partial &lo, const Partial &hi, bool upper, int d) {
-  const Partial keep = upper ? hi : lo, send = upper ? lo : hi;
-  Partial o;
-  o.m1 = __shfl_xor(send.m1, d); o.m2 = __shfl_xor(send.m2, d); o.s = __shfl_xor(send.s, d); o.idx = __shfl_xor(send.idx, d);
-  return fold(keep, o);
+// Which lane keeps which half: the upper of the two (in lane number) takes `hi`, the lower one `lo`; the swap leaves a lane with
+// its own half and the other lane's, in an order that the fold does not see.
+template <int D>
+__device__ __forceinline__ void swap_halves(uint32_t &lo, uint32_t &hi) {
+  const auto r = D == 32 ? __builtin_amdgcn_permlane32_swap(lo, hi, false, false) : __builtin_amdgcn_permlane16_swap(lo, hi, false, false);
+  lo = r[0];
+  hi = r[1];
+}
+template <int D>
+__device__ __forceinline__ Partial exchange(const Partial &lo, const Partial &hi) {
+  uint32_t a[4] = {__builtin_bit_cast(uint32_t, lo.m1), __builtin_bit_cast(uint32_t, lo.m2), __builtin_bit_cast(uint32_t, lo.s), uint32_t(lo.idx)};
+  uint32_t b[4] = {__builtin_bit_cast(uint32_t, hi.m1), __builtin_bit_cast(uint32_t, hi.m2), __builtin_bit_cast(uint32_t, hi.s), uint32_t(hi.idx)};
+#pragma unroll
+  for (int k = 0; k < 4; ++k) swap_halves<D>(a[k], b[k]);
+  auto part = [](const uint32_t (&x)[4]) {
+    return Partial{__builtin_bit_cast(float, x[0]), __builtin_bit_cast(float, x[1]), __builtin_bit_cast(float, x[2]), int32_t(x[3])};
+  };
+  return fold(part(a), part(b));
 }
 // One thread per row folds the results of the tile's four groups of entries and leaves the tile's partial result.
 __device__ __forceinline__ void finish_tile(const LmArgs &a, const Tiles &tb, const Partial *lds_part, const Cursor &cur, int vt) {
@@ -439,7 +452,7 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
     // element r of 16x16 block (i, j) is z[v][row], v = v0 + wv*(TV/WV) + 16 i + 4 grp + r (increasing in (i, r)),
     // row = wr*(H/WR) + 16 j + l16
     // Four groups of 64 entries per row and tile at every height, so that a row's sum of exponentials has one order
-    // (a wave of the 256-row tile holds two of them: reduced together they would save 0.6 us of a 100 us tile).
+XX.
     Partial *lds_part = reinterpret_cast<Partial *>(part);  // [H][4]
     const bool up32 = lane >= 32, up16 = (lane & 16) != 0;
 #pragma unroll
@@ -455,11 +468,11 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
       Partial p;
       int j;
       if constexpr (MR == 4) {
-        p = exchange(exchange(pj[0], pj[2], up32, 32), exchange(pj[1], pj[3], up32, 32), up16, 16);
+        p = exchange<16>(exchange<32>(pj[0], pj[2]), exchange<32>(pj[1], pj[3]));
         j = 2 * up32 + up16;
       } else {
-        p = exchange(pj[0], pj[1], up32, 32);
-        p = exchange(p, p, false, 16);
+        p = exchange<32>(pj[0], pj[1]);
+        p = exchange<16>(p, p);
         j = up32;
       }
       lds_part[(wr * (H / WR) + 16 * j + l16) * 4 + wv * (MV / 4) + u] = p;
