@@ -452,7 +452,8 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
     // element r of 16x16 block (i, j) is z[v][row], v = v0 + wv*(TV/WV) + 16 i + 4 grp + r (increasing in (i, r)),
     // row = wr*(H/WR) + 16 j + l16
     // Four groups of 64 entries per row and tile at every height, so that a row's sum of exponentials has one order
-XX.
+    // (a wave of the 256-row tile holds two of them; what reducing them apart costs, 0.6 us of a 100 us tile, the register
+    // swaps of exchange() give back: 838 rows x 152 064 entries x K = 1024 304 us with LDS shuffles, 297 now).
     Partial *lds_part = reinterpret_cast<Partial *>(part);  // [H][4]
     const bool up32 = lane >= 32, up16 = (lane & 16) != 0;
 #pragma unroll
