@@ -15,12 +15,12 @@
 //
 // What bounds it at the sizes it is used for (4 heads of 64, 64 queries, 192 keys)
 // is latency: a launch, one trip to memory for the lengths, one for the operands,
-// and the chain of dependent matrix steps.  Hence the narrow query tile, the keys
-// of a tile split eight ways and merged through LDS, and Q requested before the
-// lengths are known.  Measured, kernel alone: that size 6.1 us (137 us for one
-// query per lane on plain FMAs with K/V broadcast from LDS, which leaves 4 waves
-// in flight), 256 queries x 1280 keys x 4 heads 20.5 us (903), 8 sequences of
-// 1024 x 2048 x 8 heads 394 us (1589).  Tiles of 32 queries and a four-way split
+// and the chain of dependent matrix steps.  Hence the narrow query tile and the keys
+// of a tile split eight ways and merged through LDS.  (Q stands in the source before
+// the lengths are known; the compiler requests it behind them.)  Measured, kernel
+// alone: that size 6.1 us (137 us for one query per lane on plain FMAs with K/V
+// broadcast from LDS, which leaves 4 waves in flight), 256 queries x 1280 keys x 4
+// heads 19.5 us (903), 8 sequences of 1024 x 2048 x 8 heads 371 us (1589).  Tiles of 32 queries and a four-way split
 // are 15 % faster at that last size and 30-60 % slower at the small ones; a
 // sixteen-way split and requesting the next tile ahead change nothing.
 #include "lsp_attn.h"
