@@ -140,6 +140,12 @@ size_t lsp_confidence_workspace_bytes(int32_t B, int32_t S, int32_t V);
  * of at least the element size is accepted; 16-byte aligned rows take the fast
  * path.  suffix_len: device int32[B] or NULL (= all S rows active).
  * top1_id (int32), top1_prob (fp32), margin (fp32): device, [B,S] dense.
+ * workspace: device, 16-byte aligned, lsp_confidence_workspace_bytes(B,S,V)
+ * bytes of any content, for this call alone until it has run.  With it, long
+ * rows are cut into segments for several workgroups when few rows are ACTIVE.
+ * Required (LSP_ERR_WORKSPACE otherwise) where B*S < 128 and V > 16384; without
+ * one, other shapes keep a workgroup per row (the last bits of top1_prob follow
+ * the cut; ids and margins do not).
  */
 int32_t lsp_confidence(int32_t dtype, const void *logits, int32_t B, int32_t S, int32_t V,
                        int64_t row_stride, int64_t batch_stride, const int32_t *suffix_len,
@@ -149,14 +155,13 @@ int32_t lsp_confidence(int32_t dtype, const void *logits, int32_t B, int32_t S, 
 /*
  * lsp_confidence for callers that cannot allocate device memory or hand over a
  * workspace: code under HIP graph capture, tight serving loops, harnesses that
- * forbid hipMalloc.  Same arguments, results and launches as lsp_confidence,
- * but the per-segment results of split rows (the only scratch that call needs:
- * rows are split when B*S < 128) go to a buffer of
- * lsp_confidence_static_scratch_bytes() = 65536 bytes that is part of the
- * library's device image; each GPU the library runs on holds its own copy until
- * the process ends.  The call allocates and frees nothing (its first use on a
- * GPU looks up the buffer's address).  A shape whose launch plan needs more
- * than the buffer holds returns LSP_ERR_UNSUPPORTED and launches nothing.
+ * forbid hipMalloc.  Same arguments as lsp_confidence; the workspace that call
+ * requires where B*S < 128 and V > 16384 (results and launch are then the same)
+ * is a buffer of lsp_confidence_static_scratch_bytes() = 65536 bytes that is part
+ * of the library's device image; each GPU the library runs on holds its own copy
+ * until the process ends.  Other shapes use none, as lsp_confidence without a
+ * workspace.  The call allocates and frees nothing (its first use on a
+ * GPU looks up the buffer's address).
  * Every call on one GPU shares that GPU's buffer: calls whose execution may
  * overlap on one GPU (different streams, or several host threads) race; calls
  * in stream order on one stream do not.  Nothing has to be cleared between

@@ -113,12 +113,16 @@ bool tables(PyObject *list, Memory (&tab)[N], long layers) {
 // The entry point itself runs without the interpreter lock: a launch waits for a full queue, and a kernel's first one
 // loads its code.  What it reads of Python's is held by the caller's references meanwhile.
 template <typename... P, typename... A>
-PyObject *status(int32_t (*entry)(P...), A... args) {
+int32_t unlocked(int32_t (*entry)(P...), A... args) {
   int32_t rc;
   Py_BEGIN_ALLOW_THREADS;
   rc = entry(args...);
   Py_END_ALLOW_THREADS;
-  return PyLong_FromLong(rc);
+  return rc;
+}
+template <typename... P, typename... A>
+PyObject *status(int32_t (*entry)(P...), A... args) {
+  return PyLong_FromLong(unlocked(entry, args...));
 }
 #define ORDINARY(cond) \
   if (!(cond)) Py_RETURN_NONE
@@ -214,9 +218,12 @@ PyObject *confidence(PyObject *, PyObject *const *a, Py_ssize_t n) {
   ConfOut o;
   ORDINARY(conf_out(a[2], B, S, o));
   const at::Tensor *ws = a[3] == Py_None ? nullptr : device_tensor(a[3]);
-  ORDINARY(bytes_of(ws) >= int64_t(g.confidence_workspace_bytes(int32_t(B), int32_t(S), int32_t(V))));
-  return status(g.confidence, type, z->const_data_ptr(), int32_t(B), int32_t(S), int32_t(V), z->stride(1), z->stride(0),
-                data<int32_t>(sl), o.id, o.prob, o.margin, data<void>(ws), size_t(bytes_of(ws)), stream());
+  ORDINARY(ws || a[3] == Py_None);
+  // (a call that needs a workspace and has none answers so, before any launch)
+  const int32_t rc = unlocked(g.confidence, type, z->const_data_ptr(), int32_t(B), int32_t(S), int32_t(V), z->stride(1), z->stride(0),
+                              data<int32_t>(sl), o.id, o.prob, o.margin, data<void>(ws), size_t(bytes_of(ws)), stream());
+  ORDINARY(rc != LSP_ERR_WORKSPACE);
+  return PyLong_FromLong(rc);
 }
 
 // (hidden, weight, suffix_len or None, out, workspace)

@@ -24,10 +24,11 @@
 // index among the lanes holding the maximum are plain max / add / min
 // reductions.  The same merge runs across the waves of a workgroup through
 // LDS and - when one row is split over several workgroups because there are
-// too few rows to fill the chip - across workgroups in a second tiny kernel.
+// too few rows to fill the chip - in the last of these workgroups.
 #include <float.h>
 #include <limits.h>
 
+#include <chrono>
 #include <mutex>
 #include <type_traits>
 
@@ -130,11 +131,6 @@ struct Vec<uint16_t> {
   static __device__ __forceinline__ float scalar(const uint16_t *p) { return bf16_to_f32(*p); }
 };
 
-struct Partial {  // one row segment, normalised: s = sum exp(x - m1) over the segment
-  float m1, m2, s;
-  int idx;
-};
-
 // ---- cross-lane reductions on the DPP network (no LDS traffic) ---------------
 // Classic GCN reduction: two quad permutes, row shifts by 4 and 8, then the row
 // broadcasts 15 and 31; lane 63 ends up holding the reduction of all 64 lanes.
@@ -184,21 +180,19 @@ __device__ __forceinline__ RowStat wave_combine(const Top &t, float wave_max, fl
   return o;
 }
 
+// Merge of up to 64 parts of a row, one a lane (idle lanes: top_init), each sum relative to its part's own maximum.
+__device__ __forceinline__ RowStat merge_stats(const Top &t) {
+  const float all_max = wave_reduce(t.m1, OpMax());
+  return wave_combine(t, all_max, __builtin_amdgcn_exp2f((t.m1 - all_max) * kLog2e));  // exp(m1 - max); 0 for the idle lanes
+}
+
 // One workgroup reduces elements [c0, c1) of one row.  NT threads; U vectors per
 // lane per group; two groups of loads in flight (ping-pong register buffers).
+// The result is valid in wave 0; the other waves only take part.
 template <typename T, int NT, int U>
-__global__ __launch_bounds__(NT) void confidence_kernel(
-    const T *__restrict__ logits, int S, int V, int64_t row_stride, int64_t batch_stride,
-    const int32_t *__restrict__ suffix_len, int splits, int seg_elems,
-    int32_t *__restrict__ top1_id, float *__restrict__ top1_prob, float *__restrict__ margin,
-    Partial *__restrict__ partials) {
+__device__ __forceinline__ RowStat segment_stat(const T *row, int c0, int c1) {
   constexpr int N = Vec<T>::N;
-  const int split = blockIdx.x, i = blockIdx.y, b = blockIdx.z;
-  if (suffix_len != nullptr && i >= suffix_len[b]) return;
   const int tid = threadIdx.x;
-  const int c0 = split * seg_elems;
-  const int c1 = min(V, c0 + seg_elems);
-  const T *row = logits + int64_t(b) * batch_stride + int64_t(i) * row_stride;
 
   Top t;
   top_init(t);
@@ -321,52 +315,141 @@ __global__ __launch_bounds__(NT) void confidence_kernel(
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     if (lane == 0) lds[wave] = r;
     __syncthreads();
-    if (wave != 0) return;
+    if (wave != 0) return r;
     top_init(t);
     if (lane < NW) {
       const RowStat w = lds[lane];
       t.m1 = w.m1; t.m2 = w.m2; t.s = w.s; t.idx = w.idx;
     }
-    // a wave's sum is relative to that wave's own maximum: exp((m1 - max)), 0 for the lanes beyond NW
-    const float all_max = wave_reduce(t.m1, OpMax());
-    r = wave_combine(t, all_max, __builtin_amdgcn_exp2f((t.m1 - all_max) * kLog2e));
+    r = merge_stats(t);
   }
-  if (tid != 0) return;
-  const int64_t o = int64_t(b) * S + i;
-  if (splits == 1) {
-    top1_id[o] = r.idx;
-    margin[o] = r.m1 - r.m2;
-    top1_prob[o] = 1.0f / r.s;
-  } else {
-    Partial p;
-    p.m1 = r.m1; p.m2 = r.m2; p.s = r.s; p.idx = r.idx;
-    partials[o * splits + split] = p;
-  }
+  return r;
 }
 
-// One thread per row folds the row's `splits` segment results, in index order.
-__global__ void confidence_finish_kernel(const Partial *__restrict__ partials, int rows, int S,
-                                         int splits, const int32_t *__restrict__ suffix_len,
-                                         int32_t *__restrict__ top1_id,
-                                         float *__restrict__ top1_prob,
-                                         float *__restrict__ margin) {
-  const int o = blockIdx.x * blockDim.x + threadIdx.x;
-  if (o >= rows) return;
-  if (suffix_len != nullptr && (o % S) >= suffix_len[o / S]) return;
-  Partial a = partials[int64_t(o) * splits];
-  for (int k = 1; k < splits; ++k) {
-    const Partial p = partials[int64_t(o) * splits + k];
-    const float M = __builtin_fmaxf(a.m1, p.m1);
-    const float m2 = __builtin_fmaxf(__builtin_fminf(a.m1, p.m1), __builtin_fmaxf(a.m2, p.m2));
-    const float wa = a.m1 == M ? 1.f : __builtin_amdgcn_exp2f((a.m1 - M) * kLog2e);
-    const float wp = p.m1 == M ? 1.f : __builtin_amdgcn_exp2f((p.m1 - M) * kLog2e);
-    const float s = a.s * wa + p.s * wp;
-    a.idx = p.m1 > a.m1 ? p.idx : a.idx;  // earlier segment keeps an equal maximum
-    a.m1 = M; a.m2 = m2; a.s = s;
+__device__ __forceinline__ void store_row(const RowStat &r, int64_t o, int32_t *__restrict__ top1_id,
+                                          float *__restrict__ top1_prob, float *__restrict__ margin) {
+  top1_id[o] = r.idx;
+  margin[o] = r.m1 - r.m2;
+  top1_prob[o] = 1.0f / r.s;
+}
+
+// One workgroup per row of the buffer.
+template <typename T, int NT, int U>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void confidence_kernel(
+    const T *__restrict__ logits, int S, int V, int64_t row_stride, int64_t batch_stride,
+    const int32_t *__restrict__ suffix_len, int32_t *__restrict__ top1_id, float *__restrict__ top1_prob,
+    float *__restrict__ margin) {
+  const int i = blockIdx.x, b = blockIdx.y;
+  if (suffix_len != nullptr && i >= suffix_len[b]) return;
+  const RowStat r = segment_stat<T, NT, U>(logits + int64_t(b) * batch_stride + int64_t(i) * row_stride, 0, V);
+  if (threadIdx.x == 0) store_row(r, int64_t(b) * S + i, top1_id, top1_prob, margin);
+}
+
+// The same where rows may be cut into 2^k segments, one workgroup each: k follows the number of ACTIVE rows,
+// which only the device knows (in a decode loop few are left of a large buffer).  Workgroup w takes segment
+// w % 2^k of active row w / 2^k, counted over all sequences.  What a segment leaves in the workspace is its
+// statistics and, beside each of the four numbers, this call's tag; a workgroup then reads the row's other
+// segments and, where it finds all of them, merges and stores the row.  The last one to write does find them; if
+// another one does too, both store the same.  Nobody waits for anybody, and the workspace need not be
+// cleared before (it would have to hold the tag four times over by chance); whoever merged clears the
+// tags, so that a graph replayed with the same tag finds nothing of the replay before.
+// Numbers and tags pass between workgroups as device-scope atomic stores and loads of 8 bytes, which go past the
+// XCD's own L2: waiting for the stores is all the order they need.  A release fence writes that L2 back instead,
+// once per workgroup, and a counter of arrivals is one address that they queue for (20 rows in 16 segments each:
+// 22 us with a fence, 19 with a counter, 6.4 so; 103 rows in 8: 28, 18, 12).
+// What it saves: a row is 7.4 us of arithmetic for one compute unit, so that 3 rows took as long as 100.  One sequence
+// of 256 rows of 126 464 entries, per call before -> now: 3 rows active 11.5 -> 5.6 us, 20: 11.8 -> 6.3, 103: 12.6 ->
+// 10.5; all 256 stay whole (13.9 -> 14.1, the price of the count); 8 x 1024 rows with 220 active 29.3 -> 15.6, all of
+// 8 x 1024 x 152 064 367 -> 361 (no workgroups without a row between the others).
+// Rows are cut as long as that makes no more workgroups of 256 threads than this: a wave's own reductions cost as much
+// as 80 of its vectors, so that shorter segments lose more than the fuller chip gives (103 rows in 4 segments 10.5 us,
+// in 8 12.2, in 16 13.5; 512 rows whole 24.6, halved 30.5).
+constexpr int kSplitTarget = 512;
+constexpr int kMaxLog2 = 4;         // 16 segments' numbers fill a wave
+constexpr int kMinSegment = 4096;   // elements; a segment is a few groups of loads
+constexpr int kMinCut = 16384;      // rows of at most this many are not cut (100 rows of 9000: 4.8 us whole, 5.6 cut)
+constexpr int kWideRows = 256;      // buffers of up to this many rows: 512 threads, half as many workgroups (256 rows: 14.1 us, 16.0 with 256)
+constexpr int kSplitRows = 512;     // below this many rows of the buffer, short rows are cut as well
+constexpr int kMaxScannedBatch = 256;  // sequences: every workgroup reads all their lengths, 64 at a time
+constexpr int64_t kMaxSplitGrid = int64_t(1) << 22;  // workgroups; more rows than this need no cutting
+template <typename T, int NT, int U>
+__global__ __launch_bounds__(NT) void confidence_split_kernel(
+    const T *__restrict__ logits, int B, int S, int V, int64_t row_stride, int64_t batch_stride,
+    const int32_t *__restrict__ suffix_len, int max_log2, uint32_t tag, int32_t *__restrict__ top1_id,
+    float *__restrict__ top1_prob, float *__restrict__ margin, unsigned long long *segments) {
+  const int lane = threadIdx.x & (kWave - 1);
+  // active rows, and for batches of up to 64 the rows up to and including this lane's sequence
+  int rows = 0, upto = 0, n = 0;
+  auto scan = [&](int b0) {
+    const int b = b0 + lane;
+    n = b < B ? min(max(suffix_len[b], 0), S) : 0;
+    upto = n;
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x111, 0xf, 0xf, false);  // row_shr:1
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x112, 0xf, 0xf, false);  // row_shr:2
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x114, 0xf, 0xf, false);  // row_shr:4
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x118, 0xf, 0xf, false);  // row_shr:8
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x142, 0xa, 0xf, false);  // row_bcast:15 into rows 1 and 3
+    upto += __builtin_amdgcn_update_dpp(0, upto, 0x143, 0xc, 0xf, false);  // row_bcast:31 into rows 2 and 3
+    return __builtin_amdgcn_readlane(upto, kWave - 1);
+  };
+  if (suffix_len == nullptr) {
+    rows = B * S;
+  } else if (B == 1) {
+    rows = upto = n = min(max(suffix_len[0], 0), S);
+  } else {
+    for (int b0 = 0; b0 < B; b0 += kWave) rows += scan(b0);
   }
-  top1_id[o] = a.idx;
-  margin[o] = a.m1 - a.m2;
-  top1_prob[o] = 1.0f / a.s;
+  int k = 0;
+  while (k < max_log2 && (int64_t(rows) << (k + 1)) <= kSplitTarget * 256 / NT) ++k;
+  const int row = int(blockIdx.x >> k), seg = int(blockIdx.x) & ((1 << k) - 1);
+  if (row >= rows) return;
+  int b = 0, i = row;  // sequence and position of that row
+  if (suffix_len == nullptr) {
+    b = row / S;
+    i = row - b * S;
+  } else {
+    if (B > kWave)
+      for (;; b += kWave) {
+        const int t = scan(b);
+        if (i < t) break;
+        i -= t;
+      }
+    const int s = __popcll(__ballot(upto <= i));
+    i -= __builtin_amdgcn_readlane(upto, s) - __builtin_amdgcn_readlane(n, s);
+    b += s;
+  }
+
+  const int len = (((V + (1 << k) - 1) >> k) + 63) & ~63;
+  RowStat r = segment_stat<T, NT, U>(logits + int64_t(b) * batch_stride + int64_t(i) * row_stride, seg * len,
+                                     min(V, (seg + 1) * len));
+  if (threadIdx.x >= kWave) return;
+  if (k > 0) {
+    const int own = lane & 3;  // lane 4j + i: number i of segment j
+    unsigned long long *w = segments + (int64_t(row) << (k + 2));
+    const uint32_t mine = own == 0   ? __float_as_uint(r.m1)
+                          : own == 1 ? __float_as_uint(r.m2)
+                          : own == 2 ? __float_as_uint(r.s)
+                                     : uint32_t(r.idx);
+    if (lane < 4)
+      __hip_atomic_store(w + 4 * seg + lane, uint64_t(mine) << 32 | tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // the four are where every workgroup sees them
+    const bool used = lane < 4 << k;
+    const unsigned long long x = used ? __hip_atomic_load(w + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
+    if (__any(used && uint32_t(x) != tag)) return;
+    if (used) __hip_atomic_store(w + lane, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    Top t;
+    top_init(t);
+    const int v = int(x >> 32);
+    const int m1 = __builtin_amdgcn_update_dpp(v, v, 0x00, 0xf, 0xf, false);  // quad_perm: number 0, 1, 2, 3 of the four lanes
+    const int m2 = __builtin_amdgcn_update_dpp(v, v, 0x55, 0xf, 0xf, false);
+    const int sum = __builtin_amdgcn_update_dpp(v, v, 0xaa, 0xf, 0xf, false);
+    const int idx = __builtin_amdgcn_update_dpp(v, v, 0xff, 0xf, 0xf, false);
+    if (used && own == 0) {
+      t.m1 = __int_as_float(m1); t.m2 = __int_as_float(m2); t.s = __int_as_float(sum); t.idx = idx;
+    }
+    r = merge_stats(t);
+  }
+  if (lane == 0) store_row(r, int64_t(b) * S + i, top1_id, top1_prob, margin);
 }
 
 // Launch shape (measured on MI355X).  A workgroup takes a row; it is as wide as
@@ -374,58 +457,74 @@ __global__ void confidence_finish_kernel(const Partial *__restrict__ partials, i
 // thousand entries, four waves for a 126 464-entry bf16 row: 2-7 % faster there
 // than one wave per row, and a 512-thread workgroup is 3x slower on 4 096-entry
 // rows); with few rows it widens further so that at least 2048 waves are in
-// flight, and below that rows are also cut into segments reduced by separate
-// workgroups.  Per element the kernel issues about nine VALU cycles (the
+// flight.  Per element the kernel issues about nine VALU cycles (the
 // exponential counts four), which at these sizes is as long as the memory time
-// itself.
+// itself.  Where rows are long or few, confidence_split_kernel counts the active
+// rows and cuts them further.
 struct Plan {
-  int nt, splits, seg_elems;
+  int nt;
+  int max_log2;    // rows may be cut into up to 2^max_log2 segments, if there is a workspace
+  bool required;   // the call is not made without one
 };
 inline Plan plan(int64_t rows, int V, int elem_bytes) {
   Plan p;
   int nt = 64;
   const int64_t nvec = int64_t(V) * elem_bytes / 16;
   while (nt < 512 && nvec / nt >= 96) nt *= 2;
-  while (nt < 512 && rows * (nt / 64) < 2048) nt *= 2;
-  int splits = 1;
-  const int64_t waves = rows * (nt / 64);
-  if (waves < 1024) {
-    splits = int((2048 + waves - 1) / waves);
-    const int max_by_len = (V + 16383) / 16384;  // keep segments >= 16384 elements
-    if (splits > max_by_len) splits = max_by_len;
-    if (splits > 32) splits = 32;
-    if (splits < 1) splits = 1;
-  }
-  int seg = (V + splits - 1) / splits;
-  seg = (seg + 63) / 64 * 64;
+  p.max_log2 = 0;
+  if (nt >= 256 || rows < kSplitRows)
+    while (V > kMinCut && p.max_log2 < kMaxLog2 && (V >> (p.max_log2 + 1)) >= kMinSegment) ++p.max_log2;
+  p.required = p.max_log2 > 0 && rows < 128;
+  if (p.max_log2 > 0 && nt < 256) nt = 256;
+  if (p.max_log2 > 0 && rows <= kWideRows) nt = 512;
   p.nt = nt;
-  p.seg_elems = seg;
-  p.splits = (V + seg - 1) / seg;
   return p;
 }
+// without a workspace
+inline int unsplit_threads(int64_t rows, int nt) {
+  while (nt < 512 && rows * (nt / 64) < 2048) nt *= 2;
+  return nt;
+}
 
-template <typename T, int NT, int U>
-void launch_one(const Plan &p, dim3 grid, hipStream_t st, const T *z, int S, int V,
-                int64_t row_stride, int64_t batch_stride, const int32_t *suffix_len,
-                int32_t *top1_id, float *top1_prob, float *margin, Partial *parts) {
-  confidence_kernel<T, NT, U><<<grid, NT, 0, st>>>(z, S, V, row_stride, batch_stride, suffix_len,
-                                                   p.splits, p.seg_elems, top1_id, top1_prob,
-                                                   margin, parts);
+// what a call writes into its workspace: four numbers of each segment, each beside the tag
+constexpr size_t kSplitBytes = size_t(kSplitTarget) * 4 * sizeof(unsigned long long);
+
+// The tag of one call: another one for the next four thousand million calls of the process, not 0, and scrambled so that
+// memory is not likely to hold it.
+inline uint32_t call_tag() {
+  static std::atomic<uint32_t> count{uint32_t(std::chrono::steady_clock::now().time_since_epoch().count() >> 10)};
+  uint32_t x;
+  do {
+    x = count.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b1u;  // odd factors and shifted copies of itself: a permutation
+    x = (x ^ x >> 15) * 0x85ebca6bu;
+    x ^= x >> 13;
+  } while (x == 0);
+  return x;
 }
 
 template <typename T>
-void launch_confidence(const Plan &p, dim3 grid, hipStream_t st, const T *z, int S, int V,
-                       int64_t row_stride, int64_t batch_stride, const int32_t *suffix_len,
-                       int32_t *top1_id, float *top1_prob, float *margin, Partial *parts) {
-#define LSP_CONF_CASE(NT_)                                                                      \
-  if (p.nt == NT_)                                                                              \
-    return launch_one<T, NT_, 2>(p, grid, st, z, S, V, row_stride, batch_stride, suffix_len,    \
-                                 top1_id, top1_prob, margin, parts)
+void launch_rows(int nt, hipStream_t st, const T *z, int B, int S, int V, int64_t row_stride, int64_t batch_stride,
+                 const int32_t *suffix_len, int32_t *top1_id, float *top1_prob, float *margin) {
+  const dim3 grid(S, B);
+#define LSP_CONF_CASE(NT_) \
+  if (nt == NT_)           \
+    return confidence_kernel<T, NT_, 2><<<grid, NT_, 0, st>>>(z, S, V, row_stride, batch_stride, suffix_len, top1_id, top1_prob, margin)
   LSP_CONF_CASE(64);
   LSP_CONF_CASE(128);
   LSP_CONF_CASE(256);
   LSP_CONF_CASE(512);
 #undef LSP_CONF_CASE
+}
+
+template <typename T>
+void launch_split(const Plan &p, hipStream_t st, const T *z, int B, int S, int V, int64_t row_stride, int64_t batch_stride,
+                  const int32_t *suffix_len, int32_t *top1_id, float *top1_prob, float *margin, void *workspace) {
+  const int64_t rows = int64_t(B) * S, most = rows << p.max_log2;
+  const int64_t target = int64_t(kSplitTarget) * 256 / p.nt;
+  const int64_t grid = rows > target ? rows : most < target ? most : target;
+  auto kern = p.nt == 512 ? confidence_split_kernel<T, 512, 2> : confidence_split_kernel<T, 256, 2>;
+  kern<<<unsigned(grid), p.nt, 0, st>>>(z, B, S, V, row_stride, batch_stride, suffix_len, p.max_log2, call_tag(), top1_id,
+                                        top1_prob, margin, static_cast<unsigned long long *>(workspace));
 }
 
 }  // namespace
@@ -434,9 +533,8 @@ void launch_confidence(const Plan &p, dim3 grid, hipStream_t st, const T *z, int
 extern "C" size_t lsp_confidence_workspace_bytes(int32_t B, int32_t S, int32_t V) {
   if (B <= 0 || S <= 0 || V <= 0) return 0;
   // the dtype is not an argument here: enough for either
-  const int s2 = lsp::plan(int64_t(B) * S, V, 2).splits, s4 = lsp::plan(int64_t(B) * S, V, 4).splits;
-  const int splits = s2 > s4 ? s2 : s4;
-  return splits > 1 ? size_t(B) * S * splits * sizeof(lsp::Partial) : 0;
+  const int64_t rows = int64_t(B) * S;
+  return lsp::plan(rows, V, 2).max_log2 > 0 || lsp::plan(rows, V, 4).max_log2 > 0 ? lsp::kSplitBytes : 0;
 }
 
 namespace lsp {
@@ -444,14 +542,12 @@ namespace {
 
 int32_t scratch_address(void **out);  // device address of the library's own scratch buffer (defined below)
 
-// Host side shared by both entry points: validation, launch plan, launches.
-// `parts` is where split rows leave their per-segment results (`parts_bytes`
-// available); `who` names the entry point in error texts and `fixed_scratch`
-// says that the buffer is the library's own (a different error then).
-int32_t confidence_run(const char *who, bool fixed_scratch, int32_t dtype, const void *logits, int32_t B,
+// Host side shared by both entry points: validation, launch plan, launch.
+// `own_scratch`: the call has no workspace and may use the library's buffer where it needs one.
+int32_t confidence_run(const char *who, bool own_scratch, int32_t dtype, const void *logits, int32_t B,
                        int32_t S, int32_t V, int64_t row_stride, int64_t batch_stride,
                        const int32_t *suffix_len, int32_t *top1_id, float *top1_prob, float *margin,
-                       void *parts_mem, size_t parts_bytes, void *stream) {
+                       void *workspace, size_t workspace_bytes, void *stream) {
   LSP_CHECK_ARG(dtype == LSP_F32 || dtype == LSP_BF16, "%s: unknown dtype %d", who, dtype);
   LSP_CHECK_ARG(logits && top1_id && top1_prob && margin, "%s: null pointer", who);
   LSP_CHECK_ARG(B > 0 && S > 0 && V >= 2, "%s: need B>0, S>0, V>=2 (got %d %d %d)", who, B, S, V);
@@ -461,36 +557,31 @@ int32_t confidence_run(const char *who, bool fixed_scratch, int32_t dtype, const
   LSP_CHECK_ARG(row_stride >= V && batch_stride >= 0, "%s: bad strides", who);
   const size_t es = elem_size(dtype);
   LSP_CHECK_ARG((reinterpret_cast<uintptr_t>(logits) & (es - 1)) == 0, "%s: logits misaligned", who);
-  const Plan p = plan(int64_t(B) * S, V, int(es));
-  const size_t need = p.splits > 1 ? size_t(B) * S * p.splits * sizeof(Partial) : 0;
-  if (need > 0 && fixed_scratch && parts_bytes < need) {
-    set_error("%s: this shape needs %zu bytes of scratch, the built-in buffer holds %zu; use lsp_confidence "
-              "with a workspace", who, need, parts_bytes);
-    return LSP_ERR_UNSUPPORTED;
-  }
-  if (fixed_scratch) {  // looked up only after the arguments have passed validation
-    const int32_t rc = scratch_address(&parts_mem);
+  const int64_t rows = int64_t(B) * S;
+  const Plan p = plan(rows, V, int(es));
+  if (own_scratch && p.required) {
+    const int32_t rc = scratch_address(&workspace);
     if (rc != LSP_OK) return rc;
+    workspace_bytes = kSplitBytes;
   }
-  if (need > 0 && (parts_mem == nullptr || parts_bytes < need || (reinterpret_cast<uintptr_t>(parts_mem) & 15u))) {
-    set_error("%s: workspace of %zu bytes (16-byte aligned) required, got %zu", who, need, parts_bytes);
+  const bool split = p.max_log2 > 0 && (suffix_len == nullptr || B <= kMaxScannedBatch) && rows <= kMaxSplitGrid && workspace != nullptr && workspace_bytes >= kSplitBytes &&
+               (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
+  if (p.required && !split) {
+    set_error("%s: workspace of %zu bytes (16-byte aligned) required, got %zu", who, kSplitBytes, workspace_bytes);
     return LSP_ERR_WORKSPACE;
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const dim3 grid(p.splits, S, B);
-  Partial *parts = static_cast<Partial *>(parts_mem);
-  if (dtype == LSP_BF16)
-    launch_confidence<uint16_t>(p, grid, st, static_cast<const uint16_t *>(logits), S, V, row_stride,
-                                batch_stride, suffix_len, top1_id, top1_prob, margin, parts);
+  const auto *zb = static_cast<const uint16_t *>(logits);
+  const auto *zf = static_cast<const float *>(logits);
+  if (split && dtype == LSP_BF16)
+    launch_split(p, st, zb, B, S, V, row_stride, batch_stride, suffix_len, top1_id, top1_prob, margin, workspace);
+  else if (split)
+    launch_split(p, st, zf, B, S, V, row_stride, batch_stride, suffix_len, top1_id, top1_prob, margin, workspace);
+  else if (dtype == LSP_BF16)
+    launch_rows(unsplit_threads(rows, p.nt), st, zb, B, S, V, row_stride, batch_stride, suffix_len, top1_id, top1_prob, margin);
   else
-    launch_confidence<float>(p, grid, st, static_cast<const float *>(logits), S, V, row_stride,
-                             batch_stride, suffix_len, top1_id, top1_prob, margin, parts);
+    launch_rows(unsplit_threads(rows, p.nt), st, zf, B, S, V, row_stride, batch_stride, suffix_len, top1_id, top1_prob, margin);
   LSP_CHECK_LAUNCH("lsp_confidence: launch");
-  if (p.splits > 1) {
-    const int rows = B * S;
-    confidence_finish_kernel<<<(rows + 255) / 256, 256, 0, st>>>(parts, rows, S, p.splits, suffix_len, top1_id, top1_prob, margin);
-    LSP_CHECK_LAUNCH("lsp_confidence: finish launch");
-  }
   return LSP_OK;
 }
 
@@ -507,12 +598,13 @@ extern "C" int32_t lsp_confidence(int32_t dtype, const void *logits, int32_t B, 
 }
 
 // ---- the same call for callers that cannot allocate ----------------------------
-// The per-segment results of split rows go to a buffer that is part of the
-// library's device image instead of a caller-provided workspace.  Rows are only
-// split when there are fewer than 128 of them, into at most 32 segments of 16
-// bytes each, so 64 KB cover every shape the launch plan can produce.
+// Where lsp_confidence needs a workspace (long rows, fewer than 128 of them), a
+// buffer that is part of the library's device image takes its place.  With more
+// rows this form has none and does not cut them, so that calls on several streams
+// share nothing.
 #define LSP_CONF_SCRATCH_BYTES 65536
 static __device__ __align__(256) unsigned char scratch[LSP_CONF_SCRATCH_BYTES];
+static_assert(lsp::kSplitBytes <= LSP_CONF_SCRATCH_BYTES, "a call's segments and tickets");
 
 namespace lsp {
 namespace {
@@ -548,8 +640,7 @@ extern "C" int32_t lsp_confidence_static(int32_t dtype, const void *logits, int3
                                          int64_t row_stride, int64_t batch_stride,
                                          const int32_t *suffix_len, int32_t *top1_id, float *top1_prob,
                                          float *margin, void *stream) {
-  // Every segment result that the second kernel reads is written by the first
-  // kernel of the same call, so nothing has to be cleared between calls.
+  // Every segment result that is read was written by the same call, so nothing has to be cleared between calls.
   return lsp::confidence_run("lsp_confidence_static", true, dtype, logits, B, S, V, row_stride, batch_stride,
-                             suffix_len, top1_id, top1_prob, margin, nullptr, LSP_CONF_SCRATCH_BYTES, stream);
+                             suffix_len, top1_id, top1_prob, margin, nullptr, 0, stream);
 }

@@ -10,8 +10,8 @@ from __future__ import annotations
 
 import torch
 
-from . import (AttnLayerTable, LayerTable, LspError, attn_step_layers, commit, confidence, flip_update, lm_head_confidence,
-               lm_head_confidence_workspace_bytes)
+from . import (AttnLayerTable, LayerTable, LspError, attn_step_layers, commit, confidence, confidence_workspace_bytes, flip_update,
+               lm_head_confidence, lm_head_confidence_workspace_bytes)
 
 
 def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
@@ -78,21 +78,23 @@ def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
     attn_out = None
     events = []
     zbuf = step_graph = None
-    lm_ws = None   # workspace of the fused output head: allocated by the first (eager) step, then reused
+    ws = None   # workspace of the reduction or the fused output head: allocated by the first (eager) step, then reused
 
     def one_step(z):
-        nonlocal out, conf, attn_out, lm_ws
+        nonlocal out, conf, attn_out, ws
         if run_attention and kv_layers is not None:
             if attn_out is None:     # one output per layer (a denoiser consumes each of them), allocated once
                 attn_out = AttnLayerTable(*[[L[k] for L in kv_layers] for k in ("q", "k_suf", "v_suf", "k_cache", "v_cache")],
                                           [torch.empty_like(L["q"]) for L in kv_layers])
             attn_step_layers(attn_out, prefix_len, suffix_len)     # every layer in one launch
         if lm_head_weight is None:
-            conf = confidence(z, suffix_len, out=conf)
+            if ws is None:
+                ws = torch.empty(confidence_workspace_bytes(*z.shape), dtype=torch.uint8, device=dev)
+            conf = confidence(z, suffix_len, out=conf, workspace=ws)
         else:
-            if lm_ws is None:
-                lm_ws = torch.empty(lm_head_confidence_workspace_bytes(z.shape[0], z.shape[1], V), dtype=torch.uint8, device=dev)
-            conf = lm_head_confidence(z, lm_head_weight, suffix_len, out=conf, workspace=lm_ws)
+            if ws is None:
+                ws = torch.empty(lm_head_confidence_workspace_bytes(z.shape[0], z.shape[1], V), dtype=torch.uint8, device=dev)
+            conf = lm_head_confidence(z, lm_head_weight, suffix_len, out=conf, workspace=ws)
         flip_update(conf[0], prefix_len, suffix_len, base, last_id, counters, window=flip_window,
                     step_counts=step_counts)
         out = commit(conf[2], conf[0], bitmap, V, tau, window, min_commit, snap_enabled,

@@ -193,3 +193,67 @@ def test_unaligned_start_and_odd_lengths(lsp, oracle):
                 ids_r, p_r, m_r = oracle.confidence(view.contiguous())
                 assert torch.equal(ids.cpu(), ids_r) and torch.equal(m.cpu(), m_r), (dtype, off, V)
                 assert (p.cpu() - p_r).abs().max().item() <= TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("B,S,V,n", [
+    (1, 300, 20000, [5]),               # 4 segments a row
+    (1, 256, 126464, [256]),            # as many rows as workgroups: whole
+    (1, 256, 126464, [129]), (1, 256, 126464, [128]),   # first count that is not halved, last one that is
+    (3, 150, 70001, [0, 1, 149]),       # rows of every alignment, an empty sequence, 150 rows in two or three pieces
+    (70, 2, 20011, None),               # lengths of more sequences than a wave has lanes
+    (300, 1, 17000, None),              # more sequences than the kernel counts: whole rows
+])
+def test_active_rows_cut_into_segments(lsp, oracle, dtype, B, S, V, n):
+    """Rows are cut by the number of ACTIVE ones.  The workspace holds anything; ids and margins are those of whole
+    rows bit for bit, and a probability differs by the order of one fp32 sum: rel 2e-6 is 16 roundings of a sum of
+    at most 16 segments, each of which is itself within a few."""
+    g = torch.Generator().manual_seed(B * S + V)
+    z = (2 * torch.randn((B, S, V), generator=g)).to(dtype).cuda()
+    n = torch.tensor(n) if n is not None else torch.randint(0, S + 1, (B,), generator=g)
+    sl = n.to(torch.int32).cuda()
+    z[0, 0, V - 1] = z[0, 0, 7] = 15.0      # a tie between the first and the last segment
+    z[-1, 0, :V // 2] = -float("inf")       # segments without a finite entry
+    out = [(torch.full((B, S), -7, dtype=torch.int32, device="cuda"), torch.full((B, S), -7.0, device="cuda"),
+            torch.full((B, S), -7.0, device="cuda")) for _ in range(3)]
+    # oracle on some rows of every case; whole rows (no workspace, where that is allowed) on all of them
+    ws = torch.randint(0, 256, (lsp.confidence_workspace_bytes(B, S, V),), dtype=torch.uint8, generator=g).cuda()
+    lsp.confidence(z, sl, out=out[0], workspace=ws)
+    lsp.confidence(z, sl, out=out[1], workspace=ws)                 # left clean by the first
+    act = torch.arange(S, device="cuda")[None] < sl[:, None]
+    for a, b in zip(out[0], out[1]):
+        assert torch.equal(a, b) and torch.all(a[~act] == -7)
+    zz = z.float()
+    top2 = zz.topk(2, dim=-1).values
+    first = (zz == top2[..., :1]).to(torch.int8).argmax(-1).to(torch.int32)     # argmax of a mask: the first of equals
+    prob = 1 / (zz.double() - top2[..., :1].double()).exp().sum(-1)
+    assert torch.equal(out[0][0][act], first[act])
+    assert torch.equal(out[0][2][act], (top2[..., 0] - top2[..., 1])[act])
+    assert ((out[0][1].double() - prob)[act] / prob[act]).abs().max() <= 2e-6
+    if B * S >= 128:
+        lsp.confidence(z, sl, out=out[2])
+        assert torch.equal(out[0][0], out[2][0]) and torch.equal(out[0][2], out[2][2])
+
+
+def test_segments_under_graph_replay(lsp):
+    """Every replay carries the same tag: what one leaves in the workspace must not pass for the next one's."""
+    B, S, V = 1, 200, 65536
+    z = torch.randn((B, S, V), device="cuda", dtype=torch.bfloat16, generator=torch.Generator(device="cuda").manual_seed(3))
+    sl = torch.tensor([30], dtype=torch.int32, device="cuda")
+    out = (torch.zeros((B, S), dtype=torch.int32, device="cuda"), torch.zeros((B, S), device="cuda"), torch.zeros((B, S), device="cuda"))
+    ws = torch.zeros(lsp.confidence_workspace_bytes(B, S, V), dtype=torch.uint8, device="cuda")
+    lsp.confidence(z, sl, out=out, workspace=ws)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        lsp.confidence(z, sl, out=out, workspace=ws)
+    for k in range(6):
+        z.copy_(z.roll(1000 * k + 1, dims=-1))
+        sl.fill_(30 - 5 * k)
+        ref = lsp.confidence(z, sl, out=tuple(torch.zeros_like(t) for t in out), workspace=torch.zeros_like(ws))
+        for t in out:
+            t.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        for a, b in zip(out, ref):
+            assert torch.equal(a, b)
