@@ -146,16 +146,46 @@ def block_max(E, sn, part):
             E.e(f"v_max3_f32 v{BM}, v{BM}, v{sn[r]}, v{sn[r + 1]}")
 
 
-def iteration(E, u):
-    """Block j = 8n + u: soft-max of S(j) under S(j+1) = K(j+1).Q^T, then O += V(j)^T.P(j)^T."""
-    cur, nxt = S[u & 1], S[(u + 1) & 1]
-    # reference check on the maximum of S(j) (computed while the previous block's second product ran)
-    # (any lane's own half-column above the reference by 8 octaves sends the wave to the cold path)
+def check_reference(E, u):
+    """The maximum of S(j), computed while the previous block's second product ran, against the running reference
+    (any lane's own half-column above it by 8 octaves sends the wave to the cold path)."""
     E.e(f"v_fma_f32 v{X0}, v{BM}, %[sc], v{NM}")
     E.e(f"v_cmp_lt_f32 vcc, 0x41000000, v{X0}")
     E.e(f"s_cbranch_vccnz .Lresc_{u}_%=")
     E.e(f".Lafter_{u}_%=:")
+
+
+def iteration(E, u):
+    """Block j = 8n + u: soft-max of S(j) under S(j+1) = K(j+1).Q^T, then O += V(j)^T.P(j)^T."""
+    check_reference(E, u)
     load_block(E, (u + LA) % NS, f"i{u}")
+    products(E, u, v_at=u * TILE, k_stage=(u + 2) % NS)
+    E.e(f"s_add_u32 s{SG['jn']}, s{SG['jn']}, 1")
+    E.e(f"s_cmp_lt_u32 s{SG['jn']}, %[nb]")
+    E.e("s_cbranch_scc0 .Lexit_%=")
+    if u & 1:
+        E.e(f"s_waitcnt vmcnt({2 * (LA - 4)})")
+        E.e("s_barrier")
+
+
+def first_scores(E):
+    """S(0) = K(0).Q^T, its maximum, and the K fragments of block 1."""
+    read_k_frags(E, 0, range(8))
+    for kk in range(8):
+        E.need(KF[kk])
+        c = vr(S[0][0], 16) if kk else "0"
+        E.e(f"v_mfma_f32_32x32x16_bf16 {vr(S[0][0], 16)}, {vr(KF[kk], 4)}, {vr(QF[kk], 4)}, {c}")
+    E.e("s_nop 7")
+    read_k_frags(E, 1, range(8))
+    E.e("s_nop 7")
+    for part in range(3):
+        block_max(E, S[0], part)
+
+
+def products(E, u, v_at, k_stage):
+    """The two products and the soft-max of block j (j % 2 = u % 2); v_at: offset of V(j) from the fragment addresses,
+    k_stage: stage of K(j+2)."""
+    cur, nxt = S[u & 1], S[(u + 1) & 1]
 
     def stage_f(i):
         for e in (2 * i, 2 * i + 1):
@@ -181,8 +211,8 @@ def iteration(E, u):
         c = vr(nxt[0], 16) if kk else "0"
         E.e(f"v_mfma_f32_32x32x16_bf16 {vr(nxt[0], 16)}, {vr(KF[kk], 4)}, {vr(QF[kk], 4)}, {c}")
         k2, db = kk // 4, kk % 4
-        E.lds_read("ds_read_b64_tr_b16", VF[kk], 2, VADDR[db], VBASE * 0 + u * TILE + 4096 * k2)
-        E.lds_read("ds_read_b64_tr_b16", VF[kk] + 2, 2, VADDR[db], u * TILE + 4096 * k2 + 2048)
+        E.lds_read("ds_read_b64_tr_b16", VF[kk], 2, VADDR[db], v_at + 4096 * k2)
+        E.lds_read("ds_read_b64_tr_b16", VF[kk] + 2, 2, VADDR[db], v_at + 4096 * k2 + 2048)
         stage_f(kk)
         if kk >= 1:
             stage_e(kk - 1)
@@ -202,23 +232,145 @@ def iteration(E, u):
         elif m == 1:
             stage_c(7)
         elif m == 2:
-            read_k_frags(E, (u + 2) % NS, (0, 1))
+            read_k_frags(E, k_stage, (0, 1))
         elif m == 3:
-            read_k_frags(E, (u + 2) % NS, (2, 3))
+            read_k_frags(E, k_stage, (2, 3))
         elif m == 4:
-            read_k_frags(E, (u + 2) % NS, (4, 5))
+            read_k_frags(E, k_stage, (4, 5))
             block_max(E, nxt, 0)
         elif m == 5:
-            read_k_frags(E, (u + 2) % NS, (6, 7))
+            read_k_frags(E, k_stage, (6, 7))
             block_max(E, nxt, 1)
         elif m == 6:
             block_max(E, nxt, 2)
-    E.e(f"s_add_u32 s{SG['jn']}, s{SG['jn']}, 1")
-    E.e(f"s_cmp_lt_u32 s{SG['jn']}, %[nb]")
-    E.e("s_cbranch_scc0 .Lexit_%=")
-    if u & 1:
-        E.e(f"s_waitcnt vmcnt({2 * (LA - 4)})")
-        E.e("s_barrier")
+
+
+# ---- the loop of workgroups of four waves (128 queries), two to a compute unit ----
+# Same block arithmetic, registers and issue order.  What differs: a ring of NSH = 5 stages of K and of V (80 KB, so
+# that two workgroups fit), a barrier after every block (the other workgroup's waves fill the wait), and four loads per
+# wave and block (8 rows of K and of V).  Iteration j requests K(j + 5) into the stage of K(j), whose fragments every wave
+# had in registers in iteration j - 1, and V(j + 4) into that of V(j - 1); before the barrier that ends it a wave
+# waits for its part of K(j + 3) and V(j + 1), which are read before the next one: all but its newest 10 loads (V of
+# iteration j - 2, K and V of j - 1 and j).
+NSH, UNROLL_H = 5, 10
+VBASE_H = NSH * TILE
+OFFS_H = dict(k=(164, 165), v=(166, 167))          # lane offsets of this wave's two loads of a block
+SUFFIX_H = dict(k=(240, 241), v=(242, 243))        # the same for suffix rows
+SH = dict(m0save=64, jn=65, kp=66, kstep=68, kcnt=69, kleft=70, t=71, vp=72, vstep=74, vcnt=75, vleft=76)
+WAIT_H = 10
+
+
+def load_half(E, which, stage, tag):
+    """Request the next block of K or V.  A stream counts down to the end of its cache rows, then to its last block, and
+    from there on requests that one again; the code for both events is out of line."""
+    p, step, cnt = SH[which + "p"], SH[which + "step"], SH[which + "cnt"]
+    base = stage * TILE + (VBASE_H if which == "v" else 0)
+    E.e(f"s_add_u32 m0, %[ldsk], {base}")
+    E.e(f"s_sub_u32 s{cnt}, s{cnt}, 1")
+    E.e(f"s_cbranch_scc1 .Lev{which}_{tag}_%=")
+    E.e(f".Lis{which}_{tag}_%=:")
+    E.e(f"global_load_lds_dwordx4 v{OFFS_H[which][0]}, s[{p}:{p + 1}]")
+    E.e(f"s_add_u32 m0, %[ldsk], {base + 1024}")
+    E.e("s_nop 0")
+    E.e(f"global_load_lds_dwordx4 v{OFFS_H[which][1]}, s[{p}:{p + 1}]")
+    E.e(f"s_add_u32 s{p}, s{p}, s{step}")
+    E.e(f"s_addc_u32 s{p + 1}, s{p + 1}, 0")
+
+
+def event_half(E, which, tag):
+    """The countdown of a stream has run out: on to the suffix rows, or, after these (or where there are none: `left` is 0),
+    back to the last block and no further."""
+    p, step, cnt, left, t = SH[which + "p"], SH[which + "step"], SH[which + "cnt"], SH[which + "left"], SH["t"]
+    E.e(f".Lev{which}_{tag}_%=:")
+    E.e(f"s_cmp_eq_u32 s{left}, 0")
+    E.e(f"s_cselect_b32 s{t}, s{step}, 0")
+    E.e(f"s_sub_u32 s{p}, s{p}, s{t}")
+    E.e(f"s_subb_u32 s{p + 1}, s{p + 1}, 0")
+    E.e(f"s_sub_u32 s{t}, s{left}, 1")
+    E.e(f"s_cmp_eq_u32 s{left}, 0")
+    E.e(f"s_cselect_b64 s[{p}:{p + 1}], s[{p}:{p + 1}], %[{which}s]")
+    E.e(f"s_cselect_b32 s{step}, 0, %[sstep]")
+    E.e(f"s_cselect_b32 s{cnt}, 0x7fffffff, s{t}")
+    E.e(f"s_mov_b32 s{left}, 0")
+    for to, of in zip(OFFS_H[which], SUFFIX_H[which]):     # (without suffix rows the caller gives the cache's offsets twice)
+        E.e(f"v_mov_b32 v{to}, v{of}")
+    E.e(f"s_branch .Lis{which}_{tag}_%=")
+
+
+def begin_half(E):
+    E.e(f"s_mov_b32 s{SH['m0save']}, m0")
+    for w in "kv":
+        E.e(f"s_mov_b64 s[{SH[w + 'p']}:{SH[w + 'p'] + 1}], %[{w}c]")
+        E.e(f"s_mov_b32 s{SH[w + 'step']}, %[cstep]")
+        E.e(f"s_mov_b32 s{SH[w + 'cnt']}, %[nc]")
+        E.e(f"s_mov_b32 s{SH[w + 'left']}, %[nsuf]")
+    E.e(f"s_add_u32 s{SH['jn']}, %[nc], %[nsuf]")
+    E.e(f"s_sub_u32 s{SH['jn']}, s{SH['jn']}, 1")      # counts down, borrows after the last block
+    for t in range(NSH):
+        load_half(E, "k", t, f"p{t}")
+        if t >= 1:
+            load_half(E, "v", t - 1, f"p{t - 1}")
+    E.e(f"s_waitcnt vmcnt({WAIT_H})")
+    E.e("s_barrier")
+
+
+def end_of_iteration_half(E):
+    E.e(f"s_sub_u32 s{SH['jn']}, s{SH['jn']}, 1")
+    E.e("s_cbranch_scc1 .Lexit_%=")
+    E.e(f"s_waitcnt vmcnt({WAIT_H})")
+    E.e("s_barrier")
+
+
+def events_half(E):
+    for tag in [f"p{t}" for t in range(NSH)] + [f"i{u}" for u in range(UNROLL_H)]:
+        event_half(E, "k", tag)
+        if tag != f"p{NSH - 1}":
+            event_half(E, "v", tag)
+
+
+def generate_half():
+    E = Emitter()
+    begin_half(E)
+    first_scores(E)
+    E.e("s_barrier")                                   # every wave has its fragments of K(0): iteration 0 requests K(5) into that stage
+    E.e(".Lloop_%=:")
+    for u in range(UNROLL_H):
+        check_reference(E, u)
+        load_half(E, "k", u % NSH, f"i{u}")
+        load_half(E, "v", (u + NSH - 1) % NSH, f"i{u}")
+        products(E, u, v_at=u % NSH * TILE, k_stage=(u + 2) % NSH)
+        end_of_iteration_half(E)
+    E.e("s_branch .Lloop_%=")
+    E.e(".Lexit_%=:")
+    E.e("s_waitcnt vmcnt(0) lgkmcnt(0)")
+    E.e(f"s_mov_b32 m0, s{SH['m0save']}")
+    E.e("s_nop 15")
+    E.e("s_branch .Lend_%=")
+    for u in range(UNROLL_H):
+        rescale(E, u)
+    events_half(E)
+    E.e(".Lend_%=:")
+    return E.lines
+
+
+def generate_half_idle():
+    """As generate_idle: the loads, waits and barriers of a wave without an active query."""
+    E = Emitter()
+    begin_half(E)
+    E.e("s_barrier")
+    E.e(".Lloop_%=:")
+    for u in range(UNROLL_H):
+        load_half(E, "k", u % NSH, f"i{u}")
+        load_half(E, "v", (u + NSH - 1) % NSH, f"i{u}")
+        end_of_iteration_half(E)
+    E.e("s_branch .Lloop_%=")
+    E.e(".Lexit_%=:")
+    E.e("s_waitcnt vmcnt(0)")
+    E.e(f"s_mov_b32 m0, s{SH['m0save']}")
+    E.e("s_branch .Lend_%=")
+    events_half(E)
+    E.e(".Lend_%=:")
+    return E.lines
 
 
 def rescale(E, u):
@@ -266,17 +418,7 @@ def generate():
     # blocks 0..3 have landed everywhere
     E.e(f"s_waitcnt vmcnt({2 * (LA - 4)})")
     E.e("s_barrier")
-    # S(0) = K(0).Q^T, its maximum, and the K fragments of block 1
-    read_k_frags(E, 0, range(8))
-    for kk in range(8):
-        E.need(KF[kk])
-        c = vr(S[0][0], 16) if kk else "0"
-        E.e(f"v_mfma_f32_32x32x16_bf16 {vr(S[0][0], 16)}, {vr(KF[kk], 4)}, {vr(QF[kk], 4)}, {c}")
-    E.e("s_nop 7")
-    read_k_frags(E, 1, range(8))
-    E.e("s_nop 7")
-    for part in range(3):
-        block_max(E, S[0], part)
+    first_scores(E)
     E.e(".Lloop_%=:")
     for u in range(NS):
         iteration(E, u)
@@ -343,25 +485,36 @@ HEADER = """// GENERATED by gen_attn_pipe.py - do not edit; the register map, th
 """
 
 
-def main():
-    lines = generate()
+def statement(lines, outputs, inputs, vclob):
     body = "\n".join(f'    "{l}\\n"' for l in lines)
-    clob = [f"v{i}" for i in list(range(0, 32)) + list(range(64, 152)) + list(range(170, 176))]
-    clob += [f"s{i}" for i in range(64, 80)] + ["vcc", "scc", "memory"]
-    text = HEADER + "asm volatile(\n" + body + "\n"
-    text += ('    : "+{v[176:191]}"(oacc[0]), "+{v[192:207]}"(oacc[1]), "+{v[208:223]}"(oacc[2]), "+{v[224:239]}"(oacc[3]),\n'
-             '      "+{v168}"(nm), "+{v169}"(lsum), "+{v[152:167]}"(addr)\n'
-             '    : "{v[32:47]}"(qf_lo), "{v[48:63]}"(qf_hi),\n'
-             '      [kc] "s"(kc_base), [vc] "s"(vc_base), [ks] "s"(ks_base), [vs] "s"(vs_base),\n'
-             '      [cstep] "s"(cstep), [sstep] "s"(sstep), [nc] "s"(nc), [nb] "s"(nb), [ldsk] "s"(ldsk), [sc] "s"(sc)\n')
-    text += "    : " + ", ".join(f'"{c}"' for c in clob) + ");\n"
+    clob = [f"v{i}" for i in vclob] + [f"s{i}" for i in range(64, 80)] + (["vcc"] if vclob else []) + ["scc", "memory"]
+    return ("asm volatile(\n" + body + "\n    : " + outputs + "\n    : " + inputs + "\n    : "
+            + ", ".join(f'"{c}"' for c in clob) + ");\n")
+
+
+ACC = ('"+{v[176:191]}"(oacc[0]), "+{v[192:207]}"(oacc[1]), "+{v[208:223]}"(oacc[2]), "+{v[224:239]}"(oacc[3]),\n'
+       '      "+{v168}"(nm), "+{v169}"(lsum), "+{v[152:167]}"(addr)')
+QREGS = '"{v[32:47]}"(qf_lo), "{v[48:63]}"(qf_hi),\n      '
+STREAM = '[kc] "s"(kc_base), [vc] "s"(vc_base), [ks] "s"(ks_base), [vs] "s"(vs_base),\n      '
+BLOCKS = '[cstep] "s"(cstep), [sstep] "s"(sstep), [nc] "s"(nc), [nb] "s"(nb), [ldsk] "s"(ldsk)'
+BLOCKS_H = '[cstep] "s"(cstep), [sstep] "s"(sstep), [nc] "s"(nc), [nsuf] "s"(nsuf), [ldsk] "s"(ldsk), "{v[240:243]}"(soffs)'
+SCRATCH_V = list(range(0, 32)) + list(range(64, 152)) + list(range(170, 176))
+
+HEADER_HALF = """// GENERATED by gen_attn_pipe.py - do not edit; described there (the loop of workgroups of four waves).
+// Expects in scope what lsp_attn_pipe_loop.inc does, but u32x4 soffs (lane offsets of suffix rows) and uint32_t nsuf for nb.
+"""
+
+
+def main():
     here = os.path.dirname(os.path.abspath(__file__))
-    out = os.path.join(here, "lsp_attn_pipe_loop.inc")
-    with open(out, "w") as f:
-        f.write(text)
-    with open(os.path.join(here, "lsp_attn_pipe_idle_loop.inc"), "w") as f:
-        f.write(idle_text())
-    return out
+    for name, text in (
+            ("pipe_loop", HEADER + statement(generate(), ACC, QREGS + STREAM + BLOCKS + ', [sc] "s"(sc)', SCRATCH_V)),
+            ("pipe_idle_loop", IDLE_HEADER + statement(generate_idle(), '"+{v[152:167]}"(addr)', STREAM + BLOCKS, [])),
+            ("half_loop", HEADER_HALF + statement(generate_half(), ACC, QREGS + STREAM + BLOCKS_H + ', [sc] "s"(sc)', SCRATCH_V)),
+            ("half_idle_loop", HEADER_HALF + statement(generate_half_idle(), '"+{v[152:167]}"(addr)', STREAM + BLOCKS_H, []))):
+        with open(os.path.join(here, f"lsp_attn_{name}.inc"), "w") as f:
+            f.write(text)
+    return here
 
 
 IDLE_HEADER = """// GENERATED by gen_attn_pipe.py - do not edit: the block loop of a wave without an active query
@@ -369,17 +522,6 @@ IDLE_HEADER = """// GENERATED by gen_attn_pipe.py - do not edit: the block loop 
 // Expects in scope: u32x16 addr; uint64_t kc_base, vc_base, ks_base, vs_base;
 // uint32_t cstep, sstep, nc, nb, ldsk.
 """
-
-
-def idle_text():
-    body = "\n".join(f'    "{l}\\n"' for l in generate_idle())
-    clob = [f"s{i}" for i in range(64, 80)] + ["scc", "memory"]
-    text = IDLE_HEADER + "asm volatile(\n" + body + "\n"
-    text += ('    : "+{v[152:167]}"(addr)\n'
-             '    : [kc] "s"(kc_base), [vc] "s"(vc_base), [ks] "s"(ks_base), [vs] "s"(vs_base),\n'
-             '      [cstep] "s"(cstep), [sstep] "s"(sstep), [nc] "s"(nc), [nb] "s"(nb), [ldsk] "s"(ldsk)\n')
-    text += "    : " + ", ".join(f'"{c}"' for c in clob) + ");\n"
-    return text
 
 
 if __name__ == "__main__":

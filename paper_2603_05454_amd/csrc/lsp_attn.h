@@ -59,6 +59,11 @@ __device__ __forceinline__ int workgroup_id() { return blockIdx.y << kGridBits |
 // active length fell from 1024 to 256).  Runs of kUnitGroup live workgroups
 // spread over all of them, and the tiles of one unit still run close enough
 // together to share its K/V stream in L2.
+// A launch of up to one and a half times the workgroups that run at once is one group: the tiles of a unit meet anyway,
+// and the live workgroups, then first in the order, find a compute unit each before the hardware gives one a second
+// (one layer, 32 heads, 4 x 128 rows with 50 active on 1000: 22.2 us in groups of 8 units, 16.9 in one; 3 x 700
+// with 300 active on 500: 31.4, 27.5).  With two rounds the tiles of a unit would no longer meet (8 x 512 on 512: 82, 87).
+// For the live ones' sake the tile is the slow index also among the heads of a unit.
 constexpr int kUnitGroup = 8;
 struct Place {
   int layer, b, g, h, q0;
@@ -94,14 +99,14 @@ __device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
   p.layer = layer;
   p.b = unit / a.Hkv;
   p.g = unit - p.b * a.Hkv;
-  const int hr = wu / QT;
-  p.h = p.g * rep + hr;
-  p.q0 = (wu - hr * QT) * qtile;
+  const int tile = wu / rep;
+  p.h = p.g * rep + wu - tile * rep;
+  p.q0 = tile * qtile;
   return p;
 }
 // Fields of that placement in `a`, and its number of workgroups.  Units are cut only where an XCD would get more than
-// `enough` workgroups.
-inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile, int unit_group = kUnitGroup, int enough = 0) {
+// `enough` workgroups.  resident: workgroups that run at once on an XCD (0: groups as above whatever their number).
+inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile, int resident = 0, int unit_group = kUnitGroup, int enough = 0) {
   const int64_t QT = (a.S + qtile - 1) / qtile, per_unit = a.Hq / a.Hkv * QT;
   a.layers = layers.n > 0 ? layers.n : 1;
   const int64_t units = int64_t(a.layers) * a.B * a.Hkv;
@@ -112,7 +117,8 @@ inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile, int 
   a.rep = a.Hq / a.Hkv;
   a.chunk = int32_t(chunk);
   const int64_t pieces8 = ((units << a.spread) + 7) / 8;  // pieces per XCD
-  const int64_t G = pieces8 < unit_group ? pieces8 : unit_group;
+  const bool one_group = 2 * pieces8 * chunk <= 3 * resident;
+  const int64_t G = pieces8 < unit_group || one_group ? pieces8 : unit_group;
   a.unit_group = int32_t(G);
   return (pieces8 + G - 1) / G * G * chunk * 8;
 }

@@ -30,7 +30,8 @@
 //    active rows still fills 256 compute units and runs at memory latency.
 //    With head_dim 128 its K/V rows go from global memory straight into the
 //    wave's LDS region (global_load_lds_dwordx4, rows unpadded and swizzled).
-//  * attn_bf16_tile_kernel (long suffixes): the WM waves of a workgroup share
+//  * attn_bf16_tile_kernel (long suffixes at head_dim 64, or up to 128 rows and an
+//    index list): the WM waves of a workgroup share
 //    each K/V block through a two-stage LDS ring (every wave fetches 1/WM of
 //    the block), one barrier per block; L1/L2 traffic per flop drops WM-fold,
 //    which is what the matrix cores need once the problem is compute bound.
@@ -38,7 +39,7 @@
 //    more than 128 rows, cache rows addressed through an index list): eight
 //    waves, K/V straight from global memory into an eight-stage LDS ring, one
 //    barrier every four blocks; described where it is defined.
-//  * attn_bf16_pipe_kernel (the same shapes with a contiguous cache, i.e. the
+//  * attn_bf16_pipe_kernel (head_dim 128, contiguous cache, all but the smallest launches, i.e. the
 //    long-context and decode-loop configurations): the same ring, but the block
 //    loop is a generated, hand-scheduled inline-asm statement
 //    (gen_attn_pipe.py -> lsp_attn_pipe_loop.inc) in which the first product of
@@ -61,6 +62,7 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLagOctaves = 8.0f;
+constexpr float kPartOctaves = 32.0f;
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -104,7 +106,9 @@ struct Geo {
   static constexpr int KBYTES = 32 * KPITCH;
   static constexpr int VBYTES = 32 * VPITCH;
   static constexpr int OBYTES = 32 * OPITCH + 2 * 32 * 4;  // O^T block + m[32] + l[32]
-  static constexpr int WAVE_LDS = KBYTES + VBYTES > OBYTES ? KBYTES + VBYTES : OBYTES;
+  // (head_dim 128 stages unpadded rows)
+  static constexpr int STAGED = D == 128 ? 2 * 32 * D * 2 : KBYTES + VBYTES;
+  static constexpr int WAVE_LDS = STAGED > OBYTES ? STAGED : OBYTES;
 };
 
 // V^T fragments of a 32-key block for O^T += V^T . P^T, read from an LDS tile of
@@ -150,7 +154,7 @@ __device__ __forceinline__ void load_v_frags(bf16x8 (&vf)[D / 32][2], int lane, 
 template <int D>
 __device__ __forceinline__ void softmax_pv(f32x16 &s, f32x16 (&oacc)[D / 32], float &mref, float &lsum,
                                            int key0, int T, float sc, int lane,
-                                           const bf16x8 (&vf)[D / 32][2]) {
+                                           const bf16x8 (&vf)[D / 32][2], bool fresh = false) {
   constexpr int DB = D / 32;
   const int hf = lane >> 5;
   if (key0 + 32 > T) {  // ragged last block: keys >= T get -inf
@@ -164,8 +168,9 @@ __device__ __forceinline__ void softmax_pv(f32x16 &s, f32x16 (&oacc)[D / 32], fl
 #pragma unroll
   for (int r = 2; r < 16; r += 2) bm = fmax3_raw(bm, s[r], s[r + 1]);
   bm = half_max(bm) * sc;  // finite: key0 < T is a valid key
-  if (__any(bm > mref + kLagOctaves)) {
-    const float mn = bm > mref + kLagOctaves ? bm : mref;
+  if (fresh || __any(bm > mref + kLagOctaves)) {
+    float mn = bm > mref + kLagOctaves ? bm : mref;
+    if (fresh) mn = fmax_raw(bm, mref - kPartOctaves);
     const float alpha = __builtin_amdgcn_exp2f(mref - mn);  // 0 on the first block (mref = -inf)
     mref = mn;
     lsum *= alpha;
@@ -203,6 +208,7 @@ constexpr int kShortSuffix = 64;  // sequences with at most this many active row
 // without a query, a tile with two active waves is faster than two key-split workgroups - 38 against
 // 50 us per C5 layer - while a tile with one active wave is slower than one key-split workgroup)
 constexpr int kShortSuffixPipe = 32;
+constexpr int kSpreadBlocks = 512;  // blocks of 32 rows in the whole launch
 
 // Final step shared by both kernels: the WK partial results of every query
 // block are combined through LDS (each wave's region holds O^T as [query][d]
@@ -283,7 +289,11 @@ constexpr int kWaitLgkm0 = 0xC07F;    // s_waitcnt lgkmcnt(0), other counters un
 // Body of the wave-private kernel for the WM*32 queries from q0 of (sequence b,
 // query head h, KV head g); every thread of a workgroup of 64*WM*WK threads
 // calls it with the same arguments (it contains barriers).
-template <int D, int WM, int WK, bool GATHER>
+// PARTS: parts of the key range that a wave takes one after the other, each with a reference of its own: the first block
+// of the second part sets the reference anew (as far down as matters: what lies kPartOctaves below the first part's
+// adds nothing to a bf16 result) and the sums are brought to it.  Four waves with two parts so round every
+// probability as eight waves do, whatever workgroup a launch uses (head_dim 128 only).
+template <int D, int WM, int WK, bool GATHER, int PARTS = 1>
 __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, int h, int q0, int N, int P,
                                                unsigned char *smem) {
   using G = Geo<D>;
@@ -473,15 +483,22 @@ __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, 
     // the V^T fragments do.
     const int y16 = 16 * (hf ^ (lq & 15));
     int jb = wk_s;
+    bool first_part = PARTS > 1, fresh = false;
     // (the first block was requested before the Q rows, see above)
-    for (; jb < NB; jb += WK) {
-      const bool more = jb + WK < NB;
+    while (jb < NB) {
+      int jn = jb + WK * PARTS;
+      const bool turn = first_part && jn >= NB;  // to this wave's second part
+      if (turn) {
+        jn = wk_s + WK;
+        first_part = false;
+      }
+      const bool more = jn < NB;
       __builtin_amdgcn_s_waitcnt(kWaitVm8);  // all but the newest 8 loads (this block's V rows) have landed: K is there
       bf16x8 kf[KK];
 #pragma unroll
       for (int kk = 0; kk < KK; ++kk) kf[kk] = *reinterpret_cast<const bf16x8 *>(wlds + lq * (D * 2) + ((32 * kk) ^ y16));
       __builtin_amdgcn_s_waitcnt(kWaitLgkm0);  // fragments are in registers: the K rows may be overwritten
-      if (more) issue_k(jb + WK);
+      if (more) issue_k(jn);
       f32x16 s;
 #pragma unroll
       for (int r = 0; r < 16; ++r) s[r] = 0.f;
@@ -497,8 +514,10 @@ __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, 
       bf16x8 vf[DB][2];
       load_v_frags<D, true>(vf, lane, wlds + KB);
       __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-      if (more) issue_v(jb + WK);
-      softmax_pv<D>(s, oacc, mref, lsum, 32 * jb, T, sc, lane, vf);
+      if (more) issue_v(jn);
+      softmax_pv<D>(s, oacc, mref, lsum, 32 * jb, T, sc, lane, vf, fresh);
+      fresh = turn;
+      jb = jn;
     }
     __builtin_amdgcn_s_waitcnt(kWaitVm0);  // nothing of this wave is still on its way into LDS
   } else {
@@ -524,7 +543,7 @@ __global__ __launch_bounds__(64 * WM * WK, 2) void attn_bf16_kernel(AttnArgs a_i
 
 template <int D, int WM, int WK, bool GATHER>
 int32_t launch_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
-  const int64_t nwg = place_grid(a, layers, 32 * WM);
+  const int64_t nwg = place_grid(a, layers, 32 * WM, 32 * 8 / (WM * WK));
   if (nwg > kMaxGrid) {
     set_error("lsp_attn_step: launch of %lld workgroups is too large", (long long)nwg);
     return LSP_ERR_UNSUPPORTED;
@@ -973,9 +992,11 @@ int32_t launch_ring_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
   return LSP_OK;
 }
 
-// ---- long-suffix kernel, head_dim 128, contiguous cache: hand-scheduled block loop ----
-// Same tile (256 queries, 8 waves of 32, two waves per SIMD), same LDS ring and the
-// same arithmetic as attn_bf16_ring_kernel; what differs is who fixes the issue
+// ---- head_dim 128, contiguous cache: hand-scheduled block loop ----
+// WM = 8: same tile (256 queries, 8 waves of 32, two waves per SIMD), same LDS ring and the
+// same arithmetic as attn_bf16_ring_kernel.  WM = 4: 128 queries, a ring of five stages and so two
+// workgroups per compute unit, whose prologues, merges and barriers cover each other, and half the rows of padding
+// (which to take is measured at dispatch_contiguous128).  What differs is who fixes the issue
 // order.  The block loop is one generated inline-asm statement (gen_attn_pipe.py
 // describes its pipeline, register map and synchronisation): a one-block software
 // pipeline per wave in which the soft-max of block j is issued between the matrix
@@ -986,10 +1007,12 @@ int32_t launch_ring_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
 // rows: at most two blocks per tile) are done first, by compiler-scheduled code with
 // the same fragment layout, on the same running (m, l, O) state.
 typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
-__global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_pipe_kernel(AttnArgs a_in,
-                                                                                                       AttnLayers layers) {
+template <int WM>
+__global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_pipe_kernel(AttnArgs a_in,
+                                                                                                           AttnLayers layers) {
   AttnArgs a = a_in;
-  constexpr int D = 128, WM = 8, KK = D / 16, DB = D / 32, NS = 8;
+  constexpr int D = 128, KK = D / 16, DB = D / 32, NS = WM == 8 ? 8 : 5;
+  constexpr int LPB = 8 / WM;  // wave-wide loads of K (and of V) that a wave makes per block
   constexpr int TILE = 32 * D * 2, VBASE = NS * TILE;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
@@ -999,13 +1022,18 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int b = pl.b, g = pl.g, h = pl.h, q0 = pl.q0;
   const int N = min(max(a.suffix_len[b], 0), a.S);
   const int P = min(max(a.prefix_len[b], 0), a.C);
-  if (q0 >= N) return;
   // A tile with at most 32 active rows - a sequence down to its last rows, or the tail of a longer
-  // suffix that ends just past a multiple of 256 - would keep seven waves idle for the whole key
+  // suffix that ends just past a multiple of the tile - would keep all waves but one idle for the whole key
   // range: its one block of queries goes to the key-split body (as in attn_bf16_ring_kernel), which
-  // shares the KEY range between the eight waves instead.
-  if (N - q0 <= kShortSuffixPipe) {
-    key_split_body<D, 1, WM, false>(a, b, g, h, q0, N, P, smem);
+  // shares the KEY range between the waves instead.  The same where so few tiles are left of the whole launch that
+  // workgroups of 32 rows still find a compute unit each: the workgroups of the tiles that have ended take them
+  // (one layer, 32 heads, 200 of 1024 rows on 4000 cached ones: 102 us with one tile of 256, 39 so).
+  const int blocks = (N + 31) >> 5;
+  const bool spread = WM == 4 && blocks <= (a.S + 32 * WM - 1) / (32 * WM) && int64_t(blocks) * a.B * a.Hq * a.layers <= kSpreadBlocks;
+  const int qs = spread ? q0 / WM : q0;
+  if (qs >= N) return;
+  if (spread || N - q0 <= kShortSuffixPipe) {
+    key_split_body<D, 1, WM, false, 8 / WM>(a, b, g, h, qs, N, P, smem);
     return;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1023,9 +1051,10 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const char *ks = reinterpret_cast<const char *>(static_cast<const uint16_t *>(a.k_suf) + b * a.ks[0] + g * a.ks[2]);
   const char *vs = reinterpret_cast<const char *>(static_cast<const uint16_t *>(a.v_suf) + b * a.ks[0] + g * a.ks[2]);
   const int64_t cpitch = a.cs[1] * 2, spitch = a.ks[1] * 2;
-  // loader: this lane owns row lr of every block and 16-byte position pp of it
-  const int pp = lane & 15, lr = 4 * wave + (lane >> 4);
-  const int kcol = 16 * (pp ^ (lr & 15)), vcol = 64 * ((pp >> 2) ^ (lr & 3)) + 16 * (pp & 3);
+  // loader: this lane owns rows lr + 4 i (i < LPB) of every block and 16-byte position pp of them
+  const int pp = lane & 15, lr = 4 * LPB * wave + (lane >> 4);
+  const int vcol = 64 * ((pp >> 2) ^ (lr & 3)) + 16 * (pp & 3);
+  auto kcol = [=](int i) { return 16 * (pp ^ ((lr + 4 * i) & 15)); };
 
   f32x16 oacc[DB];
 #pragma unroll
@@ -1050,12 +1079,17 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // ---- ragged ends: rows [32*nc, P) of the cache and rows [32*ns, N) of the suffix ----
   const int nc = P >> 5, ns = N >> 5;
   auto ragged_block = [&](const char *kbase, const char *vbase, int64_t pitch, int cnt) {
-    // this lane's row, clamped into the block; rows >= cnt are masked below and their V slots zeroed
-    const int64_t off = int64_t(min(lr, cnt - 1)) * pitch;
-    load_to_lds(kbase + off + kcol, smem + 1024 * wave_s);
-    load_to_lds(vbase + off + vcol, smem + VBASE + 1024 * wave_s);
+    // this lane's rows, clamped into the block; rows >= cnt are masked below and their V slots zeroed
+#pragma unroll
+    for (int i = 0; i < LPB; ++i) {
+      const int64_t off = int64_t(min(lr + 4 * i, cnt - 1)) * pitch;
+      load_to_lds(kbase + off + kcol(i), smem + 1024 * (LPB * wave_s + i));
+      load_to_lds(vbase + off + vcol, smem + VBASE + 1024 * (LPB * wave_s + i));
+    }
     __builtin_amdgcn_s_waitcnt(kWaitVm0);
-    if (lr >= cnt) *reinterpret_cast<u32x4 *>(smem + VBASE + 1024 * wave + 16 * lane) = u32x4{0, 0, 0, 0};
+#pragma unroll
+    for (int i = 0; i < LPB; ++i)
+      if (lr + 4 * i >= cnt) *reinterpret_cast<u32x4 *>(smem + VBASE + 1024 * (LPB * wave + i) + 16 * lane) = u32x4{0, 0, 0, 0};
     __syncthreads();
     bf16x8 kf[KK];
 #pragma unroll
@@ -1090,24 +1124,41 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
     for (int kk = 0; kk < KK; ++kk) addr[kk] = uint32_t(uintptr_t((__attribute__((address_space(3))) const unsigned char *)kaddr[kk]));
 #pragma unroll
     for (int db = 0; db < DB; ++db) addr[8 + db] = uint32_t(uintptr_t((__attribute__((address_space(3))) const unsigned char *)vaddr[db]));
-    addr[12] = uint32_t(lr * cpitch + kcol);
-    addr[13] = uint32_t(lr * cpitch + vcol);
-    addr[14] = uint32_t(lr * spitch + kcol);
-    addr[15] = uint32_t(lr * spitch + vcol);
     const uint64_t kc_base = reinterpret_cast<uint64_t>(kc), vc_base = reinterpret_cast<uint64_t>(vc);
     const uint64_t ks_base = reinterpret_cast<uint64_t>(ks), vs_base = reinterpret_cast<uint64_t>(vs);
     const uint32_t cstep = uint32_t(32 * cpitch), sstep = uint32_t(32 * spitch);
-    const uint32_t nc_u = uint32_t(nc), nb = uint32_t(nc + ns);
-    const uint32_t ldsk = lds0 + 1024u * uint32_t(wave_s);
+    const uint32_t nc_u = uint32_t(nc), ns_u = uint32_t(ns);
+    const uint32_t ldsk = lds0 + 1024u * LPB * uint32_t(wave_s);
     float nm = -mref;
-    if (q0 + 32 * wave_s < N) {
-      const uint32_t nc = nc_u;  // (the name the generated statement uses)
+    // a wave none of whose 32 queries is active (last tile of a suffix that is not a multiple of the tile) keeps its
+    // share of the loads and meets the others at the barriers, nothing else
+    const bool live = q0 + 32 * wave_s < N;
+    if constexpr (WM == 8) {
+      addr[12] = uint32_t(lr * cpitch + kcol(0));
+      addr[13] = uint32_t(lr * cpitch + vcol);
+      addr[14] = uint32_t(lr * spitch + kcol(0));
+      addr[15] = uint32_t(lr * spitch + vcol);
+      const uint32_t nc = nc_u, nb = nc_u + ns_u;  // (the names the generated statements use)
+      if (live) {
 #include "lsp_attn_pipe_loop.inc"
-    } else {
-      // none of this wave's 32 queries is active (last tile of a suffix that is not a multiple of 256
-      // rows): it keeps its share of the loads and meets the others at the barriers, nothing else
-      const uint32_t nc = nc_u;
+      } else {
 #include "lsp_attn_pipe_idle_loop.inc"
+      }
+    } else {
+      u32x4 soffs;
+#pragma unroll
+      for (int i = 0; i < 2; ++i) {
+        addr[12 + i] = uint32_t((lr + 4 * i) * cpitch + kcol(i));
+        addr[14 + i] = uint32_t((lr + 4 * i) * cpitch + vcol);
+        soffs[i] = ns > 0 ? uint32_t((lr + 4 * i) * spitch + kcol(i)) : addr[12 + i];
+        soffs[2 + i] = ns > 0 ? uint32_t((lr + 4 * i) * spitch + vcol) : addr[14 + i];
+      }
+      const uint32_t nc = nc_u, nsuf = ns_u;
+      if (live) {
+#include "lsp_attn_half_loop.inc"
+      } else {
+#include "lsp_attn_half_idle_loop.inc"
+      }
     }
     mref = -nm;
   }
@@ -1128,19 +1179,20 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   }
 }
 
+template <int WM>
 int32_t launch_pipe(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
-  const int64_t nwg = place_grid(a, layers, 256);
+  const int64_t nwg = place_grid(a, layers, 32 * WM, 32 * 8 / WM);
   if (nwg > kMaxGrid) {
     set_error("lsp_attn_step: launch of %lld workgroups is too large", (long long)nwg);
     return LSP_ERR_UNSUPPORTED;
   }
-  const size_t lds_ring = size_t(8) * 2 * 32 * 256;
-  const size_t lds_split = 8 * size_t(Geo<128>::WAVE_LDS) + 32 * size_t(Geo<128>::KPITCH);
+  const size_t lds_ring = size_t(WM == 8 ? 8 : 5) * 2 * 32 * 256;
+  const size_t lds_split = WM * size_t(Geo<128>::WAVE_LDS) + 32 * size_t(Geo<128>::KPITCH);
   const size_t lds = lds_ring > lds_split ? lds_ring : lds_split;
-  auto kern = attn_bf16_pipe_kernel;
+  auto kern = attn_bf16_pipe_kernel<WM>;
   static std::atomic<uint64_t> configured{0};
   if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured, "lsp_attn_step: hipFuncSetAttribute")) return rc;
-  kern<<<grid_of(nwg), 512, lds, st>>>(a, layers);
+  kern<<<grid_of(nwg), 64 * WM, lds, st>>>(a, layers);
   LSP_CHECK_LAUNCH("lsp_attn_step: bf16 pipelined launch");
   return LSP_OK;
 }
@@ -1150,9 +1202,32 @@ template <int D, int WM, int WK>
 int32_t launch(const AttnArgs &a, const AttnLayers &layers, hipStream_t st) {
   return a.cache_rows ? launch_g<D, WM, WK, true>(a, layers, st) : launch_g<D, WM, WK, false>(a, layers, st);
 }
-template <int D, int WM, int OCC, int PD>
-int32_t launch_tile(const AttnArgs &a, const AttnLayers &layers, hipStream_t st) {
-  return a.cache_rows ? launch_tile_g<D, WM, OCC, PD, true>(a, layers, st) : launch_tile_g<D, WM, OCC, PD, false>(a, layers, st);
+
+// Contiguous cache, head_dim 128.  The host knows the buffers (S rows, C cache rows), not the active lengths.
+// us per call, one layer of 32/32 or 28/4 heads unless said otherwise, B x S rows on P cached ones:
+//  * more than 128 tiles of 128 rows: the hand-scheduled loop with four waves, two workgroups to a compute unit.  Before
+//    it there were tiles of 256 rows, the shared-tile kernel for S <= 128 and the key split below 256 tiles of 128:
+//    3 x 256 on 800 33.8 -> 21.6, 28/4 heads 1 x 1024 on 1024 64 -> 35, 8 x 128 on 2000 97 -> 61; 32 layers:
+//    8 x 128 with 20 active on 4000 4333 -> 2994, 8 x 100 on 400 615 -> 524, 1 x 256 on 512 148 -> 139;
+//  * of these, eight waves with 256-row tiles, which fetch every K/V block for twice as many rows: long caches and at
+//    least four rounds of them (32 layers, 8 x 1024 on 4096: 19.9 ms, with four waves 20.6; 4 x 700 on 3000 5.4 and 5.6);
+//    one round that is nearly full (28/4 heads, 4 x 497 on 1021: 47.3 and 48.6); and at least two rounds of up to 256
+//    heads, where a compute unit is left with one workgroup when the sequences are down to their last rows (28/4
+//    heads, 8 x 1024 on 1000: 239 and 228 when full, 20.5 and 28.3 with 30 rows left).  Otherwise
+//    what the smaller tiles save in part-filled ones and in rounds weighs more (3 x 1024 on 4000, one round and a
+//    half: 254 and 231; 32 layers, 8 x 600 on 600, 28/4 heads: 3025 and 2903);
+//  * fewer: the key split, eight ways while its workgroups are at most one to a compute unit, four ways beyond, where
+//    two fit one (1 x 384 on 800: 18.9 four ways, 23.4 eight, 21.1 with 128-row tiles).
+int32_t dispatch_contiguous128(const AttnArgs &a, const AttnLayers &layers, hipStream_t st) {
+  const int64_t heads = int64_t(a.B) * a.Hq * (layers.n > 0 ? layers.n : 1);
+  auto tiles = [&](int rows) { return heads * ((a.S + rows - 1) / rows); };
+  if (tiles(128) > 128) {
+    const int64_t wide = a.S > 128 ? tiles(256) : 0;
+    if ((wide > 192 && wide <= 256) || (wide >= 512 && heads <= 256) || (wide >= 1024 && a.C > 2048))
+      return launch_pipe<8>(a, layers, st);
+    return launch_pipe<4>(a, layers, st);
+  }
+  return tiles(32) <= 256 ? launch_g<128, 1, 8, false>(a, layers, st) : launch_g<128, 1, 4, false>(a, layers, st);
 }
 
 template <int D>
@@ -1162,18 +1237,18 @@ int32_t dispatch(const AttnArgs &a, const AttnLayers &layers, hipStream_t st) {
   // Otherwise the wave-private kernel with the key range split between waves.
   // upper bound on (b,h,row) triples of the launch
   const int64_t rows = int64_t(a.B) * a.Hq * a.S * (layers.n > 0 ? layers.n : 1);
-  if (rows / 128 >= 256) {
-    if constexpr (D == 128) {
-      // suffix buffers of more than 128 rows: the hand-scheduled loop (its loads keep a row's byte offset inside
-      // a 32-row block in 32 bits, which the row-stride limit of the entry point guarantees); an indexed cache
-      // keeps the compiler-scheduled ring kernel
-      if (a.S > 128) return a.cache_rows ? launch_ring_g<8, 4, true>(a, layers, st) : launch_pipe(a, layers, st);
-    }
-    return launch_tile<D, 4, 2, 4>(a, layers, st);
+  if constexpr (D == 128) {
+    if (!a.cache_rows) return dispatch_contiguous128(a, layers, st);
+    if (rows / 128 >= 256) return a.S > 128 ? launch_ring_g<8, 4, true>(a, layers, st) : launch_tile_g<D, 4, 2, 4, true>(a, layers, st);
+    if (rows / 64 >= 512) return launch_g<D, 2, 2, true>(a, layers, st);
+    return rows / 32 >= 512 ? launch_g<D, 1, 4, true>(a, layers, st) : launch_g<D, 1, 8, true>(a, layers, st);
+  } else {
+    if (rows / 128 >= 256)
+      return a.cache_rows ? launch_tile_g<D, 4, 2, 4, true>(a, layers, st) : launch_tile_g<D, 4, 2, 4, false>(a, layers, st);
+    if (rows / 64 >= 512) return launch<D, 2, 2>(a, layers, st);
+    if (rows / 32 >= 512) return launch<D, 1, 4>(a, layers, st);
+    return launch<D, 1, 8>(a, layers, st);
   }
-  if (rows / 64 >= 512) return launch<D, 2, 2>(a, layers, st);
-  if (rows / 32 >= 512) return launch<D, 1, 4>(a, layers, st);
-  return launch<D, 1, 8>(a, layers, st);
 }
 
 }  // namespace

@@ -465,3 +465,30 @@ def test_more_layers_than_one_launch_holds(lsp, oracle, S, Hq):
         if l in (0, 31, 32, nl - 1):
             ref = oracle.attention(**host[l], prefix_len=pl, suffix_len=sl, rows=rows)
             assert (got[rows[:, 0].long(), rows[:, 1].long(), rows[:, 2].long()] - ref).abs().max().item() <= TOL["bf16"], l
+
+
+@pytest.mark.parametrize("layers,C,what", [(1, 800, "128-row tiles"), (32, 2100, "256-row tiles"), (32, 2048, "128-row tiles")])
+def test_tile_of_the_hand_scheduled_loop(lsp, oracle, layers, C, what):
+    """Both workgroup sizes of the hand-scheduled loop (cache capacity and number of tiles choose) on the same sequences:
+    last tiles with 32, 33 and every multiple of 32 rows, up to 20 blocks of cache before the suffix, ragged ends of both,
+    empty prefixes, single keys.  Every active row of every layer (all layers have the same operands)."""
+    lens = [256 + 32 * k - d for k in range(1, 9) for d in (0, 5)] + [1, 32, 33, 64, 65, 96, 97, 127, 128, 129, 160, 161, 255, 0, 290, 512]
+    B = len(lens)
+    w = W.scaled(W.C2, B=B, S=512, P=640, C=C, Hq=4 if layers == 1 else 2, Hkv=2 if layers == 1 else 1, D=128, seed=1234)
+    pl = torch.tensor([0 if b % 11 == 10 else 32 * (b % 21) + (0, 1, 31, 17)[b // 7 % 4] * (b % 3 > 0) for b in range(B)], dtype=torch.int32).clamp_(max=C)
+    sl = torch.tensor(lens, dtype=torch.int32)
+    kv = W.make_layer_kv(w, 0, prefix_len=pl)
+    g = {k: v.cuda() for k, v in kv.items()}
+    outs = [torch.full(g["q"].shape, 123.0, dtype=g["q"].dtype, device="cuda") for _ in range(layers)]
+    if layers == 1:
+        lsp.attn_step(g["q"], g["k_suf"], g["v_suf"], g["k_cache"], g["v_cache"], pl.cuda(), sl.cuda(), out=outs[0])
+    else:
+        table = lsp.AttnLayerTable(*[[g[k]] * layers for k in ("q", "k_suf", "v_suf", "k_cache", "v_cache")], outs)
+        lsp.attn_step_layers(table, pl.cuda(), sl.cuda())
+    torch.cuda.synchronize()
+    ref = oracle.attention(**kv, prefix_len=pl, suffix_len=sl)
+    act = ~torch.isnan(ref)
+    got = outs[0].float().cpu()
+    assert (got[act] - ref[act]).abs().max().item() <= TOL["bf16"]
+    assert torch.all(got[~act] == 123.0)
+    assert all(torch.equal(o, outs[0]) for o in outs[1:])
