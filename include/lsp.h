@@ -357,6 +357,15 @@ int32_t lsp_flip_update(const int32_t *top1_id, int32_t B, int32_t S, int32_t G,
                         int32_t *step_counts, void *stream);
 
 /* ------------------------------------------------------------------------- *
+ * Termination test of a decode loop (Algorithm 1 line 3), for the host to wait
+ * for.  Writes to host[0] the largest suffix_len[b] and to host[1] whether some
+ * sequence with suffix_len[b] > 0 has commit_len[b] = 0 (0 without commit_len,
+ * which may be NULL), then 1 to host[2].  host: int32[4] in host memory that the
+ * device can write (pinned); the caller clears host[2] before the call.
+ * ------------------------------------------------------------------------- */
+int32_t lsp_poll_lengths(const int32_t *suffix_len, const int32_t *commit_len, int32_t B, int32_t *host, void *stream);
+
+/* ------------------------------------------------------------------------- *
  * Measurement helper (used by the benchmark, not part of the scheduler step):
  * a bare streaming read of `bytes` bytes of device memory by `workgroups`
  * workgroups of 512 threads (16-byte non-temporal loads, each workgroup one

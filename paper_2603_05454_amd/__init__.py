@@ -22,6 +22,7 @@ import torch
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "liblsp.so")
 _lib = None
+_nat_addresses = None
 _nat = None     # the native marshalling module, bound to the loaded library (None: not loaded, or not built)
 
 LSP_F32, LSP_BF16 = 0, 1
@@ -54,17 +55,17 @@ class CommitDesc(ctypes.Structure):
 EXPORTS = ["lsp_version", "lsp_last_error", "lsp_attn_workspace_bytes", "lsp_attn_step", "lsp_attn_step_layers",
            "lsp_confidence_workspace_bytes", "lsp_confidence", "lsp_confidence_static_scratch_bytes",
            "lsp_confidence_static", "lsp_commit_workspace_bytes",
-           "lsp_commit", "lsp_flip_update", "lsp_select_scattered", "lsp_kv_gather_append",
+           "lsp_commit", "lsp_flip_update", "lsp_poll_lengths", "lsp_select_scattered", "lsp_kv_gather_append",
            "lsp_attn_step_gather", "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_bench_read", "lsp_bench_mfma"]
 
 # entry points that the native module calls, in the order of its table
 NATIVE_ENTRIES = ("lsp_attn_workspace_bytes", "lsp_attn_step", "lsp_attn_step_layers", "lsp_confidence_workspace_bytes", "lsp_confidence",
-                  "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_commit", "lsp_flip_update")
+                  "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_commit", "lsp_flip_update", "lsp_poll_lengths")
 
 
 def lib() -> ctypes.CDLL:
     """The loaded C-ABI library; raises LspError when it has not been built."""
-    global _lib, _nat
+    global _lib, _nat, _nat_addresses
     if _lib is None:
         if not os.path.exists(LIB_PATH):
             raise LspError(f"{LIB_PATH} is missing: run `python -m paper_2603_05454_amd.build` "
@@ -75,7 +76,7 @@ def lib() -> ctypes.CDLL:
         for n in ("lsp_attn_workspace_bytes", "lsp_confidence_workspace_bytes", "lsp_commit_workspace_bytes",
                   "lsp_lm_head_confidence_workspace_bytes", "lsp_confidence_static_scratch_bytes"):
             getattr(L, n).restype = ctypes.c_size_t
-        for n in ("lsp_attn_step", "lsp_attn_step_layers", "lsp_confidence", "lsp_confidence_static", "lsp_commit", "lsp_flip_update", "lsp_select_scattered",
+        for n in ("lsp_attn_step", "lsp_attn_step_layers", "lsp_confidence", "lsp_confidence_static", "lsp_commit", "lsp_flip_update", "lsp_poll_lengths", "lsp_select_scattered",
                   "lsp_kv_gather_append", "lsp_attn_step_gather", "lsp_lm_head_confidence", "lsp_bench_read", "lsp_bench_mfma"):
             getattr(L, n).restype = ctypes.c_int32
         try:
@@ -86,6 +87,7 @@ def lib() -> ctypes.CDLL:
         else:
             _binding.bind(*[ctypes.cast(getattr(L, n), ctypes.c_void_p).value for n in NATIVE_ENTRIES])
             _nat = _binding
+            _nat_addresses = _binding.addresses     # (not a call of a step: serves the tables, which are built beforehand)
         _lib = L
     return _lib
 
@@ -212,6 +214,13 @@ def attn_step(q, k_suf, v_suf, k_cache, v_cache, prefix_len, suffix_len, scale=0
     return out
 
 
+def _addresses(tensors):
+    """ctypes array of the addresses of device tensors that share shape, strides and element type; None where they do
+    not, or where there is no native module: the caller then looks at them one by one."""
+    b = _nat_addresses(tensors) if _nat_addresses is not None else None
+    return None if b is None else (ctypes.c_void_p * len(tensors)).from_buffer_copy(b)
+
+
 class AttnLayerTable:
     """Host arrays of per-layer device pointers for lsp_attn_step_layers, built once and
     reused (all layers must share shape, dtype and strides)."""
@@ -220,15 +229,17 @@ class AttnLayerTable:
         n = len(q)
         if not (len(k_suf) == len(v_suf) == len(k_cache) == len(v_cache) == len(out) == n > 0):
             raise LspError("AttnLayerTable: one tensor of each kind per layer, at least one layer")
-        for lst in (q, k_suf, v_suf, k_cache, v_cache, out):
-            for t in lst:
+        arrays = [_addresses(lst) for lst in (q, k_suf, v_suf, k_cache, v_cache, out)]
+        for lst, array in zip((q, k_suf, v_suf, k_cache, v_cache, out), arrays):
+            for t in lst if array is None else lst[:1]:
                 _dev(t)
                 if t.shape != lst[0].shape or t.stride() != lst[0].stride() or t.dtype != q[0].dtype:
                     raise LspError("AttnLayerTable: all layers must share shape, strides and element type")
         _need_kv(q[0], k_suf[0], v_suf[0], k_cache[0], v_cache[0], out[0])
         Arr = ctypes.c_void_p * n
         self.n = n
-        self.arrays = [Arr(*[t.data_ptr() for t in lst]) for lst in (q, k_suf, v_suf, k_cache, v_cache, out)]
+        self.arrays = [Arr(*[t.data_ptr() for t in lst]) if array is None else array
+                       for lst, array in zip((q, k_suf, v_suf, k_cache, v_cache, out), arrays)]
         self.keep = (q, k_suf, v_suf, k_cache, v_cache, out)
         B, S, Hq, D = q[0].shape
         self.desc = AttnDesc(dtype=_dtype(q[0]), B=B, S=S, Hq=Hq, Hkv=k_suf[0].shape[2], D=D, C=k_cache[0].shape[1])
@@ -370,8 +381,9 @@ class LayerTable:
         n = len(k_suf)
         if not (len(v_suf) == len(k_cache) == len(v_cache) == n > 0):
             raise LspError("LayerTable: one tensor of each kind per layer, at least one layer")
-        for lst in (k_suf, v_suf, k_cache, v_cache):
-            for t in lst:
+        arrays = [_addresses(lst) for lst in (k_suf, v_suf, k_cache, v_cache)]
+        for lst, array in zip((k_suf, v_suf, k_cache, v_cache), arrays):
+            for t in lst if array is None else lst[:1]:
                 _dev(t)
                 if t.dim() != 4 or t.dtype != k_suf[0].dtype or t.shape != lst[0].shape or t.stride() != lst[0].stride():
                     raise LspError("LayerTable: all layers must share shape, strides and element type")
@@ -382,7 +394,8 @@ class LayerTable:
             raise LspError("LayerTable: caches and suffix buffers disagree on batch, heads or head size")
         Arr = ctypes.c_void_p * n
         self.n = n
-        self.arrays = [Arr(*[t.data_ptr() for t in lst]) for lst in (k_suf, v_suf, k_cache, v_cache)]
+        self.arrays = [Arr(*[t.data_ptr() for t in lst]) if array is None else array
+                       for lst, array in zip((k_suf, v_suf, k_cache, v_cache), arrays)]
         self.keep = (k_suf, v_suf, k_cache, v_cache)
         self.kv_dtype = _dtype(k_suf[0])
         self.B = k_suf[0].shape[0]
@@ -473,6 +486,29 @@ def flip_update(top1_id, prefix_len, suffix_len, base_prefix_len, last_id, count
                                _ptr(base_prefix_len), _ptr(last_id), _ptr(counters), int(lo), int(hi),
                                _ptr(step_counts), _stream())
     _check(rc, "lsp_flip_update")
+
+
+class LengthPoll:
+    """lsp_poll_lengths with a pinned buffer of its own: the test between two steps of a decode loop."""
+
+    def __init__(self):
+        self.host = torch.zeros(4, dtype=torch.int32, pin_memory=True)
+
+    def __call__(self, suffix_len, commit_len=None):
+        """Waits for the work on the current stream up to here.  Returns (largest suffix_len, whether a sequence with
+        active positions has commit_len 0)."""
+        if _nat is not None:
+            got = _nat.poll_lengths(suffix_len, commit_len, self.host)
+            if isinstance(got, int):
+                _check(got, "lsp_poll_lengths")
+            if got is not None:
+                return got
+        _dev(suffix_len, commit_len)
+        _need("suffix_len", suffix_len, torch.int32, (suffix_len.shape[0],))
+        _need("commit_len", commit_len, torch.int32, (suffix_len.shape[0],), optional=True)
+        _check(lib().lsp_poll_lengths(_ptr(suffix_len), _ptr(commit_len), suffix_len.shape[0], _ptr(self.host), _stream()), "lsp_poll_lengths")
+        torch.cuda.current_stream().synchronize()
+        return tuple(self.host[:2].tolist())
 
 
 def select_scattered(margin, suffix_len, count, out=None):

@@ -15,6 +15,8 @@
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
+#include <chrono>
+
 #include "lsp.h"
 
 namespace {
@@ -30,8 +32,9 @@ struct Entry {
   decltype(&lsp_lm_head_confidence) lm_head_confidence;
   decltype(&lsp_commit) commit;
   decltype(&lsp_flip_update) flip_update;
+  decltype(&lsp_poll_lengths) poll_lengths;
 } g;
-constexpr int kEntries = 9;
+constexpr int kEntries = 10;
 
 const at::Tensor *tensor(PyObject *o) { return THPVariable_Check(o) ? &THPVariable_Unpack(o) : nullptr; }
 const at::Tensor *device_tensor(PyObject *o) {
@@ -146,6 +149,7 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
   g.lm_head_confidence = reinterpret_cast<decltype(g.lm_head_confidence)>(p[6]);
   g.commit = reinterpret_cast<decltype(g.commit)>(p[7]);
   g.flip_update = reinterpret_cast<decltype(g.flip_update)>(p[8]);
+  g.poll_lengths = reinterpret_cast<decltype(g.poll_lengths)>(p[9]);
   Py_RETURN_NONE;
 }
 
@@ -331,6 +335,58 @@ PyObject *flip_update(PyObject *, PyObject *const *a, Py_ssize_t n) {
                 data<int32_t>(steps), stream());
 }
 
+struct Unlocked {  // the interpreter lock is given back until the end of the scope, also by an exception
+  PyThreadState *state = PyEval_SaveThread();
+  ~Unlocked() { PyEval_RestoreThread(state); }
+};
+// (suffix_len, commit_len or None, host): launches lsp_poll_lengths and waits for what it writes; host is pinned memory of
+// the caller's own.  Answers (left, stalled), or the status of a failed launch.
+PyObject *poll_lengths(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  ARGUMENTS(3);
+  const at::Tensor *sl = device_tensor(a[0]), *host = tensor(a[2]);
+  ORDINARY(sl && sl->dim() == 1);
+  const int64_t B = sl->size(0);
+  sl = plain(a[0], at::kInt, B);
+  const at::Tensor *len = a[1] == Py_None ? nullptr : plain(a[1], at::kInt, B);
+  ORDINARY(sl && (len || a[1] == Py_None) && host && host->is_cpu() && host->scalar_type() == at::kInt && host->is_contiguous() &&
+           host->numel() >= 4);
+  auto *h = data<int32_t>(host);
+  const auto st = c10::hip::getCurrentHIPStream();
+  __atomic_store_n(h + 2, 0, __ATOMIC_RELAXED);
+  const int32_t rc = unlocked(g.poll_lengths, data<int32_t>(sl), data<int32_t>(len), int32_t(B), h, static_cast<void *>(st.stream()));
+  if (rc != LSP_OK) return PyLong_FromLong(rc);
+  {
+    // the flag comes some microseconds before the runtime would tell; a long step is left to the runtime
+    Unlocked without_lock;
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+    while (!__atomic_load_n(h + 2, __ATOMIC_ACQUIRE))
+      if (std::chrono::steady_clock::now() > until) {
+        st.synchronize();
+        break;
+      }
+  }
+  return Py_BuildValue("(ii)", int(h[0]), int(h[1]));
+}
+
+// Addresses of a list of device tensors that share shape, strides and element type, as bytes.
+PyObject *addresses(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  ARGUMENTS(1);
+  ORDINARY(PyList_Check(a[0]) && PyList_GET_SIZE(a[0]) > 0);
+  const Py_ssize_t count = PyList_GET_SIZE(a[0]);
+  Object bytes(PyBytes_FromStringAndSize(nullptr, count * Py_ssize_t(sizeof(void *))));
+  if (!bytes.o) return nullptr;
+  auto *out = reinterpret_cast<void **>(PyBytes_AS_STRING(bytes.o));
+  const at::Tensor *first = device_tensor(PyList_GET_ITEM(a[0], 0));
+  ORDINARY(first);
+  for (Py_ssize_t k = 0; k < count; ++k) {
+    const at::Tensor *t = device_tensor(PyList_GET_ITEM(a[0], k));
+    ORDINARY(t && t->scalar_type() == first->scalar_type() && t->sizes() == first->sizes() && t->strides() == first->strides());
+    out[k] = t->mutable_data_ptr();
+  }
+  Py_INCREF(bytes.o);
+  return bytes.o;
+}
+
 // No C++ exception may reach the interpreter: torch throws where a tensor has no strides or no
 // storage (sparse, batched by vmap), there is no device or a subclass written in Python raises (the error is then
 // set as well), and the general path meets the same and raises it.
@@ -349,7 +405,7 @@ PyMethodDef fast(const char *name) {
 }
 PyMethodDef methods[] = {fast<bind>("bind"), fast<attn_step>("attn_step"), fast<attn_step_layers>("attn_step_layers"),
                          fast<confidence>("confidence"), fast<lm_head_confidence>("lm_head_confidence"), fast<commit>("commit"),
-                         fast<flip_update>("flip_update"), {nullptr, nullptr, 0, nullptr}};
+                         fast<flip_update>("flip_update"), fast<poll_lengths>("poll_lengths"), fast<addresses>("addresses"), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

@@ -1,4 +1,5 @@
 // Library-wide pieces of liblsp: error text, version, flip bookkeeping.
+#include <limits.h>
 #include <stdarg.h>
 
 #include "lsp_common.h"
@@ -66,6 +67,33 @@ __global__ __launch_bounds__(256) void flip_kernel(
       atomicAdd(&counters[3], (unsigned long long)total[1]);
     }
   }
+}
+
+// What a decode loop asks between two steps, in one launch and written straight to host memory: the host reads the flag
+// without a copy or a synchronisation behind it.  (As seven small torch operations and a transfer it stood 60-80 us
+// between a step's append and the next step's attention; now about 20.)
+__global__ __launch_bounds__(256) void poll_kernel(const int32_t *__restrict__ suffix_len,
+                                                   const int32_t *__restrict__ commit_len, int B, int32_t *host) {
+  __shared__ int s_left, s_stalled;
+  if (threadIdx.x == 0) {
+    s_left = INT_MIN;
+    s_stalled = 0;
+  }
+  __syncthreads();
+  int left = INT_MIN;
+  bool stalled = false;
+  for (int b = threadIdx.x; b < B; b += blockDim.x) {
+    const int n = suffix_len[b];
+    left = max(left, n);
+    stalled |= commit_len != nullptr && n > 0 && commit_len[b] == 0;
+  }
+  atomicMax(&s_left, left);
+  if (stalled) s_stalled = 1;
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  __hip_atomic_store(host, s_left, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(host + 1, s_stalled, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+  __hip_atomic_store(host + 2, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // Measurement helper: a bare streaming read.  Workgroup w reads segment w of the buffer
@@ -142,6 +170,14 @@ extern "C" int32_t lsp_bench_read(const void *buffer, int64_t bytes, int32_t wor
   read_kernel<<<workgroups, 512, 0, static_cast<hipStream_t>(stream)>>>(static_cast<const u32x4 *>(buffer),
                                                                          bytes / (int64_t(workgroups) * 16), out);
   LSP_CHECK_LAUNCH("lsp_bench_read: launch");
+  return LSP_OK;
+}
+
+extern "C" int32_t lsp_poll_lengths(const int32_t *suffix_len, const int32_t *commit_len, int32_t B, int32_t *host, void *stream) {
+  using namespace lsp;
+  LSP_CHECK_ARG(suffix_len && host && B > 0, "lsp_poll_lengths: bad argument");
+  poll_kernel<<<1, 256, 0, static_cast<hipStream_t>(stream)>>>(suffix_len, commit_len, B, host);
+  LSP_CHECK_LAUNCH("lsp_poll_lengths: launch");
   return LSP_OK;
 }
 

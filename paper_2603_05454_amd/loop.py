@@ -10,7 +10,7 @@ from __future__ import annotations
 
 import torch
 
-from . import (AttnLayerTable, LayerTable, LspError, attn_step_layers, commit, confidence, confidence_workspace_bytes, flip_update,
+from . import (AttnLayerTable, LayerTable, LengthPoll, LspError, attn_step_layers, commit, confidence, confidence_workspace_bytes, flip_update,
                lm_head_confidence, lm_head_confidence_workspace_bytes)
 
 
@@ -78,14 +78,17 @@ def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
     attn_out = None
     events = []
     zbuf = step_graph = None
+    lengths = LengthPoll()
     ws = None   # workspace of the reduction or the fused output head: allocated by the first (eager) step, then reused
 
     def one_step(z):
         nonlocal out, conf, attn_out, ws
         if run_attention and kv_layers is not None:
             if attn_out is None:     # one output per layer (a denoiser consumes each of them), allocated once
+                q = kv_layers[0]["q"]
+                outs = torch.empty((len(kv_layers), *q.shape), dtype=q.dtype, device=q.device)
                 attn_out = AttnLayerTable(*[[L[k] for L in kv_layers] for k in ("q", "k_suf", "v_suf", "k_cache", "v_cache")],
-                                          [torch.empty_like(L["q"]) for L in kv_layers])
+                                          list(outs.unbind(0)))
             attn_step_layers(attn_out, prefix_len, suffix_len)     # every layer in one launch
         if lm_head_weight is None:
             if ws is None:
@@ -103,10 +106,8 @@ def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
 
     while True:
         if (steps - first) % poll == 0:
-            if out is None:
-                left, stalled = int(suffix_len.max().item()), 0
-            else:   # one transfer: positions left, and whether a sequence that has some committed nothing
-                left, stalled = torch.stack([suffix_len.max(), ((out["commit_len"] == 0) & (suffix_len > 0)).any().to(torch.int32)]).tolist()
+            # positions left, and whether a sequence that has some committed nothing
+            left, stalled = lengths(suffix_len, None if out is None else out["commit_len"])
             if left == 0:
                 break
             if stalled and min_commit >= 1:
@@ -140,8 +141,7 @@ def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
         if observer is not None:
             observer(steps, z, conf, out)
         steps += 1
-    c = counters.tolist()
-    committed = int((prefix_len - base).sum().item())
+    *c, committed = torch.cat([counters, (prefix_len - base).sum().view(1)]).tolist()
     res = dict(steps=steps, flips=c[0], flip_denominator=c[1], window_flips=c[2], window_denominator=c[3],
                committed=committed, state=dict(base=base, last_id=last_id, counters=counters, steps=steps))
     if flip_trace:

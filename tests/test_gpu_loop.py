@@ -268,3 +268,21 @@ def test_state_of_another_batch_is_refused(lsp):
                counters=torch.zeros(4, dtype=torch.int64, device="cuda"), steps=0)
     with pytest.raises(lsp.LspError, match="state does not belong"):
         gpu_loop(lambda s, p: None, bm.cuda(), w.V, 0.9, w.window, 1, 1, pl_g, sl_g, tok_g, gen_len=G, state=bad)
+
+
+@pytest.mark.parametrize("native", [True, False])
+@pytest.mark.parametrize("B", [1, 64, 256, 300])
+def test_length_poll(lsp, B, native, monkeypatch):
+    """What the loop asks between steps, by both ways of making the call, on a buffer used again and again."""
+    lsp.lib()
+    if not native:
+        monkeypatch.setattr(lsp, "_nat", None)
+    g = torch.Generator().manual_seed(B)
+    poll = lsp.LengthPoll()
+    for n, c in ((torch.zeros(B), torch.zeros(B)), (torch.randint(0, 900, (B,), generator=g), torch.ones(B)),
+                 (torch.randint(0, 900, (B,), generator=g), torch.randint(0, 2, (B,), generator=g)), (torch.arange(B), 1 - torch.arange(B).clamp(max=1))):
+        n, c = n.to(torch.int32), c.to(torch.int32)
+        assert poll(n.cuda()) == (int(n.max()), 0)
+        assert tuple(poll(n.cuda(), c.cuda())) == (int(n.max()), int(((n > 0) & (c == 0)).any()))
+    with pytest.raises(lsp.LspError):
+        poll(n.cuda().long())
