@@ -189,13 +189,12 @@ struct Tiles {
 //    not 129-256 (256 rows: 284 against 254 us) or more (640 rows would need five);
 //  - where a launch has fewer tiles than compute units (400 rows x 5000 entries: 41 us in 140 tiles of
 //    64, 55 in 80 of 128, 82 in 40 of 256).
-// Both kernels of a launch take the same decision; tiles of 256 are the tall kernel's.
-__device__ __forceinline__ void cut_rows(const LmArgs &a, Tiles &t, bool tall) {
+__device__ __forceinline__ void cut_rows(const LmArgs &a, Tiles &t) {
   const int R = t.map.R;
   t.tr = int64_t(a.VT) * ((R + 63) / 64) <= kComputeUnits                                               ? 64
          : int64_t(a.VT) * ((R + 127) / 128) <= kComputeUnits || R <= 128 || (R > 256 && R <= 384) ? 128
                                                                                                : 256;
-  t.RT = tall == (t.tr == 256) ? (R + t.tr - 1) / t.tr : 0;
+  t.RT = (R + t.tr - 1) / t.tr;
   const int xcd = blockIdx.x & 7, slots = gridDim.x >> 3;
   t.nv = a.VT / 8 + (xcd < a.VT % 8);
   t.first = xcd * (a.VT / 8) + min(xcd, a.VT % 8);
@@ -494,26 +493,35 @@ __device__ __forceinline__ void run_tiles(const LmArgs &a, unsigned char *smem, 
 // 70 and 70, 450 MB (110 000 x 2048) 93 and 102.
 constexpr int64_t kStreamWeights = int64_t(320) << 19;
 
-// Persistent kernels: one workgroup per compute unit walks its tiles.
+// Persistent kernel: one workgroup per compute unit walks its tiles.  How many rows are active, and with that the height of
+// the tiles, is only known here (two kernels, one of which left at once, took 2 us more).  TALL: there may be tiles of 256
+// rows; buffers of up to 128 never have any, and without their loop the kernel needs no scratch and starts sooner.
 template <bool TALL>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(2, 2))) void lm_head_kernel(LmArgs a) {
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
   __shared__ int32_t s_pre[kThreads], s_wave[kThreads / 64];
-  constexpr int CAP = TALL ? 256 : 128;
-  __shared__ int32_t s_row[2 * CAP];
-  __shared__ int64_t s_off[2 * CAP];
+  __shared__ int32_t s_row[2 * 128];
+  __shared__ int64_t s_off[2 * 128];
   Tiles tb;
-  tb.row = s_row; tb.off = s_off; tb.cap = CAP;
   tb.map = map_rows(a, s_pre, s_wave);
-  cut_rows(a, tb, TALL);
+  cut_rows(a, tb);
   Cursor cur = {int(blockIdx.x >> 3), 0, 0, 0};
   if (cur.m >= tb.total) return;
   tile_at(tb, cur.m, cur.vt, cur.rt);
-  fill_rows(a, tb, 0, cur.rt);
   auto run = [&](auto stream) {
     constexpr bool STREAM = decltype(stream)::value;
-    if constexpr (TALL) run_tiles<256, STREAM>(a, smem, tb, cur);
-    else if (min(tb.tr, tb.map.R) <= 64) run_tiles<64, STREAM>(a, smem, tb, cur);
+    tb.row = s_row; tb.off = s_off; tb.cap = 128;
+    if constexpr (TALL)
+      if (tb.tr == 256) {  // (the tables of taller tiles lie behind their two stages, where the lower ones have a third)
+        tb.off = reinterpret_cast<int64_t *>(smem + lds_bytes<256>());
+        tb.row = reinterpret_cast<int32_t *>(tb.off + 2 * 256);
+        tb.cap = 256;
+        fill_rows(a, tb, 0, cur.rt);
+        run_tiles<256, STREAM>(a, smem, tb, cur);
+        return;
+      }
+    fill_rows(a, tb, 0, cur.rt);
+    if (min(tb.tr, tb.map.R) <= 64) run_tiles<64, STREAM>(a, smem, tb, cur);
     else run_tiles<128, STREAM>(a, smem, tb, cur);
   };
   if (tb.RT == 1 && int64_t(a.V) * a.wrs >= kStreamWeights) run(std::true_type{});
@@ -533,7 +541,16 @@ __global__ __launch_bounds__(256) void lm_head_finish_kernel(const Partial *__re
     if (suffix_len != nullptr && (r % S) >= suffix_len[r / S]) continue;
     Partial p;
     p.m1 = -INFINITY; p.m2 = -INFINITY; p.s = 0.f; p.idx = 0x7fffffff;
-    for (int t = lane; t < VT; t += 64) p = fold(p, partials[int64_t(r) * VT + t]);
+    // eight loads in flight (one after the other they were most of this kernel)
+    constexpr int U = 8;
+    for (int t = lane; t < VT; t += 64 * U) {
+      Partial q[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) q[u] = partials[int64_t(r) * VT + min(t + 64 * u, VT - 1)];
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (t + 64 * u < VT) p = fold(p, q[u]);
+    }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
       Partial o;
@@ -549,25 +566,18 @@ __global__ __launch_bounds__(256) void lm_head_finish_kernel(const Partial *__re
 }
 
 template <bool TALL>
-int32_t launch_lm_head_t(const LmArgs &a, int64_t row_tiles, size_t lds, hipStream_t st) {
+int32_t launch_lm_head(const LmArgs &a, hipStream_t st) {
   // at most one workgroup per compute unit, a multiple of 8 (the same number on every XCD)
-  const int64_t per_xcd = (int64_t(a.VT) + 7) / 8 * row_tiles;
+  const int64_t rows = int64_t(a.B) * a.S;
+  const int64_t per_xcd = (int64_t(a.VT) + 7) / 8 * ((rows + 63) / 64);
   const unsigned nwg = 8 * unsigned(per_xcd < kComputeUnits / 8 ? per_xcd : kComputeUnits / 8);
-  auto kern = lm_head_kernel<TALL>;
+  constexpr size_t lds = lds_bytes<128>();
+  static_assert(lds_bytes<256>() + 2 * 256 * 12 <= lds && lds_bytes<64>() <= lds, "");
   static std::atomic<uint64_t> configured{0};  // per instantiation, one bit per device
-  if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured, "lsp_lm_head_confidence: hipFuncSetAttribute")) return rc;
-  kern<<<dim3(nwg), kThreads, lds, st>>>(a);
+  if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(lm_head_kernel<TALL>), lds, configured, "lsp_lm_head_confidence: hipFuncSetAttribute")) return rc;
+  lm_head_kernel<TALL><<<dim3(nwg), kThreads, lds, st>>>(a);
   LSP_CHECK_LAUNCH("lsp_lm_head_confidence: launch");
   return LSP_OK;
-}
-
-int32_t launch_lm_head(const LmArgs &a, hipStream_t st) {
-  // How many rows are active is only known on the device, so both kernels are launched
-  // (each leaves at once where nothing is its own) unless the buffers decide.
-  const int64_t rows = int64_t(a.B) * a.S;
-  if (rows > 128)
-    if (const int32_t rc = launch_lm_head_t<true>(a, (rows + 255) / 256, lds_bytes<256>(), st)) return rc;
-  return launch_lm_head_t<false>(a, (rows + 63) / 64, lds_bytes<128>(), st);
 }
 
 }  // namespace
@@ -621,7 +631,7 @@ extern "C" int32_t lsp_lm_head_confidence(int32_t dtype, const void *hidden, con
     return LSP_ERR_UNSUPPORTED;
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  const int32_t rc = launch_lm_head(a, st);
+  const int32_t rc = rows > 128 ? launch_lm_head<true>(a, st) : launch_lm_head<false>(a, st);
   if (rc != LSP_OK) return rc;
   const int64_t finish = (rows + 3) / 4;
   lm_head_finish_kernel<<<dim3(unsigned(finish < kFinishGrid ? finish : kFinishGrid)), 256, 0, st>>>(
