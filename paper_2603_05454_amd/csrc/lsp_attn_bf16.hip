@@ -48,6 +48,8 @@
 //    short sequences are handled in C++ around it.  A wave with no active
 //    query (last tile of a ragged suffix) runs lsp_attn_pipe_idle_loop.inc:
 //    its loads, waits and barriers only.
+#include <type_traits>
+
 #include "lsp_attn.h"
 
 namespace lsp {
@@ -208,6 +210,11 @@ constexpr int kShortSuffix = 64;  // sequences with at most this many active row
 // without a query, a tile with two active waves is faster than two key-split workgroups - 38 against
 // 50 us per C5 layer - while a tile with one active wave is slower than one key-split workgroup)
 constexpr int kShortSuffixPipe = 32;
+// K/V that no cache can hold (a quarter more than the last-level cache) and that this one workgroup reads, once, are loaded
+// with the non-temporal hint: 32 layers of 32/32 heads, 16 x 21 rows of 1536 keys 2242 -> 2130 us (6.1 TB/s), 8 x 20 of 1128
+// 832 -> 741, 2 x 16 of 4016 717 -> 664.  With a query group's heads on one KV head the hint costs a factor (284 -> 523), in
+// the generated loops it gains and loses as often (32 layers, 128 rows on 512 98 -> 93, 8 x 100 on 400 509 -> 541).
+constexpr int64_t kStreamBytes = int64_t(320) << 20;
 constexpr int kSpreadBlocks = 512;  // blocks of 32 rows in the whole launch
 
 // Final step shared by both kernels: the WK partial results of every query
@@ -279,8 +286,9 @@ __device__ __forceinline__ void merge_store(const AttnArgs &a, const f32x16 (&oa
 // One wave-wide load from global memory straight into LDS: lane l fetches 16
 // bytes at its own address g and they land at lds_base + 16 l (lds_base is
 // wave-uniform; the counter to wait on is vmcnt, and loads complete in order).
+template <bool STREAM = false>  // true: with the non-temporal hint
 __device__ __forceinline__ void load_to_lds(const char *g, unsigned char *lds_base) {
-  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void *)lds_base, 16, 0, 0);
+  __builtin_amdgcn_global_load_lds(g, (__attribute__((address_space(3))) void *)lds_base, 16, 0, STREAM ? 2 : 0);
 }
 constexpr int kWaitVm0 = 0x0F70;      // s_waitcnt vmcnt(0), other counters untouched
 constexpr int kWaitVm8 = 0x0F78;      // s_waitcnt vmcnt(8)
@@ -293,9 +301,10 @@ constexpr int kWaitLgkm0 = 0xC07F;    // s_waitcnt lgkmcnt(0), other counters un
 // of the second part sets the reference anew (as far down as matters: what lies kPartOctaves below the first part's
 // adds nothing to a bf16 result) and the sums are brought to it.  Four waves with two parts so round every
 // probability as eight waves do, whatever workgroup a launch uses (head_dim 128 only).
+// once: nobody else reads these K/V rows (see kStreamBytes; head_dim 128 only).
 template <int D, int WM, int WK, bool GATHER, int PARTS = 1>
 __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, int h, int q0, int N, int P,
-                                               unsigned char *smem) {
+                                               unsigned char *smem, bool once = false) {
   using G = Geo<D>;
   constexpr int KK = D / 16;  // d-steps of the first product
   constexpr int DB = D / 32;  // 32-row blocks of O^T
@@ -396,18 +405,19 @@ __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, 
     kofs[q] = uint32_t(lr * spitch + kcol[q]);
   }
   const uint32_t vofc = uint32_t(lr * cpitch + vswz), vofs = uint32_t(lr * spitch + vswz);
-  auto issue_k = [=, &roff](int jb) __attribute__((always_inline)) {
+  auto issue_k_as = [=, &roff](int jb, auto hint) __attribute__((always_inline)) {
+    constexpr bool NT = decltype(hint)::value;
     const int t0 = 32 * jb;
     if (!GATHER && t0 + 32 <= P) {
       const char *base = kcb + int64_t(t0) * cpitch;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) load_to_lds(base + int64_t(4 * i) * cpitch + kofc[i & 3], wl + 1024 * i);
+      for (int i = 0; i < 8; ++i) load_to_lds<NT>(base + int64_t(4 * i) * cpitch + kofc[i & 3], wl + 1024 * i);
       return;
     }
     if (t0 >= P && t0 + 32 <= T) {
       const char *base = ksb + int64_t(t0 - P) * spitch;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) load_to_lds(base + int64_t(4 * i) * spitch + kofs[i & 3], wl + 1024 * i);
+      for (int i = 0; i < 8; ++i) load_to_lds<NT>(base + int64_t(4 * i) * spitch + kofs[i & 3], wl + 1024 * i);
       return;
     }
 #pragma unroll
@@ -416,28 +426,35 @@ __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, 
       int crow = t;
       if (GATHER && t < P) crow = min(max(crows[t], 0), Cmax);  // a bad index must not leave the buffer
       roff[i] = t < P ? int64_t(crow) * cpitch : int64_t(t - P) * spitch;
-      load_to_lds((t < P ? kcb : ksb) + roff[i] + kcol[i & 3], wl + 1024 * i);
+      load_to_lds<NT>((t < P ? kcb : ksb) + roff[i] + kcol[i & 3], wl + 1024 * i);
     }
   };
-  auto issue_v = [=, &roff](int jb) __attribute__((always_inline)) {
+  auto issue_v_as = [=, &roff](int jb, auto hint) __attribute__((always_inline)) {
+    constexpr bool NT = decltype(hint)::value;
     const int t0 = 32 * jb;
     if (!GATHER && t0 + 32 <= P) {
       const char *base = vcb + int64_t(t0) * cpitch;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) load_to_lds(base + int64_t(4 * i) * cpitch + vofc, wl + KB + 1024 * i);
+      for (int i = 0; i < 8; ++i) load_to_lds<NT>(base + int64_t(4 * i) * cpitch + vofc, wl + KB + 1024 * i);
       return;
     }
     if (t0 >= P && t0 + 32 <= T) {
       const char *base = vsb + int64_t(t0 - P) * spitch;
 #pragma unroll
-      for (int i = 0; i < 8; ++i) load_to_lds(base + int64_t(4 * i) * spitch + vofs, wl + KB + 1024 * i);
+      for (int i = 0; i < 8; ++i) load_to_lds<NT>(base + int64_t(4 * i) * spitch + vofs, wl + KB + 1024 * i);
       return;
     }
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       const int t = min(32 * jb + 4 * i + lr, T - 1);
-      load_to_lds((t < P ? vcb : vsb) + roff[i] + vswz, wl + KB + 1024 * i);
+      load_to_lds<NT>((t < P ? vcb : vsb) + roff[i] + vswz, wl + KB + 1024 * i);
     }
+  };
+  auto issue_k = [&](int jb) __attribute__((always_inline)) {
+    if (once) issue_k_as(jb, std::true_type{}); else issue_k_as(jb, std::false_type{});
+  };
+  auto issue_v = [&](int jb) __attribute__((always_inline)) {
+    if (once) issue_v_as(jb, std::true_type{}); else issue_v_as(jb, std::false_type{});
   };
   const int wk_s = __builtin_amdgcn_readfirstlane(wk);  // the same value, known to be wave-uniform
   if constexpr (D == 128) {
@@ -1033,7 +1050,7 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int qs = spread ? q0 / WM : q0;
   if (qs >= N) return;
   if (spread || N - q0 <= kShortSuffixPipe) {
-    key_split_body<D, 1, WM, false, 8 / WM>(a, b, g, h, qs, N, P, smem);
+    key_split_body<D, 1, WM, false, 8 / WM>(a, b, g, h, qs, N, P, smem, a.rep == 1 && N <= 32 && int64_t(P + N) * a.Hkv * (4 * D) * a.B * a.layers >= kStreamBytes);
     return;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
