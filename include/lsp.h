@@ -365,6 +365,21 @@ int32_t lsp_flip_update(const int32_t *top1_id, int32_t B, int32_t S, int32_t G,
  * ------------------------------------------------------------------------- */
 int32_t lsp_poll_lengths(const int32_t *suffix_len, const int32_t *commit_len, int32_t B, int32_t *host, void *stream);
 
+/*
+ * lsp_flip_update and lsp_commit of one step in the launches of lsp_commit: a sequence's workgroup counts its flips
+ * where it searches its boundary.  Arguments as in these two.
+ */
+int32_t lsp_commit_step(const lsp_commit_desc *desc, const float *margin, const int32_t *top1_id,
+                        const uint32_t *delimiter_bitmap,
+                        const void *const *k_suf_layers, const void *const *v_suf_layers,
+                        void *const *k_cache_layers, void *const *v_cache_layers,
+                        int32_t *tokens, int32_t *prefix_len, int32_t *suffix_len,
+                        uint8_t *stable_mask, int32_t *raw_boundary,
+                        int32_t *snapped_boundary, int32_t *commit_len,
+                        int32_t *status_flags, float *tau_used, int32_t G, const int32_t *base_prefix_len,
+                        int32_t *last_id, int64_t *counters, int32_t window_lo, int32_t window_hi,
+                        int32_t *step_counts, void *stream);
+
 /* ------------------------------------------------------------------------- *
  * Measurement helper (used by the benchmark, not part of the scheduler step):
  * a bare streaming read of `bytes` bytes of device memory by `workgroups`

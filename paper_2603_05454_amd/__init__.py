@@ -55,12 +55,12 @@ class CommitDesc(ctypes.Structure):
 EXPORTS = ["lsp_version", "lsp_last_error", "lsp_attn_workspace_bytes", "lsp_attn_step", "lsp_attn_step_layers",
            "lsp_confidence_workspace_bytes", "lsp_confidence", "lsp_confidence_static_scratch_bytes",
            "lsp_confidence_static", "lsp_commit_workspace_bytes",
-           "lsp_commit", "lsp_flip_update", "lsp_poll_lengths", "lsp_select_scattered", "lsp_kv_gather_append",
+           "lsp_commit", "lsp_commit_step", "lsp_flip_update", "lsp_poll_lengths", "lsp_select_scattered", "lsp_kv_gather_append",
            "lsp_attn_step_gather", "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_bench_read", "lsp_bench_mfma"]
 
 # entry points that the native module calls, in the order of its table
 NATIVE_ENTRIES = ("lsp_attn_workspace_bytes", "lsp_attn_step", "lsp_attn_step_layers", "lsp_confidence_workspace_bytes", "lsp_confidence",
-                  "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_commit", "lsp_flip_update", "lsp_poll_lengths")
+                  "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_commit", "lsp_flip_update", "lsp_poll_lengths", "lsp_commit_step")
 
 
 def lib() -> ctypes.CDLL:
@@ -76,7 +76,7 @@ def lib() -> ctypes.CDLL:
         for n in ("lsp_attn_workspace_bytes", "lsp_confidence_workspace_bytes", "lsp_commit_workspace_bytes",
                   "lsp_lm_head_confidence_workspace_bytes", "lsp_confidence_static_scratch_bytes"):
             getattr(L, n).restype = ctypes.c_size_t
-        for n in ("lsp_attn_step", "lsp_attn_step_layers", "lsp_confidence", "lsp_confidence_static", "lsp_commit", "lsp_flip_update", "lsp_poll_lengths", "lsp_select_scattered",
+        for n in ("lsp_attn_step", "lsp_attn_step_layers", "lsp_confidence", "lsp_confidence_static", "lsp_commit", "lsp_commit_step", "lsp_flip_update", "lsp_poll_lengths", "lsp_select_scattered",
                   "lsp_kv_gather_append", "lsp_attn_step_gather", "lsp_lm_head_confidence", "lsp_bench_read", "lsp_bench_mfma"):
             getattr(L, n).restype = ctypes.c_int32
         try:
@@ -405,6 +405,14 @@ class LayerTable:
         self.cache_bs = k_cache[0].stride(0)
 
 
+def _commit_out(B, S, dev):
+    out = {"stable_mask": torch.empty((B, S), dtype=torch.uint8, device=dev)}
+    for k in ("raw_boundary", "snapped_boundary", "commit_len", "status_flags"):
+        out[k] = torch.empty(B, dtype=torch.int32, device=dev)
+    out["tau_used"] = torch.empty(B, dtype=torch.float32, device=dev)
+    return out
+
+
 def commit(margin, top1_id, bitmap, V, tau, window, min_commit, snap_enabled,
            prefix_len, suffix_len, tokens=None, layers: LayerTable | None = None, C=None, out=None,
            adaptive=False, alpha=0.25, beta=0.5, max_commit=0):
@@ -430,10 +438,7 @@ def commit(margin, top1_id, bitmap, V, tau, window, min_commit, snap_enabled,
     if tokens is not None:
         _need("tokens", tokens, torch.int32, (B, tokens.shape[1]) if tokens.dim() == 2 else (B, -1))
     if out is None:
-        out = {"stable_mask": torch.empty((B, S), dtype=torch.uint8, device=dev)}
-        for k in ("raw_boundary", "snapped_boundary", "commit_len", "status_flags"):
-            out[k] = torch.empty(B, dtype=torch.int32, device=dev)
-        out["tau_used"] = torch.empty(B, dtype=torch.float32, device=dev)
+        out = _commit_out(B, S, dev)
     _dev(*out.values())
     _need("out['stable_mask']", out["stable_mask"], torch.uint8, (B, S))
     for k in ("raw_boundary", "snapped_boundary", "commit_len", "status_flags"):
@@ -486,6 +491,22 @@ def flip_update(top1_id, prefix_len, suffix_len, base_prefix_len, last_id, count
                                _ptr(base_prefix_len), _ptr(last_id), _ptr(counters), int(lo), int(hi),
                                _ptr(step_counts), _stream())
     _check(rc, "lsp_flip_update")
+
+
+def commit_step(margin, top1_id, bitmap, V, tau, window, min_commit, snap_enabled, prefix_len, suffix_len, base_prefix_len, last_id,
+                counters, flip_window, step_counts=None, tokens=None, layers=None, C=None, out=None, adaptive=False, alpha=0.25, beta=0.5,
+                max_commit=0):
+    """lsp_commit_step: flip_update and then commit, in the commit's launches."""
+    if _nat is not None and out is not None and (layers is not None or C is not None):
+        rc = _nat.commit_step(margin, top1_id, bitmap, prefix_len, suffix_len, tokens, layers, out,
+                              (V, tau, window, min_commit, snap_enabled, adaptive, alpha, beta, max_commit, 0 if C is None else C),
+                              (base_prefix_len, last_id, counters, *flip_window, step_counts))
+        if rc is not None:
+            _check(rc, "lsp_commit_step")
+            return out
+    flip_update(top1_id, prefix_len, suffix_len, base_prefix_len, last_id, counters, window=flip_window, step_counts=step_counts)
+    return commit(margin, top1_id, bitmap, V, tau, window, min_commit, snap_enabled, prefix_len, suffix_len, tokens=tokens, layers=layers,
+                  C=C, out=out, adaptive=adaptive, alpha=alpha, beta=beta, max_commit=max_commit)
 
 
 class LengthPoll:

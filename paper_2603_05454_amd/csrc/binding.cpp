@@ -33,8 +33,9 @@ struct Entry {
   decltype(&lsp_commit) commit;
   decltype(&lsp_flip_update) flip_update;
   decltype(&lsp_poll_lengths) poll_lengths;
+  decltype(&lsp_commit_step) commit_step;
 } g;
-constexpr int kEntries = 10;
+constexpr int kEntries = 11;
 
 const at::Tensor *tensor(PyObject *o) { return THPVariable_Check(o) ? &THPVariable_Unpack(o) : nullptr; }
 const at::Tensor *device_tensor(PyObject *o) {
@@ -150,6 +151,7 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
   g.commit = reinterpret_cast<decltype(g.commit)>(p[7]);
   g.flip_update = reinterpret_cast<decltype(g.flip_update)>(p[8]);
   g.poll_lengths = reinterpret_cast<decltype(g.poll_lengths)>(p[9]);
+  g.commit_step = reinterpret_cast<decltype(g.commit_step)>(p[10]);
   Py_RETURN_NONE;
 }
 
@@ -249,6 +251,12 @@ PyObject *lm_head_confidence(PyObject *, PyObject *const *a, Py_ssize_t n) {
                 data<void>(ws), size_t(bytes_of(ws)), stream());
 }
 
+// int32[4] of host memory, as lsp_poll_lengths wants it
+int32_t *host_words(PyObject *o) {
+  const at::Tensor *t = tensor(o);
+  return t && t->is_cpu() && t->scalar_type() == at::kInt && t->is_contiguous() && t->numel() >= 4 ? data<int32_t>(t) : nullptr;
+}
+
 PyObject *k_mask, *k_raw, *k_snapped, *k_len, *k_flags, *k_tau;  // keys of commit's result
 // attributes of a layer table: the tables, then numbers
 PyObject *k_arrays, *k_numbers[9];
@@ -256,8 +264,11 @@ constexpr const char *kNumbers[9] = {"kv_dtype", "B", "S", "Hkv", "D", "C", "n",
 
 // (margin, top1_id, bitmap, prefix_len, suffix_len, tokens or None, layer table or None, out,
 //  (V, tau, window, min_commit, snap_enabled, adaptive, alpha, beta, max_commit, C))
+// STEP: and (base_prefix_len, last_id, counters, window_lo, window_hi, step_counts or None)
+template <bool STEP>
 PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
-  ARGUMENTS(9);
+  constexpr int kArguments = STEP ? 10 : 9;
+  ARGUMENTS(kArguments);
   ORDINARY(PyDict_Check(a[7]) && PyDict_GET_SIZE(a[7]) == 6 && PyTuple_Check(a[8]) && PyTuple_GET_SIZE(a[8]) == 10);
   const at::Tensor *margin = device_tensor(a[0]);
   ORDINARY(margin && margin->dim() == 2);
@@ -308,6 +319,27 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
                    *flags = per_sequence(k_flags, at::kInt), *tau = per_sequence(k_tau, at::kFloat);
   if (PyErr_Occurred()) return nullptr;
   ORDINARY(mask && raw && snapped && len && flags && tau);
+  if constexpr (STEP) {
+    ORDINARY(PyTuple_Check(a[9]) && PyTuple_GET_SIZE(a[9]) == 6);
+    PyObject *const *x = &PyTuple_GET_ITEM(a[9], 0);
+    const at::Tensor *last = device_tensor(x[1]);
+    ORDINARY(last && last->dim() == 2);
+    const int64_t G = last->size(1);
+    last = plain(x[1], at::kInt, B, G);
+    const at::Tensor *base = plain(x[0], at::kInt, B), *counters = plain(x[2], at::kLong, 4),
+                     *steps = x[5] == Py_None ? nullptr : plain(x[5], at::kInt, B, 2);
+    ORDINARY(base && last && counters && (steps || x[5] == Py_None));
+    const long lo = PyLong_AsLong(x[3]), hi = PyLong_AsLong(x[4]);
+    if (PyErr_Occurred()) {
+      PyErr_Clear();
+      Py_RETURN_NONE;
+    }
+    return status(g.commit_step, &d, data<float>(margin), data<int32_t>(id), data<uint32_t>(bm), static_cast<const void *const *>(tab[0].view.buf),
+                  static_cast<const void *const *>(tab[1].view.buf), static_cast<void *const *>(tab[2].view.buf),
+                  static_cast<void *const *>(tab[3].view.buf), data<int32_t>(tokens), data<int32_t>(pl), data<int32_t>(sl), data<uint8_t>(mask),
+                  data<int32_t>(raw), data<int32_t>(snapped), data<int32_t>(len), data<int32_t>(flags), data<float>(tau), int32_t(G),
+                  data<int32_t>(base), data<int32_t>(last), data<int64_t>(counters), int32_t(lo), int32_t(hi), data<int32_t>(steps), stream());
+  }
   return status(g.commit, &d, data<float>(margin), data<int32_t>(id), data<uint32_t>(bm), static_cast<const void *const *>(tab[0].view.buf),
                 static_cast<const void *const *>(tab[1].view.buf), static_cast<void *const *>(tab[2].view.buf),
                 static_cast<void *const *>(tab[3].view.buf), data<int32_t>(tokens), data<int32_t>(pl), data<int32_t>(sl), data<uint8_t>(mask), data<int32_t>(raw), data<int32_t>(snapped), data<int32_t>(len),
@@ -339,21 +371,19 @@ struct Unlocked {  // the interpreter lock is given back until the end of the sc
   PyThreadState *state = PyEval_SaveThread();
   ~Unlocked() { PyEval_RestoreThread(state); }
 };
-// (suffix_len, commit_len or None, host): launches lsp_poll_lengths and waits for what it writes; host is pinned memory of
-// the caller's own.  Answers (left, stalled), or the status of a failed launch.
+// (suffix_len, commit_len or None, host): launches lsp_poll_lengths and waits; host is pinned memory of the caller's own.
+// Answers (left, stalled), or the status of a failed launch.
 PyObject *poll_lengths(PyObject *, PyObject *const *a, Py_ssize_t n) {
   ARGUMENTS(3);
-  const at::Tensor *sl = device_tensor(a[0]), *host = tensor(a[2]);
+  const at::Tensor *sl = device_tensor(a[0]);
   ORDINARY(sl && sl->dim() == 1);
   const int64_t B = sl->size(0);
   sl = plain(a[0], at::kInt, B);
   const at::Tensor *len = a[1] == Py_None ? nullptr : plain(a[1], at::kInt, B);
-  ORDINARY(sl && (len || a[1] == Py_None) && host && host->is_cpu() && host->scalar_type() == at::kInt && host->is_contiguous() &&
-           host->numel() >= 4);
-  auto *h = data<int32_t>(host);
-  const auto st = c10::hip::getCurrentHIPStream();
+  int32_t *h = host_words(a[2]);
+  ORDINARY(sl && (len || a[1] == Py_None) && h);
   __atomic_store_n(h + 2, 0, __ATOMIC_RELAXED);
-  const int32_t rc = unlocked(g.poll_lengths, data<int32_t>(sl), data<int32_t>(len), int32_t(B), h, static_cast<void *>(st.stream()));
+  const int32_t rc = unlocked(g.poll_lengths, data<int32_t>(sl), data<int32_t>(len), int32_t(B), h, stream());
   if (rc != LSP_OK) return PyLong_FromLong(rc);
   {
     // the flag comes some microseconds before the runtime would tell; a long step is left to the runtime
@@ -361,13 +391,12 @@ PyObject *poll_lengths(PyObject *, PyObject *const *a, Py_ssize_t n) {
     const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
     while (!__atomic_load_n(h + 2, __ATOMIC_ACQUIRE))
       if (std::chrono::steady_clock::now() > until) {
-        st.synchronize();
+        c10::hip::getCurrentHIPStream().synchronize();
         break;
       }
   }
   return Py_BuildValue("(ii)", int(h[0]), int(h[1]));
 }
-
 // Addresses of a list of device tensors that share shape, strides and element type, as bytes.
 PyObject *addresses(PyObject *, PyObject *const *a, Py_ssize_t n) {
   ARGUMENTS(1);
@@ -404,7 +433,7 @@ PyMethodDef fast(const char *name) {
   return {name, reinterpret_cast<PyCFunction>(reinterpret_cast<void (*)()>(guarded<F>)), METH_FASTCALL, nullptr};
 }
 PyMethodDef methods[] = {fast<bind>("bind"), fast<attn_step>("attn_step"), fast<attn_step_layers>("attn_step_layers"),
-                         fast<confidence>("confidence"), fast<lm_head_confidence>("lm_head_confidence"), fast<commit>("commit"),
+                         fast<confidence>("confidence"), fast<lm_head_confidence>("lm_head_confidence"), fast<commit<false>>("commit"), fast<commit<true>>("commit_step"),
                          fast<flip_update>("flip_update"), fast<poll_lengths>("poll_lengths"), fast<addresses>("addresses"), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

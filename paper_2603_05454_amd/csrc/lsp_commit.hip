@@ -16,7 +16,7 @@
 // never learns L.
 #include <limits.h>
 
-#include "lsp_common.h"
+#include "lsp_flips.h"
 
 namespace lsp {
 namespace {
@@ -34,7 +34,7 @@ __global__ __launch_bounds__(kScanThreads) void boundary_kernel(
     int32_t *__restrict__ prefix_len, int32_t *__restrict__ suffix_len,
     uint8_t *__restrict__ stable_mask, int32_t *__restrict__ raw_boundary,
     int32_t *__restrict__ snapped_boundary, int32_t *__restrict__ commit_len,
-    int32_t *__restrict__ status_flags, float *__restrict__ tau_used) {
+    int32_t *__restrict__ status_flags, float *__restrict__ tau_used, FlipArgs flips) {
   const int b = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
   __shared__ int s_first, s_snap, s_lo_hit, s_hi_hit;
@@ -181,6 +181,7 @@ __global__ __launch_bounds__(kScanThreads) void boundary_kernel(
     }
     for (int i = kKeep * kScanThreads + tid; i < L; i += kScanThreads) tokens[int64_t(b) * T + P + i] = id[i];
   }
+  if (flips.base_prefix_len != nullptr) count_flips(flips, b, top1_id, S, praw, N);
   if (tid == 0) {
     raw_boundary[b] = Lp;
     snapped_boundary[b] = Ls;
@@ -294,18 +295,16 @@ void launch_append(const LayerPtrs &p, int64_t max_bytes, int B, int nl, hipStre
 
 extern "C" size_t lsp_commit_workspace_bytes(const lsp_commit_desc *) { return 0; }
 
-extern "C" int32_t lsp_commit(const lsp_commit_desc *d, const float *margin, const int32_t *top1_id,
-                              const uint32_t *delimiter_bitmap,
-                              const void *const *k_suf_layers, const void *const *v_suf_layers,
-                              void *const *k_cache_layers, void *const *v_cache_layers,
-                              int32_t *tokens, int32_t *prefix_len, int32_t *suffix_len,
-                              uint8_t *stable_mask, int32_t *raw_boundary,
-                              int32_t *snapped_boundary, int32_t *commit_len,
-                              int32_t *status_flags, float *tau_used, void *workspace, size_t workspace_bytes,
-                              void *stream) {
-  using namespace lsp;
-  (void)workspace;
-  (void)workspace_bytes;
+namespace lsp {
+namespace {
+int32_t commit_run(const lsp_commit_desc *d, const float *margin, const int32_t *top1_id,
+                   const uint32_t *delimiter_bitmap,
+                   const void *const *k_suf_layers, const void *const *v_suf_layers,
+                   void *const *k_cache_layers, void *const *v_cache_layers,
+                   int32_t *tokens, int32_t *prefix_len, int32_t *suffix_len,
+                   uint8_t *stable_mask, int32_t *raw_boundary,
+                   int32_t *snapped_boundary, int32_t *commit_len,
+                   int32_t *status_flags, float *tau_used, const FlipArgs &flips, void *stream) {
   LSP_CHECK_ARG(d != nullptr, "lsp_commit: null descriptor");
   LSP_CHECK_ARG(margin && top1_id && prefix_len && suffix_len && stable_mask && raw_boundary &&
                     snapped_boundary && commit_len,
@@ -346,7 +345,7 @@ extern "C" int32_t lsp_commit(const lsp_commit_desc *d, const float *margin, con
   boundary_kernel<<<d->B, kScanThreads, 0, st>>>(
       margin, top1_id, delimiter_bitmap, d->S, d->V, d->C, d->T, d->tau, d->window, d->min_commit,
       d->snap_enabled, d->adaptive, d->alpha, d->beta, d->max_commit, tokens, prefix_len, suffix_len,
-      stable_mask, raw_boundary, snapped_boundary, commit_len, status_flags, tau_used);
+      stable_mask, raw_boundary, snapped_boundary, commit_len, status_flags, tau_used, flips);
   LSP_CHECK_LAUNCH("lsp_commit: boundary launch");
   if (d->num_layers > 0) {
     const int64_t max_bytes = int64_t(d->S) * row_bytes;
@@ -368,4 +367,36 @@ extern "C" int32_t lsp_commit(const lsp_commit_desc *d, const float *margin, con
     }
   }
   return LSP_OK;
+}
+}  // namespace
+}  // namespace lsp
+
+extern "C" int32_t lsp_commit(const lsp_commit_desc *d, const float *margin, const int32_t *top1_id,
+                              const uint32_t *delimiter_bitmap,
+                              const void *const *k_suf_layers, const void *const *v_suf_layers,
+                              void *const *k_cache_layers, void *const *v_cache_layers,
+                              int32_t *tokens, int32_t *prefix_len, int32_t *suffix_len,
+                              uint8_t *stable_mask, int32_t *raw_boundary,
+                              int32_t *snapped_boundary, int32_t *commit_len,
+                              int32_t *status_flags, float *tau_used, void *, size_t,
+                              void *stream) {
+  return lsp::commit_run(d, margin, top1_id, delimiter_bitmap, k_suf_layers, v_suf_layers, k_cache_layers, v_cache_layers, tokens,
+                         prefix_len, suffix_len, stable_mask, raw_boundary, snapped_boundary, commit_len, status_flags, tau_used,
+                         lsp::FlipArgs{}, stream);
+}
+
+extern "C" int32_t lsp_commit_step(const lsp_commit_desc *d, const float *margin, const int32_t *top1_id,
+                                   const uint32_t *delimiter_bitmap,
+                                   const void *const *k_suf_layers, const void *const *v_suf_layers,
+                                   void *const *k_cache_layers, void *const *v_cache_layers,
+                                   int32_t *tokens, int32_t *prefix_len, int32_t *suffix_len,
+                                   uint8_t *stable_mask, int32_t *raw_boundary,
+                                   int32_t *snapped_boundary, int32_t *commit_len,
+                                   int32_t *status_flags, float *tau_used, int32_t G, const int32_t *base_prefix_len,
+                                   int32_t *last_id, int64_t *counters, int32_t window_lo, int32_t window_hi,
+                                   int32_t *step_counts, void *stream) {
+  LSP_CHECK_ARG(base_prefix_len && last_id && counters && G > 0, "lsp_commit_step: bad argument");
+  const lsp::FlipArgs f = {base_prefix_len, last_id, reinterpret_cast<unsigned long long *>(counters), G, window_lo, window_hi, step_counts};
+  return lsp::commit_run(d, margin, top1_id, delimiter_bitmap, k_suf_layers, v_suf_layers, k_cache_layers, v_cache_layers, tokens,
+                         prefix_len, suffix_len, stable_mask, raw_boundary, snapped_boundary, commit_len, status_flags, tau_used, f, stream);
 }

@@ -10,8 +10,8 @@ from __future__ import annotations
 
 import torch
 
-from . import (AttnLayerTable, LayerTable, LengthPoll, LspError, attn_step_layers, commit, confidence, confidence_workspace_bytes, flip_update,
-               lm_head_confidence, lm_head_confidence_workspace_bytes)
+from . import (AttnLayerTable, LayerTable, LengthPoll, LspError, _commit_out, attn_step_layers, commit_step, confidence,
+               confidence_workspace_bytes, lm_head_confidence, lm_head_confidence_workspace_bytes)
 
 
 def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
@@ -98,11 +98,11 @@ def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
             if ws is None:
                 ws = torch.empty(lm_head_confidence_workspace_bytes(z.shape[0], z.shape[1], V), dtype=torch.uint8, device=dev)
             conf = lm_head_confidence(z, lm_head_weight, suffix_len, out=conf, workspace=ws)
-        flip_update(conf[0], prefix_len, suffix_len, base, last_id, counters, window=flip_window,
-                    step_counts=step_counts)
-        out = commit(conf[2], conf[0], bitmap, V, tau, window, min_commit, snap_enabled,
-                     prefix_len, suffix_len, tokens=tokens, layers=table, C=tokens.shape[1], out=out,
-                     **(commit_kw or {}))
+        if out is None:
+            out = _commit_out(*conf[0].shape, dev)
+        commit_step(conf[2], conf[0], bitmap, V, tau, window, min_commit, snap_enabled, prefix_len, suffix_len,
+                    base, last_id, counters, flip_window, step_counts, tokens=tokens, layers=table, C=tokens.shape[1], out=out,
+                    **(commit_kw or {}))
 
     while True:
         if (steps - first) % poll == 0:

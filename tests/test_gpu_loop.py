@@ -286,3 +286,36 @@ def test_length_poll(lsp, B, native, monkeypatch):
         assert tuple(poll(n.cuda(), c.cuda())) == (int(n.max()), int(((n > 0) & (c == 0)).any()))
     with pytest.raises(lsp.LspError):
         poll(n.cuda().long())
+
+
+@pytest.mark.parametrize("native", [True, False])
+@pytest.mark.parametrize("B,S,G", [(1, 1, 1), (3, 300, 310), (66, 40, 60)])
+def test_commit_step_is_flip_update_then_commit(lsp, B, S, G, native, monkeypatch):
+    """Random ids and margins over several steps, sequences that end early, positions beyond the last id's buffer."""
+    lsp.lib()
+    if not native:
+        monkeypatch.setattr(lsp, "_nat", None)
+    g = torch.Generator().manual_seed(B + S)
+    V = 50
+    bm = torch.full((2,), 3, dtype=torch.int32, device="cuda")
+
+    def state():
+        return dict(pl=torch.full((B,), 5, dtype=torch.int32, device="cuda"), sl=torch.full((B,), S, dtype=torch.int32, device="cuda"),
+                    last=torch.full((B, G), -1, dtype=torch.int32, device="cuda"), counters=torch.zeros(4, dtype=torch.int64, device="cuda"),
+                    steps=torch.zeros((B, 2), dtype=torch.int32, device="cuda"), tok=torch.zeros((B, S + 8), dtype=torch.int32, device="cuda"),
+                    base=torch.full((B,), 5, dtype=torch.int32, device="cuda"), out=lsp._commit_out(B, S, "cuda"))
+    a, b = state(), state()
+    b["sl"] -= torch.arange(B, device="cuda", dtype=torch.int32) % 2
+    a["sl"].copy_(b["sl"])
+    for k in range(4):
+        ids = torch.randint(0, 3 if k else V, (B, S), generator=g, dtype=torch.int32).cuda()
+        margin = torch.rand((B, S), generator=g).cuda()
+        rules = (bm, V, 0.2, 4, 1, 1)
+        lsp.flip_update(ids, a["pl"], a["sl"], a["base"], a["last"], a["counters"], window=(1, S // 2), step_counts=a["steps"])
+        lsp.commit(margin, ids, *rules, a["pl"], a["sl"], tokens=a["tok"], C=S + 8, out=a["out"], max_commit=S // 3 + 1)
+        lsp.commit_step(margin, ids, *rules, b["pl"], b["sl"], b["base"], b["last"], b["counters"], (1, S // 2), b["steps"], tokens=b["tok"],
+                        C=S + 8, out=b["out"], max_commit=S // 3 + 1)
+        torch.cuda.synchronize()
+        assert all(torch.equal(a[n], b[n]) for n in a if n != "out")
+        assert all(torch.equal(a["out"][n].view(torch.int8), b["out"][n].view(torch.int8)) for n in a["out"])
+    assert a["counters"][1] > 0 or S == 1
