@@ -372,8 +372,12 @@ constexpr int kWideRows = 256;      // buffers of up to this many rows: 512 thre
 constexpr int kSplitRows = 512;     // below this many rows of the buffer, short rows are cut as well
 constexpr int kMaxScannedBatch = 256;  // sequences: every workgroup reads all their lengths, 64 at a time
 constexpr int64_t kMaxSplitGrid = int64_t(1) << 22;  // workgroups; more rows than this need no cutting
-template <typename T, int NT, int U>
-__global__ __launch_bounds__(NT) void confidence_split_kernel(
+// OCC: waves per SIMD that registers are allotted for.  bf16 rows are 129 registers where nothing is asked for, which leaves three
+// workgroups of 256 threads to a compute unit: a little faster over many rounds of them (8192 rows of 126 464: 299 us,
+// 305 with four), slower where the rows just do not fit one or two (900 rows of 152 064: 55.6 and 48.8).
+constexpr int kManyRows = 4096;  // of the buffer
+template <typename T, int NT, int U, int OCC>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC))) void confidence_split_kernel(
     const T *__restrict__ logits, int B, int S, int V, int64_t row_stride, int64_t batch_stride,
     const int32_t *__restrict__ suffix_len, int max_log2, uint32_t tag, int32_t *__restrict__ top1_id,
     float *__restrict__ top1_prob, float *__restrict__ margin, unsigned long long *segments) {
@@ -522,7 +526,7 @@ void launch_split(const Plan &p, hipStream_t st, const T *z, int B, int S, int V
   const int64_t rows = int64_t(B) * S, most = rows << p.max_log2;
   const int64_t target = int64_t(kSplitTarget) * 256 / p.nt;
   const int64_t grid = rows > target ? rows : most < target ? most : target;
-  auto kern = p.nt == 512 ? confidence_split_kernel<T, 512, 2> : confidence_split_kernel<T, 256, 2>;
+  auto kern = p.nt == 512 ? confidence_split_kernel<T, 512, 2, 4> : rows < kManyRows ? confidence_split_kernel<T, 256, 2, 4> : confidence_split_kernel<T, 256, 2, 3>;
   kern<<<unsigned(grid), p.nt, 0, st>>>(z, B, S, V, row_stride, batch_stride, suffix_len, p.max_log2, call_tag(), top1_id,
                                         top1_prob, margin, static_cast<unsigned long long *>(workspace));
 }
