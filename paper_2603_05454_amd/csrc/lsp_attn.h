@@ -43,6 +43,10 @@ struct AttnLayers {
   const void *k_cache[kMaxAttnLayers], *v_cache[kMaxAttnLayers];
   void *out[kMaxAttnLayers];
 };
+__device__ __forceinline__ void fetch_operands(const AttnArgs &a) {
+  fetch_now(a.q, a.k_suf, a.v_suf, a.k_cache, a.v_cache, a.out, a.scale, a.C, a.qs[0], a.qs[1], a.qs[2], a.ks[0], a.ks[1], a.ks[2],
+            a.cs[0], a.cs[1], a.cs[2], a.os[0], a.os[1], a.os[2]);
+}
 // This workgroup's layer replaces the operand pointers.
 __device__ __forceinline__ void for_layer(AttnArgs &a, const AttnLayers &L, int l) {
   if (L.n > 0) {

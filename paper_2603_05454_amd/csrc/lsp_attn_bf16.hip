@@ -549,6 +549,7 @@ __global__ __launch_bounds__(64 * WM * WK, 2) void attn_bf16_kernel(AttnArgs a_i
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   AttnArgs a = a_in;
   if (ONE) a.layers = 1;
+  fetch_operands(a);
   const Place pl = place(a, 32 * WM);
   if (!pl.valid) return;
   if (!ONE) for_layer(a, layers, pl.layer);
@@ -1030,6 +1031,7 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   AttnArgs a = a_in;
   constexpr int D = 128, KK = D / 16, DB = D / 32, NS = WM == 8 ? 8 : 5;
   constexpr int LPB = 8 / WM;  // wave-wide loads of K (and of V) that a wave makes per block
+  fetch_operands(a);
   constexpr int TILE = 32 * D * 2, VBASE = NS * TILE;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 

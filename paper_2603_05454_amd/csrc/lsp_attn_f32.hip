@@ -51,6 +51,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a_in)
   constexpr int OP = D + 4;   // floats per merged O row
   AttnArgs a = a_in;
   a.layers = 1;
+  fetch_operands(a);
   const Place pl = place<false>(a, kTile);
   if (!pl.valid) return;
   const int b = pl.b, g = pl.g, h = pl.h, q0 = pl.q0;

@@ -37,6 +37,8 @@ __global__ __launch_bounds__(kScanThreads) void boundary_kernel(
     int32_t *__restrict__ status_flags, float *__restrict__ tau_used, FlipArgs flips) {
   const int b = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
+  fetch_now(margin, top1_id, bitmap, S, V, C, T, tau, window, min_commit, snap_enabled, adaptive, alpha, beta, max_commit, tokens, prefix_len,
+            suffix_len, stable_mask, raw_boundary, snapped_boundary, commit_len, status_flags, tau_used);
   __shared__ int s_first, s_snap, s_lo_hit, s_hi_hit;
   __shared__ float s_min[kScanThreads];
   __shared__ unsigned long long s_delim[kMaxScanRows / 64];  // bit i%64 of word i/64: position i predicts a delimiter
@@ -218,6 +220,7 @@ __global__ __launch_bounds__(kAppendThreads) void append_kernel(
   constexpr int NT = kAppendThreads, VECS = kAppendVecs, DEP = kAppendDepth;
   constexpr int kBytes = NT * VECS * 16;
   const int lane = threadIdx.x & (kWave - 1);
+  fetch_now(copies, B, row_bytes, suf_batch_bytes, cache_batch_bytes, ptrs.src[0], ptrs.dst[0]);
   // lane l looks after sequence 64 * blockIdx.y + l (in every wave alike)
   const int b0 = blockIdx.y * kWave, bl = min(b0 + lane, B - 1);
   const int L = b0 + lane < B ? commit_len[bl] : 0;

@@ -21,6 +21,7 @@ __global__ __launch_bounds__(256) void flip_kernel(FlipArgs f, const int32_t *__
                                                    const int32_t *__restrict__ prefix_len,
                                                    const int32_t *__restrict__ suffix_len) {
   const int b = blockIdx.x;
+  fetch_now(f.base_prefix_len, f.last_id, f.counters, f.G, f.window_lo, f.window_hi, f.step_counts, top1_id, S, prefix_len, suffix_len);
   count_flips(f, b, top1_id, S, prefix_len[b], min(max(suffix_len[b], 0), S));
 }
 

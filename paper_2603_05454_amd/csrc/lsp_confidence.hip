@@ -340,6 +340,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void co
     const int32_t *__restrict__ suffix_len, int32_t *__restrict__ top1_id, float *__restrict__ top1_prob,
     float *__restrict__ margin) {
   const int i = blockIdx.x, b = blockIdx.y;
+  fetch_now(logits, S, V, row_stride, batch_stride, top1_id, top1_prob, margin);
   if (suffix_len != nullptr && i >= suffix_len[b]) return;
   const RowStat r = segment_stat<T, NT, U>(logits + int64_t(b) * batch_stride + int64_t(i) * row_stride, 0, V);
   if (threadIdx.x == 0) store_row(r, int64_t(b) * S + i, top1_id, top1_prob, margin);
@@ -382,6 +383,7 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC))) void 
     const int32_t *__restrict__ suffix_len, int max_log2, uint32_t tag, int32_t *__restrict__ top1_id,
     float *__restrict__ top1_prob, float *__restrict__ margin, unsigned long long *segments) {
   const int lane = threadIdx.x & (kWave - 1);
+  fetch_now(logits, row_stride, batch_stride, V, max_log2, top1_id, top1_prob, margin, segments, tag);
   // active rows, and for batches of up to 64 the rows up to and including this lane's sequence
   int rows = 0, upto = 0, n = 0;
   auto scan = [&](int b0) {
@@ -404,7 +406,8 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC))) void 
     for (int b0 = 0; b0 < B; b0 += kWave) rows += scan(b0);
   }
   int k = 0;
-  while (k < max_log2 && (int64_t(rows) << (k + 1)) <= kSplitTarget * 256 / NT) ++k;
+  if (rows <= kSplitTarget * 128 / NT)
+    while (k < max_log2 && rows << (k + 1) <= kSplitTarget * 256 / NT) ++k;
   const int row = int(blockIdx.x >> k), seg = int(blockIdx.x) & ((1 << k) - 1);
   if (row >= rows) return;
   int b = 0, i = row;  // sequence and position of that row
