@@ -27,6 +27,7 @@ struct AttnArgs {
   int32_t rep, chunk, spread, layers, unit_group;  // placement of the workgroups (place_grid); read first, with the line above
   Div by_group, by_unit_group, by_units, by_heads, by_rep;  // its divisors: unit_group * chunk, unit_group, B * Hkv, Hkv, rep
   int32_t D, C;
+  int32_t rounding;  // head_dim 128, contiguous cache: which reference short tiles' probabilities are rounded against (Reference)
   float scale;
   int64_t qs[3], ks[3], cs[3], os[3];  // element strides: batch, row, head
   void *workspace;

@@ -210,6 +210,15 @@ constexpr int kShortSuffix = 64;  // sequences with at most this many active row
 // without a query, a tile with two active waves is faster than two key-split workgroups - 38 against
 // 50 us per C5 layer - while a tile with one active wave is slower than one key-split workgroup)
 constexpr int kShortSuffixPipe = 32;
+// A probability is rounded to bf16 relative to the running reference of its pass over the keys, so the last bits of a row follow
+// how the keys are divided between references.  That stays a matter of the launch's shape alone (buffers, not active
+// rows), whichever workgroups compute a tile of up to 32 rows or the spread ones:
+enum Reference : int32_t {
+  kEightParts,  // fewer than 512 tiles of 32 rows: key block j belongs to part j % 8
+  kFourParts,   // fewer than 1024: j % 4
+  kOnePass,     // suffix buffers of up to 128 rows: one pass from the first key block on
+  kTiles256,    // longer ones: one pass that begins with the ragged ends, and for the last up to 32 rows behind a multiple of 256 eight parts
+};
 // K/V that no cache can hold (a quarter more than the last-level cache) and that this one workgroup reads, once, are loaded
 // with the non-temporal hint: 32 layers of 32/32 heads, 16 x 21 rows of 1536 keys 2242 -> 2130 us (6.1 TB/s), 8 x 20 of 1128
 // 832 -> 741, 2 x 16 of 4016 717 -> 664.  With a query group's heads on one KV head the hint costs a factor (284 -> 523), in
@@ -302,9 +311,14 @@ constexpr int kWaitLgkm0 = 0xC07F;    // s_waitcnt lgkmcnt(0), other counters un
 // adds nothing to a bf16 result) and the sums are brought to it.  Four waves with two parts so round every
 // probability as eight waves do, whatever workgroup a launch uses (head_dim 128 only).
 // once: nobody else reads these K/V rows (see kStreamBytes; head_dim 128 only).
+// ref: keys whose maximum is every wave's reference to begin with (count 0: each wave's own first block is); with these and
+// one part the probabilities are rounded as in one pass over all keys that begins there (head_dim 128 only).
+struct RefKeys {
+  int first, count;
+};
 template <int D, int WM, int WK, bool GATHER, int PARTS = 1>
 __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, int h, int q0, int N, int P,
-                                               unsigned char *smem, bool once = false) {
+                                               unsigned char *smem, bool once = false, int parts = PARTS, RefKeys ref = {0, 0}) {
   using G = Geo<D>;
   constexpr int KK = D / 16;  // d-steps of the first product
   constexpr int DB = D / 32;  // 32-row blocks of O^T
@@ -487,6 +501,29 @@ __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, 
   for (int kk = 0; kk < KK; ++kk)
     qf[kk] = *reinterpret_cast<const bf16x8 *>(smem + WM * WK * G::WAVE_LDS + (wm * 32 + lq) * G::KPITCH + (16 * kk + 8 * hf) * 2);
 
+  if constexpr (D == 128 && WM == 1 && !GATHER) {
+    if (ref.count > 0) {
+      float *mshare = reinterpret_cast<float *>(smem + WM * WK * G::WAVE_LDS + WM * 32 * G::KPITCH);
+      if (wk_s == 0) {
+        const uint16_t *kp = row_ptr(kc, ks, min(ref.first + lq, ref.first + ref.count - 1)) + 8 * hf;
+        f32x16 s;
+#pragma unroll
+        for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk)
+          s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(kp + 16 * kk), qf[kk], s, 0, 0, 0);
+        // (rows beyond the count repeat the last one; no maximum in asm straight behind the matrix instructions, whose
+        // results the compiler waits for on behalf of its own instructions only)
+        float bm = s[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) bm = __builtin_fmaxf(bm, s[r]);
+        bm = half_max(bm) * sc;
+        if (hf == 0) mshare[lq] = bm;
+      }
+      __syncthreads();
+      mref = mshare[lq];
+    }
+  }
   if constexpr (D == 128) {
     // head_dim 128: K and V rows go from global memory straight into this wave's
     // LDS region (no staging registers, no LDS store instructions on the critical
@@ -500,10 +537,11 @@ __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, 
     // the V^T fragments do.
     const int y16 = 16 * (hf ^ (lq & 15));
     int jb = wk_s;
-    bool first_part = PARTS > 1, fresh = false;
+    const int stride = PARTS > 1 && parts > 1 ? WK * PARTS : WK;
+    bool first_part = PARTS > 1 && parts > 1, fresh = false;
     // (the first block was requested before the Q rows, see above)
     while (jb < NB) {
-      int jn = jb + WK * PARTS;
+      int jn = jb + stride;
       const bool turn = first_part && jn >= NB;  // to this wave's second part
       if (turn) {
         jn = wk_s + WK;
@@ -544,7 +582,7 @@ __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, 
 }
 
 // ONE: a single layer, whose operand pointers need not wait for the placement (0.1 of 11 us)
-template <int D, int WM, int WK, bool GATHER, bool ONE>
+template <int D, int WM, int WK, bool GATHER, bool ONE, int PARTS>
 __global__ __launch_bounds__(64 * WM * WK, 2) void attn_bf16_kernel(AttnArgs a_in, AttnLayers layers) {
   extern __shared__ __attribute__((aligned(16))) unsigned char smem[];
   AttnArgs a = a_in;
@@ -556,10 +594,10 @@ __global__ __launch_bounds__(64 * WM * WK, 2) void attn_bf16_kernel(AttnArgs a_i
   const int N = min(max(a.suffix_len[pl.b], 0), a.S);
   if (pl.q0 >= N) return;
   const int P = min(max(a.prefix_len[pl.b], 0), a.C);
-  key_split_body<D, WM, WK, GATHER>(a, pl.b, pl.g, pl.h, pl.q0, N, P, smem);
+  key_split_body<D, WM, WK, GATHER, PARTS>(a, pl.b, pl.g, pl.h, pl.q0, N, P, smem);
 }
 
-template <int D, int WM, int WK, bool GATHER>
+template <int D, int WM, int WK, bool GATHER, int PARTS = 1>
 int32_t launch_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
   const int64_t nwg = place_grid(a, layers, 32 * WM, 32 * 8 / (WM * WK));
   if (nwg > kMaxGrid) {
@@ -567,7 +605,7 @@ int32_t launch_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
     return LSP_ERR_UNSUPPORTED;
   }
   const size_t lds = size_t(WM * WK) * Geo<D>::WAVE_LDS + size_t(WM) * 32 * Geo<D>::KPITCH;  // wave regions + Q rows
-  auto kern = layers.n == 0 ? attn_bf16_kernel<D, WM, WK, GATHER, true> : attn_bf16_kernel<D, WM, WK, GATHER, false>;
+  auto kern = layers.n == 0 ? attn_bf16_kernel<D, WM, WK, GATHER, true, PARTS> : attn_bf16_kernel<D, WM, WK, GATHER, false, PARTS>;
   static std::atomic<uint64_t> configured[2];  // per instantiation, one bit per device
   if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured[layers.n == 0], "lsp_attn_step: hipFuncSetAttribute")) return rc;
   kern<<<grid_of(nwg), 64 * WM * WK, lds, st>>>(a, layers);
@@ -1052,7 +1090,16 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int qs = spread ? q0 / WM : q0;
   if (qs >= N) return;
   if (spread || N - q0 <= kShortSuffixPipe) {
-    key_split_body<D, 1, WM, false, 8 / WM>(a, b, g, h, qs, N, P, smem, a.rep == 1 && N <= 32 && int64_t(P + N) * a.Hkv * (4 * D) * a.B * a.layers >= kStreamBytes);
+    const bool one_pass = a.rounding == kOnePass || (a.rounding == kTiles256 && N - (qs & ~255) > kShortSuffixPipe);
+    RefKeys ref = {0, 0};
+    if (one_pass) {
+      ref.count = min(32, P + N);
+      if (a.rounding == kTiles256 && (P & 31)) ref = {P & ~31, P & 31};
+      else if (a.rounding == kTiles256 && (N & 31)) ref = {P + (N & ~31), N & 31};
+    }
+    key_split_body<D, 1, WM, false, 8 / WM>(a, b, g, h, qs, N, P, smem,
+                                            a.rep == 1 && N <= 32 && int64_t(P + N) * a.Hkv * (4 * D) * a.B * a.layers >= kStreamBytes,
+                                            one_pass || a.rounding == kFourParts ? 1 : 8 / WM, ref);
     return;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1206,7 +1253,7 @@ int32_t launch_pipe(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
     return LSP_ERR_UNSUPPORTED;
   }
   const size_t lds_ring = size_t(WM == 8 ? 8 : 5) * 2 * 32 * 256;
-  const size_t lds_split = WM * size_t(Geo<128>::WAVE_LDS) + 32 * size_t(Geo<128>::KPITCH);
+  const size_t lds_split = WM * size_t(Geo<128>::WAVE_LDS) + 32 * size_t(Geo<128>::KPITCH) + 32 * sizeof(float);
   const size_t lds = lds_ring > lds_split ? lds_ring : lds_split;
   auto kern = attn_bf16_pipe_kernel<WM>;
   static std::atomic<uint64_t> configured{0};
@@ -1237,16 +1284,19 @@ int32_t launch(const AttnArgs &a, const AttnLayers &layers, hipStream_t st) {
 //    half: 254 and 231; 32 layers, 8 x 600 on 600, 28/4 heads: 3025 and 2903);
 //  * fewer: the key split, eight ways while its workgroups are at most one to a compute unit, four ways beyond, where
 //    two fit one (1 x 384 on 800: 18.9 four ways, 23.4 eight, 21.1 with 128-row tiles).
-int32_t dispatch_contiguous128(const AttnArgs &a, const AttnLayers &layers, hipStream_t st) {
+int32_t dispatch_contiguous128(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
   const int64_t heads = int64_t(a.B) * a.Hq * (layers.n > 0 ? layers.n : 1);
   auto tiles = [&](int rows) { return heads * ((a.S + rows - 1) / rows); };
+  const int64_t rows = heads * a.S;
+  a.rounding = rows >= 32768 ? (a.S > 128 ? kTiles256 : kOnePass) : rows >= 16384 ? kFourParts : kEightParts;
   if (tiles(128) > 128) {
-    const int64_t wide = a.S > 128 ? tiles(256) : 0;
+    const int64_t wide = a.rounding == kTiles256 ? tiles(256) : 0;
     if ((wide > 192 && wide <= 256) || (wide >= 512 && heads <= 256) || (wide >= 1024 && a.C > 2048))
       return launch_pipe<8>(a, layers, st);
     return launch_pipe<4>(a, layers, st);
   }
-  return tiles(32) <= 256 ? launch_g<128, 1, 8, false>(a, layers, st) : launch_g<128, 1, 4, false>(a, layers, st);
+  if (tiles(32) <= 256) return launch_g<128, 1, 8, false>(a, layers, st);
+  return a.rounding == kEightParts ? launch_g<128, 1, 4, false, 2>(a, layers, st) : launch_g<128, 1, 4, false>(a, layers, st);
 }
 
 template <int D>
