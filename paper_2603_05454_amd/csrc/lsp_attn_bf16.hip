@@ -1084,7 +1084,7 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   // range: its one block of queries goes to the key-split body (as in attn_bf16_ring_kernel), which
   // shares the KEY range between the waves instead.  The same where so few tiles are left of the whole launch that
   // workgroups of 32 rows still find a compute unit each: the workgroups of the tiles that have ended take them
-  // (one layer, 32 heads, 200 of 1024 rows on 4000 cached ones: 102 us with one tile of 256, 39 so).
+  // (one layer, 32 heads, 200 of 1024 rows on 4000 cached ones: 102 us with one tile of 256, 40 so).
   const int blocks = (N + 31) >> 5;
   const bool spread = WM == 4 && blocks <= (a.S + 32 * WM - 1) / (32 * WM) && int64_t(blocks) * a.B * a.Hq * a.layers <= kSpreadBlocks;
   const int qs = spread ? q0 / WM : q0;

@@ -11,9 +11,8 @@
 //   - the arg-max index is not tracked per element.  A lane only remembers in
 //     which group of its 16-byte vectors its running maximum last rose
 //     strictly; since a lane visits its elements in increasing index order,
-//     that group holds the lane's first occurrence of its maximum, and it is
-//     re-read once at the end - by the lanes that hold the wave's maximum only
-//     (every lane doing so would add 16 KB of scattered cache lines per wave);
+//     that group holds the lane's first occurrence of its maximum; the lane keeps a
+//     copy of it in registers, which is scanned once at the end;
 //   - the soft-max sum uses one exp2 per element against a lagging per-lane
 //     reference r (log2 domain) which is only moved when the lane maximum has
 //     run more than 32 octaves ahead of it, so the rescale branch is cold.  A
