@@ -65,6 +65,9 @@ typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLagOctaves = 8.0f;
 constexpr float kPartOctaves = 32.0f;
+// Lowering the reference by that many octaves multiplies what has been summed by as many: not where it is large (V beyond
+// 2^64), lest values that fp32 holds overflow on the way.
+constexpr float kLiftedSum = 0x1p64f;
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -172,7 +175,14 @@ __device__ __forceinline__ void softmax_pv(f32x16 &s, f32x16 (&oacc)[D / 32], fl
   bm = half_max(bm) * sc;  // finite: key0 < T is a valid key
   if (fresh || __any(bm > mref + kLagOctaves)) {
     float mn = bm > mref + kLagOctaves ? bm : mref;
-    if (fresh) mn = fmax_raw(bm, mref - kPartOctaves);
+    if (fresh) {
+      float most = 0.f;
+#pragma unroll
+      for (int db = 0; db < DB; ++db)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) most = __builtin_fmaxf(most, __builtin_fabsf(oacc[db][r]));
+      mn = fmax_raw(bm, half_max(most) > kLiftedSum ? mref : mref - kPartOctaves);
+    }
     const float alpha = __builtin_amdgcn_exp2f(mref - mn);  // 0 on the first block (mref = -inf)
     mref = mn;
     lsum *= alpha;

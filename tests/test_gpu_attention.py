@@ -492,3 +492,26 @@ def test_tile_of_the_hand_scheduled_loop(lsp, oracle, layers, C, what):
     assert (got[act] - ref[act]).abs().max().item() <= TOL["bf16"]
     assert torch.all(got[~act] == 123.0)
     assert all(torch.equal(o, outs[0]) for o in outs[1:])
+
+
+@pytest.mark.parametrize("first", [True, False])
+@pytest.mark.parametrize("B,S,H,N,P", [(4, 545, 4, 545, 512), (32, 300, 5, 20, 300)])
+def test_values_near_the_end_of_the_range(lsp, oracle, B, S, H, N, P, first):
+    """Values of 2^100 whose scores lead by 58 octaves in one half of the key blocks: a wave takes blocks j % 8 = w and then
+    w + 4, and what it has summed of the one must not leave fp32's range when the other sets its reference.  Both
+    kernels that do so: four-way key split, and short tiles of the four-wave workgroups."""
+    w = W.scaled(W.C2, B=B, S=S, P=P, C=P + 8, Hq=H, Hkv=H, D=128, seed=77)
+    pl, sl = torch.full((B,), P, dtype=torch.int32), torch.full((B,), N, dtype=torch.int32)
+    kv = W.make_layer_kv(w, 0, prefix_len=pl)
+    kv["q"].fill_(1.0)
+    for name, base in (("k_cache", 0), ("k_suf", P)):
+        t = base + torch.arange(kv[name].shape[1])
+        lead = ((t // 32) % 8 < 4) == first
+        kv[name][:] = (lead * 40 / 128 ** 0.5).to(kv[name].dtype)[None, :, None, None]      # score 40, and 0
+    for name in ("v_cache", "v_suf"):
+        kv[name].mul_(2.0 ** 100)
+    got = _run(lsp, kv, pl, sl)
+    ref = oracle.attention(**kv, prefix_len=pl, suffix_len=sl)
+    act = ~torch.isnan(ref)
+    assert torch.isfinite(got[act]).all()
+    assert ((got[act] - ref[act]) * 2.0 ** -100).abs().max().item() <= TOL["bf16"]
