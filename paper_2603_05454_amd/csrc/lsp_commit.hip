@@ -26,6 +26,9 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 constexpr int kScanThreads = 256;
 constexpr int kMaxScanRows = 65536;  // S at most this (one delimiter ballot bit per row in LDS)
 
+// FLIPS: FlipArgs (lsp_commit_step), or nothing: a plain commit takes 144 bytes of arguments and 76 scalar registers, with the
+// count behind a test of its own they were 448 and 94.
+template <typename... FLIPS>
 __global__ __launch_bounds__(kScanThreads) void boundary_kernel(
     const float *__restrict__ margin, const int32_t *__restrict__ top1_id,
     const uint32_t *__restrict__ bitmap, int S, int V, int C, int T, float tau, int window,
@@ -34,11 +37,9 @@ __global__ __launch_bounds__(kScanThreads) void boundary_kernel(
     int32_t *__restrict__ prefix_len, int32_t *__restrict__ suffix_len,
     uint8_t *__restrict__ stable_mask, int32_t *__restrict__ raw_boundary,
     int32_t *__restrict__ snapped_boundary, int32_t *__restrict__ commit_len,
-    int32_t *__restrict__ status_flags, float *__restrict__ tau_used, FlipArgs flips) {
+    int32_t *__restrict__ status_flags, float *__restrict__ tau_used, FLIPS... flips) {
   const int b = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & (kWave - 1);
-  fetch_now(margin, top1_id, bitmap, S, V, C, T, tau, window, min_commit, snap_enabled, adaptive, alpha, beta, max_commit, tokens, prefix_len,
-            suffix_len, stable_mask, raw_boundary, snapped_boundary, commit_len, status_flags, tau_used);
   __shared__ int s_first, s_snap, s_lo_hit, s_hi_hit;
   __shared__ float s_min[kScanThreads];
   __shared__ unsigned long long s_delim[kMaxScanRows / 64];  // bit i%64 of word i/64: position i predicts a delimiter
@@ -183,7 +184,7 @@ __global__ __launch_bounds__(kScanThreads) void boundary_kernel(
     }
     for (int i = kKeep * kScanThreads + tid; i < L; i += kScanThreads) tokens[int64_t(b) * T + P + i] = id[i];
   }
-  if (flips.base_prefix_len != nullptr) count_flips(flips, b, top1_id, S, praw, N);
+  if constexpr (sizeof...(FLIPS) > 0) count_flips<kScanThreads>(flips..., b, top1_id, S, praw, N);
   if (tid == 0) {
     raw_boundary[b] = Lp;
     snapped_boundary[b] = Ls;
@@ -307,7 +308,7 @@ int32_t commit_run(const lsp_commit_desc *d, const float *margin, const int32_t 
                    int32_t *tokens, int32_t *prefix_len, int32_t *suffix_len,
                    uint8_t *stable_mask, int32_t *raw_boundary,
                    int32_t *snapped_boundary, int32_t *commit_len,
-                   int32_t *status_flags, float *tau_used, const FlipArgs &flips, void *stream) {
+                   int32_t *status_flags, float *tau_used, const FlipArgs *flips, void *stream) {
   LSP_CHECK_ARG(d != nullptr, "lsp_commit: null descriptor");
   LSP_CHECK_ARG(margin && top1_id && prefix_len && suffix_len && stable_mask && raw_boundary &&
                     snapped_boundary && commit_len,
@@ -345,10 +346,16 @@ int32_t commit_run(const lsp_commit_desc *d, const float *margin, const int32_t 
     }
   }
   hipStream_t st = static_cast<hipStream_t>(stream);
-  boundary_kernel<<<d->B, kScanThreads, 0, st>>>(
-      margin, top1_id, delimiter_bitmap, d->S, d->V, d->C, d->T, d->tau, d->window, d->min_commit,
-      d->snap_enabled, d->adaptive, d->alpha, d->beta, d->max_commit, tokens, prefix_len, suffix_len,
-      stable_mask, raw_boundary, snapped_boundary, commit_len, status_flags, tau_used, flips);
+  auto boundary = [&](auto kernel, auto... more) {
+    kernel<<<d->B, kScanThreads, 0, st>>>(
+        margin, top1_id, delimiter_bitmap, d->S, d->V, d->C, d->T, d->tau, d->window, d->min_commit,
+        d->snap_enabled, d->adaptive, d->alpha, d->beta, d->max_commit, tokens, prefix_len, suffix_len,
+        stable_mask, raw_boundary, snapped_boundary, commit_len, status_flags, tau_used, more...);
+  };
+  if (flips != nullptr)
+    boundary(boundary_kernel<FlipArgs>, *flips);
+  else
+    boundary(boundary_kernel<>);
   LSP_CHECK_LAUNCH("lsp_commit: boundary launch");
   if (d->num_layers > 0) {
     const int64_t max_bytes = int64_t(d->S) * row_bytes;
@@ -385,7 +392,7 @@ extern "C" int32_t lsp_commit(const lsp_commit_desc *d, const float *margin, con
                               void *stream) {
   return lsp::commit_run(d, margin, top1_id, delimiter_bitmap, k_suf_layers, v_suf_layers, k_cache_layers, v_cache_layers, tokens,
                          prefix_len, suffix_len, stable_mask, raw_boundary, snapped_boundary, commit_len, status_flags, tau_used,
-                         lsp::FlipArgs{}, stream);
+                         nullptr, stream);
 }
 
 extern "C" int32_t lsp_commit_step(const lsp_commit_desc *d, const float *margin, const int32_t *top1_id,
@@ -401,5 +408,5 @@ extern "C" int32_t lsp_commit_step(const lsp_commit_desc *d, const float *margin
   LSP_CHECK_ARG(base_prefix_len && last_id && counters && G > 0, "lsp_commit_step: bad argument");
   const lsp::FlipArgs f = {base_prefix_len, last_id, reinterpret_cast<unsigned long long *>(counters), G, window_lo, window_hi, step_counts};
   return lsp::commit_run(d, margin, top1_id, delimiter_bitmap, k_suf_layers, v_suf_layers, k_cache_layers, v_cache_layers, tokens,
-                         prefix_len, suffix_len, stable_mask, raw_boundary, snapped_boundary, commit_len, status_flags, tau_used, f, stream);
+                         prefix_len, suffix_len, stable_mask, raw_boundary, snapped_boundary, commit_len, status_flags, tau_used, &f, stream);
 }

@@ -17,18 +17,19 @@ void set_error(const char *fmt, ...) {
 
 namespace {
 
-__global__ __launch_bounds__(256) void flip_kernel(FlipArgs f, const int32_t *__restrict__ top1_id, int S,
+constexpr int kFlipThreads = 256;
+__global__ __launch_bounds__(kFlipThreads) void flip_kernel(FlipArgs f, const int32_t *__restrict__ top1_id, int S,
                                                    const int32_t *__restrict__ prefix_len,
                                                    const int32_t *__restrict__ suffix_len) {
   const int b = blockIdx.x;
-  fetch_now(f.base_prefix_len, f.last_id, f.counters, f.G, f.window_lo, f.window_hi, f.step_counts, top1_id, S, prefix_len, suffix_len);
-  count_flips(f, b, top1_id, S, prefix_len[b], min(max(suffix_len[b], 0), S));
+  count_flips<kFlipThreads>(f, b, top1_id, S, prefix_len[b], min(max(suffix_len[b], 0), S));
 }
 
 // What a decode loop asks between two steps, in one launch and written straight to host memory: the host reads the flag
 // without a copy or a synchronisation behind it.  (As seven small torch operations and a transfer it stood 60-80 us
 // between a step's append and the next step's attention; now about 20.)
-__global__ __launch_bounds__(256) void poll_kernel(const int32_t *__restrict__ suffix_len,
+constexpr int kPollThreads = 256;
+__global__ __launch_bounds__(kPollThreads) void poll_kernel(const int32_t *__restrict__ suffix_len,
                                                    const int32_t *__restrict__ commit_len, int B, int32_t *host) {
   __shared__ int s_left, s_stalled;
   if (threadIdx.x == 0) {
@@ -38,7 +39,7 @@ __global__ __launch_bounds__(256) void poll_kernel(const int32_t *__restrict__ s
   __syncthreads();
   int left = INT_MIN;
   bool stalled = false;
-  for (int b = threadIdx.x; b < B; b += blockDim.x) {
+  for (int b = threadIdx.x; b < B; b += kPollThreads) {
     const int n = suffix_len[b];
     left = max(left, n);
     stalled |= commit_len != nullptr && n > 0 && commit_len[b] == 0;
@@ -132,7 +133,7 @@ extern "C" int32_t lsp_bench_read(const void *buffer, int64_t bytes, int32_t wor
 extern "C" int32_t lsp_poll_lengths(const int32_t *suffix_len, const int32_t *commit_len, int32_t B, int32_t *host, void *stream) {
   using namespace lsp;
   LSP_CHECK_ARG(suffix_len && host && B > 0, "lsp_poll_lengths: bad argument");
-  poll_kernel<<<1, 256, 0, static_cast<hipStream_t>(stream)>>>(suffix_len, commit_len, B, host);
+  poll_kernel<<<1, kPollThreads, 0, static_cast<hipStream_t>(stream)>>>(suffix_len, commit_len, B, host);
   LSP_CHECK_LAUNCH("lsp_poll_lengths: launch");
   return LSP_OK;
 }
@@ -150,7 +151,7 @@ extern "C" int32_t lsp_flip_update(const int32_t *top1_id, int32_t B, int32_t S,
                 "lsp_flip_update: null pointer");
   LSP_CHECK_ARG(B > 0 && S > 0 && G > 0, "lsp_flip_update: bad B/S/G");
   const FlipArgs f = {base_prefix_len, last_id, reinterpret_cast<unsigned long long *>(counters), G, window_lo, window_hi, step_counts};
-  flip_kernel<<<B, 256, 0, static_cast<hipStream_t>(stream)>>>(f, top1_id, S, prefix_len, suffix_len);
+  flip_kernel<<<B, kFlipThreads, 0, static_cast<hipStream_t>(stream)>>>(f, top1_id, S, prefix_len, suffix_len);
   LSP_CHECK_LAUNCH("lsp_flip_update: launch");
   return LSP_OK;
 }

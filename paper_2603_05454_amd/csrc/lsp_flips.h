@@ -5,7 +5,7 @@
 namespace lsp {
 
 struct FlipArgs {
-  const int32_t *base_prefix_len;  // null: no bookkeeping
+  const int32_t *base_prefix_len;
   int32_t *last_id;
   unsigned long long *counters;
   int G, window_lo, window_hi;
@@ -16,13 +16,15 @@ struct FlipArgs {
 // when it already had a prediction at the previous step.  The sequence's counts
 // also go to the mid-generation window when the number of its positions already
 // committed lies in [window_lo, window_hi].  P, N: the sequence's lengths before this step's commit.
+// THREADS: of the workgroup (asked of the hardware, it would be an implicit argument, and 256 bytes more to fetch).
+template <int THREADS>
 __device__ __forceinline__ void count_flips(const FlipArgs &f, int b, const int32_t *__restrict__ top1_id, int S, int P, int N) {
   __shared__ int total[2];
   const int done = P - f.base_prefix_len[b];
   if (threadIdx.x < 2) total[threadIdx.x] = 0;
   __syncthreads();
   int flips = 0, seen = 0;
-  for (int u = threadIdx.x; u < N; u += blockDim.x) {
+  for (int u = threadIdx.x; u < N; u += THREADS) {
     const int j = done + u;
     if (j < 0 || j >= f.G) continue;
     const int32_t cur = top1_id[int64_t(b) * S + u];
