@@ -332,9 +332,10 @@ __device__ __forceinline__ void store_row(const RowStat &r, int64_t o, int32_t *
   top1_prob[o] = 1.0f / r.s;
 }
 
-// One workgroup per row of the buffer.
+// One workgroup per row of the buffer.  (Registers as in confidence_split_kernel; fp32 rows take 68 and get another order of loads where
+// something is asked for: 5 x 600 rows of 30 000 with 360 active 31.7 us, 33.5 so.)
 template <typename T, int NT, int U>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void confidence_kernel(
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 4 : 1))) void confidence_kernel(
     const T *__restrict__ logits, int S, int V, int64_t row_stride, int64_t batch_stride,
     const int32_t *__restrict__ suffix_len, int32_t *__restrict__ top1_id, float *__restrict__ top1_prob,
     float *__restrict__ margin) {
@@ -359,32 +360,48 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(4))) void co
 // 22 us with a fence, 19 with a counter, 6.4 so; 103 rows in 8: 28, 18, 12).
 // What it saves: a row is 7.4 us of arithmetic for one compute unit, so that 3 rows took as long as 100.  One sequence
 // of 256 rows of 126 464 entries, per call before -> now: 3 rows active 11.5 -> 5.6 us, 20: 11.8 -> 6.3, 103: 12.6 ->
-// 10.5; all 256 stay whole (13.9 -> 14.1, the price of the count); 8 x 1024 rows with 220 active 29.3 -> 15.6, all of
+// 9.9; all 256 stay whole (13.5 -> 13.8, the price of the count); 8 x 1024 rows with 220 active 29.3 -> 15.6, all of
 // 8 x 1024 x 152 064 367 -> 361 (no workgroups without a row between the others).
-// Rows are cut as long as that makes no more workgroups of 256 threads than this: a wave's own reductions cost as much
-// as 80 of its vectors, so that shorter segments lose more than the fuller chip gives (103 rows in 4 segments 10.5 us,
-// in 8 12.2, in 16 13.5; 512 rows whole 24.6, halved 30.5).
+// Rows are cut as long as that makes no more workgroups of 256 threads than this, or half as many of 512: a wave's own
+// reductions cost as much as 80 of its vectors, so that shorter segments lose more than the fuller chip gives (100 rows with 512
+// threads whole 12.3 us, in 2 segments 9.9, 4 10.1, 8 12.5; with 256 threads 16.4, 11.9, 9.8, 10.1; 505 rows with 256 threads
+// whole 23.2, halved 25.5).
 constexpr int kSplitTarget = 512;
 constexpr int kMaxLog2 = 4;         // 16 segments' numbers fill a wave
 constexpr int kMinSegment = 4096;   // elements; a segment is a few groups of loads
 constexpr int kMinCut = 16384;      // rows of at most this many are not cut (100 rows of 9000: 4.8 us whole, 5.6 cut)
-constexpr int kWideRows = 256;      // buffers of up to this many rows: 512 threads, half as many workgroups (256 rows: 14.1 us, 16.0 with 256)
-constexpr int kSplitRows = 512;     // below this many rows of the buffer, short rows are cut as well
+// fp32 rows are twice the bytes for the same arithmetic and are cut once more, down to segments of this many elements (65 rows of
+// 126 464 in 2 segments 13.6 us, in 4 10.4; 40 in 4 9.2, in 8 8.3; 100 rows of 20 000 in 2 5.9, in 4 6.4).
+constexpr int kMinSegmentF32 = 7168;
+// bf16 rows up to this long are not merely halved: half a row is a group and a quarter of loads (100 rows of 20 000 whole 5.3 us, halved 5.9,
+// 40 in 4 segments 5.0 for 5.1; 100 of 30 000 whole 6.1, halved 6.1).
+constexpr int kMinHalved = 24576;
+// Buffers of fewer rows than this: short rows are cut as well, and all with 512 threads (400 rows of 30 000 in fp32 10.5 us, 12.4
+// with 256; 130 of them of 126 464 in bf16 12.7 and 13.2; 505 rows 23.4 and 23.2).
+constexpr int kSplitRows = 512;
+// FEW: buffers of up to this many sequences, and more rows than run at once: lengths through the scalar cache, where all workgroups but
+// the first find them (6 x 189 rows of 126 464 54.4 -> 53.0 us; 2 x 200, which run at once, 24.1 -> 24.7).
+// Not with three workgroups to a compute unit: 8 x 1024 rows with 204 active 49.6 -> 53.4, all of 152 064 359 -> 365.
+constexpr int kFewSequences = 8;
+constexpr int kFewRows = 768;
 constexpr int kMaxScannedBatch = 256;  // sequences: every workgroup reads all their lengths, 64 at a time
 constexpr int64_t kMaxSplitGrid = int64_t(1) << 22;  // workgroups; more rows than this need no cutting
 // OCC: waves per SIMD that registers are allotted for.  bf16 rows are 129 registers where nothing is asked for, which leaves three
 // workgroups of 256 threads to a compute unit: a little faster over many rounds of them (8192 rows of 126 464: 299 us,
 // 305 with four), slower where the rows just do not fit one or two (900 rows of 152 064: 55.6 and 48.8).
 constexpr int kManyRows = 4096;  // of the buffer
-template <typename T, int NT, int U, int OCC>
-__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC))) void confidence_split_kernel(
+// (with 256 threads it would be more segments than the workspace holds)
+template <typename T>
+__host__ __device__ constexpr bool cut_once_more(int threads) { return sizeof(T) == 4 && threads == 512; }
+template <typename T, int NT, int U, int OCC, bool FEW>
+__global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? OCC : 1))) void confidence_split_kernel(
     const T *__restrict__ logits, int B, int S, int V, int64_t row_stride, int64_t batch_stride,
     const int32_t *__restrict__ suffix_len, int max_log2, uint32_t tag, int32_t *__restrict__ top1_id,
     float *__restrict__ top1_prob, float *__restrict__ margin, unsigned long long *segments) {
   const int lane = threadIdx.x & (kWave - 1);
   fetch_now(logits, row_stride, batch_stride, V, max_log2, top1_id, top1_prob, margin, segments, tag);
   // active rows, and for batches of up to 64 the rows up to and including this lane's sequence
-  int rows = 0, upto = 0, n = 0;
+  int rows = 0, upto = 0, n = 0, lens[kFewSequences];
   auto scan = [&](int b0) {
     const int b = b0 + lane;
     n = b < B ? min(max(suffix_len[b], 0), S) : 0;
@@ -399,20 +416,38 @@ __global__ __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(OCC))) void 
   };
   if (suffix_len == nullptr) {
     rows = B * S;
+  } else if (FEW) {
+#pragma unroll
+    for (int j = 0; j < kFewSequences; ++j) lens[j] = suffix_len[min(j, B - 1)];
+#pragma unroll
+    for (int j = 0; j < kFewSequences; ++j) rows += lens[j] = j < B ? min(max(lens[j], 0), S) : 0;
   } else if (B == 1) {
     rows = upto = n = min(max(suffix_len[0], 0), S);
   } else {
     for (int b0 = 0; b0 < B; b0 += kWave) rows += scan(b0);
   }
   int k = 0;
-  if (rows <= kSplitTarget * 128 / NT)
+  if (rows <= kSplitTarget * 128 / NT) {
     while (k < max_log2 && rows << (k + 1) <= kSplitTarget * 256 / NT) ++k;
+    if (cut_once_more<T>(NT) && k > 0 && k < max_log2 && V >> (k + 1) >= kMinSegmentF32) ++k;
+    if (sizeof(T) == 2 && k == 1 && V <= kMinHalved) k = 0;
+  }
   const int row = int(blockIdx.x >> k), seg = int(blockIdx.x) & ((1 << k) - 1);
   if (row >= rows) return;
   int b = 0, i = row;  // sequence and position of that row
   if (suffix_len == nullptr) {
     b = row / S;
     i = row - b * S;
+  } else if (FEW) {
+    bool beyond = true;
+#pragma unroll
+    for (int j = 0; j < kFewSequences - 1; ++j) {
+      beyond = beyond && i >= lens[j];
+      if (beyond) {
+        i -= lens[j];
+        ++b;
+      }
+    }
   } else {
     if (B > kWave)
       for (;; b += kWave) {
@@ -482,7 +517,7 @@ inline Plan plan(int64_t rows, int V, int elem_bytes) {
     while (V > kMinCut && p.max_log2 < kMaxLog2 && (V >> (p.max_log2 + 1)) >= kMinSegment) ++p.max_log2;
   p.required = p.max_log2 > 0 && rows < 128;
   if (p.max_log2 > 0 && nt < 256) nt = 256;
-  if (p.max_log2 > 0 && rows <= kWideRows) nt = 512;
+  if (p.max_log2 > 0 && rows < kSplitRows) nt = 512;
   p.nt = nt;
   return p;
 }
@@ -526,9 +561,12 @@ template <typename T>
 void launch_split(const Plan &p, hipStream_t st, const T *z, int B, int S, int V, int64_t row_stride, int64_t batch_stride,
                   const int32_t *suffix_len, int32_t *top1_id, float *top1_prob, float *margin, void *workspace) {
   const int64_t rows = int64_t(B) * S, most = rows << p.max_log2;
-  const int64_t target = int64_t(kSplitTarget) * 256 / p.nt;
+  const int64_t target = cut_once_more<T>(p.nt) ? kSplitTarget : kSplitTarget * 256 / p.nt;
   const int64_t grid = rows > target ? rows : most < target ? most : target;
-  auto kern = p.nt == 512 ? confidence_split_kernel<T, 512, 2, 4> : rows < kManyRows ? confidence_split_kernel<T, 256, 2, 4> : confidence_split_kernel<T, 256, 2, 3>;
+  const bool few = B > 1 && B <= kFewSequences && rows >= kFewRows;
+  auto kern = p.nt == 512        ? (few ? confidence_split_kernel<T, 512, 2, 4, true> : confidence_split_kernel<T, 512, 2, 4, false>)
+              : rows >= kManyRows ? confidence_split_kernel<T, 256, 2, 3, false>
+                                  : (few ? confidence_split_kernel<T, 256, 2, 4, true> : confidence_split_kernel<T, 256, 2, 4, false>);
   kern<<<unsigned(grid), p.nt, 0, st>>>(z, B, S, V, row_stride, batch_stride, suffix_len, p.max_log2, call_tag(), top1_id,
                                         top1_prob, margin, static_cast<unsigned long long *>(workspace));
 }

@@ -203,6 +203,10 @@ def test_unaligned_start_and_odd_lengths(lsp, oracle):
     (3, 150, 70001, [0, 1, 149]),       # rows of every alignment, an empty sequence, 150 rows in two or three pieces
     (70, 2, 20011, None),               # lengths of more sequences than a wave has lanes
     (300, 1, 17000, None),              # more sequences than the kernel counts: whole rows
+    (2, 37, 126464, [33, 32]),          # fp32 rows in four segments, bf16 in two
+    (1, 150, 20011, [100]),             # bf16 rows not halved
+    (4, 200, 100003, [61, 0, 7, 200]),  # lengths through the scalar cache
+    (8, 100, 60011, [100, 99, 0, 1, 100, 0, 0, 13]),
 ])
 def test_active_rows_cut_into_segments(lsp, oracle, dtype, B, S, V, n):
     """Rows are cut by the number of ACTIVE ones.  The workspace holds anything; ids and margins are those of whole
