@@ -91,7 +91,7 @@ def test_strided_rows(lsp, oracle):
 @pytest.mark.parametrize("rows", [1, 3, 40])
 def test_few_rows_split_over_workgroups(lsp, oracle, rows):
     """With few rows each row is cut into segments reduced by separate
-    workgroups and merged by a second kernel."""
+    workgroups; one of them merges the row."""
     V = 126464
     assert lsp.confidence_workspace_bytes(1, rows, V) > 0
     g = torch.Generator().manual_seed(rows)
@@ -200,7 +200,8 @@ def test_unaligned_start_and_odd_lengths(lsp, oracle):
     (1, 300, 20000, [5]),               # 4 segments a row
     (1, 256, 126464, [256]),            # as many rows as workgroups: whole
     (1, 256, 126464, [129]), (1, 256, 126464, [128]),   # first count that is not halved, last one that is
-    (3, 150, 70001, [0, 1, 149]),       # rows of every alignment, an empty sequence, 150 rows in two or three pieces
+    (3, 150, 70001, [0, 1, 149]),       # rows of every alignment, an empty sequence, whole
+    (3, 150, 70001, [0, 1, 99]),        # the same, halved
     (70, 2, 20011, None),               # lengths of more sequences than a wave has lanes
     (300, 1, 17000, None),              # more sequences than the kernel counts: whole rows
     (2, 37, 126464, [33, 32]),          # fp32 rows in four segments, bf16 in two
@@ -208,7 +209,7 @@ def test_unaligned_start_and_odd_lengths(lsp, oracle):
     (4, 200, 100003, [61, 0, 7, 200]),  # lengths through the scalar cache
     (8, 100, 60011, [100, 99, 0, 1, 100, 0, 0, 13]),
 ])
-def test_active_rows_cut_into_segments(lsp, oracle, dtype, B, S, V, n):
+def test_active_rows_cut_into_segments(lsp, dtype, B, S, V, n):
     """Rows are cut by the number of ACTIVE ones.  The workspace holds anything; ids and margins are those of whole
     rows bit for bit, and a probability differs by the order of one fp32 sum: rel 2e-6 is 16 roundings of a sum of
     at most 16 segments, each of which is itself within a few."""
@@ -216,11 +217,15 @@ def test_active_rows_cut_into_segments(lsp, oracle, dtype, B, S, V, n):
     z = (2 * torch.randn((B, S, V), generator=g)).to(dtype).cuda()
     n = torch.tensor(n) if n is not None else torch.randint(0, S + 1, (B,), generator=g)
     sl = n.to(torch.int32).cuda()
-    z[0, 0, V - 1] = z[0, 0, 7] = 15.0      # a tie between the first and the last segment
-    z[-1, 0, :V // 2] = -float("inf")       # segments without a finite entry
+    active = [(b, i) for b in range(B) for i in range(int(n[b]))]
+    tie, low, high = active[0], active[-1], active[len(active) // 2]
+    assert len({tie, low, high}) == 3
+    z[tie][V - 1] = z[tie][7] = 15.0        # a tie between the first and the last segment
+    z[low][:V // 2] = -float("inf")         # first segments without a finite entry
+    z[high][V // 2:] = -float("inf")        # last ones
     out = [(torch.full((B, S), -7, dtype=torch.int32, device="cuda"), torch.full((B, S), -7.0, device="cuda"),
             torch.full((B, S), -7.0, device="cuda")) for _ in range(3)]
-    # oracle on some rows of every case; whole rows (no workspace, where that is allowed) on all of them
+    # against fp64 sums of all active rows, and against whole rows (no workspace, where that is allowed)
     ws = torch.randint(0, 256, (lsp.confidence_workspace_bytes(B, S, V),), dtype=torch.uint8, generator=g).cuda()
     lsp.confidence(z, sl, out=out[0], workspace=ws)
     lsp.confidence(z, sl, out=out[1], workspace=ws)                 # left clean by the first
@@ -231,11 +236,12 @@ def test_active_rows_cut_into_segments(lsp, oracle, dtype, B, S, V, n):
     top2 = zz.topk(2, dim=-1).values
     first = (zz == top2[..., :1]).to(torch.int8).argmax(-1).to(torch.int32)     # argmax of a mask: the first of equals
     prob = 1 / (zz.double() - top2[..., :1].double()).exp().sum(-1)
+    assert out[0][0][tie] == 7 and out[0][2][tie] == 0 and out[0][0][low] >= V // 2 and out[0][0][high] < V // 2
     assert torch.equal(out[0][0][act], first[act])
     assert torch.equal(out[0][2][act], (top2[..., 0] - top2[..., 1])[act])
     assert ((out[0][1].double() - prob)[act] / prob[act]).abs().max() <= 2e-6
     if B * S >= 128:
-        lsp.confidence(z, sl, out=out[2])
+        lsp.confidence(z, sl, out=out[2])       # whole rows
         assert torch.equal(out[0][0], out[2][0]) and torch.equal(out[0][2], out[2][2])
 
 
