@@ -141,8 +141,9 @@ size_t lsp_confidence_workspace_bytes(int32_t B, int32_t S, int32_t V);
  * path.  suffix_len: device int32[B] or NULL (= all S rows active).
  * top1_id (int32), top1_prob (fp32), margin (fp32): device, [B,S] dense.
  * workspace: device, 16-byte aligned, lsp_confidence_workspace_bytes(B,S,V)
- * bytes of any content, for this call alone until it has run.  With it, long
- * rows are cut into segments for several workgroups when few rows are ACTIVE.
+ * bytes of any content, for this call alone until it has run (where another
+ * call writes to it meanwhile, rows may keep what their outputs held).  With it,
+ * long rows are cut into segments for several workgroups when few rows are ACTIVE.
  * Required (LSP_ERR_WORKSPACE otherwise) where B*S < 128 and V > 16384; without
  * one, other shapes keep a workgroup per row (the last bits of top1_prob follow
  * the cut; ids and margins do not).

@@ -287,8 +287,9 @@ def _conf_out(t):
 
 def confidence(logits, suffix_len=None, out=None, workspace=None):
     """lsp_confidence: logits [B,S,V] -> (top1_id int32, top1_prob f32, margin f32), [B,S].
-    workspace: confidence_workspace_bytes(B, S, V) bytes of any content; with it the rows that are
-    left of a large buffer are shared by all compute units."""
+    workspace: contiguous device memory of confidence_workspace_bytes(B, S, V) bytes and any content, for this call
+    alone until it has run (calls that may overlap, on other streams, need one each: a row whose notes another call
+    overwrites is not written); with it the rows that are left of a large buffer are shared by all compute units."""
     if _nat is not None:
         if out is None:
             out = _conf_out(logits)
@@ -306,14 +307,13 @@ def confidence(logits, suffix_len=None, out=None, workspace=None):
     _need_conf_out(out, B, S)
     _need("suffix_len", suffix_len, torch.int32, (B,), optional=True)
 
-
     def call(ws):
         wb = 0 if ws is None else ws.numel() * ws.element_size()
         return lib().lsp_confidence(_dtype(logits), _ptr(logits), B, S, V,
                                     ctypes.c_int64(logits.stride(1)), ctypes.c_int64(logits.stride(0)),
                                     _ptr(suffix_len), _ptr(out[0]), _ptr(out[1]), _ptr(out[2]),
                                     _ptr(ws), ctypes.c_size_t(wb), _stream())
-    rc = call(workspace if workspace is not None and workspace.is_cuda else None)
+    rc = call(workspace if workspace is not None and workspace.is_cuda and workspace.is_contiguous() else None)
     if rc == LSP_ERR_WORKSPACE:     # few long rows: needed, not only useful
         rc = call(torch.empty(lib().lsp_confidence_workspace_bytes(B, S, V), dtype=torch.uint8, device=logits.device))
     _check(rc, "lsp_confidence")

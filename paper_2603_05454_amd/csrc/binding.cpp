@@ -224,7 +224,7 @@ PyObject *confidence(PyObject *, PyObject *const *a, Py_ssize_t n) {
   ConfOut o;
   ORDINARY(conf_out(a[2], B, S, o));
   const at::Tensor *ws = a[3] == Py_None ? nullptr : device_tensor(a[3]);
-  ORDINARY(ws || a[3] == Py_None);
+  ORDINARY(ws ? ws->is_contiguous() : a[3] == Py_None);
   // (a call that needs a workspace and has none answers so, before any launch)
   const int32_t rc = unlocked(g.confidence, type, z->const_data_ptr(), int32_t(B), int32_t(S), int32_t(V), z->stride(1), z->stride(0),
                               data<int32_t>(sl), o.id, o.prob, o.margin, data<void>(ws), size_t(bytes_of(ws)), stream());

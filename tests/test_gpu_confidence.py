@@ -267,3 +267,21 @@ def test_segments_under_graph_replay(lsp):
         torch.cuda.synchronize()
         for a, b in zip(out, ref):
             assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("native", [True, False])
+@pytest.mark.parametrize("rows", [60, 200])
+def test_strided_workspace_is_not_written(lsp, rows, native, monkeypatch):
+    """A workspace that is one column of something else: the call does without it, and what lies between stays."""
+    lsp.lib()
+    if not native:
+        monkeypatch.setattr(lsp, "_nat", None)
+    V = 40000
+    z = torch.randn((1, rows, V), generator=torch.Generator().manual_seed(rows)).to(torch.bfloat16).cuda()
+    sl = torch.tensor([20], dtype=torch.int32, device="cuda")
+    held = torch.full((lsp.confidence_workspace_bytes(1, rows, V), 4), 77, dtype=torch.uint8, device="cuda")
+    ids, prob, margin = lsp.confidence(z, sl, workspace=held[:, 0])
+    assert torch.all(held == 77)
+    zz = z[0, :20].float()
+    top2 = zz.topk(2, dim=-1).values
+    assert torch.equal(zz.gather(1, ids[0, :20, None].long()), top2[:, :1]) and torch.equal(margin[0, :20], top2[:, 0] - top2[:, 1])
