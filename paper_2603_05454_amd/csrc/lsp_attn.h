@@ -91,10 +91,12 @@ struct Place {
   bool valid;
 };
 // Units are numbered over layers, sequences and KV heads.  When they are few, each is cut into
-// 2^spread pieces (runs of its (head, tile) list) so that every XCD gets as many: four KV heads of
+// 2^spread pieces so that every XCD gets as many: four KV heads of
 // one sequence kept four of the eight XCDs idle (28 query heads, one layer, prefix 4096, suffix
 // 1024: 234 us whole, 139 us in two pieces; fp32, 8 query heads of 64 on one KV head, same lengths:
-// 905 us whole, 122 in eight).
+// 905 us whole, 122 in eight).  A piece takes every 2^spread-th of the unit's (tile, head) list, so that the live tiles, which are
+// the first ones, are shared evenly; as runs of that list the last pieces' XCDs had none (28/4 heads, 5 x 400 rows on 3500 with
+// 128 active 80 -> 64 us, with 300 138 -> 90, all 156 -> 122).
 template <bool GROUPS = true>  // false: groups of one unit
 __device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
   Place p;
@@ -107,7 +109,7 @@ __device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
   int wu = GROUPS ? quotient(r, a.by_unit_group) : r, layer = 0;
   int unit = (grp * G + r - wu * G) * 8 + (n & 7);
   if (a.spread > 0) {
-    wu += (unit & ((1 << a.spread) - 1)) * chunk;
+    wu = (wu << a.spread) + (unit & ((1 << a.spread) - 1));
     unit >>= a.spread;
   }
   const int units = a.B * a.Hkv;
