@@ -27,6 +27,7 @@ struct AttnArgs {
   int32_t rep, chunk, spread, layers, unit_group;  // placement of the workgroups (place_grid); read first, with the line above
   Div by_group, by_unit_group, by_units, by_heads, by_rep;  // its divisors: unit_group * chunk, unit_group, B * Hkv, Hkv, rep
   int32_t D, C;
+  int32_t spread_limit;  // head_dim 128, contiguous cache: blocks of 32 rows in a launch that are spread (launch_pipe)
   int32_t rounding;  // head_dim 128, contiguous cache: which reference short tiles' probabilities are rounded against (Reference)
   float scale;
   int64_t qs[3], ks[3], cs[3], os[3];  // element strides: batch, row, head
@@ -127,8 +128,10 @@ __device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
   return p;
 }
 // Fields of that placement in `a`, and its number of workgroups.  Units are cut only where an XCD would get more than
-// `enough` workgroups.  resident: workgroups that run at once on an XCD (0: groups as above whatever their number).
-inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile, int resident = 0, int unit_group = kUnitGroup, int enough = 0) {
+// `enough` workgroups.  resident: workgroups that run at once on an XCD (0: groups as above whatever their number).  whole: whether
+// the launch is one group for that reason.
+inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile, int resident = 0, int unit_group = kUnitGroup, int enough = 0,
+                          bool *whole = nullptr) {
   const int64_t QT = (a.S + qtile - 1) / qtile, per_unit = a.Hq / a.Hkv * QT;
   a.layers = layers.n > 0 ? layers.n : 1;
   const int64_t units = int64_t(a.layers) * a.B * a.Hkv;
@@ -141,6 +144,7 @@ inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile, int 
   const int64_t pieces8 = ((units << a.spread) + 7) / 8;  // pieces per XCD
   const bool one_group = 2 * pieces8 * chunk <= 3 * resident;
   const int64_t G = pieces8 < unit_group || one_group ? pieces8 : unit_group;
+  if (whole != nullptr) *whole = one_group;
   a.unit_group = int32_t(G);
   a.by_group = div_by(G * chunk);
   a.by_unit_group = div_by(G);
@@ -149,6 +153,67 @@ inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile, int 
   a.by_rep = div_by(a.rep);
   return (pieces8 + G - 1) / G * G * chunk * 8;
 }
+
+// ---- which kernel: bf16, head_dim 128, contiguous cache --------------------------------
+// A probability is rounded to bf16 relative to the running reference of its pass over the keys, so the last bits of a row follow
+// how the keys are divided between references.  What the passes begin with is a matter of the launch's buffers for tiles of up to 32
+// rows and the spread ones, whichever workgroups compute them:
+enum Reference : int32_t {
+  kEightParts,  // fewer than 512 tiles of 32 rows: key block j belongs to part j % 8
+  kFourParts,   // fewer than 1024: j % 4
+  kOnePass,     // suffix buffers of up to 128 rows: every wave begins with the reference of the first key block
+  kTiles256,    // longer ones: with that of a ragged end, and for the last up to 32 rows behind a multiple of 256 eight parts
+};
+// (A wave moves its own reference on when a maximum exceeds it by 8 octaves, and taller tiles are one pass by all waves: there the last
+// bits may follow the active lengths too.)
+struct Contiguous128 {
+  enum Kernel { kSplit8, kSplit4TwoParts, kSplit4, kTiles128Rows, kFineTiles128Rows, kTiles256Rows } kernel;
+  Reference rounding;
+};
+// The host knows the buffers (S rows, C cache rows; heads: of all sequences and layers), not the active lengths.
+// us per call, one layer of 32/32 or 28/4 heads unless said otherwise, B x S rows on P cached ones:
+//  * more than 128 tiles of 128 rows: the hand-scheduled loop with four waves, two workgroups to a compute unit.  Before
+//    it there were tiles of 256 rows, the shared-tile kernel for S <= 128 and the key split below 256 tiles of 128:
+//    3 x 256 on 800 33.8 -> 21.6, 28/4 heads 1 x 1024 on 1024 64 -> 35, 8 x 128 on 2000 97 -> 61; 32 layers:
+//    8 x 128 with 20 active on 4000 4333 -> 2994, 8 x 100 on 400 615 -> 524, 1 x 256 on 512 148 -> 139.
+//    Not everywhere: 32 layers of 2 x 162 on 1430 447 when full and 425 with eight waves (353 and 363 with 113 active, 273
+//    and 281 with 24), 3 x 140 on 1500 with 90 active 27 and 20 with the key split (28 and 32 with 128);
+//  * of these, eight waves with 256-row tiles, which fetch every K/V block for twice as many rows: long caches and at
+//    least four rounds of them (32 layers, 8 x 1024 on 4096: 19.9 ms, with four waves 20.6; 4 x 700 on 3000 5.4 and 5.6);
+//    one round that is nearly full (28/4 heads, 4 x 497 on 1021: 47.3 and 48.6; 2 x 1024 on 1800: 87 and 89, but 61 and 43 with
+//    256 active); and at least two rounds of up to 256
+//    heads, where a compute unit is left with one workgroup when the sequences are down to their last rows (28/4
+//    heads, 8 x 1024 on 1000: 239 and 228 when full, 20.5 and 28.3 with 30 rows left).  Otherwise
+//    what the smaller tiles save in part-filled ones and in rounds weighs more (3 x 1024 on 4000, one round and a
+//    half: 254 and 231; 32 layers, 8 x 600 on 600, 28/4 heads: 3025 and 2903);
+//  * fewer: the key split, eight ways while its workgroups are at most one to a compute unit, four ways beyond, where
+//    two fit one (1 x 384 on 800: 18.9 four ways, 23.4 eight, 21.1 with 128-row tiles).
+inline Contiguous128 contiguous128(int64_t heads, int32_t S, int32_t C) {
+  auto tiles = [&](int rows) { return heads * ((S + rows - 1) / rows); };
+  const int64_t rows = heads * S;
+  Contiguous128 r;
+  r.rounding = rows >= 32768 ? (S > 128 ? kTiles256 : kOnePass) : rows >= 16384 ? kFourParts : kEightParts;
+  if (tiles(128) > 128) {
+    const int64_t wide = r.rounding == kTiles256 ? tiles(256) : 0;
+    if ((wide > 192 && wide <= 256) || (wide >= 512 && heads <= 256) || (wide >= 1024 && C > 2048)) r.kernel = Contiguous128::kTiles256Rows;
+    else r.kernel = r.rounding == kFourParts && S > 128 ? Contiguous128::kFineTiles128Rows : Contiguous128::kTiles128Rows;
+  } else {
+    r.kernel = tiles(32) <= 256            ? Contiguous128::kSplit8
+               : r.rounding == kEightParts ? Contiguous128::kSplit4TwoParts
+                                           : Contiguous128::kSplit4;
+  }
+  return r;
+}
+// Where few blocks of 32 rows are left in a whole launch, workgroups take one each and share its keys (one layer, 45 of 640 rows of
+// 64 heads on 1000 cached ones: 25.6 -> 19.7 us).  That is up to about one to a compute unit.  Beyond, two share one, and each streams
+// its head's whole K/V: 32/32 heads, 4 x 640 rows on 3500 with 128 active 59 us in tiles and 97 in blocks, 8 x 140 on 700
+// with 50 active 22.5 and 31.7; 3 x 640 on 3500 with 90 active 55 and 38.  Up to two a compute unit it pays
+//  * where the heads of a group stream the same K/V (28/4 heads, 6 x 400 on 1500 with 90 active 34.5 in tiles, 29.2 in blocks; 9 x
+//    320 with 50 active 34.8 and 28.6), but not with a grid of blocks (FINE; 3 x 250 on 3500 with 200 active 54 and 62),
+//  * where the launch is placed in groups, so that live tiles share a compute unit while others have none (5 x 640 on 1500 with
+//    90 active 45 and 38).
+// What it still takes: 3 x 400 rows of 32/32 heads on 100 with 128 active 15.2 in tiles, 13.4 in blocks; on longer caches the other way.
+inline int32_t spread_limit(int rep, bool fine, bool one_group) { return fine || (rep == 1 && one_group) ? 288 : 512; }
 
 // Cache row that holds key t (t < P_b) of sequence b.
 template <bool GATHER>

@@ -220,22 +220,11 @@ constexpr int kShortSuffix = 64;  // sequences with at most this many active row
 // without a query, a tile with two active waves is faster than two key-split workgroups - 38 against
 // 50 us per C5 layer - while a tile with one active wave is slower than one key-split workgroup)
 constexpr int kShortSuffixPipe = 32;
-// A probability is rounded to bf16 relative to the running reference of its pass over the keys, so the last bits of a row follow
-// how the keys are divided between references.  That stays a matter of the launch's shape alone (buffers, not active
-// rows), whichever workgroups compute a tile of up to 32 rows or the spread ones:
-enum Reference : int32_t {
-  kEightParts,  // fewer than 512 tiles of 32 rows: key block j belongs to part j % 8
-  kFourParts,   // fewer than 1024: j % 4
-  kOnePass,     // suffix buffers of up to 128 rows: one pass from the first key block on
-  kTiles256,    // longer ones: one pass that begins with the ragged ends, and for the last up to 32 rows behind a multiple of 256 eight parts
-};
 // K/V that no cache can hold (a quarter more than the last-level cache) and that this one workgroup reads, once, are loaded
 // with the non-temporal hint: 32 layers of 32/32 heads, 16 x 21 rows of 1536 keys 2242 -> 2130 us (6.1 TB/s), 8 x 20 of 1128
 // 832 -> 741, 2 x 16 of 4016 717 -> 664.  With a query group's heads on one KV head the hint costs a factor (284 -> 523), in
 // the generated loops it gains and loses as often (32 layers, 128 rows on 512 98 -> 93, 8 x 100 on 400 509 -> 541).
 constexpr int64_t kStreamBytes = int64_t(320) << 20;
-constexpr int kSpreadBlocks = 512;  // blocks of 32 rows in the whole launch
-
 // Final step shared by both kernels: the WK partial results of every query
 // block are combined through LDS (each wave's region holds O^T as [query][d]
 // fp32 plus m and l), normalised and stored as 16-byte bf16 chunks.
@@ -1062,7 +1051,7 @@ int32_t launch_ring_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
 // WM = 8: same tile (256 queries, 8 waves of 32, two waves per SIMD), same LDS ring and the
 // same arithmetic as attn_bf16_ring_kernel.  WM = 4: 128 queries, a ring of five stages and so two
 // workgroups per compute unit, whose prologues, merges and barriers cover each other, and half the rows of padding
-// (which to take is measured at dispatch_contiguous128).  What differs is who fixes the issue
+// (which to take is measured at contiguous128).  What differs is who fixes the issue
 // order.  The block loop is one generated inline-asm statement (gen_attn_pipe.py
 // describes its pipeline, register map and synchronisation): a one-block software
 // pipeline per wave in which the soft-max of block j is issued between the matrix
@@ -1073,7 +1062,11 @@ int32_t launch_ring_g(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
 // rows: at most two blocks per tile) are done first, by compiler-scheduled code with
 // the same fragment layout, on the same running (m, l, O) state.
 typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
-template <int WM>
+// FINE: the grid has a workgroup for every 32 rows, not for every 128, for launches whose blocks of 32 rows all find a place at once even
+// when tiles do not (16 384 to 32 767 rows): a sequence's blocks are then spread when there are more of them than tiles
+// (28/4 heads, 2 x 320 rows on 3500 with 128 active 52 -> 29 us, 1 x 640 with 200 active 58 -> 31; the key split that these
+// launches once were 29 and 32).  The workgroups too many leave at once, behind the others.
+template <int WM, bool FINE>
 __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_pipe_kernel(AttnArgs a_in,
                                                                                                            AttnLayers layers) {
   AttnArgs a = a_in;
@@ -1083,33 +1076,40 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   constexpr int TILE = 32 * D * 2, VBASE = NS * TILE;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
-  const Place pl = place(a, 32 * WM);
+  const Place pl = place(a, FINE ? 32 : 32 * WM);
   if (!pl.valid) return;
   for_layer(a, layers, pl.layer);
-  const int b = pl.b, g = pl.g, h = pl.h, q0 = pl.q0;
+  const int b = pl.b, g = pl.g, h = pl.h, q0 = FINE ? WM * pl.q0 : pl.q0;
   const int N = min(max(a.suffix_len[b], 0), a.S);
   const int P = min(max(a.prefix_len[b], 0), a.C);
   // A tile with at most 32 active rows - a sequence down to its last rows, or the tail of a longer
   // suffix that ends just past a multiple of the tile - would keep all waves but one idle for the whole key
   // range: its one block of queries goes to the key-split body (as in attn_bf16_ring_kernel), which
-  // shares the KEY range between the waves instead.  The same where so few tiles are left of the whole launch that
-  // workgroups of 32 rows still find a compute unit each: the workgroups of the tiles that have ended take them
-  // (one layer, 32 heads, 200 of 1024 rows on 4000 cached ones: 102 us with one tile of 256, 40 so).
+  // shares the KEY range between the waves instead.  The same where few are left in the whole launch (spread_limit; one
+  // layer, 32 heads, 200 of 1024 rows on 4000 cached ones: 102 us with one tile of 256, 40 so).
   const int blocks = (N + 31) >> 5;
-  const bool spread = WM == 4 && blocks <= (a.S + 32 * WM - 1) / (32 * WM) && int64_t(blocks) * a.B * a.Hq * a.layers <= kSpreadBlocks;
+  const bool spread = WM == 4 && (FINE || blocks <= (a.S + 32 * WM - 1) / (32 * WM)) &&
+                      int64_t(blocks) * a.B * a.Hq * a.layers <= a.spread_limit;
   const int qs = spread ? q0 / WM : q0;
   if (qs >= N) return;
   if (spread || N - q0 <= kShortSuffixPipe) {
-    const bool one_pass = a.rounding == kOnePass || (a.rounding == kTiles256 && N - (qs & ~255) > kShortSuffixPipe);
+    const bool one_pass = !FINE && (a.rounding == kOnePass || (a.rounding == kTiles256 && N - (qs & ~255) > kShortSuffixPipe));
     RefKeys ref = {0, 0};
     if (one_pass) {
       ref.count = min(32, P + N);
       if (a.rounding == kTiles256 && (P & 31)) ref = {P & ~31, P & 31};
       else if (a.rounding == kTiles256 && (N & 31)) ref = {P + (N & ~31), N & 31};
     }
-    key_split_body<D, 1, WM, false, 8 / WM>(a, b, g, h, qs, N, P, smem,
-                                            a.rep == 1 && N <= 32 && int64_t(P + N) * a.Hkv * (4 * D) * a.B * a.layers >= kStreamBytes,
-                                            one_pass || a.rounding == kFourParts ? 1 : 8 / WM, ref);
+    // (FINE has the plain body: what the other one decides in its loop costs a workgroup that has its compute unit to itself
+    // a fifth, 64 of 640 rows of 28/4 heads on 3500 35.3 and 28.4 us; both in one kernel cost 5 % where caches are short, 32 layers of 4 x 21 on 81
+    // 68.3 and 72.1)
+    if constexpr (FINE) {
+      key_split_body<D, 1, WM, false>(a, b, g, h, qs, N, P, smem);
+    } else {
+      const bool once = a.rep == 1 && N <= 32 && int64_t(P + N) * a.Hkv * (4 * D) * a.B * a.layers >= kStreamBytes;
+      const bool whole = WM == 8 || one_pass || a.rounding == kFourParts;
+      key_split_body<D, 1, WM, false, 8 / WM>(a, b, g, h, qs, N, P, smem, once, whole ? 1 : 8 / WM, ref);
+    }
     return;
   }
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1255,9 +1255,11 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   }
 }
 
-template <int WM>
+template <int WM, bool FINE = false>
 int32_t launch_pipe(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
-  const int64_t nwg = place_grid(a, layers, 32 * WM, 32 * 8 / WM);
+  bool one_group;
+  const int64_t nwg = place_grid(a, layers, FINE ? 32 : 32 * WM, FINE ? 1 << 20 : 32 * 8 / WM, kUnitGroup, 0, &one_group);  // FINE: always one
+  a.spread_limit = spread_limit(a.rep, FINE, one_group);
   if (nwg > kMaxGrid) {
     set_error("lsp_attn_step: launch of %lld workgroups is too large", (long long)nwg);
     return LSP_ERR_UNSUPPORTED;
@@ -1265,7 +1267,7 @@ int32_t launch_pipe(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
   const size_t lds_ring = size_t(WM == 8 ? 8 : 5) * 2 * 32 * 256;
   const size_t lds_split = WM * size_t(Geo<128>::WAVE_LDS) + 32 * size_t(Geo<128>::KPITCH) + 32 * sizeof(float);
   const size_t lds = lds_ring > lds_split ? lds_ring : lds_split;
-  auto kern = attn_bf16_pipe_kernel<WM>;
+  auto kern = attn_bf16_pipe_kernel<WM, FINE>;
   static std::atomic<uint64_t> configured{0};
   if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured, "lsp_attn_step: hipFuncSetAttribute")) return rc;
   kern<<<grid_of(nwg), 64 * WM, lds, st>>>(a, layers);
@@ -1279,34 +1281,17 @@ int32_t launch(const AttnArgs &a, const AttnLayers &layers, hipStream_t st) {
   return a.cache_rows ? launch_g<D, WM, WK, true>(a, layers, st) : launch_g<D, WM, WK, false>(a, layers, st);
 }
 
-// Contiguous cache, head_dim 128.  The host knows the buffers (S rows, C cache rows), not the active lengths.
-// us per call, one layer of 32/32 or 28/4 heads unless said otherwise, B x S rows on P cached ones:
-//  * more than 128 tiles of 128 rows: the hand-scheduled loop with four waves, two workgroups to a compute unit.  Before
-//    it there were tiles of 256 rows, the shared-tile kernel for S <= 128 and the key split below 256 tiles of 128:
-//    3 x 256 on 800 33.8 -> 21.6, 28/4 heads 1 x 1024 on 1024 64 -> 35, 8 x 128 on 2000 97 -> 61; 32 layers:
-//    8 x 128 with 20 active on 4000 4333 -> 2994, 8 x 100 on 400 615 -> 524, 1 x 256 on 512 148 -> 139;
-//  * of these, eight waves with 256-row tiles, which fetch every K/V block for twice as many rows: long caches and at
-//    least four rounds of them (32 layers, 8 x 1024 on 4096: 19.9 ms, with four waves 20.6; 4 x 700 on 3000 5.4 and 5.6);
-//    one round that is nearly full (28/4 heads, 4 x 497 on 1021: 47.3 and 48.6); and at least two rounds of up to 256
-//    heads, where a compute unit is left with one workgroup when the sequences are down to their last rows (28/4
-//    heads, 8 x 1024 on 1000: 239 and 228 when full, 20.5 and 28.3 with 30 rows left).  Otherwise
-//    what the smaller tiles save in part-filled ones and in rounds weighs more (3 x 1024 on 4000, one round and a
-//    half: 254 and 231; 32 layers, 8 x 600 on 600, 28/4 heads: 3025 and 2903);
-//  * fewer: the key split, eight ways while its workgroups are at most one to a compute unit, four ways beyond, where
-//    two fit one (1 x 384 on 800: 18.9 four ways, 23.4 eight, 21.1 with 128-row tiles).
 int32_t dispatch_contiguous128(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
-  const int64_t heads = int64_t(a.B) * a.Hq * (layers.n > 0 ? layers.n : 1);
-  auto tiles = [&](int rows) { return heads * ((a.S + rows - 1) / rows); };
-  const int64_t rows = heads * a.S;
-  a.rounding = rows >= 32768 ? (a.S > 128 ? kTiles256 : kOnePass) : rows >= 16384 ? kFourParts : kEightParts;
-  if (tiles(128) > 128) {
-    const int64_t wide = a.rounding == kTiles256 ? tiles(256) : 0;
-    if ((wide > 192 && wide <= 256) || (wide >= 512 && heads <= 256) || (wide >= 1024 && a.C > 2048))
-      return launch_pipe<8>(a, layers, st);
-    return launch_pipe<4>(a, layers, st);
+  const Contiguous128 r = contiguous128(int64_t(a.B) * a.Hq * (layers.n > 0 ? layers.n : 1), a.S, a.C);
+  a.rounding = r.rounding;
+  switch (r.kernel) {
+    case Contiguous128::kTiles256Rows: return launch_pipe<8>(a, layers, st);
+    case Contiguous128::kTiles128Rows: return launch_pipe<4>(a, layers, st);
+    case Contiguous128::kFineTiles128Rows: return launch_pipe<4, true>(a, layers, st);
+    case Contiguous128::kSplit8: return launch_g<128, 1, 8, false>(a, layers, st);
+    case Contiguous128::kSplit4TwoParts: return launch_g<128, 1, 4, false, 2>(a, layers, st);
+    default: return launch_g<128, 1, 4, false>(a, layers, st);
   }
-  if (tiles(32) <= 256) return launch_g<128, 1, 8, false>(a, layers, st);
-  return a.rounding == kEightParts ? launch_g<128, 1, 4, false, 2>(a, layers, st) : launch_g<128, 1, 4, false>(a, layers, st);
 }
 
 template <int D>

@@ -7,6 +7,7 @@ from collections import Counter
 import pytest
 
 from paper_2603_05454_amd.build import CSRC, ROOT
+from test_gpu_attention import MOVING, NEAR_THE_END, SPREAD, TILES
 
 STUB = r"""
 #pragma once
@@ -32,11 +33,16 @@ using std::max;
 """
 MAIN = r"""
 #include <stdio.h>
+#include <stdlib.h>
 #include "lsp_attn.h"
 namespace lsp { void set_error(const char *, ...) {} }
-int main() {
+int main(int argc, char **argv) {
   using namespace lsp;
   int L, B, S, Hq, Hkv, qtile, resident, group, enough;
+  if (argc > 1) {  // heads, S, C -> kernel, rounding
+    const Contiguous128 r = contiguous128(atoll(argv[1]), atoi(argv[2]), atoi(argv[3]));
+    return printf("%d %d\n", int(r.kernel), int(r.rounding)), 0;
+  }
   while (scanf("%d %d %d %d %d %d %d %d %d", &L, &B, &S, &Hq, &Hkv, &qtile, &resident, &group, &enough) == 9) {
     AttnArgs a = {};
     AttnLayers layers = {};
@@ -92,3 +98,12 @@ def test_every_tile_once_and_live_ones_on_all_xcds(program, form):
         for q in tiles:
             live = Counter(w % 8 for w, _, _, _, _, q0 in placed if q0 <= q)
             assert max(live.values()) - min(live[x] for x in range(8)) <= pieces, (q, live)
+
+
+KERNELS = ["split8", "split4x2", "split4", "128", "128 fine", "256"]
+
+
+@pytest.mark.parametrize("heads,S,C,kernel", [(layers * B * Hq, S, C, kernel) for layers, B, Hq, S, C, kernel in TILES + SPREAD + MOVING + NEAR_THE_END])
+def test_shapes_of_the_gpu_tests_reach_the_kernel_they_name(program, heads, S, C, kernel):
+    out = subprocess.run([program, str(heads), str(S), str(C)], capture_output=True, text=True, check=True).stdout.split()
+    assert KERNELS[int(out[0])] == kernel

@@ -8,6 +8,13 @@ import workloads as W
 pytestmark = pytest.mark.gpu
 TOL = {"f32": 1e-5, "bf16": 2e-2}
 
+# Shapes of bf16 calls at head_dim 128 with a contiguous cache, and the kernel that each is there for (test_attn_placement.py
+# asks the library's rule): layers, B, Hq, S, C, kernel
+TILES = [(1, 32, 4, 512, 800, "256"), (1, 32, 6, 512, 800, "128"), (32, 32, 2, 512, 2100, "256"), (32, 32, 2, 512, 2048, "128")]
+SPREAD = [(1, 8, 4, 600, 700, "128 fine"), (1, 16, 9, 300, 400, "128"), (1, 4, 27, 150, 300, "128"), (1, 8, 32, 20, 2600, "128")]
+MOVING = [(1, 8, 16, 320, 256, "256"), (1, 8, 18, 320, 256, "128"), (1, 8, 4, 600, 256, "128 fine")]
+NEAR_THE_END = [(1, 4, 4, 545, 520, "split4x2"), (1, 32, 5, 300, 308, "128")]
+
 
 @pytest.fixture(scope="module")
 def lsp():
@@ -123,7 +130,7 @@ def test_f32_scores_of_minus_infinity(lsp, oracle, lo, hi):
     assert torch.isfinite(ref).all() and (got - ref).abs().max().item() <= TOL["f32"]
 
 
-@pytest.mark.parametrize("dtype,B,Hq,S", [("f32", 2, 2, 150), ("bf16", 2, 2, 150), ("bf16", 8, 16, 320)])
+@pytest.mark.parametrize("dtype,B,Hq,S", [("f32", 2, 2, 150), ("bf16", 2, 2, 150)] + [("bf16", B, Hq, S) for _, B, Hq, S, _, _ in MOVING])
 def test_large_scores_and_moving_maximum(lsp, oracle, dtype, B, Hq, S):
     """Scores spanning hundreds of units whose maximum keeps rising along the key
     axis (the soft-max reference has to move again and again), rows where a single
@@ -467,14 +474,14 @@ def test_more_layers_than_one_launch_holds(lsp, oracle, S, Hq):
             assert (got[rows[:, 0].long(), rows[:, 1].long(), rows[:, 2].long()] - ref).abs().max().item() <= TOL["bf16"], l
 
 
-@pytest.mark.parametrize("layers,C,what", [(1, 800, "128-row tiles"), (32, 2100, "256-row tiles"), (32, 2048, "128-row tiles")])
-def test_tile_of_the_hand_scheduled_loop(lsp, oracle, layers, C, what):
+@pytest.mark.parametrize("layers,B,Hq,S,C,kernel", TILES)
+def test_tile_of_the_hand_scheduled_loop(lsp, oracle, layers, B, Hq, S, C, kernel):
     """Both workgroup sizes of the hand-scheduled loop (cache capacity and number of tiles choose) on the same sequences:
     last tiles with 32, 33 and every multiple of 32 rows, up to 20 blocks of cache before the suffix, ragged ends of both,
     empty prefixes, single keys.  Every active row of every layer (all layers have the same operands)."""
     lens = [256 + 32 * k - d for k in range(1, 9) for d in (0, 5)] + [1, 32, 33, 64, 65, 96, 97, 127, 128, 129, 160, 161, 255, 0, 290, 512]
-    B = len(lens)
-    w = W.scaled(W.C2, B=B, S=512, P=640, C=C, Hq=4 if layers == 1 else 2, Hkv=2 if layers == 1 else 1, D=128, seed=1234)
+    assert B == len(lens)
+    w = W.scaled(W.C2, B=B, S=S, P=640, C=C, Hq=Hq, Hkv=2 if layers == 1 else 1, D=128, seed=1234)
     pl = torch.tensor([0 if b % 11 == 10 else 32 * (b % 21) + (0, 1, 31, 17)[b // 7 % 4] * (b % 3 > 0) for b in range(B)], dtype=torch.int32).clamp_(max=C)
     sl = torch.tensor(lens, dtype=torch.int32)
     kv = W.make_layer_kv(w, 0, prefix_len=pl)
@@ -495,12 +502,13 @@ def test_tile_of_the_hand_scheduled_loop(lsp, oracle, layers, C, what):
 
 
 @pytest.mark.parametrize("first", [True, False])
-@pytest.mark.parametrize("B,S,H,N,P", [(4, 545, 4, 545, 512), (32, 300, 5, 20, 300)])
-def test_values_near_the_end_of_the_range(lsp, oracle, B, S, H, N, P, first):
+@pytest.mark.parametrize("shape,N,P", zip(NEAR_THE_END, (545, 20), (512, 300)))
+def test_values_near_the_end_of_the_range(lsp, oracle, shape, N, P, first):
     """Values of 2^100 whose scores lead by 58 octaves in one half of the key blocks: a wave takes blocks j % 8 = w and then
     w + 4, and what it has summed of the one must not leave fp32's range when the other sets its reference.  Both
     kernels that do so: four-way key split, and short tiles of the four-wave workgroups."""
-    w = W.scaled(W.C2, B=B, S=S, P=P, C=P + 8, Hq=H, Hkv=H, D=128, seed=77)
+    _, B, H, S, C, _ = shape
+    w = W.scaled(W.C2, B=B, S=S, P=P, C=C, Hq=H, Hkv=H, D=128, seed=77)
     pl, sl = torch.full((B,), P, dtype=torch.int32), torch.full((B,), N, dtype=torch.int32)
     kv = W.make_layer_kv(w, 0, prefix_len=pl)
     kv["q"].fill_(1.0)
@@ -515,3 +523,34 @@ def test_values_near_the_end_of_the_range(lsp, oracle, B, S, H, N, P, first):
     act = ~torch.isnan(ref)
     assert torch.isfinite(got[act]).all()
     assert ((got[act] - ref[act]) * 2.0 ** -100).abs().max().item() <= TOL["bf16"]
+
+
+@pytest.mark.parametrize("shape,Hkv,lens", [
+    (SPREAD[0], 4, [1, 32, 33, 64, 250, 288, 289, 600]),    # a grid of blocks: up to 288 of them in the launch are spread, 289 rows are tiles
+    (SPREAD[0], 2, [600, 0, 31, 97, 128, 129, 287, 257]),
+    (SPREAD[1], 9, [1, 31, 32, 33, 48, 63, 64, 65, 96, 97, 128, 129, 160, 0, 299, 300]),    # 64 rows spread, 65 a tile
+    (SPREAD[1], 3, [1, 31, 32, 33, 48, 63, 64, 65, 96, 97, 128, 129, 160, 0, 299, 300]),    # 96 and 97
+    (SPREAD[2], 27, [33, 64, 65, 150]),                     # two parts a wave
+])
+def test_blocks_spread_over_workgroups(lsp, oracle, shape, Hkv, lens):
+    """Workgroups of ended tiles, or of a grid of blocks, take 32 rows each where few are left: both sides of every
+    limit in one call, odd prefixes, every active row."""
+    _, B, Hq, S, C, _ = shape
+    w = W.scaled(W.C2, B=B, S=S, P=C, C=C, Hq=Hq, Hkv=Hkv, D=128, seed=31 + Hkv)
+    pl = torch.tensor([(0, C, C - 31, 97, 64, 1, C - 1, 33)[b % 8] for b in range(B)], dtype=torch.int32)
+    _check_full(lsp, oracle, w, pl, torch.tensor(lens, dtype=torch.int32))
+
+
+def test_streamed_cache(lsp, oracle):
+    """K/V of more than 320 MB that one workgroup reads, once, are loaded past the caches; sampled rows."""
+    _, B, H, S, C, _ = SPREAD[3]
+    w = W.scaled(W.C2, B=B, S=S, P=C, C=C, Hq=H, Hkv=H, D=128, seed=3)
+    pl, sl = torch.full((B,), C, dtype=torch.int32), torch.tensor([20, 1, 19, 7, 20, 0, 13, 20], dtype=torch.int32)
+    assert all((C + int(n)) * H * 512 * B >= 320 << 20 for n in sl)
+    kv = W.make_layer_kv(w, 0, prefix_len=pl)
+    got = _run(lsp, kv, pl, sl)
+    rows = torch.tensor([[b, i, h] for b in range(B) for i in {0, int(sl[b]) - 1} if 0 <= i < sl[b] for h in (0, 13, 31)], dtype=torch.int32)
+    ref = oracle.attention(**kv, prefix_len=pl, suffix_len=sl, rows=rows)
+    assert (got[rows[:, 0].long(), rows[:, 1].long(), rows[:, 2].long()] - ref).abs().max().item() <= TOL["bf16"]
+    for b in range(B):
+        assert torch.all(got[b, int(sl[b]):] == 123.0)
