@@ -1304,12 +1304,10 @@ int32_t dispatch(const AttnArgs &a, const AttnLayers &layers, hipStream_t st) {
   if constexpr (D == 128) {
     if (!a.cache_rows) return dispatch_contiguous128(a, layers, st);
     if (rows / 128 >= 256) return a.S > 128 ? launch_ring_g<8, 4, true>(a, layers, st) : launch_tile_g<D, 4, 2, 4, true>(a, layers, st);
-    if (rows / 64 >= 512) return launch_g<D, 2, 2, true>(a, layers, st);
     return rows / 32 >= 512 ? launch_g<D, 1, 4, true>(a, layers, st) : launch_g<D, 1, 8, true>(a, layers, st);
   } else {
     if (rows / 128 >= 256)
       return a.cache_rows ? launch_tile_g<D, 4, 2, 4, true>(a, layers, st) : launch_tile_g<D, 4, 2, 4, false>(a, layers, st);
-    if (rows / 64 >= 512) return launch<D, 2, 2>(a, layers, st);
     if (rows / 32 >= 512) return launch<D, 1, 4>(a, layers, st);
     return launch<D, 1, 8>(a, layers, st);
   }
