@@ -78,7 +78,7 @@ def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
     attn_out = None
     events = []
     zbuf = step_graph = None
-    lengths = LengthPoll()
+    lengths = None
     ws = None   # workspace of the reduction or the fused output head: allocated by the first (eager) step, then reused
 
     def one_step(z):
@@ -107,7 +107,11 @@ def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
     while True:
         if (steps - first) % poll == 0:
             # positions left, and whether a sequence that has some committed nothing
-            left, stalled = lengths(suffix_len, None if out is None else out["commit_len"])
+            if out is None and not (suffix_len.is_cuda and suffix_len.dtype == torch.int32 and suffix_len.is_contiguous()):
+                left, stalled = int(suffix_len.max().item()), False     # nothing to do is no error, whatever the lengths' type
+            else:
+                lengths = lengths or LengthPoll()
+                left, stalled = lengths(suffix_len, None if out is None else out["commit_len"])
             if left == 0:
                 break
             if stalled and min_commit >= 1:
