@@ -342,7 +342,8 @@ PyObject *commit(PyObject *, PyObject *const *a, Py_ssize_t n) {
   }
   return status(g.commit, &d, data<float>(margin), data<int32_t>(id), data<uint32_t>(bm), static_cast<const void *const *>(tab[0].view.buf),
                 static_cast<const void *const *>(tab[1].view.buf), static_cast<void *const *>(tab[2].view.buf),
-                static_cast<void *const *>(tab[3].view.buf), data<int32_t>(tokens), data<int32_t>(pl), data<int32_t>(sl), data<uint8_t>(mask), data<int32_t>(raw), data<int32_t>(snapped), data<int32_t>(len),
+                static_cast<void *const *>(tab[3].view.buf), data<int32_t>(tokens), data<int32_t>(pl), data<int32_t>(sl), data<uint8_t>(mask),
+                data<int32_t>(raw), data<int32_t>(snapped), data<int32_t>(len),
                 data<int32_t>(flags), data<float>(tau), nullptr, 0, stream());
 }
 

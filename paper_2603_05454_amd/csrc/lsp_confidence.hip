@@ -608,8 +608,8 @@ int32_t confidence_run(const char *who, bool own_scratch, int32_t dtype, const v
     if (rc != LSP_OK) return rc;
     workspace_bytes = kSplitBytes;
   }
-  const bool split = p.max_log2 > 0 && (suffix_len == nullptr || B <= kMaxScannedBatch) && rows <= kMaxSplitGrid && workspace != nullptr && workspace_bytes >= kSplitBytes &&
-               (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
+  const bool room = workspace != nullptr && workspace_bytes >= kSplitBytes && (reinterpret_cast<uintptr_t>(workspace) & 15u) == 0;
+  const bool split = p.max_log2 > 0 && (suffix_len == nullptr || B <= kMaxScannedBatch) && rows <= kMaxSplitGrid && room;
   if (p.required && !split) {
     set_error("%s: workspace of %zu bytes (16-byte aligned) required, got %zu", who, kSplitBytes, workspace_bytes);
     return LSP_ERR_WORKSPACE;
@@ -648,7 +648,7 @@ extern "C" int32_t lsp_confidence(int32_t dtype, const void *logits, int32_t B, 
 // share nothing.
 #define LSP_CONF_SCRATCH_BYTES 65536
 static __device__ __align__(256) unsigned char scratch[LSP_CONF_SCRATCH_BYTES];
-static_assert(lsp::kSplitBytes <= LSP_CONF_SCRATCH_BYTES, "a call's segments and tickets");
+static_assert(lsp::kSplitBytes <= LSP_CONF_SCRATCH_BYTES, "a call's segments");
 
 namespace lsp {
 namespace {
