@@ -313,8 +313,13 @@ def confidence(logits, suffix_len=None, out=None, workspace=None):
                                     ctypes.c_int64(logits.stride(1)), ctypes.c_int64(logits.stride(0)),
                                     _ptr(suffix_len), _ptr(out[0]), _ptr(out[1]), _ptr(out[2]),
                                     _ptr(ws), ctypes.c_size_t(wb), _stream())
-    rc = call(workspace if workspace is not None and workspace.is_cuda and workspace.is_contiguous() else None)
-    if rc == LSP_ERR_WORKSPACE:     # few long rows: needed, not only useful
+    if workspace is not None and not (workspace.is_cuda and workspace.is_contiguous()):
+        workspace = None
+    rc = LSP_ERR_WORKSPACE
+    need = lib().lsp_confidence_workspace_bytes(B, S, V) if B * S < 128 else 0      # few long rows: needed, not only useful
+    if need == 0 or (workspace is not None and workspace.numel() * workspace.element_size() >= need):
+        rc = call(workspace)
+    if rc == LSP_ERR_WORKSPACE:     # (or one that is not aligned)
         rc = call(torch.empty(lib().lsp_confidence_workspace_bytes(B, S, V), dtype=torch.uint8, device=logits.device))
     _check(rc, "lsp_confidence")
     return out

@@ -225,7 +225,8 @@ PyObject *confidence(PyObject *, PyObject *const *a, Py_ssize_t n) {
   ORDINARY(conf_out(a[2], B, S, o));
   const at::Tensor *ws = a[3] == Py_None ? nullptr : device_tensor(a[3]);
   ORDINARY(ws ? ws->is_contiguous() : a[3] == Py_None);
-  // (a call that needs a workspace and has none answers so, before any launch)
+  // few long rows need one, which the general path allocates; one that is not aligned is found out by the call, before any launch
+  ORDINARY(B * S >= 128 || bytes_of(ws) >= int64_t(g.confidence_workspace_bytes(int32_t(B), int32_t(S), int32_t(V))));
   const int32_t rc = unlocked(g.confidence, type, z->const_data_ptr(), int32_t(B), int32_t(S), int32_t(V), z->stride(1), z->stride(0),
                               data<int32_t>(sl), o.id, o.prob, o.margin, data<void>(ws), size_t(bytes_of(ws)), stream());
   ORDINARY(rc != LSP_ERR_WORKSPACE);

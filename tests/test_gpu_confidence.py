@@ -285,3 +285,32 @@ def test_strided_workspace_is_not_written(lsp, rows, native, monkeypatch):
     zz = z[0, :20].float()
     top2 = zz.topk(2, dim=-1).values
     assert torch.equal(zz.gather(1, ids[0, :20, None].long()), top2[:, :1]) and torch.equal(margin[0, :20], top2[:, 0] - top2[:, 1])
+
+
+@pytest.mark.parametrize("native", [True, False])
+@pytest.mark.parametrize("given", ["none", "small", "unaligned", "host", "right"])
+def test_workspace_that_is_needed(lsp, given, native, monkeypatch):
+    """Few long rows: a call without a workspace that will do brings its own, and no call is made in vain where it can be seen
+    beforehand."""
+    lsp.lib()
+    if not native:
+        monkeypatch.setattr(lsp, "_nat", None)
+    library, tried = lsp.lib(), []
+
+    class Counted:      # the library, as the general path calls it
+        def __getattr__(self, name):
+            return getattr(library, name)
+
+        def lsp_confidence(self, *a):
+            tried.append(library.lsp_confidence(*a))
+            return tried[-1]
+
+    z = torch.randn((1, 6, 40000), generator=torch.Generator().manual_seed(1)).cuda()
+    need = lsp.confidence_workspace_bytes(1, 6, 40000)
+    ws = dict(none=None, small=torch.empty(16, dtype=torch.uint8, device="cuda"), unaligned=torch.empty(need + 4, dtype=torch.uint8, device="cuda")[4:],
+              host=torch.empty(need, dtype=torch.uint8), right=torch.empty(need, dtype=torch.uint8, device="cuda"))[given]
+    monkeypatch.setattr(lsp, "_lib", Counted())
+    ids, prob, margin = lsp.confidence(z, workspace=ws)
+    top2 = z.topk(2, dim=-1)
+    assert torch.equal(ids.long(), top2.indices[..., 0]) and torch.equal(margin, top2.values[..., 0] - top2.values[..., 1])
+    assert tried == ([-3, 0] if given == "unaligned" else [] if native and given == "right" else [0])
