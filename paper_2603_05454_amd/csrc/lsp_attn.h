@@ -170,7 +170,7 @@ struct Contiguous128 {
   enum Kernel { kSplit8, kSplit4TwoParts, kSplit4, kTiles128Rows, kFineTiles128Rows, kTiles256Rows } kernel;
   Reference rounding;
 };
-// The host knows the buffers (S rows, C cache rows; heads: of all sequences and layers), not the active lengths.
+// The host knows the buffers (S rows, C cache rows; heads: of all sequences and layers; rep: of a KV head), not the active lengths.
 // us per call, one layer of 32/32 or 28/4 heads unless said otherwise, B x S rows on P cached ones:
 //  * more than 128 tiles of 128 rows: the hand-scheduled loop with four waves, two workgroups to a compute unit.  Before
 //    it there were tiles of 256 rows, the shared-tile kernel for S <= 128 and the key split below 256 tiles of 128:
@@ -183,19 +183,23 @@ struct Contiguous128 {
 //    one round that is nearly full (28/4 heads, 4 x 497 on 1021: 47.3 and 48.6; 2 x 1024 on 1800: 87 and 89, but 61 and 43 with
 //    256 active); and at least two rounds of up to 256
 //    heads, where a compute unit is left with one workgroup when the sequences are down to their last rows (28/4
-//    heads, 8 x 1024 on 1000: 239 and 228 when full, 20.5 and 28.3 with 30 rows left).  Otherwise
+//    heads, 8 x 1024 on 1000: 239 and 228 when full, 20.5 and 28.3 with 30 rows left).  The same from one and a half rounds of the
+//    smaller tiles on, where these are placed in groups (place_grid) and so two to a compute unit while others have none, if the
+//    heads do not share K/V (5 x 640 on 800: 25 and 35 with 51 rows left, 39 and 44 with 224, 61 and 50 with 480, 86 and 87 full; 28/4
+//    heads, 6 x 640 on 1800: 35 and 34 with 51, 54 and 45 with 160, 88 and 67 with 320).  Otherwise
 //    what the smaller tiles save in part-filled ones and in rounds weighs more (3 x 1024 on 4000, one round and a
 //    half: 254 and 231; 32 layers, 8 x 600 on 600, 28/4 heads: 3025 and 2903);
 //  * fewer: the key split, eight ways while its workgroups are at most one to a compute unit, four ways beyond, where
 //    two fit one (1 x 384 on 800: 18.9 four ways, 23.4 eight, 21.1 with 128-row tiles).
-inline Contiguous128 contiguous128(int64_t heads, int32_t S, int32_t C) {
+inline Contiguous128 contiguous128(int64_t heads, int32_t rep, int32_t S, int32_t C) {
   auto tiles = [&](int rows) { return heads * ((S + rows - 1) / rows); };
   const int64_t rows = heads * S;
   Contiguous128 r;
   r.rounding = rows >= 32768 ? (S > 128 ? kTiles256 : kOnePass) : rows >= 16384 ? kFourParts : kEightParts;
   if (tiles(128) > 128) {
     const int64_t wide = r.rounding == kTiles256 ? tiles(256) : 0;
-    if ((wide > 192 && wide <= 256) || (wide >= 512 && heads <= 256) || (wide >= 1024 && C > 2048)) r.kernel = Contiguous128::kTiles256Rows;
+    const bool rounds = heads <= 256 && (wide >= 512 || (wide > 0 && tiles(128) > 768 && rep == 1));
+    if ((wide > 192 && wide <= 256) || rounds || (wide >= 1024 && C > 2048)) r.kernel = Contiguous128::kTiles256Rows;
     else r.kernel = r.rounding == kFourParts && S > 128 ? Contiguous128::kFineTiles128Rows : Contiguous128::kTiles128Rows;
   } else {
     r.kernel = tiles(32) <= 256            ? Contiguous128::kSplit8

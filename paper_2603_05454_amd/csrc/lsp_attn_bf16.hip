@@ -1282,7 +1282,7 @@ int32_t launch(const AttnArgs &a, const AttnLayers &layers, hipStream_t st) {
 }
 
 int32_t dispatch_contiguous128(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
-  const Contiguous128 r = contiguous128(int64_t(a.B) * a.Hq * (layers.n > 0 ? layers.n : 1), a.S, a.C);
+  const Contiguous128 r = contiguous128(int64_t(a.B) * a.Hq * (layers.n > 0 ? layers.n : 1), a.Hq / a.Hkv, a.S, a.C);
   a.rounding = r.rounding;
   switch (r.kernel) {
     case Contiguous128::kTiles256Rows: return launch_pipe<8>(a, layers, st);

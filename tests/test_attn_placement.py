@@ -39,8 +39,8 @@ namespace lsp { void set_error(const char *, ...) {} }
 int main(int argc, char **argv) {
   using namespace lsp;
   int L, B, S, Hq, Hkv, qtile, resident, group, enough;
-  if (argc > 1) {  // heads, S, C -> kernel, rounding
-    const Contiguous128 r = contiguous128(atoll(argv[1]), atoi(argv[2]), atoi(argv[3]));
+  if (argc > 1) {  // heads, rep, S, C -> kernel, rounding
+    const Contiguous128 r = contiguous128(atoll(argv[1]), atoi(argv[2]), atoi(argv[3]), atoi(argv[4]));
     return printf("%d %d\n", int(r.kernel), int(r.rounding)), 0;
   }
   while (scanf("%d %d %d %d %d %d %d %d %d", &L, &B, &S, &Hq, &Hkv, &qtile, &resident, &group, &enough) == 9) {
@@ -103,7 +103,17 @@ def test_every_tile_once_and_live_ones_on_all_xcds(program, form):
 KERNELS = ["split8", "split4x2", "split4", "128", "128 fine", "256"]
 
 
+def _kernel(program, *shape):
+    return KERNELS[int(subprocess.run([program, *map(str, shape)], capture_output=True, text=True, check=True).stdout.split()[0])]
+
+
+@pytest.mark.parametrize("rep", [1, 2])
 @pytest.mark.parametrize("heads,S,C,kernel", [(layers * B * Hq, S, C, kernel) for layers, B, Hq, S, C, kernel in TILES + SPREAD + MOVING + NEAR_THE_END])
-def test_shapes_of_the_gpu_tests_reach_the_kernel_they_name(program, heads, S, C, kernel):
-    out = subprocess.run([program, str(heads), str(S), str(C)], capture_output=True, text=True, check=True).stdout.split()
-    assert KERNELS[int(out[0])] == kernel
+def test_shapes_of_the_gpu_tests_reach_the_kernel_they_name(program, heads, rep, S, C, kernel):
+    assert _kernel(program, heads, rep, S, C) == kernel
+
+
+@pytest.mark.parametrize("heads,rep,S,C,kernel", [(160, 1, 640, 1440, "256"), (160, 8, 640, 1440, "128"), (192, 1, 512, 1312, "128"), (224, 1, 512, 1312, "256"),
+                                                 (384, 1, 384, 1000, "128"), (168, 7, 640, 2440, "128"), (768, 1, 128, 900, "128")])
+def test_more_tiles_than_are_placed_at_once(program, heads, rep, S, C, kernel):
+    assert _kernel(program, heads, rep, S, C) == kernel
