@@ -24,10 +24,11 @@ struct AttnArgs {
   void *out;
   const int32_t *prefix_len, *suffix_len;
   int32_t B, S, Hq, Hkv;
-  int32_t rep, chunk, spread, layers, unit_group;  // placement of the workgroups (place_grid); read first, with the line above
+  int32_t rep, chunk, spread, layers, unit_group, per_unit;  // placement of the workgroups (place_grid); read first, with the line above
   Div by_group, by_unit_group, by_units, by_heads, by_rep;  // its divisors: unit_group * chunk, unit_group, B * Hkv, Hkv, rep
   int32_t D, C;
-  int32_t spread_limit;  // head_dim 128, contiguous cache: blocks of 32 rows in a launch that are spread (launch_pipe)
+  // head_dim 128, contiguous cache: blocks of a sequence that are still spread (spread_limit), tiles of a unit that are not yet packed (Blocks)
+  int32_t spread_blocks, unpacked_tiles;
   int32_t rounding;  // head_dim 128, contiguous cache: which reference short tiles' probabilities are rounded against (Reference)
   float scale;
   int64_t qs[3], ks[3], cs[3], os[3];  // element strides: batch, row, head
@@ -98,11 +99,14 @@ struct Place {
 // 905 us whole, 122 in eight).  A piece takes every 2^spread-th of the unit's (tile, head) list, so that the live tiles, which are
 // the first ones, are shared evenly; as runs of that list the last pieces' XCDs had none (28/4 heads, 5 x 400 rows on 3500 with
 // 128 active 80 -> 64 us, with 300 138 -> 90, all 156 -> 122).
+struct UnitPlace {
+  int layer, b, g, w;  // w: this workgroup's number among those of its unit
+  bool valid;
+};
 template <bool GROUPS = true>  // false: groups of one unit
-__device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
-  Place p;
-  const int QT = (a.S + qtile - 1) / qtile;
-  const int rep = a.rep, chunk = a.chunk;
+__device__ __forceinline__ UnitPlace place_in_unit(const AttnArgs &a) {
+  UnitPlace p;
+  const int chunk = a.chunk;
   const int n = workgroup_id();
   const int m8 = n >> 3;
   const int G = GROUPS ? a.unit_group : 1;
@@ -118,28 +122,35 @@ __device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
     layer = quotient(unit, a.by_units);
     unit -= layer * units;
   }
-  p.valid = layer < a.layers && unit < units && wu < rep * QT;
+  p.valid = layer < a.layers && unit < units && wu < a.per_unit;
   p.layer = layer;
   p.b = quotient(unit, a.by_heads);
   p.g = unit - p.b * a.Hkv;
-  const int tile = quotient(wu, a.by_rep);
-  p.h = p.g * rep + wu - tile * rep;
-  p.q0 = tile * qtile;
+  p.w = wu;
   return p;
+}
+template <bool GROUPS = true>
+__device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
+  const UnitPlace u = place_in_unit<GROUPS>(a);
+  const int tile = quotient(u.w, a.by_rep);
+  return {u.layer, u.b, u.g, u.g * a.rep + u.w - tile * a.rep, tile * qtile, u.valid};
 }
 // Fields of that placement in `a`, and its number of workgroups.  Units are cut only where an XCD would get more than
 // `enough` workgroups.  resident: workgroups that run at once on an XCD (0: groups as above whatever their number).  whole: whether
-// the launch is one group for that reason.
+// the launch is one group for that reason.  pack: blocks of 32 rows that a workgroup takes from the unit's list of them (0: tiles of
+// qtile rows of one head).
 inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile, int resident = 0, int unit_group = kUnitGroup, int enough = 0,
-                          bool *whole = nullptr) {
-  const int64_t QT = (a.S + qtile - 1) / qtile, per_unit = a.Hq / a.Hkv * QT;
+                          bool *whole = nullptr, int pack = 0) {
+  const int64_t QT = (a.S + qtile - 1) / qtile, rep = a.Hq / a.Hkv;
+  const int64_t per_unit = pack > 0 ? ((a.S + int64_t(31)) / 32 * rep + pack - 1) / pack : rep * QT;
+  a.per_unit = int32_t(per_unit);
   a.layers = layers.n > 0 ? layers.n : 1;
   const int64_t units = int64_t(a.layers) * a.B * a.Hkv;
   a.spread = 0;  // with 32 units or more an XCD has at most a quarter more than its share
   if (units < 32 && (units + 7) / 8 * per_unit > enough)
     while ((units << a.spread) % 8 != 0) ++a.spread;
   const int64_t chunk = (per_unit + (1 << a.spread) - 1) >> a.spread;
-  a.rep = a.Hq / a.Hkv;
+  a.rep = int32_t(rep);
   a.chunk = int32_t(chunk);
   const int64_t pieces8 = ((units << a.spread) + 7) / 8;  // pieces per XCD
   const bool one_group = 2 * pieces8 * chunk <= 3 * resident;
@@ -169,6 +180,7 @@ enum Reference : int32_t {
 struct Contiguous128 {
   enum Kernel { kSplit8, kSplit4TwoParts, kSplit4, kTiles128Rows, kFineTiles128Rows, kTiles256Rows } kernel;
   Reference rounding;
+  bool packed;  // tiles may hold blocks of several heads of a group (Blocks)
 };
 // The host knows the buffers (S rows, C cache rows; heads: of all sequences and layers; rep: of a KV head), not the active lengths.
 // us per call, one layer of 32/32 or 28/4 heads unless said otherwise, B x S rows on P cached ones:
@@ -206,6 +218,8 @@ inline Contiguous128 contiguous128(int64_t heads, int32_t rep, int32_t S, int32_
                : r.rounding == kEightParts ? Contiguous128::kSplit4TwoParts
                                            : Contiguous128::kSplit4;
   }
+  // (the choice between them on the device; more workgroups than run at once)
+  r.packed = rep > 1 && (r.kernel == Contiguous128::kTiles256Rows ? tiles(256) > 256 : r.kernel == Contiguous128::kTiles128Rows && tiles(128) > 512);
   return r;
 }
 // Where few blocks of 32 rows are left in a whole launch, workgroups take one each and share its keys (one layer, 45 of 640 rows of
@@ -218,6 +232,51 @@ inline Contiguous128 contiguous128(int64_t heads, int32_t rep, int32_t S, int32_
 //    90 active 45 and 38).
 // What it still takes: 3 x 400 rows of 32/32 heads on 100 with 128 active 15.2 in tiles, 13.4 in blocks; on longer caches the other way.
 inline int32_t spread_limit(int rep, bool fine, bool one_group) { return fine || (rep == 1 && one_group) ? 288 : 512; }
+
+// Blocks of 32 rows that the waves of a workgroup take (head_dim 128, contiguous cache, shared K/V blocks).
+//  * WM consecutive blocks of one head, or
+//  * PACK, where that takes fewer workgroups: WM entries of the unit's list of all heads' blocks (entry e: block e / rep of its head
+//    e % rep).  The heads of a group stream the same K/V, so whose rows a wave has is no matter to the others.  Otherwise seven heads
+//    with a few rows left each are seven workgroups that stream it one by one, and 33 rows leave half the waves of seven idle.
+//    28/4 heads, 32 layers: 15 x 303 rows with 6 active on 3671 2704 -> 897 us, 2 x 21 on 38 26.0 -> 14.0, 6 x 39 with 33 active on
+//    2163 550 -> 297, 8 x 165 on 2971 2256 -> 2109.  Up to kPackFrom tiles of one head each find a compute unit of their own, and
+//    more rows to a workgroup then take longer (6 x 33 on 3233, one layer, 168 tiles: 45.6 and 49.4 us packed; 9 x 954 with 61 active on
+//    154, 252 tiles: 37.1 and 32.5).  In launches that run at once (`packed` in contiguous128) even the choice would cost (9 x 48 on 56 9.1 and 9.4).
+//  * spread (spread_limit): one block, shared by all waves.
+constexpr int kPackFrom = 224;
+template <int WM, bool FINE, bool PACK>
+inline int64_t place_blocks(AttnArgs &a, const AttnLayers &layers) {
+  bool one_group;
+  const int64_t nwg = place_grid(a, layers, FINE ? 32 : 32 * WM, FINE ? 1 << 20 : 32 * 8 / WM, kUnitGroup, 0, &one_group);  // FINE: always one
+  const int64_t units = int64_t(a.B) * a.Hkv * a.layers;
+  a.spread_blocks = int32_t(spread_limit(a.rep, FINE, one_group) / (units * a.rep));
+  a.unpacked_tiles = int32_t(kPackFrom / units);
+  // with more heads than are spread every sequence is packed, unless its tiles are as few so (the limits are above kPackFrom)
+  if (PACK && a.spread_blocks == 0) return place_grid(a, layers, 32 * WM, 32 * 8 / WM, kUnitGroup, 0, nullptr, WM);
+  return nwg;
+}
+struct Blocks {
+  int w, first_head, rep, tile;  // tile: w / rep
+  int count;                     // blocks in the list from this workgroup's first on: at most none, one, ...
+  bool spread, packed;
+};
+template <int WM, bool FINE, bool PACK>
+__device__ __forceinline__ Blocks blocks_of(const AttnArgs &a, const UnitPlace &p, int N) {
+  Blocks k = {p.w, p.g * a.rep, a.rep, quotient(p.w, a.by_rep), 0, false, false};
+  const int blocks = (N + 31) >> 5;
+  k.spread = WM == 4 && (FINE || blocks * a.rep <= a.per_unit) && blocks <= a.spread_blocks;
+  const int tiles = a.rep * ((blocks + WM - 1) / WM), listed = a.rep * blocks;
+  k.packed = PACK && !k.spread && (listed + WM - 1) / WM < tiles && tiles > a.unpacked_tiles;
+  k.count = k.spread ? blocks - k.tile : k.packed ? listed - WM * k.w : blocks - WM * k.tile;
+  return k;
+}
+// first row and head of wave v's block (v >= count: rows beyond the suffix, of some head of the group)
+template <int WM, bool PACK>
+__device__ __forceinline__ void block_at(const AttnArgs &a, const Blocks &k, int v, int &row, int &h) {
+  const int e = WM * k.w + v, r = PACK && k.packed ? quotient(e, a.by_rep) : k.tile;
+  row = 32 * (k.packed || k.spread ? r : WM * k.tile + v);
+  h = k.first_head + (k.packed ? e - r * k.rep : k.w - k.tile * k.rep);
+}
 
 // Cache row that holds key t (t < P_b) of sequence b.
 template <bool GATHER>

@@ -1066,7 +1066,7 @@ typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 // when tiles do not (16 384 to 32 767 rows): a sequence's blocks are then spread when there are more of them than tiles
 // (28/4 heads, 2 x 320 rows on 3500 with 128 active 52 -> 29 us, 1 x 640 with 200 active 58 -> 31; the key split that these
 // launches once were 29 and 32).  The workgroups too many leave at once, behind the others.
-template <int WM, bool FINE>
+template <int WM, bool FINE, bool PACK>
 __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_pipe_kernel(AttnArgs a_in,
                                                                                                            AttnLayers layers) {
   AttnArgs a = a_in;
@@ -1076,23 +1076,22 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   constexpr int TILE = 32 * D * 2, VBASE = NS * TILE;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
-  const Place pl = place(a, FINE ? 32 : 32 * WM);
+  const UnitPlace pl = place_in_unit(a);
   if (!pl.valid) return;
   for_layer(a, layers, pl.layer);
-  const int b = pl.b, g = pl.g, h = pl.h, q0 = FINE ? WM * pl.q0 : pl.q0;
+  const int b = pl.b, g = pl.g;
   const int N = min(max(a.suffix_len[b], 0), a.S);
   const int P = min(max(a.prefix_len[b], 0), a.C);
-  // A tile with at most 32 active rows - a sequence down to its last rows, or the tail of a longer
+  // A tile of one block - a sequence down to its last rows, or the tail of a longer
   // suffix that ends just past a multiple of the tile - would keep all waves but one idle for the whole key
   // range: its one block of queries goes to the key-split body (as in attn_bf16_ring_kernel), which
   // shares the KEY range between the waves instead.  The same where few are left in the whole launch (spread_limit; one
   // layer, 32 heads, 200 of 1024 rows on 4000 cached ones: 102 us with one tile of 256, 40 so).
-  const int blocks = (N + 31) >> 5;
-  const bool spread = WM == 4 && (FINE || blocks <= (a.S + 32 * WM - 1) / (32 * WM)) &&
-                      int64_t(blocks) * a.B * a.Hq * a.layers <= a.spread_limit;
-  const int qs = spread ? q0 / WM : q0;
-  if (qs >= N) return;
-  if (spread || N - q0 <= kShortSuffixPipe) {
+  const Blocks list = blocks_of<WM, FINE, PACK>(a, pl, N);
+  if (list.count <= 0) return;
+  if (list.spread || list.count == 1) {
+    int qs, h;
+    block_at<WM, PACK>(a, list, 0, qs, h);
     const bool one_pass = !FINE && (a.rounding == kOnePass || (a.rounding == kTiles256 && N - (qs & ~255) > kShortSuffixPipe));
     RefKeys ref = {0, 0};
     if (one_pass) {
@@ -1116,7 +1115,10 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const int lq = lane & 31, hf = lane >> 5;
 
-  const int qi = q0 + wave * 32 + lq;
+  const bool live = wave_s < list.count;  // waves of a last workgroup may have no block
+  int row0, h;
+  block_at<WM, PACK>(a, list, wave_s, row0, h);
+  const int qi = row0 + lq;
   const uint16_t *qp = static_cast<const uint16_t *>(a.q) + b * a.qs[0] + int64_t(min(qi, N - 1)) * a.qs[1] + h * a.qs[2];
   bf16x8 qf[KK];
 #pragma unroll
@@ -1206,9 +1208,7 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const uint32_t nc_u = uint32_t(nc), ns_u = uint32_t(ns);
     const uint32_t ldsk = lds0 + 1024u * LPB * uint32_t(wave_s);
     float nm = -mref;
-    // a wave none of whose 32 queries is active (last tile of a suffix that is not a multiple of the tile) keeps its
-    // share of the loads and meets the others at the barriers, nothing else
-    const bool live = q0 + 32 * wave_s < N;
+    // a wave without a block of queries keeps its share of the loads and meets the others at the barriers, nothing else
     if constexpr (WM == 8) {
       addr[12] = uint32_t(lr * cpitch + kcol(0));
       addr[13] = uint32_t(lr * cpitch + vcol);
@@ -1240,7 +1240,7 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   }
 
   lsum = half_sum(lsum);
-  if (qi < N) {
+  if (live && qi < N) {
     const float inv = 1.0f / lsum;
     uint16_t *op = static_cast<uint16_t *>(a.out) + b * a.os[0] + int64_t(qi) * a.os[1] + h * a.os[2];
 #pragma unroll
@@ -1255,11 +1255,9 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   }
 }
 
-template <int WM, bool FINE = false>
+template <int WM, bool FINE = false, bool PACK = false>
 int32_t launch_pipe(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
-  bool one_group;
-  const int64_t nwg = place_grid(a, layers, FINE ? 32 : 32 * WM, FINE ? 1 << 20 : 32 * 8 / WM, kUnitGroup, 0, &one_group);  // FINE: always one
-  a.spread_limit = spread_limit(a.rep, FINE, one_group);
+  const int64_t nwg = place_blocks<WM, FINE, PACK>(a, layers);
   if (nwg > kMaxGrid) {
     set_error("lsp_attn_step: launch of %lld workgroups is too large", (long long)nwg);
     return LSP_ERR_UNSUPPORTED;
@@ -1267,7 +1265,7 @@ int32_t launch_pipe(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
   const size_t lds_ring = size_t(WM == 8 ? 8 : 5) * 2 * 32 * 256;
   const size_t lds_split = WM * size_t(Geo<128>::WAVE_LDS) + 32 * size_t(Geo<128>::KPITCH) + 32 * sizeof(float);
   const size_t lds = lds_ring > lds_split ? lds_ring : lds_split;
-  auto kern = attn_bf16_pipe_kernel<WM, FINE>;
+  auto kern = attn_bf16_pipe_kernel<WM, FINE, PACK>;
   static std::atomic<uint64_t> configured{0};
   if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured, "lsp_attn_step: hipFuncSetAttribute")) return rc;
   kern<<<grid_of(nwg), 64 * WM, lds, st>>>(a, layers);
@@ -1285,8 +1283,8 @@ int32_t dispatch_contiguous128(AttnArgs a, const AttnLayers &layers, hipStream_t
   const Contiguous128 r = contiguous128(int64_t(a.B) * a.Hq * (layers.n > 0 ? layers.n : 1), a.Hq / a.Hkv, a.S, a.C);
   a.rounding = r.rounding;
   switch (r.kernel) {
-    case Contiguous128::kTiles256Rows: return launch_pipe<8>(a, layers, st);
-    case Contiguous128::kTiles128Rows: return launch_pipe<4>(a, layers, st);
+    case Contiguous128::kTiles256Rows: return r.packed ? launch_pipe<8, false, true>(a, layers, st) : launch_pipe<8>(a, layers, st);
+    case Contiguous128::kTiles128Rows: return r.packed ? launch_pipe<4, false, true>(a, layers, st) : launch_pipe<4>(a, layers, st);
     case Contiguous128::kFineTiles128Rows: return launch_pipe<4, true>(a, layers, st);
     case Contiguous128::kSplit8: return launch_g<128, 1, 8, false>(a, layers, st);
     case Contiguous128::kSplit4TwoParts: return launch_g<128, 1, 4, false, 2>(a, layers, st);

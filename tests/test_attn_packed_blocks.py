@@ -1,0 +1,114 @@
+"""Workgroups of several heads of a group (csrc/lsp_attn.h, Blocks): the division of blocks of 32 rows among workgroups and waves on
+the CPU, and the kernels' outputs at its edges against the CPU oracle."""
+import os
+import subprocess
+
+import pytest
+import torch
+
+import workloads as W
+from paper_2603_05454_amd.build import CSRC, ROOT
+from test_attn_placement import STUB
+
+MAIN = r"""
+#include <stdio.h>
+#include "lsp_attn.h"
+namespace lsp { void set_error(const char *, ...) {} }
+using namespace lsp;
+template <int WM, bool FINE, bool PACK>
+void walk(AttnArgs &a, const AttnLayers &layers, const int *N) {
+  const int64_t n = place_blocks<WM, FINE, PACK>(a, layers);
+  for (int64_t w = 0; w < n; ++w) {
+    blockIdx.x = unsigned(w & ((1 << kGridBits) - 1));
+    blockIdx.y = unsigned(w >> kGridBits);
+    const UnitPlace p = place_in_unit(a);
+    if (!p.valid) continue;
+    const Blocks k = blocks_of<WM, FINE, PACK>(a, p, N[p.b]);
+    for (int v = 0; v < WM && (v < k.count || k.count > 0); ++v) {
+      int row, h;
+      block_at<WM, PACK>(a, k, v, row, h);
+      const bool one = k.spread || k.count == 1;
+      if (v == 0 || !one) printf("%d %d %d %d %d %d\n", p.layer, p.b, p.g, h, row, v < k.count);
+    }
+  }
+}
+int main() {
+  int WM, pack, L, B, S, Hq, Hkv, N[64];
+  while (scanf("%d %d %d %d %d %d %d", &WM, &pack, &L, &B, &S, &Hq, &Hkv) == 7) {
+    for (int b = 0; b < B; ++b) if (scanf("%d", N + b) != 1) return 1;
+    AttnArgs a = {};
+    AttnLayers layers = {};
+    layers.n = L;
+    a.B = B; a.S = S; a.Hq = Hq; a.Hkv = Hkv;
+    if (WM == 8) pack ? walk<8, false, true>(a, layers, N) : walk<8, false, false>(a, layers, N);
+    else if (pack == 2) walk<4, true, false>(a, layers, N);
+    else pack ? walk<4, false, true>(a, layers, N) : walk<4, false, false>(a, layers, N);
+  }
+}
+"""
+
+
+@pytest.fixture(scope="module")
+def program(tmp_path_factory):
+    d = tmp_path_factory.mktemp("blocks")
+    (d / "hip").mkdir()
+    (d / "hip" / "hip_runtime.h").write_text(STUB)
+    (d / "main.cpp").write_text(MAIN)
+    subprocess.run([os.environ.get("CXX", "g++"), "-O1", "-std=c++17", "-fno-strict-aliasing", "-DNDEBUG", f"-I{d}", f"-I{CSRC}", f"-I{ROOT}/include",
+                    str(d / "main.cpp"), "-o", str(d / "blocks")], check=True)
+    return str(d / "blocks")
+
+
+# waves, pack (2: a workgroup for every block), layers, S, query heads, KV heads, active rows
+FORMS = [(4, 1, 32, 20, 28, 4, (1, 20, 0)), (4, 1, 32, 700, 7, 1, (700, 33, 32, 64, 65, 0, 129)), (4, 1, 16, 100, 40, 8, (97, 96, 31)),
+         (4, 1, 1, 600, 28, 4, (600, 40, 3, 0, 300)), (4, 1, 3, 161, 12, 6, (161, 128, 127, 5)), (4, 1, 32, 300, 15, 5, (300, 161, 160, 17)),
+         (8, 1, 32, 512, 8, 2, (512, 257, 256, 255, 33, 1)), (8, 1, 9, 1000, 28, 4, (1000, 31, 0)),
+         (4, 0, 1, 150, 28, 4, (150, 1, 64, 33)), (4, 2, 1, 250, 28, 4, (250, 100, 7)), (8, 0, 1, 600, 6, 2, (600, 290)), (4, 0, 2, 300, 5, 5, (300, 129))]
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_every_active_block_once(program, form):
+    WM, pack, L, S, Hq, Hkv, N = form
+    text = " ".join(map(str, (WM, pack, L, len(N), S, Hq, Hkv, *N)))
+    out = subprocess.run([program], input=text, capture_output=True, text=True, check=True).stdout
+    placed = [tuple(map(int, l.split())) for l in out.split("\n") if l]
+    rep = Hq // Hkv
+    want = sorted((l, b, h, r) for l in range(L) for b, n in enumerate(N) for h in range(Hq) for r in range(0, n, 32))
+    assert sorted((l, b, h, r) for l, b, _, h, r, live in placed if live) == want
+    assert all(g == h // rep for _, _, g, h, _, _ in placed)
+    assert all(r >= N[b] for _, b, _, _, r, live in placed if not live)     # a wave without a block stores nothing
+
+
+@pytest.fixture(scope="module")
+def lsp():
+    import paper_2603_05454_amd as m
+    assert torch.cuda.is_available()
+    return m
+
+
+# layers, S, C, query heads, KV heads, active rows: lists whose last workgroup has one block, some, or all; lists that are cut by head
+# instead (97 .. 128 rows); caches beyond 2048 rows and 512 heads, where a workgroup has eight waves
+GPU = [(16, 100, 64, 35, 5, (100, 33, 1, 0)), (20, 40, 97, 28, 4, (40, 32, 20, 5, 33)), (16, 300, 70, 12, 4, (300, 161, 129, 64)),
+       (6, 161, 40, 60, 2, (161, 96, 97, 40)), (32, 300, 2100, 8, 2, (300, 33)), (4, 520, 50, 14, 2, (520, 3, 0, 31, 65))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layers,S,C,Hq,Hkv,N", GPU)
+def test_packed_workgroups_match_the_oracle(lsp, oracle, layers, S, C, Hq, Hkv, N):
+    """The bound is the bf16 one of test_gpu_attention.py; rows beyond a suffix stay as they were."""
+    w = W.scaled(W.C2, B=len(N), S=S, P=C, C=C, Hq=Hq, Hkv=Hkv, D=128, seed=900 + S + Hq)
+    pl = torch.tensor([max(C - 13 * b - (b & 1), 0) for b in range(len(N))], dtype=torch.int32)
+    sl = torch.tensor(N, dtype=torch.int32)
+    checked = (0, layers - 1)
+    host = {l: W.make_layer_kv(w, l, prefix_len=pl) for l in checked}
+    dev = {l: {k: v.cuda() for k, v in host[l].items()} for l in checked}
+    names = ("q", "k_suf", "v_suf", "k_cache", "v_cache")
+    ops = [dev[l if l in dev else 0] for l in range(layers)]                # the layers between repeat the first one's operands
+    outs = [torch.full(ops[0]["q"].shape, 123.0, dtype=torch.bfloat16, device="cuda") for _ in range(layers)]
+    lsp.attn_step_layers(lsp.AttnLayerTable(*[[o[k] for o in ops] for k in names], outs), pl.cuda(), sl.cuda())
+    for l in checked:
+        ref = oracle.attention(**host[l], prefix_len=pl, suffix_len=sl)
+        got, act = outs[l].float().cpu(), ~torch.isnan(ref)
+        assert (got[act] - ref[act]).abs().max().item() <= 2e-2
+        assert torch.all(got[~act] == 123.0)
+    assert all(torch.equal(outs[l], outs[0]) for l in range(1, layers - 1))
