@@ -366,6 +366,17 @@ int32_t lsp_flip_update(const int32_t *top1_id, int32_t B, int32_t S, int32_t G,
  * ------------------------------------------------------------------------- */
 int32_t lsp_poll_lengths(const int32_t *suffix_len, const int32_t *commit_len, int32_t B, int32_t *host, void *stream);
 
+/* ------------------------------------------------------------------------- *
+ * The same with a generation's totals: twelve 64-bit words, each with `call` in
+ * its upper half (the host takes a word for this call's when it finds the number
+ * there, so nothing is cleared and nothing ordered).  Lower halves: [0], [1] as
+ * host[0], host[1] above; [2], [3] the low and high 32 bits of the positions
+ * committed so far, the sum of prefix_len[b] - base_prefix_len[b]; [4]-[11] those
+ * of counters[0..3] (lsp_flip_update).  host: uint64[12], pinned.
+ * ------------------------------------------------------------------------- */
+int32_t lsp_poll_progress(const int32_t *suffix_len, const int32_t *commit_len, const int32_t *prefix_len, const int32_t *base_prefix_len,
+                          const int64_t *counters, int32_t B, uint32_t call, uint64_t *host, void *stream);
+
 /*
  * lsp_flip_update and lsp_commit of one step in the launches of lsp_commit: a sequence's workgroup counts its flips
  * where it searches its boundary.  Arguments as in these two.

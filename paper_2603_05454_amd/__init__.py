@@ -55,12 +55,13 @@ class CommitDesc(ctypes.Structure):
 EXPORTS = ["lsp_version", "lsp_last_error", "lsp_attn_workspace_bytes", "lsp_attn_step", "lsp_attn_step_layers",
            "lsp_confidence_workspace_bytes", "lsp_confidence", "lsp_confidence_static_scratch_bytes",
            "lsp_confidence_static", "lsp_commit_workspace_bytes",
-           "lsp_commit", "lsp_commit_step", "lsp_flip_update", "lsp_poll_lengths", "lsp_select_scattered", "lsp_kv_gather_append",
+           "lsp_commit", "lsp_commit_step", "lsp_flip_update", "lsp_poll_lengths", "lsp_poll_progress", "lsp_select_scattered", "lsp_kv_gather_append",
            "lsp_attn_step_gather", "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_bench_read", "lsp_bench_mfma"]
 
 # entry points that the native module calls, in the order of its table
 NATIVE_ENTRIES = ("lsp_attn_workspace_bytes", "lsp_attn_step", "lsp_attn_step_layers", "lsp_confidence_workspace_bytes", "lsp_confidence",
-                  "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_commit", "lsp_flip_update", "lsp_poll_lengths", "lsp_commit_step")
+                  "lsp_lm_head_confidence_workspace_bytes", "lsp_lm_head_confidence", "lsp_commit", "lsp_flip_update", "lsp_poll_lengths", "lsp_commit_step",
+                  "lsp_poll_progress")
 
 
 def lib() -> ctypes.CDLL:
@@ -535,6 +536,47 @@ class LengthPoll:
         _check(lib().lsp_poll_lengths(_ptr(suffix_len), _ptr(commit_len), suffix_len.shape[0], _ptr(self.host), _stream()), "lsp_poll_lengths")
         torch.cuda.current_stream().synchronize()
         return tuple(self.host[:2].tolist())
+
+
+class ProgressPoll:
+    """lsp_poll_progress with a pinned buffer of its own, in two calls, so that a loop can launch more work between them."""
+
+    def __init__(self):
+        self.host = torch.zeros(12, dtype=torch.int64, pin_memory=True)
+        self.call, self.waiting = 0, False
+
+    def start(self, suffix_len, commit_len, prefix_len, base_prefix_len, counters):
+        self.call = self.call % 0x7fffffff + 1
+        rc = None
+        if _nat is not None:
+            rc = _nat.poll_start(suffix_len, commit_len, prefix_len, base_prefix_len, counters, self.host, self.call)
+        if rc is None:
+            B = suffix_len.shape[0]
+            _dev(suffix_len, commit_len, prefix_len, base_prefix_len, counters)
+            _need("suffix_len", suffix_len, torch.int32, (B,))
+            _need("commit_len", commit_len, torch.int32, (B,), optional=True)
+            _need("prefix_len", prefix_len, torch.int32, (B,))
+            _need("base_prefix_len", base_prefix_len, torch.int32, (B,))
+            _need("counters", counters, torch.int64, (4,))
+            rc = lib().lsp_poll_progress(_ptr(suffix_len), _ptr(commit_len), _ptr(prefix_len), _ptr(base_prefix_len), _ptr(counters), B,
+                                         ctypes.c_uint32(self.call), _ptr(self.host), _stream())
+        _check(rc, "lsp_poll_progress")
+        self.waiting = True
+
+    def wait(self):
+        """Waits for what was on the current stream before start().  Returns (largest suffix_len, whether a sequence with
+        active positions has commit_len 0, positions committed, the four counters)."""
+        got = _nat.poll_wait(self.host, self.call) if _nat is not None else None
+        if got is None:
+            torch.cuda.current_stream().synchronize()
+            w = [x & 0xffffffff for x in self.host.tolist()]
+            got = (w[0] - ((w[0] & 0x80000000) << 1), w[1], *[w[k] | w[k + 1] << 32 for k in range(2, 12, 2)])
+        self.waiting = False
+        return got
+
+    def __del__(self):
+        if getattr(self, "waiting", False):     # the buffer is not given back while a kernel may still write to it
+            torch.cuda.synchronize()
 
 
 def select_scattered(margin, suffix_len, count, out=None):

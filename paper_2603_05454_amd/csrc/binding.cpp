@@ -16,6 +16,7 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <chrono>
+#include <thread>
 
 #include "lsp.h"
 
@@ -34,8 +35,9 @@ struct Entry {
   decltype(&lsp_flip_update) flip_update;
   decltype(&lsp_poll_lengths) poll_lengths;
   decltype(&lsp_commit_step) commit_step;
+  decltype(&lsp_poll_progress) poll_progress;
 } g;
-constexpr int kEntries = 11;
+constexpr int kEntries = 12;
 
 const at::Tensor *tensor(PyObject *o) { return THPVariable_Check(o) ? &THPVariable_Unpack(o) : nullptr; }
 const at::Tensor *device_tensor(PyObject *o) {
@@ -152,6 +154,7 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
   g.flip_update = reinterpret_cast<decltype(g.flip_update)>(p[8]);
   g.poll_lengths = reinterpret_cast<decltype(g.poll_lengths)>(p[9]);
   g.commit_step = reinterpret_cast<decltype(g.commit_step)>(p[10]);
+  g.poll_progress = reinterpret_cast<decltype(g.poll_progress)>(p[11]);
   Py_RETURN_NONE;
 }
 
@@ -399,6 +402,59 @@ PyObject *poll_lengths(PyObject *, PyObject *const *a, Py_ssize_t n) {
   }
   return Py_BuildValue("(ii)", int(h[0]), int(h[1]));
 }
+constexpr int kProgressWords = 12;
+uint64_t *progress_words(PyObject *o) {
+  const at::Tensor *t = tensor(o);
+  return t && t->is_cpu() && t->scalar_type() == at::kLong && t->is_contiguous() && t->numel() >= kProgressWords ? data<uint64_t>(t) : nullptr;
+}
+// (suffix_len, commit_len or None, prefix_len, base_prefix_len, counters, host, call): launches lsp_poll_progress.
+PyObject *poll_start(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  ARGUMENTS(7);
+  const at::Tensor *sl = device_tensor(a[0]);
+  ORDINARY(sl && sl->dim() == 1);
+  const int64_t B = sl->size(0);
+  sl = plain(a[0], at::kInt, B);
+  const at::Tensor *len = a[1] == Py_None ? nullptr : plain(a[1], at::kInt, B), *pl = plain(a[2], at::kInt, B),
+                   *base = plain(a[3], at::kInt, B), *counters = plain(a[4], at::kLong, 4);
+  uint64_t *h = progress_words(a[5]);
+  long call;
+  ORDINARY(sl && (len || a[1] == Py_None) && pl && base && counters && h && integer(a[6], call));
+  return status(g.poll_progress, data<int32_t>(sl), data<int32_t>(len), data<int32_t>(pl), data<int32_t>(base), data<int64_t>(counters),
+                int32_t(B), uint32_t(call), h, stream());
+}
+// (host, call): waits for that call's words and answers their lower halves.  Work launched behind the poll is not waited for: after a
+// while the thread sleeps between two looks, and a stream that has failed, or has nothing left to do, ends the wait as well (None).
+PyObject *poll_wait(PyObject *, PyObject *const *a, Py_ssize_t n) {
+  ARGUMENTS(2);
+  const uint64_t *h = progress_words(a[0]);
+  long call;
+  ORDINARY(h && integer(a[1], call));
+  uint64_t got[kProgressWords];
+  auto all = [&] {
+    bool here = true;
+    for (int k = 0; k < kProgressWords; ++k) {
+      got[k] = __atomic_load_n(h + k, __ATOMIC_ACQUIRE);
+      here = here && uint32_t(got[k] >> 32) == uint32_t(call);
+    }
+    return here;
+  };
+  bool here;
+  {
+    Unlocked without_lock;
+    const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
+    while (!(here = all())) {
+      if (std::chrono::steady_clock::now() < until) continue;
+      if (c10::hip::getCurrentHIPStream().query()) {  // (throws where the stream has failed)
+        here = all();
+        break;
+      }
+      std::this_thread::sleep_for(std::chrono::microseconds(20));
+    }
+  }
+  ORDINARY(here);
+  auto wide = [&](int k) { return (long long)(uint64_t(uint32_t(got[k + 1])) << 32 | uint32_t(got[k])); };
+  return Py_BuildValue("(iiLLLLL)", int(uint32_t(got[0])), int(uint32_t(got[1])), wide(2), wide(4), wide(6), wide(8), wide(10));
+}
 // Addresses of a list of device tensors that share shape, strides and element type, as bytes.
 PyObject *addresses(PyObject *, PyObject *const *a, Py_ssize_t n) {
   ARGUMENTS(1);
@@ -436,7 +492,8 @@ PyMethodDef fast(const char *name) {
 }
 PyMethodDef methods[] = {fast<bind>("bind"), fast<attn_step>("attn_step"), fast<attn_step_layers>("attn_step_layers"),
                          fast<confidence>("confidence"), fast<lm_head_confidence>("lm_head_confidence"), fast<commit<false>>("commit"), fast<commit<true>>("commit_step"),
-                         fast<flip_update>("flip_update"), fast<poll_lengths>("poll_lengths"), fast<addresses>("addresses"), {nullptr, nullptr, 0, nullptr}};
+                         fast<flip_update>("flip_update"), fast<poll_lengths>("poll_lengths"),
+                         fast<poll_start>("poll_start"), fast<poll_wait>("poll_wait"), fast<addresses>("addresses"), {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 
 }  // namespace

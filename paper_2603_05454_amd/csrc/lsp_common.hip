@@ -53,6 +53,32 @@ __global__ __launch_bounds__(kPollThreads) void poll_kernel(const int32_t *__res
   __hip_atomic_store(host + 2, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
+// The same for a loop that goes on launching behind it: one wave, no barrier, and every word in one store with the call's
+// number beside it, where values and a flag after them were two trips to host memory.
+constexpr int kProgressWords = 12;
+__global__ __launch_bounds__(kWave) void progress_kernel(const int32_t *__restrict__ suffix_len, const int32_t *__restrict__ commit_len,
+                                                         const int32_t *__restrict__ prefix_len, const int32_t *__restrict__ base,
+                                                         const uint32_t *__restrict__ counters, int B, uint32_t call, uint64_t *host) {
+  const int lane = threadIdx.x;
+  const uint32_t count = lane >= 4 && lane < kProgressWords ? counters[lane - 4] : 0;
+  int left = INT_MIN, stalled = 0;
+  int64_t committed = 0;
+  for (int b = lane; b < B; b += kWave) {
+    const int n = suffix_len[b];
+    left = max(left, n);
+    stalled |= commit_len != nullptr && n > 0 && commit_len[b] == 0;
+    committed += prefix_len[b] - base[b];
+  }
+#pragma unroll
+  for (int m = 1; m < kWave; m <<= 1) {
+    left = max(left, __shfl_xor(left, m));
+    stalled |= __shfl_xor(stalled, m);
+    committed += __shfl_xor(committed, m);
+  }
+  const uint32_t word = lane == 0 ? uint32_t(left) : lane == 1 ? uint32_t(stalled) : lane == 2 ? uint32_t(committed) : lane == 3 ? uint32_t(uint64_t(committed) >> 32) : count;
+  if (lane < kProgressWords) __hip_atomic_store(host + lane, uint64_t(call) << 32 | word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Measurement helper: a bare streaming read.  Workgroup w reads segment w of the buffer
 // with 16-byte non-temporal loads, four in flight per lane, and folds them with XOR; one
 // word per workgroup is written.  This is the floor under any kernel that has to read a
@@ -135,6 +161,17 @@ extern "C" int32_t lsp_poll_lengths(const int32_t *suffix_len, const int32_t *co
   LSP_CHECK_ARG(suffix_len && host && B > 0, "lsp_poll_lengths: bad argument");
   poll_kernel<<<1, kPollThreads, 0, static_cast<hipStream_t>(stream)>>>(suffix_len, commit_len, B, host);
   LSP_CHECK_LAUNCH("lsp_poll_lengths: launch");
+  return LSP_OK;
+}
+
+extern "C" int32_t lsp_poll_progress(const int32_t *suffix_len, const int32_t *commit_len, const int32_t *prefix_len,
+                                     const int32_t *base_prefix_len, const int64_t *counters, int32_t B, uint32_t call,
+                                     uint64_t *host, void *stream) {
+  using namespace lsp;
+  LSP_CHECK_ARG(suffix_len && prefix_len && base_prefix_len && counters && host && B > 0, "lsp_poll_progress: bad argument");
+  progress_kernel<<<1, kWave, 0, static_cast<hipStream_t>(stream)>>>(suffix_len, commit_len, prefix_len, base_prefix_len,
+                                                                     reinterpret_cast<const uint32_t *>(counters), B, call, host);
+  LSP_CHECK_LAUNCH("lsp_poll_progress: launch");
   return LSP_OK;
 }
 

@@ -319,3 +319,56 @@ def test_commit_step_is_flip_update_then_commit(lsp, B, S, G, native, monkeypatc
         assert all(torch.equal(a[n], b[n]) for n in a if n != "out")
         assert all(torch.equal(a["out"][n].view(torch.int8), b["out"][n].view(torch.int8)) for n in a["out"])
     assert a["counters"][1] > 0 or S == 1
+
+
+@pytest.mark.parametrize("native", [True, False])
+@pytest.mark.parametrize("B", [1, 64, 300])
+def test_progress_poll(lsp, B, native, monkeypatch):
+    """Both ways of making the call, on a buffer used again and again: lengths, totals beyond 32 bits, and work launched between
+    start and wait, which reads what was there before."""
+    lsp.lib()
+    if not native:
+        monkeypatch.setattr(lsp, "_nat", None)
+    g = torch.Generator().manual_seed(B)
+    poll = lsp.ProgressPoll()
+    base = torch.randint(0, 50, (B,), generator=g, dtype=torch.int32).cuda()
+    for n, c in ((torch.zeros(B), None), (torch.randint(0, 900, (B,), generator=g), torch.ones(B)), (torch.randint(-3, 900, (B,), generator=g), torch.randint(0, 2, (B,), generator=g)),
+                 (torch.full((B,), -5), torch.zeros(B))):
+        n = n.to(torch.int32).cuda()
+        c = None if c is None else c.to(torch.int32).cuda()
+        prefix = base + torch.randint(0, 2 ** 30, (B,), generator=g, dtype=torch.int32).cuda()
+        counters = torch.randint(0, 2 ** 50, (4,), generator=g).cuda()
+        want = (int(n.max()), int(c is not None and bool(((n > 0) & (c == 0)).any())), int((prefix - base).sum()), *counters.tolist())
+        poll.start(n, c, prefix, base, counters)
+        for t in (n, prefix, counters):
+            t += 1
+        assert tuple(poll.wait()) == want
+    with pytest.raises(lsp.LspError, match="counters must be"):
+        poll.start(n, c, prefix, base, counters.int())
+
+
+@pytest.mark.parametrize("poll,stop", [(1, None), (3, None), (3, 4), (1, 0), (2, 1)])
+def test_attention_launched_ahead_changes_no_result(lsp, oracle, poll, stop):
+    """Steps between tests, loops that are stopped, and the attention of a step whose test says that nothing is left."""
+    from paper_2603_05454_amd.loop import decode_loop as gpu_loop
+    G = 70
+    w = W.scaled(W.C5, B=2, S=G, V=512, P=10, gen_len=G, C=10 + G, layers=2, Hq=4, Hkv=2, D=128)
+    _, bm = W.make_delimiters(w)
+    fn = lambda step, p: W.make_logits(w, step=step, prefix_len=p.cpu())[0]
+    kw = dict(poll=poll, stop_after=stop, commit_kw=dict(adaptive=True, alpha=0.25, beta=0.5), gen_len=G)
+
+    def run(loop, dev, **more):
+        pl, sl = (t.to(dev) for t in W.make_lengths(w))
+        tok, lay = W.make_tokens(w, w.C).to(dev), [{k: v.to(dev) for k, v in W.make_layer_kv(w, l).items()} for l in range(2)]
+        asked = []
+        r = loop(lambda s, p: (asked.append(s), fn(s, p).to(dev))[1], bm.to(dev), w.V, 0.9, w.window, 1, 1, pl, sl, tok, kv_layers=lay, **more)
+        return r, asked, [tok, pl, sl] + [L[k] for L in lay for k in ("k_cache", "v_cache")]
+
+    a, asked_a, ta = run(gpu_loop, "cuda", run_attention=True, **kw)
+    b, asked_b, tb = run(gpu_loop, "cuda", run_attention=False, **kw)
+    assert asked_a == asked_b and all(a[k] == b[k] for k in KEYS)
+    assert all(torch.equal(x, y) for x, y in zip(ta, tb))
+    if stop is None and poll == 1:
+        ref, _, tr = run(decode_loop, "cpu", commit_kw=kw["commit_kw"])
+        _same_counts(a, ref)
+        assert all(torch.equal(x.cpu().view(torch.int8), y.view(torch.int8)) for x, y in zip(ta, tr))
