@@ -27,8 +27,7 @@ struct AttnArgs {
   int32_t rep, chunk, spread, layers, unit_group, per_unit;  // placement of the workgroups (place_grid); read first, with the line above
   Div by_group, by_unit_group, by_units, by_heads, by_rep;  // its divisors: unit_group * chunk, unit_group, B * Hkv, Hkv, rep
   int32_t D, C;
-  // head_dim 128, contiguous cache: blocks of a sequence that are still spread (spread_limit), tiles of a unit that are not yet packed (Blocks)
-  int32_t spread_blocks, unpacked_tiles;
+  int32_t spread_blocks, units;  // head_dim 128, contiguous cache: blocks of a sequence that are still spread (spread_limit); units of the launch
   int32_t rounding;  // head_dim 128, contiguous cache: which reference short tiles' probabilities are rounded against (Reference)
   float scale;
   int64_t qs[3], ks[3], cs[3], os[3];  // element strides: batch, row, head
@@ -138,11 +137,12 @@ __device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
 // Fields of that placement in `a`, and its number of workgroups.  Units are cut only where an XCD would get more than
 // `enough` workgroups.  resident: workgroups that run at once on an XCD (0: groups as above whatever their number).  whole: whether
 // the launch is one group for that reason.  pack: blocks of 32 rows that a workgroup takes from the unit's list of them (0: tiles of
-// qtile rows of one head).
+// qtile rows of one head).  least: workgroups of a unit at least.
 inline int64_t place_grid(AttnArgs &a, const AttnLayers &layers, int qtile, int resident = 0, int unit_group = kUnitGroup, int enough = 0,
-                          bool *whole = nullptr, int pack = 0) {
+                          bool *whole = nullptr, int pack = 0, int64_t least = 0) {
   const int64_t QT = (a.S + qtile - 1) / qtile, rep = a.Hq / a.Hkv;
-  const int64_t per_unit = pack > 0 ? ((a.S + int64_t(31)) / 32 * rep + pack - 1) / pack : rep * QT;
+  int64_t per_unit = pack > 0 ? ((a.S + int64_t(31)) / 32 * rep + pack - 1) / pack : rep * QT;
+  if (per_unit < least) per_unit = least;
   a.per_unit = int32_t(per_unit);
   a.layers = layers.n > 0 ? layers.n : 1;
   const int64_t units = int64_t(a.layers) * a.B * a.Hkv;
@@ -219,7 +219,7 @@ inline Contiguous128 contiguous128(int64_t heads, int32_t rep, int32_t S, int32_
                                            : Contiguous128::kSplit4;
   }
   // (the choice between them on the device; more workgroups than run at once)
-  r.packed = rep > 1 && (r.kernel == Contiguous128::kTiles256Rows ? tiles(256) > 256 : r.kernel == Contiguous128::kTiles128Rows && tiles(128) > 512);
+  r.packed = rep > 1 && (S > 32 || r.rounding == kOnePass) && (r.kernel == Contiguous128::kTiles256Rows ? tiles(256) > 256 : r.kernel == Contiguous128::kTiles128Rows && tiles(128) > 512);
   return r;
 }
 // Where few blocks of 32 rows are left in a whole launch, workgroups take one each and share its keys (one layer, 45 of 640 rows of
@@ -233,31 +233,46 @@ inline Contiguous128 contiguous128(int64_t heads, int32_t rep, int32_t S, int32_
 // What it still takes: 3 x 400 rows of 32/32 heads on 100 with 128 active 15.2 in tiles, 13.4 in blocks; on longer caches the other way.
 inline int32_t spread_limit(int rep, bool fine, bool one_group) { return fine || (rep == 1 && one_group) ? 288 : 512; }
 
-// Blocks of 32 rows that the waves of a workgroup take (head_dim 128, contiguous cache, shared K/V blocks).
+// Blocks of 32 rows that the waves of a workgroup take (head_dim 128, contiguous cache).
 //  * WM consecutive blocks of one head, or
-//  * PACK, where that takes fewer workgroups: WM entries of the unit's list of all heads' blocks (entry e: block e / rep of its head
-//    e % rep).  The heads of a group stream the same K/V, so whose rows a wave has is no matter to the others.  Otherwise seven heads
+//  * PACK, where that takes fewer rounds of workgroups: WM entries of the unit's list of all heads' blocks (entry e: block e / rep of its
+//    head e % rep).  The heads of a group stream the same K/V, so whose rows a wave has is no matter to the others.  Otherwise seven heads
 //    with a few rows left each are seven workgroups that stream it one by one, and 33 rows leave half the waves of seven idle.
-//    28/4 heads, 32 layers: 15 x 303 rows with 6 active on 3671 2704 -> 897 us, 2 x 21 on 38 26.0 -> 14.0, 6 x 39 with 33 active on
-//    2163 550 -> 297, 8 x 165 on 2971 2256 -> 2109.  Up to kPackFrom tiles of one head each find a compute unit of their own, and
-//    more rows to a workgroup then take longer (6 x 33 on 3233, one layer, 168 tiles: 45.6 and 49.4 us packed; 9 x 954 with 61 active on
-//    154, 252 tiles: 37.1 and 32.5).  In launches that run at once (`packed` in contiguous128) even the choice would cost (9 x 48 on 56 9.1 and 9.4).
+//    28/4 heads, 32 layers: 16 x 100 rows with 10 active on 2968 2264 -> 796 us, 10 x 22 with 11 on 109 132 -> 55, 2 x 30 with 4 on 32
+//    23.2 -> 11.7, 8 x 165 on 2971 2256 -> 2109.
+//    Rounds are counted as a little less than one workgroup to a compute unit (the XCDs' shares are uneven): within one, tiles
+//    of one head each find a compute unit of their own, and more rows to a workgroup take longer (6 x 33 on 3233, one layer, 168
+//    tiles: 45.6 and 49.4 us packed; 9 x 954 with 61 active on 154, 252 tiles: 37.1 and 32.5); the same for a saving that ends in the same
+//    round (32 layers, 1 x 208 on 87, 1792 and 1664: 59.2 and 63.0).  In launches that run at once (`packed` in contiguous128) even the
+//    choice would cost (9 x 48 on 56 9.1 and 9.4).  Not a block whose keys belong to four or eight parts (Reference): a wave has one pass and
+//    one reference.
 //  * spread (spread_limit): one block, shared by all waves.
-constexpr int kPackFrom = 224;
+constexpr uint32_t kPackRound = 224;
+// whether a sequence's last block (its only one, or the one behind a multiple of 256 rows) has its keys in several parts
+__device__ __forceinline__ bool in_parts(const AttnArgs &a, int N) {
+  return a.rounding == kTiles256 ? ((N - 1) & 255) < 32 : a.rounding != kOnePass && N <= 32;
+}
+template <int WM>
+__host__ __device__ __forceinline__ bool saves_rounds(const AttnArgs &a, int blocks) {
+  const uint32_t listed = uint32_t(a.rep * blocks + WM - 1) / WM, tiles = uint32_t(a.rep) * (uint32_t(blocks + WM - 1) / WM);
+  return (listed * uint32_t(a.units) + kPackRound - 1) / kPackRound < (tiles * uint32_t(a.units) + kPackRound - 1) / kPackRound;
+}
 template <int WM, bool FINE, bool PACK>
 inline int64_t place_blocks(AttnArgs &a, const AttnLayers &layers) {
   bool one_group;
   const int64_t nwg = place_grid(a, layers, FINE ? 32 : 32 * WM, FINE ? 1 << 20 : 32 * 8 / WM, kUnitGroup, 0, &one_group);  // FINE: always one
   const int64_t units = int64_t(a.B) * a.Hkv * a.layers;
+  a.units = int32_t(units);
   a.spread_blocks = int32_t(spread_limit(a.rep, FINE, one_group) / (units * a.rep));
-  a.unpacked_tiles = int32_t(kPackFrom / units);
-  // with more heads than are spread every sequence is packed, unless its tiles are as few so (the limits are above kPackFrom)
-  if (PACK && a.spread_blocks == 0) return place_grid(a, layers, 32 * WM, 32 * 8 / WM, kUnitGroup, 0, nullptr, WM);
-  return nwg;
+  if (!PACK || a.spread_blocks > 0 || !saves_rounds<WM>(a, (a.S + 31) / 32)) return nwg;
+  // Packed as the longest suffix needs it, and room for what is never packed: a last block in parts, behind a multiple of 256
+  // rows, or of a suffix of up to 32.
+  const int64_t parts = a.rounding == kOnePass ? 0 : a.rounding == kTiles256 ? (a.S - 1) / 256 * (8 / WM) + 1 : 1;
+  return place_grid(a, layers, 32 * WM, 32 * 8 / WM, kUnitGroup, 0, nullptr, WM, parts * a.rep);
 }
 struct Blocks {
   int w, first_head, rep, tile;  // tile: w / rep
-  int count;                     // blocks in the list from this workgroup's first on: at most none, one, ...
+  int count;                     // blocks in the list from this workgroup's first on: none or less, one, ...
   bool spread, packed;
 };
 template <int WM, bool FINE, bool PACK>
@@ -265,9 +280,9 @@ __device__ __forceinline__ Blocks blocks_of(const AttnArgs &a, const UnitPlace &
   Blocks k = {p.w, p.g * a.rep, a.rep, quotient(p.w, a.by_rep), 0, false, false};
   const int blocks = (N + 31) >> 5;
   k.spread = WM == 4 && (FINE || blocks * a.rep <= a.per_unit) && blocks <= a.spread_blocks;
-  const int tiles = a.rep * ((blocks + WM - 1) / WM), listed = a.rep * blocks;
-  k.packed = PACK && !k.spread && (listed + WM - 1) / WM < tiles && tiles > a.unpacked_tiles;
-  k.count = k.spread ? blocks - k.tile : k.packed ? listed - WM * k.w : blocks - WM * k.tile;
+  if (PACK)
+    k.packed = !k.spread && !in_parts(a, N) && (saves_rounds<WM>(a, blocks) || a.rep * ((blocks + WM - 1) / WM) > a.per_unit);
+  k.count = k.spread ? blocks - k.tile : k.packed ? a.rep * blocks - WM * k.w : blocks - WM * k.tile;
   return k;
 }
 // first row and head of wave v's block (v >= count: rows beyond the suffix, of some head of the group)

@@ -1096,8 +1096,9 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
     RefKeys ref = {0, 0};
     if (one_pass) {
       ref.count = min(32, P + N);
-      if (a.rounding == kTiles256 && (P & 31)) ref = {P & ~31, P & 31};
-      else if (a.rounding == kTiles256 && (N & 31)) ref = {P + (N & ~31), N & 31};
+      const bool ragged_first = a.rounding == kTiles256 || (PACK && N > 32);  // (N > 32: the last block of a list)
+      if (ragged_first && (P & 31)) ref = {P & ~31, P & 31};
+      else if (ragged_first && (N & 31)) ref = {P + (N & ~31), N & 31};
     }
     // (FINE has the plain body: what the other one decides in its loop costs a workgroup that has its compute unit to itself
     // a fifth, 64 of 640 rows of 28/4 heads on 3500 35.3 and 28.4 us; both in one kernel cost 5 % where caches are short, 32 layers of 4 x 21 on 81
@@ -1141,6 +1142,7 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
     for (int r = 0; r < 16; ++r) oacc[db][r] = 0.f;
   float mref = -INFINITY, lsum = 0.f;
   const float sc = a.scale * kLog2e;
+  const int T = P + N;
 
   // fragment addresses inside stage 0 (as in attn_bf16_ring_kernel)
   const unsigned char *kaddr[KK], *vaddr[DB];
@@ -1152,6 +1154,22 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
     const unsigned char *vbase = smem + VBASE + (4 * hf + (s16 >> 2)) * (D * 2) + (16 * ((lane >> 4) & 1) + 4 * (s16 & 3)) * 2;
 #pragma unroll
     for (int db = 0; db < DB; ++db) vaddr[db] = vbase + 64 * (db ^ r3);
+  }
+
+  // Blocks of a list that would be tiles of their own (key_split_body with ref) begin with the reference of the first 32 keys.
+  if (PACK && list.packed && a.rounding == kOnePass && N <= 32 && ((P | N) & 31) && live) {
+    const int t = min(lq, T - 1);
+    const char *kp = (t < P ? kc + int64_t(t) * cpitch : ks + int64_t(t - P) * spitch) + 16 * hf;
+    f32x16 s;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) s[r] = 0.f;
+#pragma unroll
+    for (int kk = 0; kk < KK; ++kk)
+      s = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8 *>(kp + 32 * kk), qf[kk], s, 0, 0, 0);
+    float bm = s[0];  // (as there: no maximum in asm straight behind the matrix instructions)
+#pragma unroll
+    for (int r = 1; r < 16; ++r) bm = __builtin_fmaxf(bm, s[r]);
+    mref = half_max(bm) * sc;
   }
 
   // ---- ragged ends: rows [32*nc, P) of the cache and rows [32*ns, N) of the suffix ----

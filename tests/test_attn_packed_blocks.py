@@ -40,6 +40,7 @@ int main() {
     AttnLayers layers = {};
     layers.n = L;
     a.B = B; a.S = S; a.Hq = Hq; a.Hkv = Hkv;
+    a.rounding = contiguous128(int64_t(L) * B * Hq, Hq / Hkv, S, 1000).rounding;
     if (WM == 8) pack ? walk<8, false, true>(a, layers, N) : walk<8, false, false>(a, layers, N);
     else if (pack == 2) walk<4, true, false>(a, layers, N);
     else pack ? walk<4, false, true>(a, layers, N) : walk<4, false, false>(a, layers, N);
@@ -63,6 +64,7 @@ def program(tmp_path_factory):
 FORMS = [(4, 1, 32, 20, 28, 4, (1, 20, 0)), (4, 1, 32, 700, 7, 1, (700, 33, 32, 64, 65, 0, 129)), (4, 1, 16, 100, 40, 8, (97, 96, 31)),
          (4, 1, 1, 600, 28, 4, (600, 40, 3, 0, 300)), (4, 1, 3, 161, 12, 6, (161, 128, 127, 5)), (4, 1, 32, 300, 15, 5, (300, 161, 160, 17)),
          (8, 1, 32, 512, 8, 2, (512, 257, 256, 255, 33, 1)), (8, 1, 9, 1000, 28, 4, (1000, 31, 0)),
+         (4, 1, 32, 18, 28, 4, (18, 2)), (4, 1, 32, 208, 28, 4, (208,)), (4, 1, 32, 75, 28, 4, (75,)), (4, 1, 32, 75, 28, 4, (33, 64)), (4, 1, 7, 1000, 28, 4, (70, 33, 130)), (4, 1, 32, 40, 28, 4, (40, 33, 32, 1)), (4, 1, 32, 290, 28, 4, (290, 257, 288, 289, 32, 1, 33)), (8, 1, 32, 600, 28, 4, (600, 513, 544, 20)),
          (4, 0, 1, 150, 28, 4, (150, 1, 64, 33)), (4, 2, 1, 250, 28, 4, (250, 100, 7)), (8, 0, 1, 600, 6, 2, (600, 290)), (4, 0, 2, 300, 5, 5, (300, 129))]
 
 
