@@ -76,7 +76,7 @@ int32_t attn_entry(const lsp_attn_desc *d, const void *q, const void *k_suf, con
   a.prefix_len = prefix_len; a.suffix_len = suffix_len; a.workspace = workspace;
   a.cache_rows = cache_rows;
   a.unit_group = a.layers = a.rep = a.chunk = a.per_unit = 1;
-  a.spread = a.rounding = a.spread_blocks = a.units = 0;
+  a.spread = a.table = a.rounding = a.spread_blocks = a.units = 0;
   hipStream_t st = static_cast<hipStream_t>(stream);
   AttnLayers none;
   none.n = 0;
@@ -114,7 +114,7 @@ extern "C" int32_t lsp_attn_step_layers(const lsp_attn_desc *d, int32_t num_laye
   a.prefix_len = prefix_len; a.suffix_len = suffix_len; a.workspace = workspace;
   a.cache_rows = nullptr;
   a.unit_group = a.layers = a.rep = a.chunk = a.per_unit = 1;
-  a.spread = a.rounding = a.spread_blocks = a.units = 0;
+  a.spread = a.table = a.rounding = a.spread_blocks = a.units = 0;
   hipStream_t st = static_cast<hipStream_t>(stream);
   for (int l0 = 0; l0 < num_layers; l0 += kMaxAttnLayers) {
     const int nl = num_layers - l0 < kMaxAttnLayers ? num_layers - l0 : kMaxAttnLayers;

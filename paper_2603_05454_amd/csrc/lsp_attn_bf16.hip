@@ -253,11 +253,12 @@ __device__ __forceinline__ void merge_store(const AttnArgs &a, const f32x16 (&oa
     ml[32 + lq] = lsum;
   }
   __syncthreads();
-  // wave (wm, wk) finishes d-range [wk*D/WK, (wk+1)*D/WK) of its query block: items = (query, 8 d)
-  constexpr int DW = D / WK;  // d columns per wave
-  constexpr int CH = DW / 8;  // 16-byte output chunks per query
-  for (int it = lane; it < 32 * CH; it += 64) {
-    const int qq = it / CH, dd = wk * DW + 8 * (it % CH);
+  // wave (wm, wk) finishes rows [wk*32/WK, (wk+1)*32/WK) of its query block, whole: items = (row, 8 d).  (Pieces of 32 or 64
+  // bytes of all 32 rows instead: one layer, 2 x 30 rows on 900 11.25 us, 11.01 so, 3 x 48 with 10 active on 83 6.53 and 6.29; 32 layers,
+  // 3 x 71 with 20 active on 53 53.6 and 55.2.)
+  constexpr int CH = D / 8;  // 16-byte output chunks per row
+  for (int it = lane; it < 32 / WK * CH; it += 64) {
+    const int qq = wk * (32 / WK) + it / CH, dd = 8 * (it % CH);
     const int qrow = q0 + wm * 32 + qq;
     float M = -INFINITY;
 #pragma unroll
@@ -590,9 +591,8 @@ __global__ __launch_bounds__(64 * WM * WK, 2) void attn_bf16_kernel(AttnArgs a_i
   const Place pl = place(a, 32 * WM);
   if (!pl.valid) return;
   if (!ONE) for_layer(a, layers, pl.layer);
-  const int N = min(max(a.suffix_len[pl.b], 0), a.S);
+  const auto [N, P] = lengths_of(a, pl.b);
   if (pl.q0 >= N) return;
-  const int P = min(max(a.prefix_len[pl.b], 0), a.C);
   key_split_body<D, WM, WK, GATHER, PARTS>(a, pl.b, pl.g, pl.h, pl.q0, N, P, smem);
 }
 
@@ -1073,6 +1073,7 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   constexpr int D = 128, KK = D / 16, DB = D / 32, NS = WM == 8 ? 8 : 5;
   constexpr int LPB = 8 / WM;  // wave-wide loads of K (and of V) that a wave makes per block
   fetch_operands(a);
+  fetch_now(a.rounding, a.spread_blocks, a.units, a.per_unit);
   constexpr int TILE = 32 * D * 2, VBASE = NS * TILE;
   extern __shared__ __attribute__((aligned(1024))) unsigned char smem[];
 
@@ -1080,8 +1081,7 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   if (!pl.valid) return;
   for_layer(a, layers, pl.layer);
   const int b = pl.b, g = pl.g;
-  const int N = min(max(a.suffix_len[b], 0), a.S);
-  const int P = min(max(a.prefix_len[b], 0), a.C);
+  const auto [N, P] = lengths_of(a, b);
   // A tile of one block - a sequence down to its last rows, or the tail of a longer
   // suffix that ends just past a multiple of the tile - would keep all waves but one idle for the whole key
   // range: its one block of queries goes to the key-split body (as in attn_bf16_ring_kernel), which
@@ -1258,18 +1258,33 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   }
 
   lsum = half_sum(lsum);
-  if (live && qi < N) {
-    const float inv = 1.0f / lsum;
-    uint16_t *op = static_cast<uint16_t *>(a.out) + b * a.os[0] + int64_t(qi) * a.os[1] + h * a.os[2];
+  const float inv = 1.0f / lsum;
+  // The rows go out through LDS, whole (256 bytes, 16 lanes each): a lane's own pieces would be stores of 8 bytes to 32 rows (32
+  // layers, 16 x 384 rows on 1152 5.42 ms, in pieces of 16 bytes 5.32, so 5.28; 1 x 256 on 512 144, 135 and 133 us).
+  __syncthreads();  // nobody reads the ring any more, and nothing is on its way into it
+  if (!live) return;
+  constexpr int PITCH = D * 2 + 16;
+  unsigned char *rows = smem + wave_s * (32 * PITCH);
 #pragma unroll
-    for (int db = 0; db < DB; ++db)
+  for (int db = 0; db < DB; ++db)
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        u32x2 w;
-        w.x = pack_bf16(oacc[db][4 * r4] * inv, oacc[db][4 * r4 + 1] * inv);
-        w.y = pack_bf16(oacc[db][4 * r4 + 2] * inv, oacc[db][4 * r4 + 3] * inv);
-        *reinterpret_cast<u32x2 *>(op + 32 * db + 8 * r4 + 4 * hf) = w;
+    for (int p = 0; p < 2; ++p) {
+      u32x4 w;
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        const auto s = __builtin_amdgcn_permlane32_swap(pack_bf16(oacc[db][8 * p + 2 * k] * inv, oacc[db][8 * p + 2 * k + 1] * inv),
+                                                        pack_bf16(oacc[db][8 * p + 4 + 2 * k] * inv, oacc[db][8 * p + 5 + 2 * k] * inv), false, false);
+        w[k] = s[0];
+        w[2 + k] = s[1];
       }
+      *reinterpret_cast<u32x4 *>(rows + lq * PITCH + (32 * db + 16 * p + 8 * hf) * 2) = w;
+    }
+  uint16_t *op = static_cast<uint16_t *>(a.out) + b * a.os[0] + h * a.os[2] + 8 * (lane & 15);
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = 4 * i + (lane >> 4);
+    const u32x4 w = *reinterpret_cast<const u32x4 *>(rows + r * PITCH + 16 * (lane & 15));
+    if (row0 + r < N) *reinterpret_cast<u32x4 *>(op + int64_t(row0 + r) * a.os[1]) = w;
   }
 }
 
