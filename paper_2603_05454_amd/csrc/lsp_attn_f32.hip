@@ -57,16 +57,14 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a_in)
   const int b = pl.b, g = pl.g, h = pl.h, q0 = pl.q0;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int i = lane & 15, grp = lane >> 4;
-  const int nraw = a.suffix_len[b], praw = a.prefix_len[b];
 
   // rows up to S-1 exist whatever N turns out to be
   f32x4 qf[CK];
   const float *q = static_cast<const float *>(a.q) + b * a.qs[0] + min(q0 + i, a.S - 1) * a.qs[1] + h * a.qs[2] + 4 * grp;
 #pragma unroll
   for (int c = 0; c < CK; ++c) qf[c] = *reinterpret_cast<const f32x4 *>(q + 16 * c);
-  const int N = min(max(nraw, 0), a.S);
+  const auto [N, P] = lengths_of(a, b);
   if (q0 >= N) return;
-  const int P = min(max(praw, 0), a.C);
   const int T = P + N;
   const float *kc = static_cast<const float *>(a.k_cache) + b * a.cs[0] + g * a.cs[2];
   const float *vc = static_cast<const float *>(a.v_cache) + b * a.cs[0] + g * a.cs[2];
