@@ -114,3 +114,29 @@ def test_packed_workgroups_match_the_oracle(lsp, oracle, layers, S, C, Hq, Hkv, 
         assert (got[act] - ref[act]).abs().max().item() <= 2e-2
         assert torch.all(got[~act] == 123.0)
     assert all(torch.equal(outs[l], outs[0]) for l in range(1, layers - 1))
+
+
+# cached rows, active rows: both ends ragged and fitting one block, just so, or one row too many; one end, or none; less than a block in all
+ENDS = [(50, 100), (60, 68), (63, 97), (63, 98), (64, 97), (63, 96), (64, 96), (1, 33), (0, 40), (31, 33), (5, 34), (200, 65)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [33, 100, 300])
+def test_ragged_ends_of_cache_and_suffix(lsp, oracle, rows):
+    """Sequences with every pair of ends in one launch of tiles of 128 rows, one of whole blocks among them.  The bound is the bf16 one
+    of test_gpu_attention.py."""
+    B, C = len(ENDS), 200
+    w = W.scaled(W.C2, B=B, S=rows, P=C, C=C, Hq=12, Hkv=12, D=128, seed=77 + rows)
+    pl = torch.tensor([p for p, _ in ENDS], dtype=torch.int32)
+    sl = torch.tensor([min(n + rows - 100, rows) if rows > 100 else min(n, rows) for _, n in ENDS], dtype=torch.int32)
+    kv = W.make_layer_kv(w, 0, prefix_len=pl)
+    dev = {k: v.cuda() for k, v in kv.items()}
+    names = ("q", "k_suf", "v_suf", "k_cache", "v_cache")
+    outs = [torch.full(dev["q"].shape, 123.0, dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    lsp.attn_step_layers(lsp.AttnLayerTable(*[[dev[k]] * 3 for k in names], outs), pl.cuda(), sl.cuda())
+    ref = oracle.attention(**kv, prefix_len=pl, suffix_len=sl)
+    act = ~torch.isnan(ref)
+    for o in outs:
+        got = o.float().cpu()
+        assert (got[act] - ref[act]).abs().max().item() <= 2e-2
+        assert torch.all(got[~act] == 123.0)
