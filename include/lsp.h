@@ -86,6 +86,8 @@ typedef struct {
   int64_t o_stride[3];
 } lsp_attn_desc;
 
+/* Bytes of a workspace with which an attention call may be faster (fp32 operands in few rows on many keys, which are
+ * then divided between workgroups); 0 where it is of no use.  The calls take NULL, and fewer bytes, all the same. */
 size_t lsp_attn_workspace_bytes(const lsp_attn_desc *desc);
 
 /*
@@ -94,8 +96,8 @@ size_t lsp_attn_workspace_bytes(const lsp_attn_desc *desc);
  * at most 2^24 elements.  prefix_len, suffix_len: device int32[B], with
  * 0 <= P_b <= C and 0 <= N_b <= S (not checked on the host; values are
  * clamped to those ranges on the device).  workspace: device, at least
- * lsp_attn_workspace_bytes(desc) bytes, 256-byte aligned (may be NULL when
- * that size is 0).
+ * lsp_attn_workspace_bytes(desc) bytes, 16-byte aligned, or NULL; it need not be
+ * cleared, and calls that overlap need one each.
  */
 int32_t lsp_attn_step(const lsp_attn_desc *desc, const void *q, const void *k_suf,
                       const void *v_suf, const void *k_cache, const void *v_cache,

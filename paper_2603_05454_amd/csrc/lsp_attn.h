@@ -117,10 +117,9 @@ struct UnitPlace {
   bool valid;
 };
 template <bool GROUPS = true>  // false: groups of one unit
-__device__ __forceinline__ UnitPlace place_in_unit(const AttnArgs &a) {
+__device__ __forceinline__ UnitPlace place_in_unit(const AttnArgs &a, int n) {
   UnitPlace p;
   const int chunk = a.chunk;
-  const int n = workgroup_id();
   const int m8 = n >> 3;
   const int G = GROUPS ? a.unit_group : 1;
   const int grp = quotient(m8, a.by_group), r = m8 - grp * (G * chunk);
@@ -143,10 +142,18 @@ __device__ __forceinline__ UnitPlace place_in_unit(const AttnArgs &a) {
   return p;
 }
 template <bool GROUPS = true>
-__device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
-  const UnitPlace u = place_in_unit<GROUPS>(a);
+__device__ __forceinline__ UnitPlace place_in_unit(const AttnArgs &a) {
+  return place_in_unit<GROUPS>(a, workgroup_id());
+}
+template <bool GROUPS = true>
+__device__ __forceinline__ Place place(const AttnArgs &a, int qtile, int n) {
+  const UnitPlace u = place_in_unit<GROUPS>(a, n);
   const int tile = quotient(u.w, a.by_rep);
   return {u.layer, u.b, u.g, u.g * a.rep + u.w - tile * a.rep, tile * qtile, u.valid};
+}
+template <bool GROUPS = true>
+__device__ __forceinline__ Place place(const AttnArgs &a, int qtile) {
+  return place<GROUPS>(a, qtile, workgroup_id());
 }
 // Fields of that placement in `a`, and its number of workgroups.  Units are cut only where an XCD would get more than
 // `enough` workgroups.  resident: workgroups that run at once on an XCD (0: groups as above whatever their number).  whole: whether
@@ -318,6 +325,6 @@ __device__ __forceinline__ int cache_row(const AttnArgs &a, int b, int t) {
 
 int32_t launch_attn_f32(const AttnArgs &a, hipStream_t st);
 int32_t launch_attn_bf16(const AttnArgs &a, const AttnLayers &layers, hipStream_t st);
-size_t attn_bf16_workspace_bytes(int32_t B, int32_t S, int32_t Hq, int32_t D);
+size_t attn_f32_workspace_bytes(int32_t B, int32_t S, int32_t Hq, int32_t Hkv, int32_t D, int32_t C);  // 0: of no use
 
 }  // namespace lsp

@@ -48,12 +48,17 @@ int32_t check(const lsp_attn_desc *d, AttnArgs &a) {
 }  // namespace lsp
 
 extern "C" size_t lsp_attn_workspace_bytes(const lsp_attn_desc *d) {
-  if (d == nullptr || d->dtype != LSP_BF16) return 0;
-  return lsp::attn_bf16_workspace_bytes(d->B, d->S, d->Hq, d->D);
+  if (d == nullptr || d->dtype != LSP_F32 || d->B <= 0 || d->S <= 0 || d->Hq <= 0 || d->Hkv <= 0 || d->C <= 0 || d->Hq % d->Hkv != 0) return 0;
+  return lsp::attn_f32_workspace_bytes(d->B, d->S, d->Hq, d->Hkv, d->D, d->C);
 }
 
 namespace lsp {
 namespace {
+// a workspace that the call may use; without one it goes the way that needs none
+void *usable_workspace(const lsp_attn_desc *d, void *workspace, size_t bytes) {
+  const size_t need = lsp_attn_workspace_bytes(d);
+  return need > 0 && workspace != nullptr && bytes >= need && aligned16(workspace) ? workspace : nullptr;
+}
 int32_t attn_entry(const lsp_attn_desc *d, const void *q, const void *k_suf, const void *v_suf,
                    const void *k_cache, const void *v_cache, const int32_t *cache_rows,
                    const int32_t *prefix_len, const int32_t *suffix_len, void *out, void *workspace,
@@ -66,14 +71,9 @@ int32_t attn_entry(const lsp_attn_desc *d, const void *q, const void *k_suf, con
   LSP_CHECK_ARG(aligned16(q) && aligned16(k_suf) && aligned16(v_suf) && aligned16(k_cache) &&
                     aligned16(v_cache) && aligned16(out),
                 "lsp_attn_step: pointers must be 16-byte aligned");
-  const size_t need = lsp_attn_workspace_bytes(d);
-  if (need > 0 && (workspace == nullptr || workspace_bytes < need ||
-                   (reinterpret_cast<uintptr_t>(workspace) & 255u))) {
-    set_error("lsp_attn_step: workspace of %zu bytes (256-byte aligned) required, got %zu", need, workspace_bytes);
-    return LSP_ERR_WORKSPACE;
-  }
+  a.workspace = usable_workspace(d, workspace, workspace_bytes);
   a.q = q; a.k_suf = k_suf; a.v_suf = v_suf; a.k_cache = k_cache; a.v_cache = v_cache; a.out = out;
-  a.prefix_len = prefix_len; a.suffix_len = suffix_len; a.workspace = workspace;
+  a.prefix_len = prefix_len; a.suffix_len = suffix_len;
   a.cache_rows = cache_rows;
   a.unit_group = a.layers = a.rep = a.chunk = a.per_unit = 1;
   a.spread = a.table = a.rounding = a.spread_blocks = a.units = 0;
@@ -106,12 +106,8 @@ extern "C" int32_t lsp_attn_step_layers(const lsp_attn_desc *d, int32_t num_laye
                       aligned16(k_cache_layers[l]) && aligned16(v_cache_layers[l]) && aligned16(out_layers[l]),
                   "lsp_attn_step_layers: operands of layer %d must be 16-byte aligned", l);
   }
-  const size_t need = lsp_attn_workspace_bytes(d);
-  if (need > 0 && (workspace == nullptr || workspace_bytes < need || (reinterpret_cast<uintptr_t>(workspace) & 255u))) {
-    set_error("lsp_attn_step_layers: workspace of %zu bytes (256-byte aligned) required, got %zu", need, workspace_bytes);
-    return LSP_ERR_WORKSPACE;
-  }
-  a.prefix_len = prefix_len; a.suffix_len = suffix_len; a.workspace = workspace;
+  a.workspace = usable_workspace(d, workspace, workspace_bytes);
+  a.prefix_len = prefix_len; a.suffix_len = suffix_len;
   a.cache_rows = nullptr;
   a.unit_group = a.layers = a.rep = a.chunk = a.per_unit = 1;
   a.spread = a.table = a.rounding = a.spread_blocks = a.units = 0;

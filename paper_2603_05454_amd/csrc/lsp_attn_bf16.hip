@@ -1372,8 +1372,6 @@ int32_t dispatch(const AttnArgs &a, const AttnLayers &layers, hipStream_t st) {
 
 }  // namespace
 
-size_t attn_bf16_workspace_bytes(int32_t, int32_t, int32_t, int32_t) { return 0; }
-
 int32_t launch_attn_bf16(const AttnArgs &a, const AttnLayers &layers, hipStream_t st) {
   if (a.D == 128) return dispatch<128>(a, layers, st);
   if (a.D == 64) return dispatch<64>(a, layers, st);

@@ -18,11 +18,14 @@
 // and the chain of dependent matrix steps.  Hence the narrow query tile and the keys
 // of a tile split eight ways and merged through LDS.  (Q stands in the source before
 // the lengths are known; the compiler requests it behind them.)  Measured, kernel
-// alone: that size 6.1 us (137 us for one query per lane on plain FMAs with K/V
+// alone: that size 5.4 us (137 us for one query per lane on plain FMAs with K/V
 // broadcast from LDS, which leaves 4 waves in flight), 256 queries x 1280 keys x 4
-// heads 19.5 us (903), 8 sequences of 1024 x 2048 x 8 heads 371 us (1589).  Tiles of 32 queries and a four-way split
+// heads 13.7 us (903), 8 sequences of 1024 x 2048 x 8 heads 371 us (1589).  Tiles of 32 queries and a four-way split
 // are 15 % faster at that last size and 30-60 % slower at the small ones; a
 // sixteen-way split and requesting the next tile ahead change nothing.
+#include <chrono>
+#include <type_traits>
+
 #include "lsp_attn.h"
 
 namespace lsp {
@@ -33,6 +36,7 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr int kTile = 16;  // queries per workgroup, keys per step of a wave
 constexpr int kWaves = 8;  // way split of the keys
+constexpr int kComputeUnits = 256;
 
 // over the four lanes (grp = 0..3) that hold scores of the same query
 __device__ __forceinline__ float group_max(float x) {
@@ -44,15 +48,39 @@ __device__ __forceinline__ float group_sum(float x) {
   return x + __shfl_xor(x, 32);
 }
 
+// Keys of a tile divided between workgroups as well, in parts of kPart keys dealt out in turn: a part leaves its 16 rows of
+// unnormalised output, maxima and sums in the workspace, then the call's tag.  A workgroup that finds the tags of all parts
+// there merges them in order and stores the rows (the last one to write does; if another one does too, both store the same),
+// and clears the tags for a replay.  Everything passes as device-scope atomics of 8 bytes, as in confidence_split_kernel.
+// One compute unit's matrix pipe and load path were what a tile waited for, 1.1 us for 128 keys of 64, 2.9 of 128, while
+// most of the others had none.  4 heads, 16 rows of 64: 400 keys 8.4 -> 6.9 us, 700 11.7 -> 7.3, 1280 19.1 -> 8.1; 128 rows
+// on 1280 19.3 -> 10.3; of 128: 400 keys 14.8 -> 9.8, 1000 28.1 -> 10.7.  The exchange takes 1.5 to 2 us, hence kSavedKeys,
+// the fewer keys that a part must have (16 rows of 64, 260 keys 6.97 us whole and 7.41 divided, 330 keys 7.79 and 6.84; of
+// 128, 200 keys 10.6 and 11.9, 260 keys 11.7 and 9.7).  That is decided with the lengths, on the device: a launch with room for
+// parts whose keys turn out too few takes 1 % longer for the workgroups that find nothing.  The merge requests all pieces of a
+// thread at once, for up to 4, 8 and 16 parts (16 for every number: 16 rows of 64 on 700 keys 8.2 for 7.3).  The rms
+// error against 64 bits is 0.68 to 0.99 of whole keys' (16 to 128 rows, 346 to 2016 keys, scores of deviation 1 and 4).
+constexpr int kPart = kTile * kWaves;
+constexpr int kMaxParts = 16;
 template <int D>
-__global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a_in) {
+constexpr int kSavedKeys = D == 64 ? 176 : 100;
+template <int D>
+constexpr size_t kPartBytes = kTile * D * 4 + kTile * 8;
+template <int D>
+__host__ __device__ __forceinline__ int parts_of(int keys, int most) {
+  const int rounds = (keys + kPart - 1) / kPart, parts = rounds < most ? rounds : most;
+  return parts > 1 && keys - (rounds + parts - 1) / parts * kPart >= kSavedKeys<D> ? parts : 1;
+}
+
+template <int D, bool SPLIT>
+__global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a_in, int max_parts, uint64_t tag) {
   constexpr int CK = D / 16;  // 16-byte K (and Q) pieces per lane and row
   constexpr int CV = D / 64;  // 16-byte V pieces per lane and key
   constexpr int OP = D + 4;   // floats per merged O row
   AttnArgs a = a_in;
   a.layers = 1;
   fetch_operands(a);
-  const Place pl = place<false>(a, kTile);
+  const Place pl = place<false>(a, kTile, SPLIT ? int(blockIdx.x) : workgroup_id());
   if (!pl.valid) return;
   const int b = pl.b, g = pl.g, h = pl.h, q0 = pl.q0;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -66,6 +94,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a_in)
   const auto [N, P] = lengths_of(a, b);
   if (q0 >= N) return;
   const int T = P + N;
+  const int parts = SPLIT ? parts_of<D>(T, max_parts) : 1, part = SPLIT ? int(blockIdx.y) : 0;
+  if (part >= parts) return;
   const float *kc = static_cast<const float *>(a.k_cache) + b * a.cs[0] + g * a.cs[2];
   const float *vc = static_cast<const float *>(a.v_cache) + b * a.cs[0] + g * a.cs[2];
   const float *ks = static_cast<const float *>(a.k_suf) + b * a.ks[0] + g * a.ks[2];
@@ -84,7 +114,7 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a_in)
     for (int e = 0; e < 4; ++e) o[c][e] = zero;
   float m = -INFINITY, l = 0.f;
   const float sc = a.scale * kLog2e;
-  for (int t0 = kTile * wave; t0 < T; t0 += kTile * kWaves) {
+  for (int t0 = kPart * part + kTile * wave; t0 < T; t0 += kPart * parts) {
     f32x4 kf[CK], vf[4][CV];
     const float *kp = row_of(kc, ks, t0 + i) + 4 * grp;
 #pragma unroll
@@ -152,6 +182,15 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a_in)
     sl[wave][i] = l;
   }
   __syncthreads();
+  unsigned long long *mine = nullptr, *flags = nullptr;
+  if (SPLIT && parts > 1) {
+    const int tile = blockIdx.x, tiles = gridDim.x;
+    flags = static_cast<unsigned long long *>(a.workspace) + size_t(tile) * kMaxParts;
+    mine = static_cast<unsigned long long *>(a.workspace) + size_t(tiles) * kMaxParts + size_t(tile) * max_parts * (kPartBytes<D> / 8);
+  }
+  auto pass = [](unsigned long long *p, float lo, float hi) {
+    __hip_atomic_store(p, (unsigned long long)(__float_as_uint(hi)) << 32 | __float_as_uint(lo), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  };
   for (int it = tid; it < kTile * (D / 4); it += 64 * kWaves) {
     const int qq = it / (D / 4), d = 4 * (it % (D / 4));
     if (q0 + qq >= N) continue;
@@ -160,15 +199,93 @@ __global__ __launch_bounds__(64 * kWaves, 2) void attn_f32_kernel(AttnArgs a_in)
     for (int w = 1; w < kWaves; ++w) M = fmaxf(M, sm[w][qq]);
     f32x4 acc = zero;
     float den = 0.f;
+    const float own = SPLIT && parts > 1 && M == -INFINITY ? 0.f : M;  // (a part of such scores only adds nothing to the others)
 #pragma unroll
     for (int w = 0; w < kWaves; ++w) {
-      const float wgt = __builtin_amdgcn_exp2f(sm[w][qq] - M);  // 0 for a wave that saw no key (or only scores of -infinity)
+      const float wgt = __builtin_amdgcn_exp2f(sm[w][qq] - own);  // 0 for a wave that saw no key (or only scores of -infinity)
       den += sl[w][qq] * wgt;
       acc += *reinterpret_cast<const f32x4 *>(&so[w][qq][d]) * wgt;
+    }
+    if (SPLIT && parts > 1) {
+      unsigned long long *o = mine + part * (kPartBytes<D> / 8);
+      pass(o + (qq * D + d) / 2, acc.x, acc.y);
+      pass(o + (qq * D + d) / 2 + 1, acc.z, acc.w);
+      if (d == 0) pass(o + kTile * D / 2 + qq, M, den);
+      continue;
     }
     float *out = static_cast<float *>(a.out) + b * a.os[0] + int64_t(q0 + qq) * a.os[1] + h * a.os[2] + d;
     *reinterpret_cast<f32x4 *>(out) = acc * (1.0f / den);
   }
+  if (!SPLIT || parts == 1) return;
+
+  __shared__ int s_all;
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): what this wave has passed on has arrived
+  __syncthreads();
+  if (wave == 0) {
+    if (lane == 0) __hip_atomic_store(flags + part, tag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0x0F70);
+    asm volatile("" ::: "memory");
+    const unsigned long long f = lane < parts ? __hip_atomic_load(flags + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : tag;
+    const bool all = __all(f == tag);
+    if (lane == 0) s_all = all;
+  }
+  __syncthreads();
+  if (!s_all) return;
+  auto low = [](unsigned long long x) { return __uint_as_float(uint32_t(x)); };
+  auto high = [](unsigned long long x) { return __uint_as_float(uint32_t(x >> 32)); };
+  auto merge = [&](auto most) {  // up to so many parts, all of a thread's pieces requested at once
+    constexpr int U = decltype(most)::value;
+    for (int it = tid; it < kTile * (D / 4); it += 64 * kWaves) {
+      const int qq = it / (D / 4), d = 4 * (it % (D / 4));
+      if (q0 + qq >= N) continue;
+      unsigned long long ml[U], x[U], y[U];
+#pragma unroll
+      for (int p = 0; p < U; ++p) {
+        unsigned long long *o = mine + min(p, parts - 1) * (kPartBytes<D> / 8);
+        ml[p] = __hip_atomic_load(o + kTile * D / 2 + qq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        x[p] = __hip_atomic_load(o + (qq * D + d) / 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        y[p] = __hip_atomic_load(o + (qq * D + d) / 2 + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      float M = low(ml[0]);
+#pragma unroll
+      for (int p = 1; p < U; ++p) M = fmaxf(M, low(ml[p]));
+      f32x4 acc = zero;
+      float den = 0.f;
+#pragma unroll
+      for (int p = 0; p < U; ++p)
+        if (p < parts) {
+          const float wgt = __builtin_amdgcn_exp2f(low(ml[p]) - M);
+          den += high(ml[p]) * wgt;
+          acc += f32x4{low(x[p]), high(x[p]), low(y[p]), high(y[p])} * wgt;
+        }
+      float *out = static_cast<float *>(a.out) + b * a.os[0] + int64_t(q0 + qq) * a.os[1] + h * a.os[2] + d;
+      *reinterpret_cast<f32x4 *>(out) = acc * (1.0f / den);
+    }
+  };
+  if (parts <= 4) merge(std::integral_constant<int, 4>{});
+  else if (parts <= 8) merge(std::integral_constant<int, 8>{});
+  else merge(std::integral_constant<int, kMaxParts>{});
+  if (tid < parts) __hip_atomic_store(flags + tid, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Parts that a tile's keys may be divided into: as many as there are compute units for, and as the buffers hold keys for.
+template <int D>
+int most_parts(int64_t tiles, int64_t keys) {
+  const int64_t fit = kComputeUnits / tiles, most = fit < kMaxParts ? fit : kMaxParts;
+  return parts_of<D>(int(keys < (1 << 20) ? keys : 1 << 20), int(most));
+}
+// The tag of one call: another one for the next 2^64 calls of the process, not 0, scrambled.
+inline uint64_t call_tag() {
+  static std::atomic<uint64_t> count{uint64_t(std::chrono::steady_clock::now().time_since_epoch().count())};
+  uint64_t x;
+  do {
+    x = count.fetch_add(1, std::memory_order_relaxed) * 0x9e3779b97f4a7c15u;  // odd factors and shifted copies of itself: a permutation
+    x = (x ^ x >> 30) * 0xbf58476d1ce4e5b9u;
+    x ^= x >> 27;
+  } while (x == 0);
+  return x;
 }
 
 template <int D>
@@ -183,12 +300,26 @@ int32_t launch(AttnArgs a, hipStream_t st) {
     set_error("lsp_attn_step: launch of %lld workgroups is too large", (long long)nwg);
     return LSP_ERR_UNSUPPORTED;
   }
-  attn_f32_kernel<D><<<grid_of(nwg), 64 * kWaves, 0, st>>>(a);
+  const int parts = a.workspace != nullptr ? most_parts<D>(nwg, int64_t(a.C) + a.S) : 1;
+  if (parts > 1)
+    attn_f32_kernel<D, true><<<dim3(unsigned(nwg), unsigned(parts)), 64 * kWaves, 0, st>>>(a, parts, call_tag());
+  else
+    attn_f32_kernel<D, false><<<grid_of(nwg), 64 * kWaves, 0, st>>>(a, 1, 0);
   LSP_CHECK_LAUNCH("lsp_attn_step: fp32 launch");
   return LSP_OK;
 }
 
 }  // namespace
+
+size_t attn_f32_workspace_bytes(int32_t B, int32_t S, int32_t Hq, int32_t Hkv, int32_t D, int32_t C) {
+  AttnArgs a = {};
+  AttnLayers none;
+  none.n = 0;
+  a.B = B; a.S = S; a.Hq = Hq; a.Hkv = Hkv;
+  const int64_t nwg = place_grid(a, none, kTile, 0, 1, 16), keys = int64_t(C) + S;
+  const int parts = D == 64 ? most_parts<64>(nwg, keys) : D == 128 ? most_parts<128>(nwg, keys) : 1;
+  return parts < 2 ? 0 : size_t(nwg) * (8 * kMaxParts + parts * (D == 64 ? kPartBytes<64> : kPartBytes<128>));
+}
 
 int32_t launch_attn_f32(const AttnArgs &a, hipStream_t st) {
   if (a.D == 64) return launch<64>(a, st);
