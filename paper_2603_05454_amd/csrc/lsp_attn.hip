@@ -56,8 +56,9 @@ namespace lsp {
 namespace {
 // a workspace that the call may use; without one it goes the way that needs none
 void *usable_workspace(const lsp_attn_desc *d, void *workspace, size_t bytes) {
+  if (workspace == nullptr) return nullptr;
   const size_t need = lsp_attn_workspace_bytes(d);
-  return need > 0 && workspace != nullptr && bytes >= need && aligned16(workspace) ? workspace : nullptr;
+  return need > 0 && bytes >= need && aligned16(workspace) ? workspace : nullptr;
 }
 int32_t attn_entry(const lsp_attn_desc *d, const void *q, const void *k_suf, const void *v_suf,
                    const void *k_cache, const void *v_cache, const int32_t *cache_rows,

@@ -312,12 +312,16 @@ int32_t launch(AttnArgs a, hipStream_t st) {
 }  // namespace
 
 size_t attn_f32_workspace_bytes(int32_t B, int32_t S, int32_t Hq, int32_t Hkv, int32_t D, int32_t C) {
+  // (asked on every call: most are answered without the placement, which has as many workgroups as tiles or more; and of any sizes)
+  if (B > kComputeUnits || Hq > kComputeUnits || S > kComputeUnits * kTile) return 0;
+  const int64_t keys = int64_t(C) + S, tiles = int64_t(B) * Hq * ((int64_t(S) + kTile - 1) / kTile);
+  if ((D == 64 ? most_parts<64>(tiles, keys) : D == 128 ? most_parts<128>(tiles, keys) : 1) < 2) return 0;
   AttnArgs a = {};
   AttnLayers none;
   none.n = 0;
   a.B = B; a.S = S; a.Hq = Hq; a.Hkv = Hkv;
-  const int64_t nwg = place_grid(a, none, kTile, 0, 1, 16), keys = int64_t(C) + S;
-  const int parts = D == 64 ? most_parts<64>(nwg, keys) : D == 128 ? most_parts<128>(nwg, keys) : 1;
+  const int64_t nwg = place_grid(a, none, kTile, 0, 1, 16);
+  const int parts = D == 64 ? most_parts<64>(nwg, keys) : most_parts<128>(nwg, keys);
   return parts < 2 ? 0 : size_t(nwg) * (8 * kMaxParts + parts * (D == 64 ? kPartBytes<64> : kPartBytes<128>));
 }
 

@@ -30,8 +30,8 @@ def _call(lsp, kv, pl, sl, out, workspace, nbytes):
     assert rc == 0, lsp.lib().lsp_last_error()
 
 
-# keys in all of each sequence, rows, heads, head_dim: 304 | 305 and 228 | 229 (fewest keys that are divided), parts of one or more
-# rounds with a remainder, 16 parts and more rounds than parts; an empty suffix, one row, tiles with a remainder; few parts where
+# keys in all of each sequence, rows, heads, head_dim: 303 | 304 and 227 | 228 (fewest keys that are divided: a part of 128
+# has 176 fewer, 100 at head_dim 128), parts of one or more rounds with a remainder, 16 parts and more rounds than parts; an empty suffix, one row, tiles with a remainder; few parts where
 # there are many tiles
 CASES = [([303, 304, 305, 306], [16, 7, 16, 1], 4, 4, 64), ([227, 228, 229, 384], [5, 0, 17, 17], 4, 2, 128),
          ([2048], [16], 4, 4, 64), ([2049, 1], [3, 1], 7, 1, 64), ([1921], [40], 3, 3, 128), ([1280], [256], 4, 4, 64),
@@ -96,3 +96,12 @@ def test_divided_keys_under_graph_replay(lsp):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, ref)
+
+
+def test_workspace_of_sizes_that_are_not_divided(lsp):
+    """0 for few keys, for more tiles than half the compute units, and for any sizes whatever."""
+    most = 2 ** 31 - 1
+    for sizes in ((1, 16, 4, 4, 64, 287), (1, 16, 4, 4, 128, 211), (129, 16, 1, 1, 64, 2000), (most, 16, 1, 1, 64, 2000), (most,) * 4 + (64, most)):
+        assert lsp.attn_workspace_bytes(0, *sizes) == 0
+    for sizes in ((1, 16, 4, 4, 64, 288), (1, 16, 4, 4, 128, 212), (128, 16, 1, 1, 64, 2000), (1, 16, 4, 4, 64, most)):
+        assert 0 < lsp.attn_workspace_bytes(0, *sizes) < 1 << 22
