@@ -294,7 +294,7 @@ int32_t launch(AttnArgs a, hipStream_t st) {
   none.n = 0;
   // One unit after the other (taking the tiles of eight in turn costs a division, 0.1 of 6 us, and gains nothing), cut
   // into pieces only beyond 16 tiles per XCD (4 heads of 64: 64 queries x 192 keys 6.2 us whole and 6.5 in pieces, 256 x
-  // 1280 19.5 and 19.9, three sequences of that 21.7 and 20.2).
+  // 1280 19.5 and 19.9, three sequences of that 21.7 and 20.2, keys undivided).
   const int64_t nwg = place_grid(a, none, kTile, 0, 1, 16);
   if (nwg > kMaxGrid) {
     set_error("lsp_attn_step: launch of %lld workgroups is too large", (long long)nwg);
