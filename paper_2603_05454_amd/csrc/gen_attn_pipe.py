@@ -182,9 +182,10 @@ def first_scores(E):
         block_max(E, S[0], part)
 
 
-def products(E, u, v_at, k_stage):
+def products(E, u, v_at, k_stage, wide_sums=False):
     """The two products and the soft-max of block j (j % 2 = u % 2); v_at: offset of V(j) from the fragment addresses,
-    k_stage: stage of K(j+2)."""
+    k_stage: stage of K(j+2).  wide_sums: the row sum takes the probabilities as they are in 32 bits and not as they are
+    rounded for the second product (16 additions for 8 dot products)."""
     cur, nxt = S[u & 1], S[(u + 1) & 1]
 
     def stage_f(i):
@@ -197,7 +198,11 @@ def products(E, u, v_at, k_stage):
 
     def stage_c(i):
         E.e(f"v_cvt_pk_bf16_f32 v{PF[i]}, v{T[2 * i]}, v{T[2 * i + 1]}")
-        E.e(f"v_dot2c_f32_bf16 v{LSUM}, 0x3f803f80, v{PF[i]}")
+        if wide_sums:
+            for e in (2 * i, 2 * i + 1):
+                E.e(f"v_add_f32 v{LSUM}, v{LSUM}, v{T[e]}")
+        else:
+            E.e(f"v_dot2c_f32_bf16 v{LSUM}, 0x3f803f80, v{PF[i]}")
 
     # first product of the NEXT block, soft-max of this one, V^T fragment reads of this one;
     # the wave in this half of its iteration goes first when the two waves of a SIMD both have
@@ -321,34 +326,44 @@ def end_of_iteration_half(E):
     E.e("s_barrier")
 
 
-def events_half(E):
-    for tag in [f"p{t}" for t in range(NSH)] + [f"i{u}" for u in range(UNROLL_H)]:
+def events_half(E, loops=("",)):
+    for tag in [f"p{t}" for t in range(NSH)] + [f"i{w}{u}" for w in loops for u in range(UNROLL_H)]:
         event_half(E, "k", tag)
         if tag != f"p{NSH - 1}":
             event_half(E, "v", tag)
 
 
-def generate_half():
+def generate_half(either=False):
+    """either: the loop twice, with row sums of rounded probabilities and, where the operand `wide` is not 0, of those in 32 bits
+    (one statement: as two, their pinned registers cost 80 spilled ones)."""
     E = Emitter()
+    loops = ("", "w") if either else ("",)
     begin_half(E)
     first_scores(E)
     E.e("s_barrier")                                   # every wave has its fragments of K(0): iteration 0 requests K(5) into that stage
-    E.e(".Lloop_%=:")
-    for u in range(UNROLL_H):
-        check_reference(E, u)
-        load_half(E, "k", u % NSH, f"i{u}")
-        load_half(E, "v", (u + NSH - 1) % NSH, f"i{u}")
-        products(E, u, v_at=u % NSH * TILE, k_stage=(u + 2) % NSH)
-        end_of_iteration_half(E)
-    E.e("s_branch .Lloop_%=")
+    if either:
+        E.e("s_cmp_lg_u32 %[wide], 0")
+        E.e("s_cbranch_scc1 .Lloopw_%=")
+    issued, seq = E.lds_issued, dict(E.lds_seq)
+    for w in loops:
+        E.lds_issued, E.lds_seq = issued, dict(seq)    # (the reads of first_scores are in flight at either one's start)
+        E.e(f".Lloop{w}_%=:")
+        for u in range(UNROLL_H):
+            check_reference(E, f"{w}{u}")
+            load_half(E, "k", u % NSH, f"i{w}{u}")
+            load_half(E, "v", (u + NSH - 1) % NSH, f"i{w}{u}")
+            products(E, u, v_at=u % NSH * TILE, k_stage=(u + 2) % NSH, wide_sums=w == "w")
+            end_of_iteration_half(E)
+        E.e(f"s_branch .Lloop{w}_%=")
     E.e(".Lexit_%=:")
     E.e("s_waitcnt vmcnt(0) lgkmcnt(0)")
     E.e(f"s_mov_b32 m0, s{SH['m0save']}")
     E.e("s_nop 15")
     E.e("s_branch .Lend_%=")
-    for u in range(UNROLL_H):
-        rescale(E, u)
-    events_half(E)
+    for w in loops:
+        for u in range(UNROLL_H):
+            rescale(E, f"{w}{u}")
+    events_half(E, loops)
     E.e(".Lend_%=:")
     return E.lines
 
@@ -503,6 +518,8 @@ SCRATCH_V = list(range(0, 32)) + list(range(64, 152)) + list(range(170, 176))
 HEADER_HALF = """// GENERATED by gen_attn_pipe.py - do not edit; described there (the loop of workgroups of four waves).
 // Expects in scope what lsp_attn_pipe_loop.inc does, but u32x4 soffs (lane offsets of suffix rows) and uint32_t nsuf for nb.
 """
+HEADER_EITHER = HEADER_HALF + """// And uint32_t wide: whether row sums are of probabilities in 32 bits.
+"""
 
 
 def main():
@@ -511,6 +528,7 @@ def main():
             ("pipe_loop", HEADER + statement(generate(), ACC, QREGS + STREAM + BLOCKS + ', [sc] "s"(sc)', SCRATCH_V)),
             ("pipe_idle_loop", IDLE_HEADER + statement(generate_idle(), '"+{v[152:167]}"(addr)', STREAM + BLOCKS, [])),
             ("half_loop", HEADER_HALF + statement(generate_half(), ACC, QREGS + STREAM + BLOCKS_H + ', [sc] "s"(sc)', SCRATCH_V)),
+            ("half_either_loop", HEADER_EITHER + statement(generate_half(True), ACC, QREGS + STREAM + BLOCKS_H + ', [sc] "s"(sc), [wide] "s"(wide)', SCRATCH_V)),
             ("half_idle_loop", HEADER_HALF + statement(generate_half_idle(), '"+{v[152:167]}"(addr)', STREAM + BLOCKS_H, []))):
         with open(os.path.join(here, f"lsp_attn_{name}.inc"), "w") as f:
             f.write(text)

@@ -268,6 +268,8 @@ inline int32_t spread_limit(int rep, bool fine, bool one_group) { return fine ||
 //    round (32 layers, 1 x 208 on 87, 1792 and 1664: 59.2 and 63.0).  In launches that run at once (`packed` in contiguous128) even the
 //    choice would cost (9 x 48 on 56 9.1 and 9.4).  Not a block whose keys belong to four or eight parts (Reference): a wave has one pass and
 //    one reference.
+//    Waves of taller tiles come out the same to the bit; a block that would be a tile of its own keeps the key split's 32-bit row sums
+//    (attn_bf16_pipe_kernel, own_tile), with the same times.
 //  * spread (spread_limit): one block, shared by all waves.
 constexpr uint32_t kPackRound = 224;
 // whether a sequence's last block (its only one, or the one behind a multiple of 256 rows) has its keys in several parts
@@ -294,23 +296,31 @@ inline int64_t place_blocks(AttnArgs &a, const AttnLayers &layers) {
 }
 struct Blocks {
   int w, first_head, rep, tile;  // tile: w / rep
+  int first;                     // packed: this workgroup's first entry
   int count;                     // blocks in the list from this workgroup's first on: none or less, one, ...
   bool spread, packed;
 };
 template <int WM, bool FINE, bool PACK>
 __device__ __forceinline__ Blocks blocks_of(const AttnArgs &a, const UnitPlace &p, int N) {
-  Blocks k = {p.w, p.g * a.rep, a.rep, quotient(p.w, a.by_rep), 0, false, false};
+  Blocks k = {p.w, p.g * a.rep, a.rep, quotient(p.w, a.by_rep), WM * p.w, 0, false, false};
   const int blocks = (N + 31) >> 5;
   k.spread = WM == 4 && (FINE || blocks * a.rep <= a.per_unit) && blocks <= a.spread_blocks;
   if (PACK)
     k.packed = !k.spread && !in_parts(a, N) && (saves_rounds<WM>(a, blocks) || a.rep * ((blocks + WM - 1) / WM) > a.per_unit);
-  k.count = k.spread ? blocks - k.tile : k.packed ? a.rep * blocks - WM * k.w : blocks - WM * k.tile;
+  k.count = k.spread ? blocks - k.tile : k.packed ? a.rep * blocks - k.first : blocks - WM * k.tile;
+  // A single block at a list's end goes to the key split, which is where it would be as a tile of its own.  One that would be a wave of
+  // a taller tile takes the entry before it along and stays one.
+  if (PACK && k.packed && blocks % WM != 1) {
+    if (k.count == WM + 1) k.count = WM - 1;
+    if (k.count == 1) --k.first, k.count = 2;
+  }
   return k;
 }
-// first row and head of wave v's block (v >= count: rows beyond the suffix, of some head of the group)
+// first row and head of wave v's block (v >= count: rows beyond the suffix, of some head of the group; up to two entries of a
+// packed list are behind a workgroup's own)
 template <int WM, bool PACK>
 __device__ __forceinline__ void block_at(const AttnArgs &a, const Blocks &k, int v, int &row, int &h) {
-  const int e = WM * k.w + v, r = PACK && k.packed ? quotient(e, a.by_rep) : k.tile;
+  const int e = k.first + v + (v < k.count ? 0 : 2), r = PACK && k.packed ? quotient(e, a.by_rep) : k.tile;
   row = 32 * (k.packed || k.spread ? r : WM * k.tile + v);
   h = k.first_head + (k.packed ? e - r * k.rep : k.w - k.tile * k.rep);
 }

@@ -1096,9 +1096,8 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
     RefKeys ref = {0, 0};
     if (one_pass) {
       ref.count = min(32, P + N);
-      const bool ragged_first = a.rounding == kTiles256 || (PACK && N > 32);  // (N > 32: the last block of a list)
-      if (ragged_first && (P & 31)) ref = {P & ~31, P & 31};
-      else if (ragged_first && (N & 31)) ref = {P + (N & ~31), N & 31};
+      if (a.rounding == kTiles256 && (P & 31)) ref = {P & ~31, P & 31};
+      else if (a.rounding == kTiles256 && (N & 31)) ref = {P + (N & ~31), N & 31};
     }
     // (FINE has the plain body: what the other one decides in its loop costs a workgroup that has its compute unit to itself
     // a fifth, 64 of 640 rows of 28/4 heads on 3500 35.3 and 28.4 us; both in one kernel cost 5 % where caches are short, 32 layers of 4 x 21 on 81
@@ -1119,6 +1118,10 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   const bool live = wave_s < list.count;  // waves of a last workgroup may have no block
   int row0, h;
   block_at<WM, PACK>(a, list, wave_s, row0, h);
+  // A block that would be a tile of its own in an unpacked launch keeps what the key split gives it: the reference that its
+  // keys begin with (below) and row sums of probabilities in 32 bits, before they are rounded (the generated loops'
+  // sums are of the rounded ones, which moves a row by 5e-4 to 1e-3).
+  const bool own_tile = PACK && list.packed && N - row0 <= kShortSuffixPipe && (row0 & (32 * WM - 1)) == 0;
   const int qi = row0 + lq;
   const uint16_t *qp = static_cast<const uint16_t *>(a.q) + b * a.qs[0] + int64_t(min(qi, N - 1)) * a.qs[1] + h * a.qs[2];
   bf16x8 qf[KK];
@@ -1156,8 +1159,8 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
     for (int db = 0; db < DB; ++db) vaddr[db] = vbase + 64 * (db ^ r3);
   }
 
-  // Blocks of a list that would be tiles of their own (key_split_body with ref) begin with the reference of the first 32 keys.
-  if (PACK && list.packed && a.rounding == kOnePass && N <= 32 && ((P | N) & 31) && live) {
+  // (key_split_body with ref: the first 32 keys; behind a multiple of 128 rows the ragged ends, as here)
+  if (own_tile && a.rounding == kOnePass && ((P | N) & 31) && live) {
     const int t = min(lq, T - 1);
     const char *kp = (t < P ? kc + int64_t(t) * cpitch : ks + int64_t(t - P) * spitch) + 16 * hf;
     f32x16 s;
@@ -1274,10 +1277,13 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
         soffs[2 + i] = ns > 0 ? uint32_t((lr + 4 * i) * spitch + vcol) : addr[14 + i];
       }
       const uint32_t nc = nc_u, nsuf = ns_u;
-      if (live) {
-#include "lsp_attn_half_loop.inc"
-      } else {
+      if (!live) {
 #include "lsp_attn_half_idle_loop.inc"
+      } else if constexpr (PACK) {
+        const uint32_t wide = __builtin_amdgcn_readfirstlane(own_tile);
+#include "lsp_attn_half_either_loop.inc"
+      } else {
+#include "lsp_attn_half_loop.inc"
       }
     }
     mref = -nm;

@@ -161,3 +161,43 @@ def test_ring_protocol_on_concrete_streams(gen):
                         have, last = held[e[1], e[2]]
                         assert have == blk and last <= visible, (nb, nc, j, e, have, last, visible)
                     reads.append((e[1], e[2]))
+
+
+def test_either_loop_is_the_loop_twice(gen):
+    """lsp_attn_half_either_loop.inc: committed as generated; either way through it is the loop checked above, the second with
+    two additions of unrounded probabilities in the place of each dot product of a rounded pair."""
+    half, either = gen.generate_half(), gen.generate_half(True)
+    with open(os.path.join(CSRC, "lsp_attn_half_either_loop.inc")) as f:
+        assert re.findall(r'^    "(.*)\\n"$', f.read(), flags=re.M) == either
+
+    def parts(lines):       # prologue, loops by label, exit, out-of-line blocks by label
+        begin = next(k for k, l in enumerate(lines) if l.startswith(".Lloop"))
+        leave, cold = lines.index(".Lexit_%=:"), lines.index("s_branch .Lend_%=") + 1
+        loops, outer = {}, {}
+        for into, part in ((loops, lines[begin:leave]), (outer, lines[cold:-1])):
+            for l in part:
+                if l.startswith((".Lloop", ".Lresc", ".Lev")) and l.endswith(":"):
+                    into[l] = []
+                elif not into:
+                    raise AssertionError(l)
+                list(into.values())[-1].append(l)
+        return lines[:begin], loops, lines[leave:cold], outer
+
+    (pro, loops, leave, outer), (pro2, loops2, leave2, outer2) = parts(half), parts(either)
+    assert pro2[-2:] == ["s_cmp_lg_u32 %[wide], 0", "s_cbranch_scc1 .Lloopw_%="] and pro2[:-2] == pro and leave == leave2
+    assert list(loops2) == [".Lloop_%=:", ".Lloopw_%=:"] and loops2[".Lloop_%=:"] == loops[".Lloop_%=:"]
+
+    def narrow(l):
+        return re.sub(r"\.L(loop|resc_|after_|isk_i|isv_i|evk_i|evv_i)w", r".L\1", l)
+
+    first = {f"v_cvt_pk_bf16_f32 v{p}, v{gen.T[2 * i]}, v{gen.T[2 * i + 1]}": i for i, p in enumerate(gen.PF)}
+    want, i = [], None
+    for l in loops[".Lloop_%=:"]:
+        if l.startswith("v_dot2c_f32_bf16"):
+            want += [f"v_add_f32 v{gen.LSUM}, v{gen.LSUM}, v{gen.T[e]}" for e in (2 * i, 2 * i + 1)]
+            continue
+        i = first.get(l, i)
+        want.append(l)
+    assert [narrow(l) for l in loops2[".Lloopw_%=:"]] == want and sum("v_dot2c" in l for l in half) == 8 * gen.UNROLL_H
+    assert {k: v for k, v in outer2.items() if narrow(k) == k} == outer
+    assert {narrow(k): [narrow(l) for l in v] for k, v in outer2.items() if narrow(k) != k} == {k: v for k, v in outer.items() if "_p" not in k}

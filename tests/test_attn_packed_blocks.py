@@ -140,3 +140,32 @@ def test_ragged_ends_of_cache_and_suffix(lsp, oracle, rows):
         got = o.float().cpu()
         assert (got[act] - ref[act]).abs().max().item() <= 2e-2
         assert torch.all(got[~act] == 123.0)
+
+
+# S, active rows: blocks that are tiles of their own unpacked (up to 32 rows), waves of taller tiles (whose list ends with a
+# single block at 65 and 96 rows of seven heads), both (129 .. 160 rows)
+@pytest.mark.gpu
+@pytest.mark.parametrize("S,N", [(20, (20, 7, 1)), (32, (32, 31, 9)), (100, (14, 30, 32)), (96, (96, 65, 80)), (128, (33, 64, 97)), (200, (140, 129, 160))])
+def test_packed_blocks_are_computed_as_unpacked_ones(lsp, S, N):
+    """The same launch with every head's K/V written out, which shares none and packs nothing.  Waves of taller tiles are the same to
+    the bit.  Blocks of their own differ in the order of 32-bit sums alone: some 2^-17 of a row at most, so that an output comes
+    out as the neighbouring bf16 (2^-9 to 2^-8 away) for 2^-8 of them at most; row sums of rounded probabilities change 2^-6 and
+    more of them."""
+    layers, Hkv, rep, C = 32, 4, 7, 300
+    g = torch.Generator(device="cuda").manual_seed(S)
+    q = torch.randn((len(N), S, Hkv * rep, 128), generator=g, device="cuda").to(torch.bfloat16)
+    kv = [torch.randn((len(N), n, Hkv, 128), generator=g, device="cuda").to(torch.bfloat16) for n in (S, S, C, C)]
+    pl, sl = torch.tensor([C - 13 * b for b in range(len(N))], dtype=torch.int32).cuda(), torch.tensor(N, dtype=torch.int32).cuda()
+
+    def run(operands):
+        outs = [torch.zeros_like(q) for _ in range(layers)]
+        lsp.attn_step_layers(lsp.AttnLayerTable(*[[t] * layers for t in (q, *operands)], outs), pl, sl)
+        assert all(torch.equal(outs[0], o) for o in outs)
+        return outs[0]
+
+    packed, plain = run(kv), run([t.repeat_interleave(rep, 2) for t in kv])
+    for b, n in enumerate(N):
+        own = n - n % 128 if 0 < n % 128 <= 32 else n      # rows from here on are a tile of their own
+        assert torch.equal(packed[b, :own], plain[b, :own])
+        if own < n:
+            assert (packed[b, own:n] != plain[b, own:n]).float().mean().item() <= 2 ** -8
