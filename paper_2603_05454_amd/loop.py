@@ -21,8 +21,8 @@ def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
     """logits_fn(step, prefix_len) -> device logits [B,S,V].  prefix_len,
     suffix_len, tokens and the caches in kv_layers (list of dicts q?, k_suf,
     v_suf, k_cache, v_cache) are updated in place.
-    run_attention: also run the attention of every layer over the buffers in kv_layers; the outputs
-    stay inside.  It may be launched before the step's logits_fn is called.
+    run_attention: also run the attention of every layer, behind the step's logits_fn, over what is
+    then in the buffers of kv_layers; the outputs stay inside.
     commit_kw: extra keyword arguments of commit() (adaptive, alpha, beta, max_commit).
     stop_after: leave the loop after that many steps even if positions remain.
     observer(step, logits, conf, commit_out): called after every step's commit
@@ -72,37 +72,31 @@ def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
     if min_commit < 1 and stop_after is None:
         raise LspError("decode_loop needs min_commit >= 1 (Section 3.2: at least one token per iteration) "
                        "unless stop_after bounds the number of steps")
-    # Of lengths of another type and place only the first test takes note: with nothing to do they are no error.
+    # Lengths of another type or place are no error with nothing to do.
     ordinary = all(t.is_cuda and t.dtype == torch.int32 and t.is_contiguous() for t in (prefix_len, suffix_len, base)) and counters.is_contiguous()
     progress = None
     if ordinary:
         progress = ProgressPoll()
         progress.start(suffix_len, None, prefix_len, base, counters)
     table = None
+    if kv_layers is not None:       # (built while the first test is under way)
+        table = LayerTable(*[[L[k] for L in kv_layers] for k in ("k_suf", "v_suf", "k_cache", "v_cache")])
     out = conf = None
     attn_out = None
     events = []
     zbuf = step_graph = None
     totals = None   # positions committed and the counters, where the last test has seen the final ones
-    # The attention of a step is launched before logits_fn is asked for the logits, and behind a test before the host
-    # waits for its answer: the device then has work while the host learns that the step before has ended and launches the rest
-    # (32 layers: one sequence of 256 rows 1455 -> 1325 us a loop, 2 x 34 rows 815 -> 690).  Where nothing is left it returns at once.
-    attend_first = run_attention and kv_layers is not None and not graph and not timed
     ws = None   # workspace of the reduction or the fused output head: allocated by the first (eager) step, then reused
 
-    def attend():
-        nonlocal attn_out
-        if attn_out is None:     # one output per layer (a denoiser consumes each of them), allocated once
-            q = kv_layers[0]["q"]
-            outs = torch.empty((len(kv_layers), *q.shape), dtype=q.dtype, device=q.device)
-            attn_out = AttnLayerTable(*[[L[k] for L in kv_layers] for k in ("q", "k_suf", "v_suf", "k_cache", "v_cache")],
-                                      list(outs.unbind(0)))
-        attn_step_layers(attn_out, prefix_len, suffix_len)     # every layer in one launch
-
     def one_step(z):
-        nonlocal out, conf, ws
-        if run_attention and kv_layers is not None and not attend_first:
-            attend()
+        nonlocal out, conf, attn_out, ws
+        if run_attention and kv_layers is not None:
+            if attn_out is None:     # one output per layer (a denoiser consumes each of them), allocated once
+                q = kv_layers[0]["q"]
+                outs = torch.empty((len(kv_layers), *q.shape), dtype=q.dtype, device=q.device)
+                attn_out = AttnLayerTable(*[[L[k] for L in kv_layers] for k in ("q", "k_suf", "v_suf", "k_cache", "v_cache")],
+                                          list(outs.unbind(0)))
+            attn_step_layers(attn_out, prefix_len, suffix_len)     # every layer in one launch
         if lm_head_weight is None:
             if ws is None:
                 ws = torch.empty(confidence_workspace_bytes(*z.shape), dtype=torch.uint8, device=dev)
@@ -118,7 +112,6 @@ def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
                     **(commit_kw or {}))
 
     while True:
-        more = (stop_after is None or steps - first < stop_after) and steps < max_steps
         if (steps - first) % poll == 0:
             # positions left, and whether a sequence that has some committed nothing
             if out is None and not ordinary:
@@ -126,21 +119,12 @@ def decode_loop(logits_fn, bitmap, V, tau, window, min_commit, snap_enabled,
             else:
                 if out is not None:
                     progress.start(suffix_len, out["commit_len"], prefix_len, base, counters)
-                    if attend_first and more:
-                        attend()
                 left, stalled, *totals = progress.wait()
-            if steps == first:
-                if attend_first and more and left != 0:
-                    attend()
-                if kv_layers is not None:       # (built under the first attention)
-                    table = LayerTable(*[[L[k] for L in kv_layers] for k in ("k_suf", "v_suf", "k_cache", "v_cache")])
             if left == 0:
                 break
             if stalled and min_commit >= 1:
                 raise LspError(f"decode_loop: a sequence with active positions committed nothing at step {steps - 1} "
                                f"(status_flags {out['status_flags'].tolist()}): cache or token buffer full")
-        elif attend_first and more:
-            attend()
         if stop_after is not None and steps - first >= stop_after:
             break
         assert steps < max_steps

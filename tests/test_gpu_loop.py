@@ -347,10 +347,14 @@ def test_progress_poll(lsp, B, native, monkeypatch):
         poll.start(n, c, prefix, base, counters.int())
 
 
+@pytest.mark.parametrize("timed", [False, True])
 @pytest.mark.parametrize("poll,stop", [(1, None), (3, None), (3, 4), (1, 0), (2, 1)])
-def test_attention_launched_ahead_changes_no_result(lsp, oracle, poll, stop):
-    """Steps between tests, loops that are stopped, and the attention of a step whose test says that nothing is left."""
-    from paper_2603_05454_amd.loop import decode_loop as gpu_loop
+def test_attention_of_every_step(lsp, oracle, poll, stop, timed, monkeypatch):
+    """Steps between tests, loops that are stopped, and the attention of a step whose test says that nothing is left: one call for every
+    step, behind its logits_fn, which here writes the step's Q/K/V as a model does (and gives the first Q at all), and on that step's lengths;
+    its outputs against the oracle's (the bound is the bf16 one of test_gpu_attention.py)."""
+    from paper_2603_05454_amd import loop as module
+    gpu_loop, attend = module.decode_loop, module.attn_step_layers
     G = 70
     w = W.scaled(W.C5, B=2, S=G, V=512, P=10, gen_len=G, C=10 + G, layers=2, Hq=4, Hkv=2, D=128)
     _, bm = W.make_delimiters(w)
@@ -360,15 +364,39 @@ def test_attention_launched_ahead_changes_no_result(lsp, oracle, poll, stop):
     def run(loop, dev, **more):
         pl, sl = (t.to(dev) for t in W.make_lengths(w))
         tok, lay = W.make_tokens(w, w.C).to(dev), [{k: v.to(dev) for k, v in W.make_layer_kv(w, l).items()} for l in range(2)]
-        asked = []
-        r = loop(lambda s, p: (asked.append(s), fn(s, p).to(dev))[1], bm.to(dev), w.V, 0.9, w.window, 1, 1, pl, sl, tok, kv_layers=lay, **more)
-        return r, asked, [tok, pl, sl] + [L[k] for L in lay for k in ("k_cache", "v_cache")]
+        asked, seen = [], []
+        first = [L.pop("q") for L in lay]
 
-    a, asked_a, ta = run(gpu_loop, "cuda", run_attention=True, **kw)
-    b, asked_b, tb = run(gpu_loop, "cuda", run_attention=False, **kw)
-    assert asked_a == asked_b and all(a[k] == b[k] for k in KEYS)
+        def logits(s, p):
+            for l, L in enumerate(lay):
+                L.setdefault("q", first[l])
+                for k in ("q", "k_suf", "v_suf"):
+                    L[k].copy_(L[k].roll(1 + s, dims=1))
+            asked.append((s, p.tolist()))
+            return fn(s, p).to(dev)
+
+        def recorded(table, p, n, **rest):
+            seen.append((len(asked), p.clone(), n.clone(), [{k: v.clone() for k, v in L.items()} for L in lay]))
+            outs = attend(table, p, n, **rest)
+            seen[-1] += ([o.clone() for o in outs],)
+            return outs
+
+        monkeypatch.setattr(module, "attn_step_layers", recorded)
+        r = loop(logits, bm.to(dev), w.V, 0.9, w.window, 1, 1, pl, sl, tok, kv_layers=lay, **more)
+        return r, asked, [tok, pl, sl] + [L[k] for L in lay for k in ("k_cache", "v_cache")], seen
+
+    a, asked_a, ta, seen = run(gpu_loop, "cuda", run_attention=True, timed=timed, **kw)
+    b, asked_b, tb, none = run(gpu_loop, "cuda", run_attention=False, **kw)
+    assert asked_a == asked_b and all(a[k] == b[k] for k in KEYS) and not none
     assert all(torch.equal(x, y) for x, y in zip(ta, tb))
+    assert [(n, p.tolist()) for n, p, *_ in seen] == [(k + 1, p) for k, (_, p) in enumerate(asked_a)] and len(seen) == a["steps"]
+    for _, p, n, lay, outs in seen[::5]:
+        assert torch.all(p + n == w.P + G)
+        for L, o in zip(lay, outs):
+            ref = oracle.attention(**{k: v.cpu() for k, v in L.items()}, prefix_len=p.cpu(), suffix_len=n.cpu())
+            act = ~torch.isnan(ref)
+            assert (o.float().cpu()[act] - ref[act]).abs().max().item() <= 2e-2
     if stop is None and poll == 1:
-        ref, _, tr = run(decode_loop, "cpu", commit_kw=kw["commit_kw"])
+        ref, _, tr, _ = run(decode_loop, "cpu", commit_kw=kw["commit_kw"])
         _same_counts(a, ref)
         assert all(torch.equal(x.cpu().view(torch.int8), y.view(torch.int8)) for x, y in zip(ta, tr))
