@@ -543,11 +543,11 @@ class LengthPoll:
 
 
 class ProgressPoll:
-    """lsp_poll_progress with a pinned buffer of its own, in two calls, so that a loop can launch more work between them."""
+    """lsp_poll_progress with a pinned buffer of its own, in two calls, so that the host has time for other things between them."""
 
     def __init__(self):
         self.host = torch.zeros(12, dtype=torch.int64, pin_memory=True)
-        self.call, self.waiting = 0, False
+        self.call, self.waiting, self.stream = 0, False, None
 
     def start(self, suffix_len, commit_len, prefix_len, base_prefix_len, counters):
         self.call = self.call % 0x7fffffff + 1
@@ -565,15 +565,19 @@ class ProgressPoll:
             rc = lib().lsp_poll_progress(_ptr(suffix_len), _ptr(commit_len), _ptr(prefix_len), _ptr(base_prefix_len), _ptr(counters), B,
                                          ctypes.c_uint32(self.call), _ptr(self.host), _stream())
         _check(rc, "lsp_poll_progress")
-        self.waiting = True
+        self.waiting, self.stream = True, torch.cuda.current_stream()
 
     def wait(self):
-        """Waits for what was on the current stream before start().  Returns (largest suffix_len, whether a sequence with
-        active positions has commit_len 0, positions committed, the four counters)."""
+        """Waits for what was on start()'s stream before it; where that takes more than 2 ms, for all that is there by then.  Returns (largest
+        suffix_len, whether a sequence with active positions has commit_len 0, positions committed, the four counters)."""
         got = _nat.poll_wait(self.host, self.call) if _nat is not None else None
         if got is None:
-            torch.cuda.current_stream().synchronize()
-            w = [x & 0xffffffff for x in self.host.tolist()]
+            if self.stream is not None:
+                self.stream.synchronize()
+            w = [x & 0xffffffffffffffff for x in self.host.tolist()]
+            if any(x >> 32 != self.call for x in w):
+                raise LspError("lsp_poll_progress: no answer to this call (start() comes first)")
+            w = [x & 0xffffffff for x in w]
             got = (w[0] - ((w[0] & 0x80000000) << 1), w[1], *[w[k] | w[k + 1] << 32 for k in range(2, 12, 2)])
         self.waiting = False
         return got

@@ -17,7 +17,6 @@
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <chrono>
-#include <thread>
 
 #include "lsp.h"
 
@@ -434,8 +433,8 @@ PyObject *poll_start(PyObject *, PyObject *const *a, Py_ssize_t n) {
   return status(g.poll_progress, data<int32_t>(sl), data<int32_t>(len), data<int32_t>(pl), data<int32_t>(base), data<int64_t>(counters),
                 int32_t(B), uint32_t(call), h, stream());
 }
-// (host, call): waits for that call's words and answers their lower halves.  Work launched behind the poll is not waited for: after a
-// while the thread sleeps between two looks, and a stream that has failed, or has nothing left to do, ends the wait as well (None).
+// (host, call): waits up to 2 ms for that call's words and answers their lower halves, or None: the words come some microseconds before the
+// runtime would tell, and a longer step is left to the runtime.
 PyObject *poll_wait(PyObject *, PyObject *const *a, Py_ssize_t n) {
   ARGUMENTS(2);
   const uint64_t *h = progress_words(a[0]);
@@ -454,13 +453,7 @@ PyObject *poll_wait(PyObject *, PyObject *const *a, Py_ssize_t n) {
   {
     Unlocked without_lock;
     const auto until = std::chrono::steady_clock::now() + std::chrono::milliseconds(2);
-    while (!(here = all())) {
-      if (std::chrono::steady_clock::now() < until) continue;
-      if (c10::hip::getCurrentHIPStream().query()) {  // (throws where the stream has failed)
-        here = all();
-        break;
-      }
-      std::this_thread::sleep_for(std::chrono::microseconds(20));
+    while (!(here = all()) && std::chrono::steady_clock::now() < until) {
     }
   }
   ORDINARY(here);

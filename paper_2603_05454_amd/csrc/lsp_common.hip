@@ -53,7 +53,7 @@ __global__ __launch_bounds__(kPollThreads) void poll_kernel(const int32_t *__res
   __hip_atomic_store(host + 2, 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
-// The same for a loop that goes on launching behind it: one wave, no barrier, and every word in one store with the call's
+// The same for a host that has other things to do meanwhile: one wave, no barrier, and every word in one store with the call's
 // number beside it, where values and a flag after them were two trips to host memory.
 constexpr int kProgressWords = 12;
 __global__ __launch_bounds__(kWave) void progress_kernel(const int32_t *__restrict__ suffix_len, const int32_t *__restrict__ commit_len,

@@ -347,6 +347,31 @@ def test_progress_poll(lsp, B, native, monkeypatch):
         poll.start(n, c, prefix, base, counters.int())
 
 
+@pytest.mark.parametrize("native", [True, False])
+def test_progress_poll_waits_on_its_own_stream(lsp, native, monkeypatch):
+    """A poll that was started on another stream than the one wait() is called on, behind work of many milliseconds; and one that
+    was never started."""
+    lsp.lib()
+    if not native:
+        monkeypatch.setattr(lsp, "_nat", None)
+    n, prefix, base, counters = (torch.tensor(v, dtype=t).cuda() for v, t in
+                                 (([7, 3], torch.int32), ([12, 20], torch.int32), ([10, 11], torch.int32), ([1, 2, 3, 4], torch.int64)))
+    poll, side = lsp.ProgressPoll(), torch.cuda.Stream()
+    poll.call = 1
+    with pytest.raises(lsp.LspError, match="no answer"):
+        poll.wait()
+    side.wait_stream(torch.cuda.current_stream())
+    for delay in (0, 50_000_000, 0):
+        n.add_(1)
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            if delay:
+                torch.cuda._sleep(delay)
+            poll.start(n, None, prefix, base, counters)
+        assert tuple(poll.wait()) == (int(n.max()), 0, 11, 1, 2, 3, 4)
+        assert not poll.waiting
+
+
 @pytest.mark.parametrize("timed", [False, True])
 @pytest.mark.parametrize("poll,stop", [(1, None), (3, None), (3, 4), (1, 0), (2, 1)])
 def test_attention_of_every_step(lsp, oracle, poll, stop, timed, monkeypatch):
