@@ -171,9 +171,13 @@ def attn_workspace_bytes(dtype, B, S, Hq, Hkv, D, C) -> int:
     return lib().lsp_attn_workspace_bytes(ctypes.byref(d))
 
 
-def _attn_workspace(d):
-    """A workspace of one call's own (two streams cannot meet in it), and its bytes; none where memory has run out."""
+def _attn_workspace(d, given):
+    """The caller's workspace where it will do, or one of the call's own (two streams cannot meet in it), and its bytes; none where
+    memory has run out."""
     need = lib().lsp_attn_workspace_bytes(ctypes.byref(d))
+    if (need and isinstance(given, torch.Tensor) and given.is_cuda and given.is_contiguous()
+            and given.numel() * given.element_size() >= need and given.data_ptr() % 16 == 0):
+        return given, need
     try:
         return (torch.empty(need, dtype=torch.uint8, device="cuda"), need) if need else (None, 0)
     except torch.OutOfMemoryError:
@@ -186,7 +190,8 @@ def attn_step(q, k_suf, v_suf, k_cache, v_cache, prefix_len, suffix_len, scale=0
     prefix_len/suffix_len int32 [B].  Returns out [B,S,Hq,D] (same dtype as q);
     rows >= suffix_len[b] are not written.  cache_row_index int32 [B,C] selects
     lsp_attn_step_gather (key t of the prefix is cache row cache_row_index[b,t]).
-    workspace is not used: a call that wants one takes its own."""
+    workspace: contiguous device memory of attn_workspace_bytes(...) bytes and any content, aligned to 16 bytes, for this call
+    alone while it runs; without one that will do, a call that wants one takes its own from torch's allocator."""
     if _nat is not None and cache_row_index is None:
         if out is None:
             out = torch.empty(q.shape, dtype=q.dtype, device=q.device)
@@ -207,7 +212,7 @@ def attn_step(q, k_suf, v_suf, k_cache, v_cache, prefix_len, suffix_len, scale=0
     d.kv_suf_stride = _strides3(k_suf)
     d.cache_stride = _strides3(k_cache)
     d.o_stride = _strides3(out)
-    workspace, wb = _attn_workspace(d)
+    workspace, wb = _attn_workspace(d, workspace)
     if cache_row_index is None:
         rc = lib().lsp_attn_step(ctypes.byref(d), _ptr(q), _ptr(k_suf), _ptr(v_suf), _ptr(k_cache),
                                  _ptr(v_cache), _ptr(prefix_len), _ptr(suffix_len), _ptr(out),
@@ -260,7 +265,7 @@ class AttnLayerTable:
 
 def attn_step_layers(table: AttnLayerTable, prefix_len, suffix_len, scale=0.0, workspace=None):
     """lsp_attn_step_layers: the attention of every layer of `table` in one launch.
-    Returns the list of per-layer outputs (table.out).  workspace is not used, as in attn_step."""
+    Returns the list of per-layer outputs (table.out).  workspace as in attn_step."""
     if _nat is not None:
         rc = _nat.attn_step_layers(table.desc, table.n, table.arrays, prefix_len, suffix_len, scale, workspace)
         if rc is not None:
@@ -270,7 +275,7 @@ def attn_step_layers(table: AttnLayerTable, prefix_len, suffix_len, scale=0.0, w
     _need("prefix_len", prefix_len, torch.int32, (table.desc.B,))
     _need("suffix_len", suffix_len, torch.int32, (table.desc.B,))
     table.desc.scale = float(scale)
-    workspace, wb = _attn_workspace(table.desc)
+    workspace, wb = _attn_workspace(table.desc, workspace)
     a = table.arrays
     rc = lib().lsp_attn_step_layers(ctypes.byref(table.desc), table.n, a[0], a[1], a[2], a[3], a[4],
                                     _ptr(prefix_len), _ptr(suffix_len), a[5], _ptr(workspace),

@@ -12,12 +12,12 @@
 #include <hip/hip_runtime_api.h>
 
 #include <ATen/core/Tensor.h>
-#include <c10/core/Allocator.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <chrono>
 
+#include "binding_workspace.h"
 #include "lsp.h"
 
 namespace {
@@ -158,21 +158,6 @@ PyObject *bind(PyObject *, PyObject *const *a, Py_ssize_t n) {
   Py_RETURN_NONE;
 }
 
-// A workspace of the call's own, memory of the current stream: the allocator hands it out again only behind the launch, so
-// that calls on several streams and threads cannot meet in it.  None where memory has run out: the call goes without.
-struct Workspace {
-  c10::DataPtr own;
-  size_t bytes = 0;
-  explicit Workspace(size_t need) {
-    if (need == 0) return;
-    try {
-      own = c10::GetAllocator(c10::DeviceType::CUDA)->allocate(need);
-      bytes = need;
-    } catch (...) {
-    }
-  }
-};
-
 // (q, k_suf, v_suf, k_cache, v_cache, prefix_len, suffix_len, scale, out, workspace)
 PyObject *attn_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
   ARGUMENTS(10);
@@ -192,9 +177,9 @@ PyObject *attn_step(PyObject *, PyObject *const *a, Py_ssize_t n) {
   d.B = int32_t(B); d.S = int32_t(S); d.Hq = int32_t(Hq); d.Hkv = int32_t(Hkv); d.D = int32_t(D); d.C = int32_t(C);
   ORDINARY(number(a[7], d.scale));
   ORDINARY(strides3(*q, d.q_stride) && strides3(*ks, d.kv_suf_stride) && strides3(*kc, d.cache_stride) && strides3(*out, d.o_stride));
-  const Workspace work(g.attn_workspace_bytes(&d));
+  const Workspace work(g.attn_workspace_bytes(&d), device_tensor(a[9]));
   return status(g.attn_step, &d, q->const_data_ptr(), ks->const_data_ptr(), vs->const_data_ptr(), kc->const_data_ptr(),
-                vc->const_data_ptr(), data<int32_t>(pl), data<int32_t>(sl), data<void>(out), work.own.get(), work.bytes, stream());
+                vc->const_data_ptr(), data<int32_t>(pl), data<int32_t>(sl), data<void>(out), work.at, work.bytes, stream());
 }
 
 // (table descriptor, layers, list of six tables, prefix_len, suffix_len, scale, workspace or None)
@@ -207,10 +192,10 @@ PyObject *attn_step_layers(PyObject *, PyObject *const *a, Py_ssize_t n) {
   ORDINARY(number(a[5], own.scale));
   const at::Tensor *pl = plain(a[3], at::kInt, own.B), *sl = plain(a[4], at::kInt, own.B);
   ORDINARY(pl && sl);
-  const Workspace work(g.attn_workspace_bytes(&own));
+  const Workspace work(g.attn_workspace_bytes(&own), device_tensor(a[6]));
   auto in = [&](int k) { return static_cast<const void *const *>(tab[k].view.buf); };
   return status(g.attn_step_layers, &own, int32_t(layers), in(0), in(1), in(2), in(3), in(4), data<int32_t>(pl), data<int32_t>(sl),
-                static_cast<void *const *>(tab[5].view.buf), work.own.get(), work.bytes, stream());
+                static_cast<void *const *>(tab[5].view.buf), work.at, work.bytes, stream());
 }
 
 struct ConfOut {

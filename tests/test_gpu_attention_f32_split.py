@@ -105,3 +105,34 @@ def test_workspace_of_sizes_that_are_not_divided(lsp):
         assert lsp.attn_workspace_bytes(0, *sizes) == 0
     for sizes in ((1, 16, 4, 4, 64, 288), (1, 16, 4, 4, 128, 212), (128, 16, 1, 1, 64, 2000), (1, 16, 4, 4, 64, most)):
         assert 0 < lsp.attn_workspace_bytes(0, *sizes) < 1 << 22
+
+
+@pytest.mark.parametrize("native", [True, False])
+def test_a_workspace_that_is_handed_over(lsp, native, monkeypatch):
+    """One that will do is used and nothing is allocated; one that is too small, misaligned, strided or on the host is left alone, and
+    the result is that of the call's own workspace."""
+    lsp.lib()
+    if not native:
+        monkeypatch.setattr(lsp, "_nat", None)
+    w = W.scaled(W.C2, dtype="f32", B=1, S=16, P=900, C=900, Hq=4, Hkv=4, D=64, seed=61)
+    g = {k: v.cuda() for k, v in W.make_layer_kv(w, 0).items()}
+    args, (pl, sl) = [g[n] for n in OPERANDS], [t.cuda() for t in W.make_lengths(w)]
+    need = lsp.attn_workspace_bytes(lsp._dtype(g["q"]), w.B, w.S, w.Hq, w.Hkv, w.D, w.C)
+    want, layered = lsp.attn_step(*args, pl, sl), torch.zeros_like(g["q"])
+    table = lsp.AttnLayerTable(*[[t] for t in args], [layered])
+    before = torch.randint(0, 256, (4 * need + 16,), dtype=torch.uint8).cuda()
+    held = before.clone()
+    rows = torch.arange(w.C, dtype=torch.int32, device="cuda").repeat(w.B, 1)
+    good, bad = [held[:need], held[need - need % 16:2 * need]], [held[:need - 1], held[8:8 + need], held[::4][:need], held[:need].cpu()]
+    for ws, used in [(t, True) for t in good] + [(t, False) for t in bad]:
+        for more in ({}, {"cache_row_index": rows}):
+            out = torch.zeros_like(want)
+            held.copy_(before)
+            allocated = torch.cuda.memory_stats()["allocation.all.allocated"]
+            lsp.attn_step(*args, pl, sl, out=out, workspace=ws, **more)
+            assert (torch.cuda.memory_stats()["allocation.all.allocated"] == allocated) == used
+            assert torch.equal(out, want) and torch.equal(held, before) != used
+        held.copy_(before)
+        layered.zero_()
+        lsp.attn_step_layers(table, pl, sl, workspace=ws)
+        assert torch.equal(layered, want) and torch.equal(held, before) != used
