@@ -2,6 +2,7 @@
 #pragma once
 #include <ATen/core/Tensor.h>
 #include <c10/core/Allocator.h>
+#include <c10/util/Exception.h>
 
 // The caller's, where it will do (contiguous, of so many bytes, aligned to 16).  Otherwise one of the call's own, memory of the current
 // stream: the allocator hands it out again only behind the launch, so that calls on several streams and threads cannot meet in it.
@@ -24,7 +25,7 @@ struct Workspace {
       own = c10::GetAllocator(c10::DeviceType::CUDA)->allocate(need);
       at = own.get();
       bytes = need;
-    } catch (...) {
+    } catch (const c10::OutOfMemoryError &) {
     }
   }
 };

@@ -83,3 +83,48 @@ def test_a_sparse_tensor_is_refused_in_python():
     z = torch.zeros(2, 4, 64, device="cuda").to_sparse()
     with pytest.raises((RuntimeError, lsp.LspError)):
         lsp.confidence(z, None)
+
+
+WORKSPACE = r"""
+#include <stdio.h>
+#include <string.h>
+#include <stdexcept>
+#include "binding_workspace.h"
+struct Failing : c10::Allocator {
+  int how = 0;
+  c10::DataPtr allocate(size_t n) override {
+    if (how == 1) TORCH_CHECK_WITH(OutOfMemoryError, false, "none left");
+    if (how == 2) TORCH_CHECK(false, "device error");
+    if (how == 3) throw std::runtime_error("other");
+    static char memory[64];
+    return {memory, c10::Device(c10::DeviceType::CUDA, 0)};
+  }
+  void copy_data(void *to, const void *from, size_t n) const override { memcpy(to, from, n); }
+};
+int main() {
+  static Failing f;
+  c10::SetAllocator(c10::DeviceType::CUDA, &f, 127);
+  for (f.how = 0; f.how < 4; ++f.how) {
+    try {
+      const Workspace w(48, nullptr);
+      printf("%d %d\n", w.at != nullptr, int(w.bytes));
+    } catch (...) {
+      printf("raised\n");
+    }
+  }
+}
+"""
+
+
+def test_only_a_lack_of_memory_does_without_a_workspace(tmp_path):
+    """Any other failure of the allocator reaches the caller of the attention."""
+    import os
+    import subprocess
+    from paper_2603_05454_amd import build
+    (tmp_path / "w.cpp").write_text(WORKSPACE)
+    cmd = build.binding_command()
+    cmd = [x for x in cmd[:cmd.index("-o")] if x not in ("-shared", os.path.join(build.CSRC, "binding.cpp"))]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    subprocess.run(cmd + ["-I", build.CSRC, str(tmp_path / "w.cpp"), "-o", str(tmp_path / "w"), "-L", libs, "-lc10", "-ltorch_cpu", f"-Wl,-rpath,{libs}"], check=True)
+    out = subprocess.run([str(tmp_path / "w")], capture_output=True, text=True, check=True).stdout
+    assert out.split("\n") == ["1 48", "0 0", "raised", "raised", ""]
