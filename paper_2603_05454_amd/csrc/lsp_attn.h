@@ -50,17 +50,31 @@ __device__ __forceinline__ void fetch_operands(const AttnArgs &a) {
   fetch_now(a.q, a.k_suf, a.v_suf, a.k_cache, a.v_cache, a.out, a.scale, a.C, a.qs[0], a.qs[1], a.qs[2], a.ks[0], a.ks[1], a.ks[2],
             a.cs[0], a.cs[1], a.cs[2], a.os[0], a.os[1], a.os[2]);
 }
-// Active and cached rows of a sequence.  (Both at once and through the scalar cache: as ordinary loads one followed the
-// other, with the early exit between them.  32 layers, 4 x 300 rows with 30 active on 100 171 -> 166 us, one layer of
-// 28/4 heads, 3 x 48 with 10 active on 83 6.36 -> 6.29.)
+// Active and cached rows of a sequence, requested together:
+//  * both through the scalar cache (as ordinary loads one trip followed the other, with the early exit between them: 32 layers, 2 x
+//    724 rows of 32/32 heads with 10 active on 305 193 -> 181 us, 12 x 246 with 22 on 62 414 -> 393);
+//  * the active ones only, where heads of a group share workgroups: none of those launches is then slower than with two ordinary loads,
+//    which some are with both scalar (28/4 heads, 32 layers, 5 x 335 rows with 2 active on 1669 322 us ordinary, 327 scalar, 322 so; 7 x 168
+//    with 1 on 2471 803, 783 to 834, 790; 2 x 455 with 11 on 404 64.0, 61.6, 63.0);
+//  * neither, where every workgroup has rows (suffix buffers of one tile).  Their waves then wait for an issue slot less often: 3 x 71 rows of
+//    32/32 heads with 20 active on 53, 32 layers, 59.5 -> 56.7 us; with the merge in pieces (merge_store) as well 55.3, and 11.9 of 54.0
+//    million wave cycles are such waits, 16.9 of 61.9 before, for 4 to 6 % more vector and LDS instructions.
 struct Lengths {
   int N, P;
 };
+enum LengthLoads { kScalarLengths, kScalarActive, kOrdinaryLengths };
+template <LengthLoads HOW = kScalarLengths>
 __device__ __forceinline__ Lengths lengths_of(const AttnArgs &a, int b) {
   typedef const __attribute__((address_space(4))) int32_t *Constant;
-  const int n = reinterpret_cast<Constant>(reinterpret_cast<uint64_t>(a.suffix_len))[b];
-  const int p = reinterpret_cast<Constant>(reinterpret_cast<uint64_t>(a.prefix_len))[b];
-  fetch_now(n, p);
+  int n, p;
+  if constexpr (HOW == kScalarLengths) {
+    n = reinterpret_cast<Constant>(reinterpret_cast<uint64_t>(a.suffix_len))[b];
+    p = reinterpret_cast<Constant>(reinterpret_cast<uint64_t>(a.prefix_len))[b];
+    fetch_now(n, p);
+  } else {
+    p = a.prefix_len[b];
+    n = HOW == kOrdinaryLengths ? a.suffix_len[b] : reinterpret_cast<Constant>(reinterpret_cast<uint64_t>(a.suffix_len))[b];
+  }
   return {min(max(n, 0), a.S), min(max(p, 0), a.C)};
 }
 // This workgroup's layer replaces the operand pointers.

@@ -225,10 +225,16 @@ constexpr int kShortSuffixPipe = 32;
 // 832 -> 741, 2 x 16 of 4016 717 -> 664.  With a query group's heads on one KV head the hint costs a factor (284 -> 523), in
 // the generated loops it gains and loses as often (32 layers, 128 rows on 512 98 -> 93, 8 x 100 on 400 509 -> 541).
 constexpr int64_t kStreamBytes = int64_t(320) << 20;
+// Whether the waves of merge_store finish whole rows, or pieces of all 32 rows, which are then all at work however few rows are active.  Pieces of less
+// than 64 bytes cost more than they save: eight waves, one layer of 32/32 heads, 1 x 22 rows with 14 active on 110 6.92 us in pieces and 6.63
+// whole, 4 x 24 with 2 on 120 7.09 and 6.80; four waves, 2 x 131 rows with 6 active on 33 6.63 and 6.83, 28/4 heads, 3 x 114 with 12 on 621 10.0
+// and 10.2.
+template <int D, int WK>
+constexpr bool kWholeRows = D / WK < 32;
 // Final step shared by both kernels: the WK partial results of every query
 // block are combined through LDS (each wave's region holds O^T as [query][d]
 // fp32 plus m and l), normalised and stored as 16-byte bf16 chunks.
-template <int D, int WM, int WK>
+template <int D, int WM, int WK, bool WHOLE>
 __device__ __forceinline__ void merge_store(const AttnArgs &a, const f32x16 (&oacc)[D / 32], float mref,
                                             float lsum, unsigned char *smem, int b, int h, int q0,
                                             int N) {
@@ -253,12 +259,11 @@ __device__ __forceinline__ void merge_store(const AttnArgs &a, const f32x16 (&oa
     ml[32 + lq] = lsum;
   }
   __syncthreads();
-  // wave (wm, wk) finishes rows [wk*32/WK, (wk+1)*32/WK) of its query block, whole: items = (row, 8 d).  (Pieces of 32 or 64
-  // bytes of all 32 rows instead: one layer, 2 x 30 rows on 900 11.25 us, 11.01 so, 3 x 48 with 10 active on 83 6.53 and 6.29; 32 layers,
-  // 3 x 71 with 20 active on 53 53.6 and 55.2.)
-  constexpr int CH = D / 8;  // 16-byte output chunks per row
-  for (int it = lane; it < 32 / WK * CH; it += 64) {
-    const int qq = wk * (32 / WK) + it / CH, dd = 8 * (it % CH);
+  // wave (wm, wk) finishes rows [wk*32/WK, (wk+1)*32/WK) of its query block, whole, or columns [wk*D/WK, (wk+1)*D/WK) of all rows:
+  // items = (row, 8 d)
+  constexpr int ROWS = WHOLE ? 32 / WK : 32, COLS = WHOLE ? D : D / WK, CH = COLS / 8;  // CH: 16-byte chunks per row
+  for (int it = lane; it < ROWS * CH; it += 64) {
+    const int qq = (WHOLE ? wk * ROWS : 0) + it / CH, dd = (WHOLE ? 0 : wk * COLS) + 8 * (it % CH);
     const int qrow = q0 + wm * 32 + qq;
     float M = -INFINITY;
 #pragma unroll
@@ -316,7 +321,7 @@ constexpr int kWaitLgkm0 = 0xC07F;    // s_waitcnt lgkmcnt(0), other counters un
 struct RefKeys {
   int first, count;
 };
-template <int D, int WM, int WK, bool GATHER, int PARTS = 1>
+template <int D, int WM, int WK, bool GATHER, int PARTS = 1, bool WHOLE = kWholeRows<D, WK>>
 __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, int h, int q0, int N, int P,
                                                unsigned char *smem, bool once = false, int parts = PARTS, RefKeys ref = {0, 0}) {
   using G = Geo<D>;
@@ -578,7 +583,7 @@ __device__ __forceinline__ void key_split_body(const AttnArgs &a, int b, int g, 
   } else {
     for (int jb = wk; jb < NB; jb += WK) block(jb);
   }
-  merge_store<D, WM, WK>(a, oacc, mref, lsum, smem, b, h, q0, N);
+  merge_store<D, WM, WK, WHOLE>(a, oacc, mref, lsum, smem, b, h, q0, N);
 }
 
 // ONE: a single layer, whose operand pointers need not wait for the placement (0.1 of 11 us)
@@ -1066,7 +1071,10 @@ typedef uint32_t u32x16 __attribute__((ext_vector_type(16)));
 // when tiles do not (16 384 to 32 767 rows): a sequence's blocks are then spread when there are more of them than tiles
 // (28/4 heads, 2 x 320 rows on 3500 with 128 active 52 -> 29 us, 1 x 640 with 200 active 58 -> 31; the key split that these
 // launches once were 29 and 32).  The workgroups too many leave at once, behind the others.
-template <int WM, bool FINE, bool PACK>
+// SHORT: suffix buffers of one tile, so that no workgroup leaves at once: ordinary loads of lengths, and the key split's rows merged in pieces
+// (lengths_of, merge_store).  32 layers of 32/32 heads: 16 x 64 rows with 8 active on 64 302 -> 283 us, 14 x 75 on 115 433 -> 421; in longer
+// buffers both are the slower way (one layer, 6 x 489 with 2 active on 85 13.5 and 13.9).
+template <int WM, bool FINE, bool PACK, bool SHORT>
 __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2))) void attn_bf16_pipe_kernel(AttnArgs a_in,
                                                                                                            AttnLayers layers) {
   AttnArgs a = a_in;
@@ -1081,7 +1089,7 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   if (!pl.valid) return;
   for_layer(a, layers, pl.layer);
   const int b = pl.b, g = pl.g;
-  const auto [N, P] = lengths_of(a, b);
+  const auto [N, P] = lengths_of<SHORT ? kOrdinaryLengths : PACK ? kScalarActive : kScalarLengths>(a, b);
   // A tile of one block - a sequence down to its last rows, or the tail of a longer
   // suffix that ends just past a multiple of the tile - would keep all waves but one idle for the whole key
   // range: its one block of queries goes to the key-split body (as in attn_bf16_ring_kernel), which
@@ -1103,11 +1111,11 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
     // a fifth, 64 of 640 rows of 28/4 heads on 3500 35.3 and 28.4 us; both in one kernel cost 5 % where caches are short, 32 layers of 4 x 21 on 81
     // 68.3 and 72.1)
     if constexpr (FINE) {
-      key_split_body<D, 1, WM, false>(a, b, g, h, qs, N, P, smem);
+      key_split_body<D, 1, WM, false, 1, true>(a, b, g, h, qs, N, P, smem);
     } else {
       const bool once = a.rep == 1 && N <= 32 && int64_t(P + N) * a.Hkv * (4 * D) * a.B * a.layers >= kStreamBytes;
       const bool whole = WM == 8 || one_pass || a.rounding == kFourParts;
-      key_split_body<D, 1, WM, false, 8 / WM>(a, b, g, h, qs, N, P, smem, once, whole ? 1 : 8 / WM, ref);
+      key_split_body<D, 1, WM, false, 8 / WM, !SHORT>(a, b, g, h, qs, N, P, smem, once, whole ? 1 : 8 / WM, ref);
     }
     return;
   }
@@ -1320,7 +1328,7 @@ __global__ __launch_bounds__(64 * WM) __attribute__((amdgpu_waves_per_eu(2, 2)))
   }
 }
 
-template <int WM, bool FINE = false, bool PACK = false>
+template <int WM, bool FINE = false, bool PACK = false, bool SHORT = false>
 int32_t launch_pipe(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
   const int64_t nwg = place_blocks<WM, FINE, PACK>(a, layers);
   if (nwg > kMaxGrid) {
@@ -1330,7 +1338,7 @@ int32_t launch_pipe(AttnArgs a, const AttnLayers &layers, hipStream_t st) {
   const size_t lds_ring = size_t(WM == 8 ? 8 : 5) * 2 * 32 * 256;
   const size_t lds_split = WM * size_t(Geo<128>::WAVE_LDS) + 32 * size_t(Geo<128>::KPITCH) + 32 * sizeof(float);
   const size_t lds = lds_ring > lds_split ? lds_ring : lds_split;
-  auto kern = attn_bf16_pipe_kernel<WM, FINE, PACK>;
+  auto kern = attn_bf16_pipe_kernel<WM, FINE, PACK, SHORT>;
   static std::atomic<uint64_t> configured{0};
   if (const int32_t rc = ensure_dynamic_lds(reinterpret_cast<const void *>(kern), lds, configured, "lsp_attn_step: hipFuncSetAttribute")) return rc;
   kern<<<grid_of(nwg), 64 * WM, lds, st>>>(a, layers);
@@ -1349,7 +1357,8 @@ int32_t dispatch_contiguous128(AttnArgs a, const AttnLayers &layers, hipStream_t
   a.rounding = r.rounding;
   switch (r.kernel) {
     case Contiguous128::kTiles256Rows: return r.packed ? launch_pipe<8, false, true>(a, layers, st) : launch_pipe<8>(a, layers, st);
-    case Contiguous128::kTiles128Rows: return r.packed ? launch_pipe<4, false, true>(a, layers, st) : launch_pipe<4>(a, layers, st);
+    case Contiguous128::kTiles128Rows:
+      return r.packed ? launch_pipe<4, false, true>(a, layers, st) : a.S <= 128 ? launch_pipe<4, false, false, true>(a, layers, st) : launch_pipe<4>(a, layers, st);
     case Contiguous128::kFineTiles128Rows: return launch_pipe<4, true>(a, layers, st);
     case Contiguous128::kSplit8: return launch_g<128, 1, 8, false>(a, layers, st);
     case Contiguous128::kSplit4TwoParts: return launch_g<128, 1, 4, false, 2>(a, layers, st);

@@ -169,3 +169,23 @@ def test_packed_blocks_are_computed_as_unpacked_ones(lsp, S, N):
         assert torch.equal(packed[b, :own], plain[b, :own])
         if own < n:
             assert (packed[b, own:n] != plain[b, own:n]).float().mean().item() <= 2 ** -8
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows,Hq", [(40, 96), (128, 32), (129, 32)])
+def test_last_rows_of_buffers_of_one_tile_and_longer_ones(lsp, oracle, rows, Hq):
+    """Up to 32 rows, which the key split merges in pieces of all rows in buffers of up to 128 and as whole rows beyond: numbers of rows
+    around what a wave has of either, ragged keys of one block and many.  The bound is the bf16 one of test_gpu_attention.py."""
+    N, C = (1, 7, 8, 9, 31, 32, 0, 20, 33), 150
+    w = W.scaled(W.C2, B=len(N), S=rows, P=C, C=C, Hq=Hq, Hkv=Hq, D=128, seed=500 + rows)
+    pl, sl = torch.tensor([0, 30, 150, 64, 1, 96, 9, 149, 0], dtype=torch.int32), torch.tensor(N, dtype=torch.int32)
+    kv = W.make_layer_kv(w, 0, prefix_len=pl)
+    dev = {k: v.cuda() for k, v in kv.items()}
+    outs = [torch.full(dev["q"].shape, 123.0, dtype=torch.bfloat16, device="cuda") for _ in range(3)]
+    lsp.attn_step_layers(lsp.AttnLayerTable(*[[dev[k]] * 3 for k in ("q", "k_suf", "v_suf", "k_cache", "v_cache")], outs), pl.cuda(), sl.cuda())
+    ref = oracle.attention(**kv, prefix_len=pl, suffix_len=sl)
+    act = ~torch.isnan(ref)
+    for o in outs:
+        got = o.float().cpu()
+        assert (got[act] - ref[act]).abs().max().item() <= 2e-2
+        assert torch.all(got[~act] == 123.0)
