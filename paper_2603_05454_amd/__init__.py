@@ -525,7 +525,8 @@ def commit_step(margin, top1_id, bitmap, V, tau, window, min_commit, snap_enable
 
 
 class LengthPoll:
-    """lsp_poll_lengths with a pinned buffer of its own: the test between two steps of a decode loop."""
+    """lsp_poll_lengths with a pinned buffer of its own: the test between two steps, for a loop of the caller's that keeps no
+    totals (decode_loop's has them: ProgressPoll)."""
 
     def __init__(self):
         self.host = torch.zeros(4, dtype=torch.int32, pin_memory=True)

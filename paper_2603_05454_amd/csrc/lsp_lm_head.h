@@ -14,7 +14,8 @@ constexpr int kComputeUnits = 256;
 // lower ones where the last of a few rounds would be nearly empty or the tiles are mostly padding.  us at 64, 128 and 256 rows, K = 4096:
 // 208 rows x 126 464 entries 357, 262 and 244 (8, 4 and 2 rounds), x 66 593 227, 185 and 223 (5, 3 and 2), 140 x 40 000 101, 110 and 110,
 // 450 x 40 000 202, 167 and 197, 300 x 26 145 100, 98 and 91, 580 x 26 145 162, 150 and 172, 300 x 9036 38, 49 and 81.  122 such shapes
-// (140 to 700 rows, K 1024 to 4096): 1.046x over a rule that took 256 wherever more than 384 rows gave enough tiles, 1.047x with the best of each.
+// (140 to 700 rows, K 1024 to 4096) were 1.046x over a rule that took 256 wherever more than 384 rows gave enough tiles, and 1.047x with the best of
+// each; 84 others 1.025x, and up to 1.5 % (0.2 us) slower in the smallest, whose height is the same.
 // R: active rows; VT: vocabulary tiles.  (Their product over 512 fits 32 bits by far: it is what the workspace holds partials for.)
 __host__ __device__ __forceinline__ int tile_rows(int R, int VT) {
   if (R <= 128) return int64_t(VT) * ((R + 63) / 64) <= kComputeUnits ? 64 : 128;

@@ -99,7 +99,7 @@ def test_divided_keys_under_graph_replay(lsp):
 
 
 def test_workspace_of_sizes_that_are_not_divided(lsp):
-    """0 for few keys, for more tiles than half the compute units, and for any sizes whatever."""
+    """0 for few keys, for more tiles than half as many as there are compute units, and for any sizes whatever."""
     most = 2 ** 31 - 1
     for sizes in ((1, 16, 4, 4, 64, 287), (1, 16, 4, 4, 128, 211), (129, 16, 1, 1, 64, 2000), (most, 16, 1, 1, 64, 2000), (most,) * 4 + (64, most)):
         assert lsp.attn_workspace_bytes(0, *sizes) == 0
