@@ -30,7 +30,7 @@ def binding_command():
 
 def build(verbose: bool = False, jobs: int = 6) -> str:
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    # the hand-scheduled loops are generated (csrc/gen_attn_pipe.py -> csrc/lsp_attn_pipe_loop.inc, lsp_attn_pipe_idle_loop.inc;
+    # the hand-scheduled loops are generated (csrc/gen_attn_pipe.py -> csrc/lsp_attn_{pipe,pipe_idle,half,half_either,half_idle}_loop.inc;
     # csrc/gen_lm_head.py -> csrc/lsp_lm_head_loop_{256,128,64}.inc)
     for gen in ("gen_attn_pipe.py", "gen_lm_head.py"):
         subprocess.run([sys.executable, os.path.join(CSRC, gen)], check=True, stdout=subprocess.DEVNULL)

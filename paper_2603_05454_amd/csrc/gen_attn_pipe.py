@@ -2,7 +2,8 @@
 """Generator of lsp_attn_pipe_loop.inc: the hand-scheduled block loop of the
 long-suffix bf16 attention kernel (head_dim 128) as one inline-asm statement,
 and of lsp_attn_pipe_idle_loop.inc, the loader-only loop that waves without an
-active query run beside it (generate_idle below).
+active query run beside it (generate_idle below); then the same for workgroups of
+four waves (lsp_attn_half_*.inc).
 
 Why generated assembly: with compiler scheduling a wave issues the products of a
 32-key block as one burst (waiting on every LDS fragment read just before its
